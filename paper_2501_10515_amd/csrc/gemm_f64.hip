@@ -338,46 +338,67 @@ hipError_t launch_cfg(const GP& p0, bool amf, bool bnf, int nb1, int nb1d, doubl
 
 // ---------------------------------------------------------------------------------------
 // Direct-to-LDS path for K-contiguous operands, A(m,k) = A[m*sam + k] and B(k,n) = B[n*sbn + k]:
-// rows go from global memory straight into LDS with global_load_lds_dwordx4 (lane l of an
+// rows go from global memory straight into LDS with buffer_load_dwordx4 ... lds (lane l of an
 // instruction writes LDS bytes 16l .. 16l + 15), S stages in flight, one barrier per stage and no
-// staging registers.  A stage holds KS K-values of every tile row: KS = 8 (64-byte rows, the 16-byte
-// chunk c of row r at slot c ^ ((r >> 1) & 3)) or KS = 16 (whole 128-byte lines, chunk c of row r
-// at slot c ^ (r & 7)); either swizzle makes the fragment reads conflict-free.  Each fragment read
-// returns two K-values and feeds two MFMAs: lane group g = l / 16 supplies K = 2g to the first and
-// 2g + 1 to the second, identically for A and B; a 16-deep stage is read as two 8-deep halves in
-// order, so the MFMA sequence along K, and with it every result, is the same for both depths.  Rows
-// past M or N and K-values past K are read from a 16-byte zero block instead, so every load
-// instruction runs on all lanes and the per-wave vmcnt bookkeeping is exact.  PM: B is
-// pair-combined as in gemm_f64_kernel, both rows of each pair staged and combined at the fragment
-// read (two B rows per pair leave room for two 16-deep stages only: the next stage loads while the
-// current one is computed; every wave has read the refilled slot before the barrier that precedes
-// the refill, as with more stages).
+// staging registers.  A stage holds 16 K-values of every tile row: whole 128-byte lines, the 16-byte
+// chunk c of row r at slot c ^ (r & 7), which makes the fragment reads conflict-free.  Each fragment
+// read returns two K-values and feeds two MFMAs: lane group g = l / 16 supplies K = 2g to the first
+// and 2g + 1 to the second, identically for A and B; a stage is read as two 8-deep halves in order.
+// Rows past M or N and K-values past K read as zero through the descriptor's range check, so every
+// load instruction runs on all lanes and the per-wave vmcnt bookkeeping is exact.
+//
+// Bound: the FP64 matrix pipe (77.9 TFLOP/s from registers, 64 cycles per 16x16x4 product).  What
+// keeps it from that rate is the issue of the stage loads, during which a wave issues no product:
+// without them the loop runs at 77 TFLOP/s.  Hence (one round of 256 tiles, K = 8192, before and
+// after, TFLOP/s): a scalar descriptor and one offset register per load instead of a 64-bit address
+// per lane, and the fragment reads one unit ahead of their products with reads and loads issued
+// between products instead of in a block after the barrier: 192x192 69.6 -> 71.9 (four rounds),
+// 256x128 69.0 -> 71.0, 224x128 66.3 -> 71, 240x128 64.0 -> 72.6, 208x128 63.2 -> 71.6, 128x128
+// 65.4 -> 68.8.  Spreading the loads over the whole stage was slower (66-68).
+//
+// PM: B is pair-combined as in gemm_f64_kernel, both rows of each pair staged and combined once
+// read (two B rows per pair leave room for two stages only).  The second rows of a tile's pairs lie
+// anywhere in the stored matrix, past a descriptor's range, and are loaded by address.
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) const void gbl_void_t;
 __device__ __attribute__((aligned(16))) double kZero16[2];
+constexpr int kStageK = 16;  // K-values per stage
 
-// s_waitcnt vmcnt(N) (bits 3:0 and 15:14), no wait on the other counters
+// This wave's part of a stage has landed (at most N later loads in flight) and its fragment reads so
+// far are in registers, then the same for every wave of the workgroup.  A plain s_barrier: no memory
+// fence is needed (and __syncthreads would add one that drains all stages in flight).
 template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
+__device__ __forceinline__ void wait_stage() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt(0xF70 | (N & 15) | ((N >> 4) << 14));
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x070 | (N & 15) | ((N >> 4) << 14));  // vmcnt(N) lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
-template <int BM, int BN, int WM, int WN, int S, bool PM, int KS>
+// Descriptor of `rows` rows of a tile at leading dimension ld (elements).  Every component goes
+// through readfirstlane, so the loads take it from scalar registers.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const double* base, int rows, long ld) {
+  const uint64_t b = reinterpret_cast<uint64_t>(base);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+  void* ub = reinterpret_cast<void*>(((uint64_t)hi << 32) | lo);
+  return __builtin_amdgcn_make_buffer_rsrc(ub, (short)0, __builtin_amdgcn_readfirstlane((int)(rows * ld * 8)), 0x00020000);
+}
+
+template <int BM, int BN, int WM, int WN, int S, bool PM>
 __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
   typedef double dd2 __attribute__((ext_vector_type(2)));
   typedef double d4 __attribute__((ext_vector_type(4)));
   constexpr int NW = WM * WN;
   constexpr int TM = BM / WM, TN = BN / WN, RI = TM / 16, RJ = TN / 16;
   constexpr int NB = PM ? 2 : 1;
-  constexpr int CPR = KS / 2, RPI = 64 / CPR;  // 16-byte chunks per staged row, rows per load instruction
+  constexpr int KS = kStageK, CPR = KS / 2, RPI = 64 / CPR;  // 16-byte chunks per staged row, rows per load instruction
   constexpr int IA = BM / RPI, IB = BN / RPI, NI = IA + NB * IB;  // 1 KB load instructions per stage
   constexpr int NPW = (NI + NW - 1) / NW, NPWMIN = NI / NW;        // per wave
   constexpr int ROWS = BM + NB * BN;
   static_assert(TM % 16 == 0 && TN % 16 == 0 && S >= 2 && NPWMIN >= 1, "tile config");
-  static_assert(KS == 8 || KS == 16, "stage depth");
   __shared__ __attribute__((aligned(1024))) double T[S][ROWS * KS];
-  auto swz = [](int r) { return KS == 8 ? (r >> 1) & 3 : r & 7; };  // slot of chunk 0 of row r
+  auto swz = [](int r) { return r & 7; };  // slot of chunk 0 of row r
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -403,42 +424,58 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
   const double* Bb = p.B + zs * p.sb1 + z2 * p.sb2;
   double* Cb = p.C + zs * p.sc1 + z2 * p.sc2;
 
-  // the source row (chunk included) of this lane in each instruction its wave issues
-  const double* src[NPW];
-  bool ok[NPW];
-  int ck[NPW];
+  // This lane's source in each load instruction its wave issues: rows of A and of B as byte offsets
+  // into a buffer descriptor that covers the tile's rows (rows past M or N lie past its range and
+  // read as zero; the advance along K is a scalar offset), pair rows of a pair-combined B, which lie
+  // anywhere in the stored matrix, as addresses (kZero16 past N).
+  constexpr int J2 = (IA + IB) / NW;  // first instruction of a wave that can hold pair rows
+  const __amdgpu_buffer_rsrc_t ra = tile_rsrc(Ab + (long)m0 * p.sam, min(BM, p.M - m0), p.sam);
+  const __amdgpu_buffer_rsrc_t rb = tile_rsrc(Bb + (long)n0 * p.sbn, min(BN, p.N - n0), p.sbn);
+  uint32_t off[NPW];
+  const double* src2[PM ? NPW - J2 : 1];
+  (void)src2;
+  const int ck = 2 * ((lane % CPR) ^ swz(lane / CPR));  // the same chunk in every instruction: it starts a group of 8 rows
+  static_assert(RPI == 8, "a load instruction covers one period of the swizzle");
 #pragma unroll
   for (int j = 0; j < NPW; ++j) {
     const int g = wave + NW * j;
     const int r = RPI * g + lane / CPR;
-    const int c = (lane % CPR) ^ swz(r);
-    const double* row = nullptr;
-    if (g < IA) {
-      const int gm = m0 + r;
-      if (gm < p.M) row = Ab + (long)gm * p.sam;
-    } else if (g < IA + IB) {
-      const int gn = n0 + r - BM;
-      if (gn < p.N) row = Bb + (long)gn * p.sbn;
-    } else if (g < NI) {
-      const int gn = n0 + r - BM - BN;
-      if (gn < p.N) row = Bb + (long)p.pm[gn] * p.sbn;
+    off[j] = g < IA ? (uint32_t)(r * p.sam + ck) * 8 : (uint32_t)((r - BM) * p.sbn + ck) * 8;
+    if constexpr (PM) {
+      if (j >= J2) {
+        const int gn = n0 + r - BM - BN;
+        src2[j - J2] = (g >= IA + IB && g < NI && gn < p.N) ? Bb + (long)p.pm[gn] * p.sbn + ck : nullptr;
+      }
     }
-    ok[j] = row != nullptr;
-    ck[j] = 2 * c;
-    src[j] = ok[j] ? row + 2 * c : kZero16;
   }
   // stages [kt0, kt0 + nkt) of this slice
   const int kt0 = slice * p.it_per_split;
   const int nkt = min((p.K + KS - 1) / KS, kt0 + p.it_per_split) - kt0;
-  auto issue = [&](int kt, int st) {
-#pragma unroll
-    for (int j = 0; j < NPW; ++j) {
-      const int g = wave + NW * j;
-      if (NPW * NW == NI || g < NI) {
-        const double* a = (ok[j] && kt * KS + ck[j] < p.K) ? src[j] + kt * KS : kZero16;
-        __builtin_amdgcn_global_load_lds((gbl_void_t*)a, (lds_void_t*)&T[st][g * 128], 16, 0, 0);
+  auto issue1 = [&](int kt, int st, int j) {  // load instruction j of this wave for stage kt
+    const int g = wave + NW * j;
+    if (NPW * NW == NI || g < NI) {
+      lds_void_t* dst = (lds_void_t*)&T[st][g * 128];
+      if (!PM || g < IA + IB) {
+        const uint32_t o = off[j];
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(g < IA ? ra : rb, dst, 16, o, kt * KS * 8, 0, 0);
+      } else {
+        const double* x = src2[PM && j >= J2 ? j - J2 : 0];
+        const double* a = (x && kt * KS + ck < p.K) ? x + kt * KS : kZero16;
+        __builtin_amdgcn_global_load_lds((gbl_void_t*)a, dst, 16, 0, 0);
       }
     }
+  };
+  // before the loads of the last stage of an uneven K (no stage follows it): chunks past K read as zero
+  auto mask_tail = [&](int kt) {
+    if ((kt + 1) * KS > p.K && kt * KS + ck >= p.K) {
+#pragma unroll
+      for (int j = 0; j < NPW; ++j) off[j] = 0x80000000u;  // past the range of every descriptor
+    }
+  };
+  auto issue = [&](int kt, int st) {
+    mask_tail(kt);
+#pragma unroll
+    for (int j = 0; j < NPW; ++j) issue1(kt, st, j);
   };
 
   d4 acc[RI][RJ];
@@ -448,49 +485,84 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
     for (int j = 0; j < RJ; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
   const bool minus = PM && z2 == 1;
   const int l16 = lane & 15, q = lane >> 4;
+  // Fragments are read one unit ahead of their MFMAs: a unit is one group of A fragment rows of one
+  // 8-deep half of a stage (units of a stage: half 0 group 0, half 0 group 1, half 1 group 0, ...).
+  constexpr int G = (RI > 8) ? 2 : 1, GI = (RI + G - 1) / G, U = G * (KS / 8);
+  static_assert(U % 2 == 0, "the unit parity must be static");
+  dd2 fa[2][GI], fb[2][RJ];
+  dd2 fw[PM ? RJ : 1];  // pair-combined B: second rows, combined when the unit starts
+  (void)fw;
+  // read k of unit u's fragments: first the B fragments (unit 0 of a half: they serve all its groups),
+  // then the A fragments
+  constexpr int RB = NB * RJ, NR = RB + GI;
+  auto read1 = [&](const double* Ts, int u, int k) {
+    const int kk = u / G, g = u % G;
+    if (k < RB) {
+      if (g != 0) return;
+      const int r = BM + (k / RJ) * BN + wn * TN + 16 * (k % RJ) + l16;
+      const dd2 x = *reinterpret_cast<const dd2*>(Ts + r * KS + 2 * ((q + 4 * kk) ^ swz(r)));
+      if (k < RJ)
+        fb[kk & 1][k] = x;
+      else
+        fw[k % RJ] = x;
+    } else if (g * GI + k - RB < RI) {
+      const int r = wm * TM + 16 * (g * GI + k - RB) + l16;
+      fa[u & 1][k - RB] = *reinterpret_cast<const dd2*>(Ts + r * KS + 2 * ((q + 4 * kk) ^ swz(r)));
+    }
+  };
+  auto combine = [&](int u) {  // pair-combined B of unit u's half
+    if constexpr (PM) {
+      const int kk = u / G;
+      if (u % G != 0) return;
 #pragma unroll
-  for (int st = 0; st < S - 1; ++st)
+      for (int j = 0; j < RJ; ++j) fb[kk & 1][j] = minus ? fb[kk & 1][j] - fw[j] : fb[kk & 1][j] + fw[j];
+    }
+  };
+#pragma unroll
+  for (int st = 0; st < S; ++st)
     if (st < nkt) issue(kt0 + st, st);
+  if (nkt > 0) {
+    if (S - 1 < nkt)
+      wait_stage<(S - 1) * NPWMIN>();
+    else
+      wait_stage<0>();
+#pragma unroll
+    for (int k = 0; k < NR; ++k) read1(T[0], 0, k);
+    combine(0);
+  }
   for (int kt = 0; kt < nkt; ++kt) {  // kt counts stages of this slice
     const int st = kt % S;
-    // stage kt has landed once no more than the later stages' loads of this wave are in flight
-    if (kt + S - 2 < nkt)
-      wait_vmcnt<(S - 2) * NPWMIN>();
-    else
-      wait_vmcnt<0>();
-    // every wave has waited for its own part of the stage; no memory fence is needed (and
-    // __syncthreads would add one that drains all stages in flight)
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    const double* Ts = T[st];
+    const bool more = kt + 1 < nkt, refill = kt + S < nkt;
 #pragma unroll
-    for (int kk = 0; kk < KS / 8; ++kk) {  // 8-deep halves of the stage, in K order
-      dd2 fa[RI], fb[RJ];
-#pragma unroll
-      for (int i = 0; i < RI; ++i) {
-        const int r = wm * TM + 16 * i + l16;
-        fa[i] = *reinterpret_cast<const dd2*>(Ts + r * KS + 2 * ((q + 4 * kk) ^ swz(r)));
+    for (int u = 0; u < U; ++u) {
+      const int kk = u / G, g = u % G;
+      const bool last = u + 1 == U;
+      const double* Tn = T[last ? (kt + 1) % S : st];
+      if (last && more) {
+        // stage kt + 1 has landed once no more than the later stages' loads of this wave are in
+        // flight; past the barrier it has for every wave, and every wave holds the last fragments of
+        // stage kt in registers, so its slot is refilled from here on
+        if (kt + S - 1 < nkt)
+          wait_stage<(S - 2) * NPWMIN>();
+        else
+          wait_stage<0>();
       }
+      if (last && refill) mask_tail(kt0 + kt + S);
+      // the unit's products, with a fragment read or a refill load issued behind most of them
+      constexpr int NM = 2 * GI * RJ, LS = NR + 2 * NPW <= NM ? 2 : 1;
+      constexpr int ML = S == 2 ? 0 : LS == 2 ? NR : NM - NPW;  // two stages: the refill is due soonest
+      static_assert(NR <= NM && NPW <= NM, "one read and one load per product at most");
 #pragma unroll
-      for (int j = 0; j < RJ; ++j) {
-        const int r = BM + wn * TN + 16 * j + l16;
-        fb[j] = *reinterpret_cast<const dd2*>(Ts + r * KS + 2 * ((q + 4 * kk) ^ swz(r)));
-        if constexpr (PM) {
-          const int rw = r + BN;  // (r + BN) has the same swizzle as r: BN is a multiple of 16
-          const dd2 w = *reinterpret_cast<const dd2*>(Ts + rw * KS + 2 * ((q + 4 * kk) ^ swz(rw)));
-          fb[j] = minus ? fb[j] - w : fb[j] + w;
-        }
+      for (int m = 0; m < NM; ++m) {
+        const int h = m / (GI * RJ), i = (m / RJ) % GI, j = m % RJ;
+        if (g * GI + i < RI)
+          acc[g * GI + i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[u & 1][i][h], fb[kk & 1][j][h],
+                                                                    acc[g * GI + i][j], 0, 0, 0);
+        if (m < NR && (!last || more)) read1(Tn, last ? 0 : u + 1, m);
+        if (last && refill && m >= ML && m < ML + LS * NPW && (m - ML) % LS == 0) issue1(kt0 + kt + S, st, (m - ML) / LS);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      // the stage refilled now was last read in the previous iteration, before this barrier
-      if (kk == 0 && kt + S - 1 < nkt) issue(kt0 + kt + S - 1, (kt + S - 1) % S);
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int i = 0; i < RI; ++i)
-#pragma unroll
-          for (int j = 0; j < RJ; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i][h], fb[j][h], acc[i][j], 0, 0, 0);
+      if (!last || more) combine(last ? 0 : u + 1);
     }
   }
 #pragma unroll
@@ -514,18 +586,20 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
       }
 }
 
-// K-contiguous operands with 16-byte aligned rows and an even K (the loads move K-value pairs).
+// K-contiguous operands with 16-byte aligned rows and an even K (the loads move K-value pairs); the
+// rows of a tile (256 at most) lie within the 2 GiB range of a buffer descriptor.
 bool dma_eligible(const GP& p) {
   auto al = [](const void* x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
-  return p.sak == 1 && p.sbk == 1 && p.nred == 1 && p.K % 2 == 0 && p.sam % 2 == 0 && p.sbn % 2 == 0 &&
+  auto near = [](long ld) { return ld >= 0 && ld < (1L << 20); };
+  return near(p.sam) && near(p.sbn) && p.sak == 1 && p.sbk == 1 && p.nred == 1 && p.K % 2 == 0 && p.sam % 2 == 0 && p.sbn % 2 == 0 &&
          p.sa1 % 2 == 0 && p.sa2 % 2 == 0 && p.sb1 % 2 == 0 && p.sb2 % 2 == 0 && al(p.A) && al(p.B);
 }
 
 // split > 1 (never with pm): K cut into `split` slices whose partial tiles go to ws, then summed
 // in a fixed order by splitk_reduce.
-template <int BM, int BN, int WM, int WN, int S, int KS = 8>
+template <int BM, int BN, int WM, int WN, int S>
 hipError_t launch_dma(GP p, int nb1, bool pm, int split, double* ws, hipStream_t s) {
-  static_assert(KS == 8 || KS == 16, "stage depth");
+  constexpr int KS = kStageK;
   p.tiles_m = (p.M + BM - 1) / BM;
   p.tiles_n = (p.N + BN - 1) / BN;
   const int nkt = (p.K + KS - 1) / KS;
@@ -537,14 +611,14 @@ hipError_t launch_dma(GP p, int nb1, bool pm, int split, double* ws, hipStream_t
   if (pm) {  // both halves in grid.x, padded to whole groups of 8
     if constexpr ((long)S * (BM + 2 * BN) * KS * 8 <= 160 * 1024) {
       dim3 grid(2 * ((tiles + 7) / 8 * 8), 1, nb1);
-      hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, S, true, KS>), grid, dim3(WM * WN * 64), 0, s, p);
+      hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, S, true>), grid, dim3(WM * WN * 64), 0, s, p);
       return hipGetLastError();
     } else {
       return hipErrorInvalidValue;  // two B rows per pair do not fit this many stages
     }
   }
   dim3 grid(tiles * p.split, p.nb2, nb1);
-  hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, S, false, KS>), grid, dim3(WM * WN * 64), 0, s, p);
+  hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, S, false>), grid, dim3(WM * WN * 64), 0, s, p);
   if (p.split > 1) {
     const long outs = (long)p.M * p.N * p.nb2 * nb1;
     hipLaunchKernelGGL(splitk_reduce, dim3(splitk_blocks(outs)), dim3(256), 0, s, p, nb1, outs);
@@ -575,9 +649,9 @@ hipError_t launch_dma_auto(const GP& p, int nb1, int nb1d, double* ws, long ws_e
       best_split = sp;
     }
   }
-  if (best == 0) return launch_dma<192, 192, 2, 4, 3, 16>(p, nb1, false, best_split, ws, s);
-  if (best == 1) return launch_dma<256, 128, 4, 2, 3, 16>(p, nb1, false, best_split, ws, s);
-  return launch_dma<224, 128, 2, 4, 3, 16>(p, nb1, false, best_split, ws, s);
+  if (best == 0) return launch_dma<192, 192, 2, 4, 3>(p, nb1, false, best_split, ws, s);
+  if (best == 1) return launch_dma<256, 128, 4, 2, 3>(p, nb1, false, best_split, ws, s);
+  return launch_dma<224, 128, 2, 4, 3>(p, nb1, false, best_split, ws, s);
 }
 
 // Ladder: BM x 128 tiles of 8 waves, both halves (grid.y = 2), no split-K, A/B staged k-fast.
@@ -696,7 +770,7 @@ hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
     // upper triangle (each mirrored value sums the same products in the same K order); other
     // symmetric products (odd K, unaligned rows) take the full product below
     p.lower = 1;
-    hipError_t e = launch_dma<192, 192, 2, 4, 3, 16>(p, g.nb1, false, 1, nullptr, s);
+    hipError_t e = launch_dma<192, 192, 2, 4, 3>(p, g.nb1, false, 1, nullptr, s);
     if (e != hipSuccess) return e;
     const long nbk = (g.M + 31) / 32;
     hipLaunchKernelGGL(mirror_upper_kernel, dim3((unsigned)(nbk * (nbk + 1) / 2), (unsigned)g.nb2, (unsigned)g.nb1),
@@ -794,17 +868,17 @@ hipError_t gemm_f64_ladder(int M, int Tv, const double* A, const double* V, long
     const long best = std::min({pad256, pad240, pad224, pad208, pad128});
     const int t = pad256 == best ? 0 : pad240 == best ? 4 : pad224 == best ? 1 : pad208 == best ? 2 : 3;
     if (pmode) {  // two B rows per pair: two 16-deep stages
-      if (t == 0) return launch_dma<256, 128, 4, 2, 2, 16>(p, lb.n, true, 1, nullptr, s);
-      if (t == 4) return launch_dma<240, 128, 1, 8, 2, 16>(p, lb.n, true, 1, nullptr, s);
-      if (t == 1) return launch_dma<224, 128, 2, 4, 2, 16>(p, lb.n, true, 1, nullptr, s);
-      if (t == 2) return launch_dma<208, 128, 1, 8, 2, 16>(p, lb.n, true, 1, nullptr, s);
-      return launch_dma<128, 128, 2, 4, 2, 16>(p, lb.n, true, 1, nullptr, s);
+      if (t == 0) return launch_dma<256, 128, 2, 4, 2>(p, lb.n, true, 1, nullptr, s);
+      if (t == 4) return launch_dma<240, 128, 1, 8, 2>(p, lb.n, true, 1, nullptr, s);
+      if (t == 1) return launch_dma<224, 128, 2, 4, 2>(p, lb.n, true, 1, nullptr, s);
+      if (t == 2) return launch_dma<208, 128, 1, 8, 2>(p, lb.n, true, 1, nullptr, s);
+      return launch_dma<128, 128, 2, 4, 2>(p, lb.n, true, 1, nullptr, s);
     }
-    if (t == 0) return launch_dma<256, 128, 4, 2, 3, 16>(p, lb.n, false, 1, nullptr, s);
-    if (t == 4) return launch_dma<240, 128, 1, 8, 3, 16>(p, lb.n, false, 1, nullptr, s);
-    if (t == 1) return launch_dma<224, 128, 2, 4, 3, 16>(p, lb.n, false, 1, nullptr, s);
-    if (t == 2) return launch_dma<208, 128, 1, 8, 3, 16>(p, lb.n, false, 1, nullptr, s);
-    return launch_dma<128, 128, 2, 4, 3, 16>(p, lb.n, false, 1, nullptr, s);
+    if (t == 0) return launch_dma<256, 128, 4, 2, 3>(p, lb.n, false, 1, nullptr, s);
+    if (t == 4) return launch_dma<240, 128, 1, 8, 3>(p, lb.n, false, 1, nullptr, s);
+    if (t == 1) return launch_dma<224, 128, 2, 4, 3>(p, lb.n, false, 1, nullptr, s);
+    if (t == 2) return launch_dma<208, 128, 1, 8, 3>(p, lb.n, false, 1, nullptr, s);
+    return launch_dma<128, 128, 2, 4, 3>(p, lb.n, false, 1, nullptr, s);
   }
   if (pad256 <= pad224 && pad256 <= pad128) return launch_ladder<256, 4>(p, lb.n, pmode, s);
   if (pad224 <= pad128) return launch_ladder<224, 2>(p, lb.n, pmode, s);
