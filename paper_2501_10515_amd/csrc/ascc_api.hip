@@ -177,11 +177,15 @@ struct ascc_ints {
   double* BovT;   // [o][v][Q]: the same, K = Q contiguous
   double* KL;     // [2][ov][ov]: (ib|ja), 2(ia|jb) - (ib|ja)
   double* Lijab;  // [o][o][v][v]: 2(ia|jb) - (ib|ja)
-  double* Gwz;    // [ov + o^2][v][v]: (kc|bd) at [k*v+b][c][d], (kc|ld) at [ov + k*o+l][c][d]
-  double* V;      // FULL: [v^2][v^2], (ac|bd) at [R(a,b)][R(c,d)] (pair order: a <= b first, see pack_full)
-                  // PACKED: [2][T(v)][T(v)], (ac|bd) +- (ad|bc) at [p(a,b)][p(c,d)], a <= b, c <= d
+  double* V;      // FULL: [v^2] rows at stride ldV, (ac|bd) at [R(a,b)][R(c,d)] (pair order: a <= b first,
+                  // see pack_full).  PACKED: [2][T(v) + ov + o^2] rows at stride ldT: V+-, (ac|bd) +- (ad|bc)
+                  // at [p(a,b)][p(c,d)], a <= b, c <= d, then the rows of G+-
+  double* G;      // G+-, [2][ov + o^2] rows at stride ldT: (kc|bd) +- (kd|bc) at [k*v+b][p(c,d)] and
+                  // (kc|ld) +- (kd|lc) at [ov + k*o+l][p(c,d)] (FULL only: a PACKED set holds them in V)
   double* pairtab;  // FULL: int32 [T(v)]: row R(b,a) of V for pair p(a,b), a <= b
-  double *Tp, *Rp;  // ladder operands [2][T(o)][T(v)]: t+- (pack_tpm) and R+- (unpack_rpm)
+  double *Tp, *Rp;  // ladder operands: t+- [2][T(o)] rows at stride ldT (pack_tpm), and R+- with the W/Z
+                    // pair rows behind each (unpack_rpm, wz_chi), [2][T(o)] rows at stride ldR
+  long ldT, ldV, ldR;
   // residual work arrays
   double* Bc;                    // [Q][n][o] T1 correction of the first o columns of B
   double* Bh;                    // [Q][n][n]
@@ -192,22 +196,22 @@ struct ascc_ints {
   double *G1, *G2, *G3, *G4;     // ovov, [k][i][a][c], ovov, [k][i][l][j]
   double *TU, *Y, *XZ, *P;       // each [2][ov][ov]
   double *Nq;                    // [Q][o][v]
-  double *WZ;                    // [o^2][ov + o^2]
-  double *chi;                   // [o^2][o^2]
+  double *WZ;                    // [o^2][ov + o^2] (FP64: W' in the first ov columns)
+  double *chi;                   // [o^2][o^2] (FP64: chi+-, [2][T(o)][T(o)])
   double *RL, *EM;               // [o^2][v^2]
   double *Abc, *Bkj, *Fvvp, *Foop, *Fovh;  // small
   double *partial;               // reduction scratch
   double *splitk;                // split-K partial tiles of small-output contractions
   // FP32 shadows of the large-contraction operands (only for a low-precision integral set)
-  float *Vf, *GwzTf, *KLf;       // constant: vvvv, [ov+o^2][v^2] (kc|bd)|(kc|ld), K|L
+  float *Vf, *GwzTf, *KLf;       // constant: V+-, [ov+o^2][v^2] (kc|bd)|(kc|ld), K|L
   float *Tpf, *t2f, *TUf, *XZf;  // per residual: ladder rows, t2 rows, Tx|U, Xc|Zd
   // per residual, K = naux or o^2 contiguous: B^_ai as [ia][Q], B^_ki [ki][Q], B^_ac [ac][Q],
   // B^_kc [kc][Q], B^_kc as [Q][kc], t2 as [ab][ij], chi [ij][kl]
   float *BvoTtf, *BooTf, *BvvTf, *BovTf, *Bovf, *t2Tf, *chif;
   int cur_prec = 0;              // arithmetic of the large contractions in the next residual
-  // multi-state batches (ascc_batch_reserve): stacked ladder operands and per-state RL
+  // multi-state batches (ascc_batch_reserve): stacked ladder operands
   int max_states = 0;
-  double *Tp_all = nullptr, *Rp_all = nullptr, *RL_all = nullptr;
+  double *Tp_all = nullptr, *Rp_all = nullptr;
   float* Tpf_all = nullptr;
   int group = 1;             // states per batched pass of the other terms (ascc_batch_reserve_ws)
   char* group_base = nullptr;  // `group` work blocks of group_block bytes
@@ -295,6 +299,7 @@ inline int* pair_minus(const ascc_ints* I) { return reinterpret_cast<int*>(I->pa
 
 constexpr long kSplitKElems = 1L << 23;  // 64 MiB of split-K partials
 inline long pad_even(long x) { return x + (x & 1); }  // compact slab widths, even for the direct-to-LDS path
+inline long pad_line(long x) { return (x + 15) / 16 * 16; }  // rows of whole 128-byte lines
 
 // Every device array of an integral set with its element count, in allocation order; the
 // same list gives ascc_workspace_bytes its exact answer.
@@ -302,22 +307,23 @@ std::vector<std::pair<double* ascc_ints::*, long>> ints_plan(long o, long v, lon
   const long n = o + v, nn = n * n, ov = o * v, oo = o * o, vv = v * v, ovov = ov * ov;
   const long To = o * (o + 1) / 2, Tv = v * (v + 1) / 2;
   const bool full = (mode == ASCC_VVVV_FULL);
+  const long wzl = ov + oo, ldT = pad_line(Tv), ldR = pad_line(Tv + wzl);
   return {
       {&ascc_ints::B, Q * nn},        {&ascc_ints::h, nn},           {&ascc_ints::eps, n},
       {&ascc_ints::fov, ov},          {&ascc_ints::e0, 1},
       {&ascc_ints::Bov, Q * ov},      {&ascc_ints::KL, 2 * ovov},
-      {&ascc_ints::Lijab, oo * vv},   {&ascc_ints::Gwz, vv * (ov + oo)},
+      {&ascc_ints::Lijab, oo * vv},   {&ascc_ints::G, full ? 2 * wzl * ldT : 0},
       {&ascc_ints::BovT, ov * Q},
-      {&ascc_ints::V, full ? vv * vv : 2 * Tv * Tv},
+      {&ascc_ints::V, full ? vv * pad_line(vv) : 2 * (Tv + wzl) * ldT},
       {&ascc_ints::pairtab, full ? Tv : 0},
-      {&ascc_ints::Tp, 2 * To * Tv},  {&ascc_ints::Rp, 2 * To * Tv},
+      {&ascc_ints::Tp, 2 * To * ldT}, {&ascc_ints::Rp, 2 * To * ldR},
       {&ascc_ints::Bc, Q * n * o},    {&ascc_ints::Bh, Q * nn},      {&ascc_ints::hc, n * o},
       {&ascc_ints::Fh, nn},           {&ascc_ints::J, Q},            {&ascc_ints::BvoTt, Q * ov},
       {&ascc_ints::Boo, Q * oo},      {&ascc_ints::Bvv, Q * vv},     {&ascc_ints::G1, ovov},
       {&ascc_ints::G2, oo * vv},      {&ascc_ints::G3, ovov},        {&ascc_ints::G4, oo * oo},
       {&ascc_ints::TU, 2 * ovov},     {&ascc_ints::Y, 2 * ovov},     {&ascc_ints::XZ, 2 * ovov},
       {&ascc_ints::P, 2 * ovov},      {&ascc_ints::Nq, Q * ov},      {&ascc_ints::WZ, oo * (ov + oo)},
-      {&ascc_ints::chi, oo * oo},     {&ascc_ints::RL, oo * vv},     {&ascc_ints::EM, oo * vv},
+      {&ascc_ints::chi, std::max(oo * oo, 2 * To * To)}, {&ascc_ints::RL, oo * vv},     {&ascc_ints::EM, oo * vv},
       {&ascc_ints::Abc, vv},          {&ascc_ints::Bkj, oo},         {&ascc_ints::Fvvp, vv},
       {&ascc_ints::Foop, oo},         {&ascc_ints::Fovh, ov},        {&ascc_ints::partial, 8192},
       {&ascc_ints::splitk, kSplitKElems},
@@ -627,63 +633,115 @@ hipError_t shadow(const ascc_ints* I, float* out, const double* in, long rows, l
   return hipSuccess;
 }
 
-// Particle-particle ladder RL_s[i][j][a][b] = sum_cd (t_s)_ij^cd (ac|bd) for S states in one
-// launch, computed for pairs i <= j only (RL_ji^ba = RL_ij^ab) and through the (ab)-symmetric and
-// antisymmetric halves: R+- = t+- V+- with t+-_ij^cd = (t_ij^cd +- t_ij^dc)/2 over c <= d and
-// V+-[(ab)][(cd)] = (ac|bd) +- (ad|bc) over a <= b (diagonal cd: (ac|bc) and 0), both halves in
-// one launch.  PACKED stores V+-; FULL stores the full (ac|bd) matrix in pair order, and its
-// halves are V[n][k] +- V[pm[n]][k], formed while the FP64 contraction stages them (and rounded
-// into the low-precision shadow); there the diagonal V+ is 2(ac|bc), so t+ carries t_ij^cc / 2.
-// The S states' rows are stacked, so the vvvv operand is streamed once for all of them.  Tp/Rp
-// hold [2][S*T(o)][T(v)].
-int pp_ladder_states(ascc_ints* I, int S, const double* const* t2s, double* const* RLs, double* Tp, double* Rp,
-                     float* Tpf, hipStream_t s) {
+// Low-precision shadow of `rows` rows of pairs at stride ldT.
+hipError_t shadow_pairs(const ascc_ints* I, float* out, const double* in, long rows, hipStream_t s) {
+  const long Tv = (long)I->nv * (I->nv + 1) / 2;
+  return to_lowp_2d(lowp_kind(I), out, lowp_ld(Tv), in, I->ldT, rows, Tv, s);
+}
+
+// The rows of one state among the stacked ladder operands: t+- at Tp and R+- (with the W/Z columns behind
+// them in FP64) at Rp, the - halves st and sr elements further on.
+struct LadderRows {
+  double *Tp, *Rp;
+  long st, sr;
+};
+LadderRows own_rows(const ascc_ints* I) {
+  const long To = (long)I->no * (I->no + 1) / 2;
+  return {I->Tp, I->Rp, To * I->ldT, To * I->ldR};
+}
+
+// Particle-particle ladder R_s[p(i,j)] = sum_cd (t_s)_ij^cd (ac|bd) of S states in one launch, computed for
+// pairs i <= j only (R_ji^ba = R_ij^ab) and through the (ab)-symmetric and antisymmetric halves:
+// R+- = t+- V+- with t+-_ij^cd = (t_ij^cd +- t_ij^dc)/2 over c <= d and V+-[(ab)][(cd)] = (ac|bd) +- (ad|bc)
+// over a <= b (diagonal cd: (ac|bc) and 0), both halves in one launch.  In FP64 the rows of
+// G+- = (kc|bd) +- (kd|bc) | (kc|ld) +- (kd|lc) join them: W_ij[k,b] = sum_cd (kc|bd) t_ij^cd and
+// Z_ij[k,l] = sum_cd (kc|ld) t_ij^cd in the same halves, half the products of the full sum over c, d.  PACKED
+// stores V+- and G+- as one matrix, one launch for both (a fuller last round: o30 v270 53.5 + 19.8 ms as
+// two launches, 44 as one); FULL stores the (ac|bd) matrix in pair order, whose halves V[n][k] +- V[pm[n]][k]
+// are formed while they are staged, and G+- apart.  The S states' rows are stacked, so the vvvv operand
+// is streamed once for all of them; a state's sums are those it has alone.
+int ladder_launch(ascc_ints* I, long S, const double* Tp, double* Rp, const LadderBatch* lb, hipStream_t s) {
+  const int o = I->no, v = I->nv;
+  const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2, wzl = I->ov + I->oo, M = S * To;
+  const bool full = I->vvvv_mode == ASCC_VVVV_FULL;
+  Ladder L;
+  L.M = (int)M;
+  L.Mdec = (int)To;
+  L.K = (int)pad_even(Tv);
+  L.A = Tp;
+  L.lda = I->ldT;
+  L.sa2 = M * I->ldT;
+  L.C = Rp;
+  L.ldc = I->ldR;
+  L.sc2 = M * I->ldR;
+  L.ws = I->splitk;
+  L.ws_elems = kSplitKElems;
+  if (lb) L.lb = *lb;
+  L.V = I->V;
+  if (full) {
+    L.N = (int)Tv;
+    L.ldv = I->ldV;
+    L.vrows = I->vv;
+    L.pm = pair_minus(I);
+    HIPCHK(gemm_f64_ladder(L, s));
+    L.pm = nullptr;
+    L.V = I->G;
+    L.N = (int)wzl;
+    L.ldv = I->ldT;
+    L.sv2 = wzl * I->ldT;
+    L.C = Rp + Tv;
+    if (lb) L.lb.sv = slot_stride(I->G) / 8;
+  } else {
+    L.N = (int)(Tv + wzl);
+    L.ldv = I->ldT;
+    L.sv2 = (Tv + wzl) * I->ldT;
+  }
+  HIPCHK(gemm_f64_ladder(L, s));
+  return ASCC_OK;
+}
+
+// The ladders of S states on this integral set into the stacked rows Tp, Rp (Tpf in low precision).
+// Phases: pp_pack (pair packing and low-precision operands), pp_ladder (the contraction launch, nothing
+// else), pp_unpack (back to [i][j][a][b], where it is done).
+int pp_ladder_states(ascc_ints* I, int S, const double* const* t2s, double* Tp, double* Rp, float* Tpf,
+                     hipStream_t s) {
   const int o = I->no, v = I->nv;
   const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2;
-  const long M = S * To;
+  const long M = S * To, ldT = I->ldT;
   const bool lowp = I->cur_prec != ASCC_PREC_FP64;
-  const bool full = I->vvvv_mode == ASCC_VVVV_FULL;
   const long ld = lowp_ld(Tv);
-  // Phases: pp_pack (pair packing and low-precision operands), pp_ladder (the one contraction
-  // launch, nothing else), pp_unpack (scatter back to [i][j][a][b]).
   phase_begin(I, PH_PACK, s);
-  const double dscale = full ? 0.5 : 1.0;  // full: the combined diagonal V+ is doubled
-  for (int k = 0; k < S; ++k) HIPCHK(pack_tpm(Tp + k * To * Tv, Tp + (M + k * To) * Tv, t2s[k], o, v, dscale, s));
-  if (lowp) HIPCHK(shadow(I, Tpf, Tp, 2 * M, Tv, s));
+  for (int k = 0; k < S; ++k) HIPCHK(pack_tpm(Tp + k * To * ldT, Tp + (M + k * To) * ldT, ldT, t2s[k], o, v, s));
+  if (lowp) HIPCHK(shadow_pairs(I, Tpf, Tp, 2 * M, s));
   phase_end(I, s);
   phase_begin(I, PH_LADDER, s);
   if (lowp) {  // no split-K: a state's rows are summed in the same order whatever S is
-    GemmLP g = lp_nt(I, M, Tv, Tv, 2, Tpf, ld, M * ld, I->Vf, ld, Tv * ld, Rp, Tv, M * Tv);
+    GemmLP g = lp_nt(I, M, Tv, Tv, 2, Tpf, ld, M * ld, I->Vf, ld, Tv * ld, Rp, I->ldR, M * I->ldR);
     g.ws = nullptr;
     g.m_dec = (int)To;  // the kernel choice of one state's rows
     HIPCHK(gemm_lowp(g, s));
+  } else {
+    const int rc = ladder_launch(I, S, Tp, Rp, nullptr, s);
+    if (rc) return rc;
   }
-  else if (full)
-    HIPCHK(gemm_f64_ladder((int)M, (int)Tv, Tp, I->V, I->vv, I->vv, pair_minus(I), Rp, s));
-  else
-    HIPCHK(gemm_f64_ladder((int)M, (int)Tv, Tp, I->V, Tv, 0, nullptr, Rp, s));
-  phase_end(I, s);
-  phase_begin(I, PH_UNPACK, s);
-  for (int k = 0; k < S; ++k) HIPCHK(unpack_rpm(RLs[k], Rp + k * To * Tv, Rp + (M + k * To) * Tv, o, v, s));
   phase_end(I, s);
   return ASCC_OK;
 }
 
 // The ladder of every slot of a batch, each against its own integral set: the pair packing per
-// slot, one contraction launch over the slots, the unpacking per slot.
+// slot, one contraction launch over the slots.
 int pp_ladder_slots(ascc_ints* I, const double* t2, hipStream_t s) {
   const int o = I->no, v = I->nv;
   const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2, M = To;
   const bool lowp = I->cur_prec != ASCC_PREC_FP64;
-  const bool full = I->vvvv_mode == ASCC_VVVV_FULL;
   const long ld = lowp_ld(Tv);
   phase_begin(I, PH_PACK, s);
-  EACH_SLOT HIPCHK(pack_tpm(S(I->Tp), S(I->Tp) + M * Tv, S(t2), o, v, full ? 0.5 : 1.0, s));
-  if (lowp) HIPCHK(shadow(I, I->Tpf, I->Tp, 2 * M, Tv, s));
+  EACH_SLOT HIPCHK(pack_tpm(S(I->Tp), S(I->Tp) + M * I->ldT, I->ldT, S(t2), o, v, s));
+  if (lowp) EACH_SLOT HIPCHK(shadow_pairs(I, S(I->Tpf), S(I->Tp), 2 * M, s));
   phase_end(I, s);
   phase_begin(I, PH_LADDER, s);
   if (lowp) {
-    GemmLP g = lp_nt(I, M, Tv, Tv, 2, I->Tpf, ld, M * ld, I->Vf, ld, Tv * ld, I->Rp, Tv, M * Tv);
+    GemmLP g = lp_nt(I, M, Tv, Tv, 2, I->Tpf, ld, M * ld, I->Vf, ld, Tv * ld, I->Rp, I->ldR, M * I->ldR);
     g.ws = nullptr;
     HIPCHK(glp(g, s));
   } else {
@@ -695,22 +753,16 @@ int pp_ladder_slots(ascc_ints* I, const double* t2, hipStream_t s) {
     lb.sv = slot_stride(I->V) / 8;
     lb.sc = slot_stride(I->Rp) / 8;
     if (g_sb->bad) return fail(ASCC_E_STATE, "ladder operands outside the batch's slot ranges");
-    if (full)
-      HIPCHK(gemm_f64_ladder((int)M, (int)Tv, I->Tp, I->V, I->vv, I->vv, pair_minus(I), I->Rp, s, lb));
-    else
-      HIPCHK(gemm_f64_ladder((int)M, (int)Tv, I->Tp, I->V, Tv, 0, nullptr, I->Rp, s, lb));
+    const int rc = ladder_launch(I, 1, I->Tp, I->Rp, &lb, s);
+    if (rc) return rc;
   }
-  phase_end(I, s);
-  phase_begin(I, PH_UNPACK, s);
-  EACH_SLOT HIPCHK(unpack_rpm(S(I->RL), S(I->Rp), S(I->Rp) + M * Tv, o, v, s));
   phase_end(I, s);
   return ASCC_OK;
 }
 
 int pp_ladder(ascc_ints* I, const double* t2, hipStream_t s) {
   if (nslots() > 1) return pp_ladder_slots(I, t2, s);
-  double* RL = I->RL;
-  return pp_ladder_states(I, 1, &t2, &RL, I->Tp, I->Rp, I->Tpf, s);
+  return pp_ladder_states(I, 1, &t2, I->Tp, I->Rp, I->Tpf, s);
 }
 
 size_t ints_footprint(long o, long v, long Q, int precision, int mode) {
@@ -750,7 +802,12 @@ int plascc_remove(ascc_ints* I, const double* t2, double* RL, hipStream_t s) {
   HIPCHK(mixed_doubles(tM, t2, o, v, h, pa, s));
   // --- hole-hole ladder.  tA: the occupied-cross rows of t^M; tC: the virtual-cross columns of the
   // other rows
-  const double* G = I->Gwz + ov * vv;  // (kc|ld) at [k*o + l][c*v + d]
+  double* G = I->XZ;  // (kc|ld) at [k*o + l][c*v + d], from K[kd,lc] (the rings are done with XZ)
+  {
+    int d[4] = {o, o, v, v};
+    Perm4In x = pin(I->KL, (long)v * ov, v, 1, ov, 1.0);
+    HIPCHK(permute4(G, d, 0.0, &x, 1, s));
+  }
   double* ZM = I->chi;
   HIPCHK(cross_gather_rows(I->plTa, vv, tM, vv, oo, vv, Xo, false, s));
   HIPCHK(cross_gather_cols(I->plTc, mvp, tM, vv, oo, Xv, &Xo, s));
@@ -845,14 +902,15 @@ int plascc_remove(ascc_ints* I, const double* t2, double* RL, hipStream_t s) {
   return ASCC_OK;
 }
 
-// One state's residual.  RLx == nullptr: the ladder is computed here into I->RL; otherwise RLx
-// already holds this state's particle-particle ladder (from a batched launch).
+// One state's residual.  lad == nullptr: the ladder is computed here into I->Rp; otherwise *lad are this
+// state's rows of a batched ladder launch.
 int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, double* r2, double* e,
-                  double* RLx, hipStream_t s) {
-  double* RL = RLx ? RLx : I->RL;
+                  const LadderRows* lad, hipStream_t s) {
+  double* RL = I->RL;
+  const LadderRows rows = lad ? *lad : own_rows(I);
   const int o = I->no, v = I->nv, Q = I->naux;
   const long n = I->n, nn = n * n, ov = I->ov, oo = I->oo, vv = I->vv, ovov = I->ovov;
-  const long wzl = ov + oo;  // row length of WZ and Gwz
+  const long wzl = ov + oo;  // row length of WZ
   int rc;
 
   // --- T1 dressing of B and of the one-electron operator, dressed Fock matrix
@@ -921,40 +979,90 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   HIPCHK(mm(I, gemm_rm(oo, oo, Q, 1.0, I->Boo, oo, true, I->Boo, oo, false, 0.0, I->G4, oo), s));      // g^_kilj
 
   phase_end(I, s);
-  // --- W_ij[k,b], Z_ij[k,l] in one product against [(kc|bd) | (kc|ld)]
-  phase_begin(I, PH_WZ, s);
+  // --- E-term intermediates F'_bc = F^_bc - sum_Qk N_Q[k,b] B_Q,kc ; F''_kj = F^_kj + sum_Qd B_Q,kd N_Q[j,d]
+  phase_begin(I, PH_N5, s);
+  HIPCHK(mm(I, gemm_rm(v, v, (long)Q * o, 1.0, I->Nq, v, true, I->Bov, v, false, 0.0, I->Abc, v), s));
+  {
+    Gemm g;
+    g.M = o;
+    g.N = o;
+    g.K = v;
+    g.A = I->Bov;
+    g.sam = v;
+    g.sak = 1;
+    g.sar = ov;
+    g.B = I->Nq;
+    g.sbk = 1;
+    g.sbn = v;
+    g.sbr = ov;
+    g.C = I->Bkj;
+    g.scm = o;
+    g.scn = 1;
+    g.nred = Q;
+    HIPCHK(mm(I, g, s));
+  }
+  EACH_SLOT {
+    int d[4] = {v, v, 1, 1};
+    Perm4In x[2] = {pin(S(I->Fh) + o * n + o, n, 1, 0, 0, 1.0), pin(S(I->Abc), v, 1, 0, 0, -1.0)};
+    HIPCHK(permute4(S(I->Fvvp), d, 0.0, x, 2, s));
+    int d2[4] = {o, o, 1, 1};
+    Perm4In y[2] = {pin(S(I->Fh), n, 1, 0, 0, 1.0), pin(S(I->Bkj), o, 1, 0, 0, 1.0)};
+    HIPCHK(permute4(S(I->Foop), d2, 0.0, y, 2, s));
+  }
+  phase_end(I, s);
+
   if (lowp) {
+    // --- W_ij[k,b], Z_ij[k,l] in one product against [(kc|bd) | (kc|ld)]
+    phase_begin(I, PH_WZ, s);
     const long ld = lowp_ld(vv);
     HIPCHK(shadow(I, I->t2f, t2, oo, vv, s));
     HIPCHK(glp(lp_nt(I, oo, wzl, vv, 1, I->t2f, ld, 0, I->GwzTf, ld, 0, I->WZ, wzl, 0), s));
-  } else {
-    HIPCHK(mm(I, gemm_rm(oo, wzl, vv, 1.0, t2, vv, false, I->Gwz, vv, true, 0.0, I->WZ, wzl), s));
+    phase_end(I, s);
+    // --- chi[ij][kl] = g^_kilj + Z_ij[k,l]
+    phase_begin(I, PH_HH, s);
+    EACH_SLOT {
+      int d[4] = {o, o, o, o};
+      const long o2 = oo, o3 = oo * o;
+      Perm4In x[2] = {pin(S(I->G4), o2, 1, o3, o, 1.0), pin(S(I->WZ) + ov, (long)o * wzl, wzl, o, 1, 1.0)};
+      HIPCHK(permute4(S(I->chi), d, 0.0, x, 2, s));
+    }
+    phase_end(I, s);
   }
-
-  phase_end(I, s);
-  // --- chi[ij][kl] = g^_kilj + Z_ij[k,l]
-  phase_begin(I, PH_HH, s);
-  EACH_SLOT {
-    int d[4] = {o, o, o, o};
-    const long o2 = oo, o3 = oo * o;
-    Perm4In x[2] = {pin(S(I->G4), o2, 1, o3, o, 1.0), pin(S(I->WZ) + ov, (long)o * wzl, wzl, o, 1, 1.0)};
-    HIPCHK(permute4(S(I->chi), d, 0.0, x, 2, s));
-  }
-
-  phase_end(I, s);
-  // --- particle-particle ladder over the undressed (ac|bd), plus the hole-hole ladder
-  if (!RLx && (rc = pp_ladder(I, t2, s))) return rc;
-  phase_begin(I, PH_HH, s);
-  if (lowp) {  // RL[ij][ab] += sum_kl chi[ij][kl] t2[kl][ab], with t2 transposed to K = kl contiguous
+  // --- particle-particle ladder over the undressed (ac|bd) (with W/Z in FP64), plus the hole-hole ladder
+  if (!lad && (rc = pp_ladder(I, t2, s))) return rc;
+  const bool pairs = !lowp && I->pl_hole < 0;  // the assembly reads the ladders as pair rows
+  if (lowp) {
+    phase_begin(I, PH_UNPACK, s);
+    EACH_SLOT HIPCHK(unpack_rpm(S(RL), S(rows.Rp), S(rows.Rp) + rows.sr, I->ldR, o, v, s));
+    phase_end(I, s);
+    phase_begin(I, PH_HH, s);
+    // RL[ij][ab] += sum_kl chi[ij][kl] t2[kl][ab], with t2 transposed to K = kl contiguous
     HIPCHK(shadow(I, I->chif, I->chi, oo, oo, s));
     HIPCHK(shadow_t(I, I->t2Tf, t2, vv, vv, oo, s));
     GemmLP g = lp_nt(I, oo, vv, oo, 1, I->chif, loo, 0, I->t2Tf, loo, 0, RL, vv, 0);
     g.beta = 1.0;
     HIPCHK(glp(g, s));
+    phase_end(I, s);
   } else {
-    HIPCHK(mm(I, gemm_rm(oo, vv, oo, 1.0, I->chi, oo, false, t2, vv, false, 1.0, RL, vv), s));
+    // W', chi+- with F'' in it, and R+- += chi+- t+- over the pairs k <= l: a quarter of the products of
+    // the full sum over k, l (and the F'' t2 product rides along)
+    const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2;
+    phase_begin(I, PH_HH, s);
+    EACH_SLOT HIPCHK(wz_chi(S(I->WZ), wzl, S(I->chi), S(I->chi) + To * To, S(rows.Rp) + Tv, S(rows.Rp) + rows.sr + Tv,
+                            I->ldR, S(I->G4), S(I->Foop), S(t1), o, v, s));
+    Gemm g = gemm_rm(To, Tv, To, 1.0, I->chi, To, false, rows.Tp, I->ldT, false, 1.0, rows.Rp, I->ldR);
+    g.sa2 = To * To;
+    g.sb2 = rows.st;
+    g.sc2 = rows.sr;
+    g.nb2 = 2;
+    HIPCHK(mm(I, g, s));
+    phase_end(I, s);
+    if (!pairs) {
+      phase_begin(I, PH_UNPACK, s);
+      EACH_SLOT HIPCHK(unpack_rpm(S(RL), S(rows.Rp), S(rows.Rp) + rows.sr, I->ldR, o, v, s));
+      phase_end(I, s);
+    }
   }
-  phase_end(I, s);
 
   // --- rings: Y1 = Tx K, Y2 = U L (batched pair)
   phase_begin(I, PH_RING_Y, s);
@@ -998,38 +1106,9 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
 
   phase_end(I, s);
   phase_begin(I, PH_N5, s);
-  // --- E term: F'_bc = F^_bc - sum_Qk N_Q[k,b] B_Q,kc ; F''_kj = F^_kj + sum_Qd B_Q,kd N_Q[j,d]
-  HIPCHK(mm(I, gemm_rm(v, v, (long)Q * o, 1.0, I->Nq, v, true, I->Bov, v, false, 0.0, I->Abc, v), s));
-  {
-    Gemm g;
-    g.M = o;
-    g.N = o;
-    g.K = v;
-    g.A = I->Bov;
-    g.sam = v;
-    g.sak = 1;
-    g.sar = ov;
-    g.B = I->Nq;
-    g.sbk = 1;
-    g.sbn = v;
-    g.sbr = ov;
-    g.C = I->Bkj;
-    g.scm = o;
-    g.scn = 1;
-    g.nred = Q;
-    HIPCHK(mm(I, g, s));
-  }
-  EACH_SLOT {
-    int d[4] = {v, v, 1, 1};
-    Perm4In x[2] = {pin(S(I->Fh) + o * n + o, n, 1, 0, 0, 1.0), pin(S(I->Abc), v, 1, 0, 0, -1.0)};
-    HIPCHK(permute4(S(I->Fvvp), d, 0.0, x, 2, s));
-    int d2[4] = {o, o, 1, 1};
-    Perm4In y[2] = {pin(S(I->Fh), n, 1, 0, 0, 1.0), pin(S(I->Bkj), o, 1, 0, 0, 1.0)};
-    HIPCHK(permute4(S(I->Foop), d2, 0.0, y, 2, s));
-  }
   // EM = sum_c t_ij^ac F'_bc
   HIPCHK(mm(I, gemm_rm(oo * v, v, v, 1.0, t2, v, false, I->Fvvp, v, true, 0.0, I->EM, v), s));
-  {  // EM[i][j][ab] -= sum_k F''_kj t_ik^ab   (batched over i)
+  if (lowp) {  // EM[i][j][ab] -= sum_k F''_kj t_ik^ab   (batched over i)
     Gemm g;
     g.M = o;
     g.N = vv;
@@ -1050,7 +1129,7 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     g.nb2 = o;
     HIPCHK(mm(I, g, s));
   }
-  {  // W'_ij[k,b] = W_ij[k,b] - 1/2 sum_l Z_ij[k,l] t_l^b   (batched over ij, in place)
+  if (lowp) {  // W'_ij[k,b] = W_ij[k,b] - 1/2 sum_l Z_ij[k,l] t_l^b   (batched over ij, in place)
     Gemm g;
     g.M = o;
     g.N = v;
@@ -1145,7 +1224,8 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   phase_end(I, s);
   // --- doubles assembly and energy
   phase_begin(I, PH_ASSEMBLE, s);
-  EACH_SLOT HIPCHK(assemble_r2(S(r2), S(I->G1), S(RL), S(I->EM), S(I->P), S(I->P) + ovov, o, v, s));
+  EACH_SLOT HIPCHK(assemble_r2(S(r2), S(I->G1), pairs ? S(rows.Rp) : S(RL), S(I->EM), S(I->P), S(I->P) + ovov, o, v, s,
+                               pairs ? S(rows.Rp) + rows.sr : nullptr, I->ldR));
   phase_end(I, s);
   phase_begin(I, PH_ENERGY, s);
   EACH_SLOT HIPCHK(energy(S(e), S(I->partial), S(t1), S(t2), S(I->Lijab), S(I->fov), o, v, s));
@@ -1251,7 +1331,9 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
     Perm4In z = pin(I->KL + ovov, si, sj, sa, sb, 1.0);
     HIPCHK(permute4(I->Lijab, d2, 0.0, &z, 1, s));
   }
-  // Gwz: (kc|bd) at [k*v + b][c][d] from a temporary [(k,c)][(b,d)] product (rows K-contiguous)
+  // G+- (and its low-precision shadow, unpacked) from a temporary [(k,c)][(b,d)] product
+  const bool full = I->vvvv_mode == ASCC_VVVV_FULL;
+  const long Tv = (long)v * (v + 1) / 2, vhalf = (Tv + wzl) * I->ldT;  // packed: elements of one half
   {
     double* tmp = nullptr;
     Pool tmp_alloc = sub_pool(I->pool);
@@ -1259,15 +1341,11 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
     if (rc2) return rc2;
     hipError_t e = mm(I, gemm_rm(ov, vv, Q, 1.0, I->BovT, Q, false, I->Bvv, Q, true, 0.0, tmp, vv), s);
     if (e == hipSuccess) {
-      int d[4] = {o, v, v, v};  // Gwz[k][b][c][d] <- tmp[k][c][b][d]: d contiguous on both sides
-      Perm4In x = pin(tmp, (long)v * vv, v, vv, 1, 1.0);
-      e = permute4(I->Gwz, d, 0.0, &x, 1, s);
+      double* gp = full ? I->G : I->V + Tv * I->ldT;
+      e = pack_gwz(gp, gp + (full ? wzl * I->ldT : vhalf), I->ldT, tmp, Jov, o, v, s);
     }
-    if (e == hipSuccess) {
-      int d[4] = {o, o, v, v};  // Gwz[ov + k*o + l][c][d] <- J[k][c][l][d]
-      Perm4In x = pin(Jov, (long)v * o * v, v, (long)o * v, 1, 1.0);
-      e = permute4(I->Gwz + ov * vv, d, 0.0, &x, 1, s);
-    }
+    if (e == hipSuccess && I->precision != ASCC_PREC_FP64)
+      e = to_lowp_gwz(lowp_kind(I), I->GwzTf, lowp_ld(vv), tmp, Jov, o, v, s);
     if (e == hipSuccess && !tmp_alloc.base) e = d_sync(s);  // carved temporaries need no wait
     free_all(tmp_alloc);
     if (e != hipSuccess) {
@@ -1280,7 +1358,6 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
   // operands are rows of the [a][c][Q] B_vv: K-contiguous.  The packed halves read only the slabs
   // with b >= a (V[a][b][d][c] = (ad|bc) is the same slab), so a packed build starts b at the
   // chunk's first a; the full matrix needs every b.
-  const bool full = I->vvvv_mode == ASCC_VVVV_FULL;
   auto vslab = [&](int a0, int na, double* dst) -> hipError_t {
     const int b0 = full ? 0 : a0;
     Gemm g;
@@ -1316,7 +1393,9 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
   for (int a0 = 0; a0 < v && e == hipSuccess; a0 += (int)ac) {
     const int na = (int)std::min<long>(ac, v - a0);
     e = vslab(a0, na, tmp);
-    if (e == hipSuccess) e = full ? pack_full(I->V, tmp, a0, a0 + na, v, s) : pack_vvvv(I->V, tmp, a0, a0 + na, v, s);
+    if (e == hipSuccess) 
+      e = full ? pack_full(I->V, I->ldV, tmp, a0, a0 + na, v, s)
+               : pack_vvvv(I->V, I->V + vhalf, I->ldT, tmp, a0, a0 + na, v, s);
   }
   if (e == hipSuccess && !tmp_alloc.base) e = d_sync(s);  // carved temporaries need no wait
   free_all(tmp_alloc);
@@ -1327,26 +1406,22 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
   return ASCC_OK;
 }
 
-// FP32 shadows of the constant operands: (ac|bd), [(kc|bd)|(kc|ld)] as [n][(cd)], K|L.
+// Low-precision shadows of the constant operands: V+-, K|L, B_kc ([(kc|bd)|(kc|ld)]: build_constants).
 int build_lowp_shadows(ascc_ints* I, hipStream_t s) {
   const long vv = I->vv, ov = I->ov, oo = I->oo, wzl = ov + oo;
   const long Tv = (long)I->nv * (I->nv + 1) / 2;
 
   if (I->vvvv_mode == ASCC_VVVV_FULL) {  // the packed halves, formed from the full matrix
     const int prec = (I->cur_prec == ASCC_PREC_BF16X3) ? kPrecBF16x3 : kPrecFP32;
-    HIPCHK(to_lowp_pm(prec, I->Vf, lowp_ld(Tv), I->V, vv, vv, pair_minus(I), Tv, s));
+    HIPCHK(to_lowp_pm(prec, I->Vf, lowp_ld(Tv), I->V, I->ldV, vv, pair_minus(I), Tv, s));
   } else {
-    HIPCHK(shadow(I, I->Vf, I->V, 2 * Tv, Tv, s));
+    HIPCHK(shadow_pairs(I, I->Vf, I->V, Tv, s));
+    HIPCHK(shadow_pairs(I, I->Vf + Tv * lowp_ld(Tv), I->V + (Tv + wzl) * I->ldT, Tv, s));
   }
   HIPCHK(shadow(I, I->KLf, I->KL, 2 * ov, ov, s));
   const long Q = I->naux;
   HIPCHK(shadow(I, I->BovTf, I->BovT, ov, Q, s));      // B_kc (undressed by T1) as [kc][Q]
   HIPCHK(shadow(I, I->Bovf, I->Bov, Q, ov, s));         // and as [Q][kc]
-  const hipError_t e = shadow(I, I->GwzTf, I->Gwz, wzl, vv, s);  // Gwz rows are K-contiguous already
-  if (e != hipSuccess) {
-    if (!(bounds_checking() && e == hipErrorInvalidValue)) set_error(std::string("FP32 shadows: ") + hipGetErrorString(e));
-    return ASCC_E_HIP;
-  }
   return ASCC_OK;
 }
 
@@ -1364,7 +1439,7 @@ int check_shape(int no, int nv, int naux) {
 bool is_constant(double* ascc_ints::*m) {
   return m == &ascc_ints::B || m == &ascc_ints::h || m == &ascc_ints::eps || m == &ascc_ints::fov ||
          m == &ascc_ints::e0 || m == &ascc_ints::Bov || m == &ascc_ints::KL || m == &ascc_ints::Lijab ||
-         m == &ascc_ints::Gwz || m == &ascc_ints::BovT || m == &ascc_ints::V || m == &ascc_ints::pairtab ||
+         m == &ascc_ints::G || m == &ascc_ints::BovT || m == &ascc_ints::V || m == &ascc_ints::pairtab ||
          m == &ascc_ints::Tp || m == &ascc_ints::Rp;
 }
 bool is_constant(float* ascc_ints::*m) {
@@ -1383,10 +1458,9 @@ size_t work_block_bytes(long o, long v, long Q, int precision, int mode) {
 // Stacked ladder operands and results for max_states states, then `group` work blocks (group > 1).
 size_t batch_footprint(long o, long v, long Q, int precision, int mode, long max_states, int group) {
   const long To = o * (o + 1) / 2, Tv = v * (v + 1) / 2;
-  const long rows = 2 * To * Tv, lrows = 2 * To * lowp_ld(Tv);
-  size_t off = align_up(sizeof(double) * (size_t)(max_states * rows));
-  off += align_up(sizeof(double) * (size_t)(max_states * rows));
-  off += align_up(sizeof(double) * (size_t)(max_states * o * o * v * v));
+  const long trows = 2 * To * pad_line(Tv), rrows = 2 * To * pad_line(Tv + o * v + o * o), lrows = 2 * To * lowp_ld(Tv);
+  size_t off = align_up(sizeof(double) * (size_t)(max_states * trows));
+  off += align_up(sizeof(double) * (size_t)(max_states * rrows));
   if (precision != ASCC_PREC_FP64) off += align_up(sizeof(float) * (size_t)(max_states * lrows));
   if (group > 1) off += (size_t)group * work_block_bytes(o, v, Q, precision, mode);
   return off;
@@ -1404,17 +1478,15 @@ int batch_reserve_impl(ascc_ints* I, int max_states, int group, void* ws, size_t
   I->group = 1;
   I->group_base = nullptr;
   I->group_block = 0;
-  I->Tp_all = I->Rp_all = I->RL_all = nullptr;
+  I->Tp_all = I->Rp_all = nullptr;
   I->Tpf_all = nullptr;
   if (ws) {
     I->batch.base = static_cast<char*>(ws);
     I->batch.size = ws_bytes;
   }
-  const long o = I->no, v = I->nv, To = o * (o + 1) / 2, Tv = v * (v + 1) / 2;
-  const long rows = 2 * To * Tv, lrows = 2 * To * lowp_ld(Tv);
-  int rc = dalloc(I->batch, &I->Tp_all, (size_t)(max_states * rows));
-  if (!rc) rc = dalloc(I->batch, &I->Rp_all, (size_t)(max_states * rows));
-  if (!rc) rc = dalloc(I->batch, &I->RL_all, (size_t)(max_states * I->oovv));
+  const long o = I->no, v = I->nv, To = o * (o + 1) / 2, Tv = v * (v + 1) / 2, lrows = 2 * To * lowp_ld(Tv);
+  int rc = dalloc(I->batch, &I->Tp_all, (size_t)(max_states * 2 * To * I->ldT));
+  if (!rc) rc = dalloc(I->batch, &I->Rp_all, (size_t)(max_states * 2 * To * I->ldR));
   if (!rc && I->precision != ASCC_PREC_FP64) rc = dalloc(I->batch, &I->Tpf_all, (size_t)(max_states * lrows));
   if (!rc && group > 1) {
     I->group_block = work_block_bytes(o, v, I->naux, I->precision, I->vvvv_mode);
@@ -1430,14 +1502,14 @@ int batch_reserve_impl(ascc_ints* I, int max_states, int group, void* ws, size_t
   return ASCC_OK;
 }
 
-// The residual terms other than the pp ladder (already in RL) of n states as one batched pass: the
-// handle's work arrays are pointed at the first of the group work blocks for the pass (the states'
-// arrays sit one block apart), the shared integrals are used by every state, and the states' own
-// arrays are evenly spaced (t1[k] = t1[0] + k (t1[1] - t1[0]), likewise t2, r1, r2; e[k]; RL[k] one
-// o^2 v^2 block apart).
+// The residual terms other than the pp ladder (already in the stacked rows lad) of n states as one
+// batched pass: the handle's work arrays are pointed at the first of the group work blocks for the pass
+// (the states' arrays sit one block apart), the shared integrals are used by every state, and the states'
+// own arrays are evenly spaced (t1[k] = t1[0] + k (t1[1] - t1[0]), likewise t2, r1, r2; e[k]; the ladder
+// rows T(o) rows apart in both halves).
 int residual_group(ascc_ints* I, int n, int nstates, const double* const* t1, const double* const* t2,
-                   double* const* r1, double* const* r2, double* e, double* RL, hipStream_t s) {
-  if (n == 1) return residual_core(I, t1[0], t2[0], r1[0], r2[0], e, RL, s);
+                   double* const* r1, double* const* r2, double* e, const LadderRows& lad, hipStream_t s) {
+  if (n == 1) return residual_core(I, t1[0], t2[0], r1[0], r2[0], e, &lad, s);
   const long o = I->no, v = I->nv, Q = I->naux;
   // point every work array at block 0 (restored below)
   std::vector<std::pair<double* ascc_ints::*, double*>> saved;
@@ -1473,7 +1545,9 @@ int residual_group(ascc_ints* I, int n, int nstates, const double* const* t1, co
   add(r1[0], sizeof(double) * I->ov, step((const void* const*)r1));
   add(r2[0], sizeof(double) * I->oovv, step((const void* const*)r2));
   add(e, sizeof(double), (long)sizeof(double));
-  add(RL, sizeof(double) * I->oovv, (long)(sizeof(double) * I->oovv));
+  const long trow = 8 * (o * (o + 1) / 2) * I->ldT, rrow = 8 * (o * (o + 1) / 2) * I->ldR;  // bytes of a state's rows
+  add(lad.Tp, trow, trow);
+  add(lad.Rp, rrow, rrow);
   for (const auto& item : ints_plan(o, v, Q, I->vvvv_mode))  // shared integrals: stride 0
     if (is_constant(item.first) && I->*(item.first))
       add(I->*(item.first), std::max<size_t>((size_t)item.second, 1) * sizeof(double), 0);
@@ -1484,7 +1558,7 @@ int residual_group(ascc_ints* I, int n, int nstates, const double* const* t1, co
   int rc;
   {
     SlotBatchScope scope(&sb);
-    rc = residual_core(I, t1[0], t2[0], r1[0], r2[0], e, RL, s);
+    rc = residual_core(I, t1[0], t2[0], r1[0], r2[0], e, &lad, s);
   }
   for (auto& x : saved) I->*(x.first) = x.second;
   for (auto& x : savedf) I->*(x.first) = x.second;
@@ -1766,6 +1840,10 @@ static int build_ints_impl(const double* d_B, const double* d_fock, int fock_is_
   I->vv = v * v;
   I->ovov = I->ov * I->ov;
   I->oovv = I->oo * I->vv;
+  const long Tv = v * (v + 1) / 2;
+  I->ldT = pad_line(Tv);
+  I->ldV = pad_line(I->vv);
+  I->ldR = pad_line(Tv + I->ov + I->oo);
   if (ws) {
     if ((reinterpret_cast<uintptr_t>(ws) & (kAlign - 1)) != 0) {
       delete I;
@@ -1889,17 +1967,22 @@ int ascc_residual_batch(ascc_ints* I, int nstates, const double* const* t1, cons
     user.add(r2[k], sizeof(double) * I->oovv);
   }
   user.add(e, sizeof(double) * nstates);
-  std::vector<double*> RLs(nstates);
-  for (int k = 0; k < nstates; ++k) RLs[k] = I->RL_all + (long)k * I->oovv;
-  int rc = pp_ladder_states(I, nstates, t2, RLs.data(), I->Tp_all, I->Rp_all, I->Tpf_all, s);
+  int rc = pp_ladder_states(I, nstates, t2, I->Tp_all, I->Rp_all, I->Tpf_all, s);
   if (rc) return rc;
+  const long To = (long)I->no * (I->no + 1) / 2, tstate = To * I->ldT, rstate = To * I->ldR;
+  auto rows = [&](int k) {
+    return LadderRows{I->Tp_all + k * tstate, I->Rp_all + k * rstate, nstates * tstate, nstates * rstate};
+  };
   if (!grouped) {
-    for (int k = 0; k < nstates && !rc; ++k) rc = residual_core(I, t1[k], t2[k], r1[k], r2[k], e + k, RLs[k], s);
+    for (int k = 0; k < nstates && !rc; ++k) {
+      const LadderRows lr = rows(k);
+      rc = residual_core(I, t1[k], t2[k], r1[k], r2[k], e + k, &lr, s);
+    }
     return rc;
   }
   for (int g0 = 0; g0 < nstates && !rc; g0 += I->group)
     rc = residual_group(I, std::min(I->group, nstates - g0), nstates, t1 + g0, t2 + g0, r1 + g0, r2 + g0, e + g0,
-                        RLs[g0], s);
+                        rows(g0), s);
   return rc;
 }
 

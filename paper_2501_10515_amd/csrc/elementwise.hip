@@ -94,18 +94,27 @@ __global__ __launch_bounds__(kThreads) void permute4_tiled_kernel(P4 p, int t, i
 // along), keeps both tiles in LDS and writes R2[ij] on A x B and R2[ji] on B x A, so each input
 // element is read once.  For i = j only A <= B runs; with A = B both tiles are the same block and
 // the two writes of an element carry the same value.
-__device__ __forceinline__ double assemble_x(const double* __restrict__ g1, const double* __restrict__ rl,
-                                             const double* __restrict__ em, const double* __restrict__ p1,
-                                             const double* __restrict__ p2, long x, long iajb, long jaib) {
-  return 0.5 * (g1[iajb] + rl[x]) + em[x] - 0.5 * p1[iajb] + 0.5 * p2[iajb] - p1[jaib];
+__device__ __forceinline__ double assemble_x(const double* __restrict__ g1, const double* __restrict__ em,
+                                             const double* __restrict__ p1, const double* __restrict__ p2, double rl,
+                                             long x, long iajb, long jaib) {
+  return 0.5 * (g1[iajb] + rl) + em[x] - 0.5 * p1[iajb] + 0.5 * p2[iajb] - p1[jaib];
 }
 
+// Pair index of i <= j among n: pidx(i, j) = i*n - i*(i-1)/2 + (j - i)  (row-major upper triangle).
+__device__ __forceinline__ long pidx(long i, long j, long n) { return i * n - i * (i - 1) / 2 + (j - i); }
+
+// PAIRS: the ladders come as pair rows R+-[p(i,j)][p(a,b)] (rows at stride ldr; RL_ij^ab = R+ + R- for
+// a <= b, R+ - R- for a > b) instead of RL[i][j][a][b]: each block reads its 32 x 32 pair elements once,
+// along the row, and the transposed block takes them through LDS, so no pass unpacks them.
+template <bool PAIRS>
 __global__ __launch_bounds__(kThreads) void assemble_r2_kernel(double* __restrict__ r2, const double* __restrict__ g1,
                                                               const double* __restrict__ rl,
+                                                              const double* __restrict__ rminus, long ldr,
                                                               const double* __restrict__ em,
                                                               const double* __restrict__ p1,
                                                               const double* __restrict__ p2, int o, int v) {
   __shared__ double t1[32][33], t2[32][33];  // t1[a - a0][b - b0] = X(i,j,a,b), t2[b - b0][a - a0] = X(j,i,b,a)
+  __shared__ double up[PAIRS ? 32 : 1][33], um[PAIRS ? 32 : 1][33];  // R+ + R-, R+ - R- of the block's pairs
   const int tv = (v + 31) / 32;
   const int ta = blockIdx.y / tv, tb = blockIdx.y % tv;
   // pair p = j (j + 1) / 2 + i, i <= j
@@ -119,20 +128,44 @@ __global__ __launch_bounds__(kThreads) void assemble_r2_kernel(double* __restric
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
   auto ov = [&](int q, int x, int r, int y) -> long { return ((long)(q * v + x) * o + r) * v + y; };
   const long ij = ((long)i * o + j) * v * v, ji = ((long)j * o + i) * v * v;
+  if constexpr (PAIRS) {
+    const long row = pidx(i, j, o) * ldr;
+    const int c0 = min(a0, b0), d0 = max(a0, b0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int r = ty + 8 * k, c = c0 + r, d = d0 + tx;
+      if (c <= d && d < v) {
+        const long q = row + pidx(c, d, v);
+        const double x = rl[q], y = rminus[q];
+        up[r][tx] = x + y;
+        um[r][tx] = x - y;
+      }
+    }
+    __syncthreads();
+  }
+  // RL_ij^ab of a = a0 + x, b = b0 + y
+  auto ladder = [&](int x, int y, long idx) -> double {
+    if constexpr (PAIRS) {
+      if (a0 < b0 || (a0 == b0 && x <= y)) return up[x][y];
+      return um[y][x];
+    } else {
+      return rl[idx];
+    }
+  };
   double x1[4], x2[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const int r = ty + 8 * k;
     {  // X(i,j,a,b), a = a0 + r, b = b0 + tx: along b
       const int a = a0 + r, b = b0 + tx;
-      x1[k] = (a < v && b < v) ? assemble_x(g1, rl, em, p1, p2, ij + (long)a * v + b, ov(i, a, j, b), ov(j, a, i, b))
-                               : 0.0;
+      const long x = ij + (long)a * v + b;
+      x1[k] = (a < v && b < v) ? assemble_x(g1, em, p1, p2, ladder(r, tx, x), x, ov(i, a, j, b), ov(j, a, i, b)) : 0.0;
       t1[r][tx] = x1[k];
     }
     {  // X(j,i,b,a), b = b0 + r, a = a0 + tx: along a
       const int b = b0 + r, a = a0 + tx;
-      x2[k] = (a < v && b < v) ? assemble_x(g1, rl, em, p1, p2, ji + (long)b * v + a, ov(j, b, i, a), ov(i, b, j, a))
-                               : 0.0;
+      const long x = ji + (long)b * v + a;
+      x2[k] = (a < v && b < v) ? assemble_x(g1, em, p1, p2, ladder(tx, r, x), x, ov(j, b, i, a), ov(i, b, j, a)) : 0.0;
       t2[r][tx] = x2[k];
     }
   }
@@ -596,27 +629,152 @@ __global__ __launch_bounds__(kThreads) void update_stage3(double* t1, double* t2
 // ---------------------------------------------------------------------------------------
 // Pair packing for the particle-particle ladder.
 //
-// Pair index of i <= j among n: pidx(i, j) = i*n - i*(i-1)/2 + (j - i)  (row-major upper triangle).
-__device__ __forceinline__ long pidx(long i, long j, long n) { return i * n - i * (i - 1) / 2 + (j - i); }
+// Rows of symmetric and antisymmetric halves over the pairs c <= d of a v x v block M(c, d) at row stride
+// sc: plus[p(c,d)] = f (M(c,d) + M(d,c)), minus[p(c,d)] = f (M(c,d) - M(d,c)) for c < d, and M(c,c), 0 on
+// the diagonal; columns T(v) .. ldo - 1 are zeroed.  The block of grid column x and its output row:
+//   kPackT   t+-: the pairs i <= j of t2 (f = 1/2), row p(i,j)
+//   kPackV   V+-: W[a - a0][b][.][.] of (ac|bd) for a in [a0, a1), b >= a, row p(a,b)
+//   kPackG   G+-: (kc|bd) = W[k][c][b][d], row k*v + b of the rows behind V+-
+//   kPackGo  G+-: (kc|ld) = W[k][c][l][d], row ov + k*o + l of the same
+// One workgroup per block row and 32 x 32 tile pair (C <= D): both tiles are read along their rows, the
+// transposed one through LDS, and both outputs written along theirs (o20 v180: t+- 48 -> 15 us).
+enum { kPackT, kPackV, kPackG, kPackGo };
+struct PackP {
+  double *plus, *minus;
+  long ldo;
+  const double* src;
+  int mode, o, v, a0;
+};
+__global__ __launch_bounds__(kThreads) void pack_halves_kernel(PackP p) {
+  __shared__ double tile[32][33];
+  const int o = p.o, v = p.v, nblk = (v + 31) / 32;
+  const long vv = (long)v * v, Tv = (long)v * (v + 1) / 2, y = blockIdx.x;
+  long base, sc = v, row;
+  if (p.mode == kPackT) {
+    int i = 0;
+    long rem = y;
+    while (rem >= o - i) {
+      rem -= o - i;
+      ++i;
+    }
+    base = ((long)i * o + i + rem) * vv;
+    row = y;
+  } else if (p.mode == kPackV) {
+    const int a = p.a0 + (int)(y / v), b = (int)(y % v);
+    if (b < a) return;
+    base = y * vv;
+    row = pidx(a, b, v);
+  } else if (p.mode == kPackG) {
+    base = y / v * v * vv + y % v * v;
+    sc = vv;
+    row = y;
+  } else {
+    sc = (long)o * v;
+    base = y / o * v * sc + y % o * v;
+    row = (long)o * v + y;
+  }
+  const double* M = p.src + base;
+  double* plus = p.plus + row * p.ldo;
+  double* minus = p.minus + row * p.ldo;
+  if (blockIdx.y == 0)
+    for (long x = Tv + threadIdx.x; x < p.ldo; x += kThreads) plus[x] = minus[x] = 0.0;
+  int C = 0, rem = blockIdx.y;  // tile pair (C, D), C <= D
+  while (rem >= nblk - C) {
+    rem -= nblk - C;
+    ++C;
+  }
+  const int c0 = 32 * C, d0 = 32 * (C + rem);
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int d = d0 + ty + 8 * k, c = c0 + tx;
+    if (d < v && c < v) tile[ty + 8 * k][tx] = M[d * sc + c];
+  }
+  __syncthreads();
+  const double f = p.mode == kPackT ? 0.5 : 1.0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int c = c0 + ty + 8 * k, d = d0 + tx;
+    if (c > d || d >= v) continue;
+    const double a = M[c * sc + d], b = tile[tx][ty + 8 * k];
+    const long q = pidx(c, d, v);
+    plus[q] = (c == d) ? a : f * (a + b);
+    minus[q] = (c == d) ? 0.0 : f * (a - b);
+  }
+}
 
-// t+-[p(i,j)][p(c,d)] for i <= j, c <= d:
-//   t+ = (t_ij^cd + t_ij^dc)/2 (c < d), dscale * t_ij^cc (c = d);  t- = (t_ij^cd - t_ij^dc)/2 (c < d), 0 (c = d).
-__global__ __launch_bounds__(kThreads) void pack_tpm_kernel(double* __restrict__ tplus, double* __restrict__ tminus,
-                                                           const double* __restrict__ t2, int o, int v, double dscale) {
-  const int i = blockIdx.y / o, j = blockIdx.y % o;
-  if (i > j) return;
-  const long Tv = (long)v * (v + 1) / 2, vv = (long)v * v;
-  const double* src = t2 + ((long)i * o + j) * vv;
-  const long p = pidx(i, j, o);
-  double* plus = tplus + p * Tv;
-  double* minus = tminus + p * Tv;
-  for (long x = blockIdx.x * (long)blockDim.x + threadIdx.x; x < vv; x += (long)gridDim.x * blockDim.x) {
-    const int c = x / v, d = x % v;
-    if (c > d) continue;
-    const double a = src[x], b = src[(long)d * v + c];
-    const long k = pidx(c, d, v);
-    plus[k] = (c == d) ? dscale * a : 0.5 * (a + b);
-    minus[k] = (c == d) ? 0.0 : 0.5 * (a - b);
+// From the pair rows Rw+-[p(i,j)][m] of W/Z (m = k*v + b: W_ij[k,b] = sum_cd (kc|bd) t_ij^cd, m = ov + k*o + l:
+// Z_ij[k,l] = sum_cd (kc|ld) t_ij^cd; X_ij = X+ + X-, X_ji = X+ - X-), with rows at stride ldr:
+//   wp[ij][k][b] = W_ij[k,b] - 1/2 sum_l Z_ij[k,l] t1[l][b]   (rows at stride ldw)
+//   chi+-[p(i,j)][p(k,l)] = c_kl +- c_lk (k < l), c_kk and 0 (k = l), where
+//   c_kl = g^_kilj + Z_ij[k,l] - [k = i] F''_lj - [l = j] F''_ki
+// (g4[k][i][l][j] = g^_kilj; the F'' part of the E term joins the hole-hole ladder, which sums c_kl t_kl^ab).
+// One workgroup per pair i <= j and eight k; a thread per column b keeps the sixteen sums of ij and ji.
+constexpr int kWzRows = 8;
+__global__ __launch_bounds__(kThreads) void wz_chi_kernel(double* __restrict__ wp, long ldw, double* __restrict__ chip,
+                                                         double* __restrict__ chim, const double* __restrict__ rp,
+                                                         const double* __restrict__ rm, long ldr,
+                                                         const double* __restrict__ g4, const double* __restrict__ foo,
+                                                         const double* __restrict__ t1, int o, int v) {
+  extern __shared__ double z[];  // [2][kWzRows][o]: Z_ij and Z_ji of this workgroup's k
+  int i = 0, rem = blockIdx.x;
+  while (rem >= o - i) {
+    rem -= o - i;
+    ++i;
+  }
+  const int j = i + rem, k0 = blockIdx.y * kWzRows, nk = min(kWzRows, o - k0);
+  const long ov = (long)o * v, To = (long)o * (o + 1) / 2;
+  const double* xp = rp + blockIdx.x * ldr;
+  const double* xm = rm + blockIdx.x * ldr;
+  for (int x = threadIdx.x; x < kWzRows * o; x += kThreads) {
+    double zp = 0.0, zm = 0.0;
+    if (x < nk * o) {
+      zp = xp[ov + (long)k0 * o + x];
+      zm = xm[ov + (long)k0 * o + x];
+    }
+    z[x] = zp + zm;
+    z[kWzRows * o + x] = zp - zm;
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < v; b += kThreads) {
+    double s1[kWzRows] = {}, s2[kWzRows] = {};
+    for (int l = 0; l < o; ++l) {
+      const double t = t1[(long)l * v + b];
+#pragma unroll
+      for (int r = 0; r < kWzRows; ++r) {
+        s1[r] += z[r * o + l] * t;
+        s2[r] += z[(kWzRows + r) * o + l] * t;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kWzRows; ++r) {
+      if (r >= nk) break;
+      const long m = (long)(k0 + r) * v + b;
+      const double p = xp[m], q = xm[m];
+      wp[((long)i * o + j) * ldw + m] = (p + q) - 0.5 * s1[r];
+      if (i != j) wp[((long)j * o + i) * ldw + m] = (p - q) - 0.5 * s2[r];
+    }
+  }
+  for (int x = threadIdx.x; x < nk * o; x += kThreads) {
+    const int k = k0 + x / o, l = x % o;
+    if (l < k) continue;
+    auto c = [&](int kk, int ll) {
+      const long m = ov + (long)kk * o + ll;
+      double w = g4[(((long)kk * o + i) * o + ll) * o + j] + (xp[m] + xm[m]);
+      if (kk == i) w -= foo[(long)ll * o + j];
+      if (ll == j) w -= foo[(long)kk * o + i];
+      return w;
+    };
+    const long q = blockIdx.x * To + pidx(k, l, o);
+    const double a = c(k, l);
+    if (k == l) {
+      chip[q] = a;
+      chim[q] = 0.0;
+    } else {
+      const double b = c(l, k);
+      chip[q] = a + b;
+      chim[q] = a - b;
+    }
   }
 }
 
@@ -626,10 +784,10 @@ __global__ __launch_bounds__(kThreads) void pack_tpm_kernel(double* __restrict__
 // RL[i][j][b][a] = RL[j][i][a][b] = w (the residual's pair symmetry; R- vanishes on a = b).  Each
 // packed element is read once; the transposed writes go through an LDS tile.
 __global__ __launch_bounds__(kThreads) void unpack_rpm_kernel(double* __restrict__ RL, const double* __restrict__ Rplus,
-                                                             const double* __restrict__ Rminus, int o, int v,
-                                                             int nblk) {
+                                                             const double* __restrict__ Rminus, long ldr, int o,
+                                                             int v, int nblk) {
   __shared__ double tu[32][33], tw[32][33];
-  const long Tv = (long)v * (v + 1) / 2, vv = (long)v * v;
+  const long vv = (long)v * v;
   // block pair (A, B), A <= B, from blockIdx.x
   int A = 0, rem = blockIdx.x;
   while (rem >= nblk - A) {
@@ -644,8 +802,8 @@ __global__ __launch_bounds__(kThreads) void unpack_rpm_kernel(double* __restrict
   }
   const int j = i + prem;
   const long p = pidx(i, j, o);
-  const double* plus = Rplus + p * Tv;
-  const double* minus = Rminus + p * Tv;
+  const double* plus = Rplus + p * ldr;
+  const double* minus = Rminus + p * ldr;
   double* dij = RL + ((long)i * o + j) * vv;
   double* dji = RL + ((long)j * o + i) * vv;
   const int a0 = 32 * A, b0 = 32 * B;
@@ -679,27 +837,6 @@ __global__ __launch_bounds__(kThreads) void unpack_rpm_kernel(double* __restrict
   }
 }
 
-// V+-[p(a,b)][p(c,d)] for a in [a0, a1), b >= a, from W[a - a0][b][c][d] = (ac|bd):
-//   V+ = W[.][c][d] + W[.][d][c] (c < d), W[.][c][c] (c = d);  V- = W[.][c][d] - W[.][d][c] (c < d), 0 (c = d).
-__global__ __launch_bounds__(kThreads) void pack_vvvv_kernel(double* __restrict__ Vp, const double* __restrict__ W,
-                                                            int a0, int v) {
-  const int a = a0 + blockIdx.y / v, b = blockIdx.y % v;
-  if (b < a) return;
-  const long Tv = (long)v * (v + 1) / 2, vv = (long)v * v;
-  const double* src = W + ((long)(a - a0) * v + b) * vv;
-  const long r = pidx(a, b, v);
-  double* plus = Vp + r * Tv;
-  double* minus = Vp + (Tv + r) * Tv;
-  for (long x = blockIdx.x * (long)blockDim.x + threadIdx.x; x < vv; x += (long)gridDim.x * blockDim.x) {
-    const int c = x / v, d = x % v;
-    if (c > d) continue;
-    const double w1 = src[x], w2 = src[(long)d * v + c];
-    const long k = pidx(c, d, v);
-    plus[k] = (c == d) ? w1 : w1 + w2;
-    minus[k] = (c == d) ? 0.0 : w1 - w2;
-  }
-}
-
 // Pair order of the full (ac|bd) storage: R(a,b) = p(a,b) for a <= b, T(v) + strict pair index of
 // (b,a) for a > b; pm[n] = R(b,a) for pair n = (a <= b) (n itself when a = b).
 __device__ __forceinline__ long pair_order(long a, long b, long v) {
@@ -713,16 +850,19 @@ __global__ __launch_bounds__(kThreads) void pair_minus_rows_kernel(int* __restri
   for (int b = a; b < v; ++b) pm[pidx(a, b, v)] = (int)pair_order(b, a, v);
 }
 
-// Full (ac|bd) in pair order: V[R(a,b)][R(c,d)] = W[a - a0][b][c][d] for a in [a0, a1).
-__global__ __launch_bounds__(kThreads) void pack_full_kernel(double* __restrict__ V, const double* __restrict__ W,
-                                                            int a0, int v) {
+// Full (ac|bd) in pair order, rows at stride ldv: V[R(a,b)][R(c,d)] = W[a - a0][b][c][d] for a in [a0, a1),
+// the diagonal columns c = d halved, so that V[R(a,b)] +- V[R(b,a)] are the packed halves there too.
+__global__ __launch_bounds__(kThreads) void pack_full_kernel(double* __restrict__ V, long ldv,
+                                                            const double* __restrict__ W, int a0, int v) {
   const int a = a0 + blockIdx.y / v, b = blockIdx.y % v;
   const long vv = (long)v * v;
   const double* src = W + ((long)(a - a0) * v + b) * vv;
-  double* dst = V + pair_order(a, b, v) * vv;
+  double* dst = V + pair_order(a, b, v) * ldv;
+  if (blockIdx.x == 0)
+    for (long x = vv + threadIdx.x; x < ldv; x += kThreads) dst[x] = 0.0;
   for (long x = blockIdx.x * (long)blockDim.x + threadIdx.x; x < vv; x += (long)gridDim.x * blockDim.x) {
     const int c = x / v, d = x % v;
-    dst[pair_order(c, d, v)] = src[x];
+    dst[pair_order(c, d, v)] = (c == d) ? 0.5 * src[x] : src[x];
   }
 }
 
@@ -846,19 +986,24 @@ hipError_t permute4_strided(double* out, const long ostr[4], const int dims[4], 
 }
 
 hipError_t assemble_r2(double* r2, const double* g1, const double* rl, const double* em, const double* p1,
-                       const double* p2, int no, int nv, hipStream_t s) {
+                       const double* p2, int no, int nv, hipStream_t s, const double* rminus, long ldr) {
   const long total = (long)no * no * nv * nv;
   const long ovov = (long)no * nv * no * nv;
+  const long tv = (nv + 31) / 32, pairs = (long)no * (no + 1) / 2, Tv = (long)nv * (nv + 1) / 2;
   if (bounds_checking() &&
       !(range_ok(r2, 0, total - 1, 8, "assemble r2") && range_ok(g1, 0, ovov - 1, 8, "assemble g1") &&
-        range_ok(rl, 0, total - 1, 8, "assemble rl") && range_ok(em, 0, total - 1, 8, "assemble em") &&
+        range_ok(rl, 0, rminus ? (pairs - 1) * ldr + Tv - 1 : total - 1, 8, "assemble rl") &&
+        (!rminus || range_ok(rminus, 0, (pairs - 1) * ldr + Tv - 1, 8, "assemble R-")) &&
+        range_ok(em, 0, total - 1, 8, "assemble em") &&
         range_ok(p1, 0, ovov - 1, 8, "assemble p1") && range_ok(p2, 0, ovov - 1, 8, "assemble p2")))
     return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
-  const long tv = (nv + 31) / 32, pairs = (long)no * (no + 1) / 2;
   if (tv * tv > 65535 || pairs > 0x7fffffffL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(assemble_r2_kernel, dim3((unsigned)pairs, (unsigned)(tv * tv)), dim3(kThreads), 0, s, r2, g1, rl,
-                     em, p1, p2, no, nv);
+  const dim3 grid((unsigned)pairs, (unsigned)(tv * tv));
+  if (rminus)
+    hipLaunchKernelGGL(assemble_r2_kernel<true>, grid, dim3(kThreads), 0, s, r2, g1, rl, rminus, ldr, em, p1, p2, no, nv);
+  else
+    hipLaunchKernelGGL(assemble_r2_kernel<false>, grid, dim3(kThreads), 0, s, r2, g1, rl, rl, 0L, em, p1, p2, no, nv);
   return hipGetLastError();
 }
 
@@ -1180,37 +1325,65 @@ hipError_t energy(double* e, double* partial, const double* t1, const double* t2
 
 static bool chk(const void* p, long n, const char* what) { return range_ok(p, 0, n - 1, 8, what); }
 
-hipError_t pack_tpm(double* tplus, double* tminus, const double* t2, int o, int v, double dscale, hipStream_t s) {
-  const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2, vv = (long)v * v;
-  if (bounds_checking() && !(chk(tplus, To * Tv, "pack_tpm plus") && chk(tminus, To * Tv, "pack_tpm minus") &&
-                             chk(t2, (long)o * o * vv, "pack_tpm t2")))
+static hipError_t pack_halves(int mode, double* plus, double* minus, long ldo, const double* src, int o, int v, int a0,
+                              long rows, long out_lo, long out_hi, long src_len, hipStream_t s) {
+  const long Tv = (long)v * (v + 1) / 2, nblk = (v + 31) / 32;
+  if (rows <= 0) return hipSuccess;
+  if (ldo < Tv || rows > 0x7fffffffL || nblk * (nblk + 1) / 2 > 65535) return hipErrorInvalidValue;
+  if (bounds_checking() && !(range_ok(plus, out_lo * ldo, (out_hi + 1) * ldo - 1, 8, "pair packing plus") &&
+                             range_ok(minus, out_lo * ldo, (out_hi + 1) * ldo - 1, 8, "pair packing minus") &&
+                             chk(src, src_len, "pair packing input")))
     return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
-  dim3 grid((unsigned)std::min<long>((vv + kThreads - 1) / kThreads, 64), o * o);
-  hipLaunchKernelGGL(pack_tpm_kernel, grid, dim3(kThreads), 0, s, tplus, tminus, t2, o, v, dscale);
+  hipLaunchKernelGGL(pack_halves_kernel, dim3((unsigned)rows, (unsigned)(nblk * (nblk + 1) / 2)), dim3(kThreads), 0, s,
+                     PackP{plus, minus, ldo, src, mode, o, v, a0});
   return hipGetLastError();
 }
 
-hipError_t unpack_rpm(double* RL, const double* Rplus, const double* Rminus, int o, int v, hipStream_t s) {
+hipError_t pack_tpm(double* tplus, double* tminus, long ldo, const double* t2, int o, int v, hipStream_t s) {
+  const long To = (long)o * (o + 1) / 2;
+  return pack_halves(kPackT, tplus, tminus, ldo, t2, o, v, 0, To, 0, To - 1, (long)o * o * v * v, s);
+}
+
+hipError_t pack_vvvv(double* vplus, double* vminus, long ldo, const double* W, int a0, int a1, int v, hipStream_t s) {
+  if (a1 <= a0) return hipSuccess;
+  auto row = [&](long a) { return a * v - a * (a - 1) / 2; };  // p(a, a)
+  return pack_halves(kPackV, vplus, vminus, ldo, W, 1, v, a0, (long)(a1 - a0) * v, row(a0), row(a1) - 1,
+                     (long)(a1 - a0) * v * v * v, s);
+}
+
+hipError_t pack_gwz(double* gplus, double* gminus, long ldo, const double* kcbd, const double* kcld, int o, int v,
+                    hipStream_t s) {
+  const long ov = (long)o * v, oo = (long)o * o;
+  const hipError_t e = pack_halves(kPackG, gplus, gminus, ldo, kcbd, o, v, 0, ov, 0, ov - 1, ov * v * v, s);
+  if (e != hipSuccess) return e;
+  return pack_halves(kPackGo, gplus, gminus, ldo, kcld, o, v, 0, oo, ov, ov + oo - 1, ov * ov, s);
+}
+
+hipError_t wz_chi(double* wp, long ldw, double* chip, double* chim, const double* rp, const double* rm, long ldr,
+                  const double* g4, const double* foo, const double* t1, int o, int v, hipStream_t s) {
+  const long To = (long)o * (o + 1) / 2, ov = (long)o * v, oo = (long)o * o, wzl = ov + oo;
+  if (o > 256) return hipErrorInvalidValue;
+  if (bounds_checking() &&
+      !(chk(wp, (oo - 1) * ldw + ov, "W'") && chk(chip, To * To, "chi+") && chk(chim, To * To, "chi-") &&
+        chk(rp, (To - 1) * ldr + wzl, "W/Z +") && chk(rm, (To - 1) * ldr + wzl, "W/Z -") && chk(g4, oo * oo, "g_kilj") &&
+        chk(foo, oo, "F''") && chk(t1, ov, "W' t1")))
+    return hipErrorInvalidValue;
+  if (dry_run()) return hipSuccess;
+  hipLaunchKernelGGL(wz_chi_kernel, dim3((unsigned)To, (unsigned)((o + kWzRows - 1) / kWzRows)), dim3(kThreads),
+                     2 * kWzRows * o * sizeof(double), s, wp, ldw, chip, chim, rp, rm, ldr, g4, foo, t1, o, v);
+  return hipGetLastError();
+}
+
+hipError_t unpack_rpm(double* RL, const double* Rplus, const double* Rminus, long ldr, int o, int v, hipStream_t s) {
   const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2, vv = (long)v * v;
-  if (bounds_checking() && !(chk(RL, (long)o * o * vv, "unpack_rpm RL") && chk(Rplus, To * Tv, "unpack_rpm plus") &&
-                             chk(Rminus, To * Tv, "unpack_rpm minus")))
+  if (bounds_checking() && !(chk(RL, (long)o * o * vv, "unpack_rpm RL") && chk(Rplus, (To - 1) * ldr + Tv, "unpack_rpm plus") &&
+                             chk(Rminus, (To - 1) * ldr + Tv, "unpack_rpm minus")))
     return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
   const int nblk = (v + 31) / 32;
   dim3 grid((unsigned)(nblk * (nblk + 1) / 2), (unsigned)To);
-  hipLaunchKernelGGL(unpack_rpm_kernel, grid, dim3(kThreads), 0, s, RL, Rplus, Rminus, o, v, nblk);
-  return hipGetLastError();
-}
-
-hipError_t pack_vvvv(double* Vp, const double* W, int a0, int a1, int v, hipStream_t s) {
-  const long Tv = (long)v * (v + 1) / 2, vv = (long)v * v;
-  if (a1 <= a0) return hipSuccess;
-  if (bounds_checking() && !(chk(Vp, 2 * Tv * Tv, "pack_vvvv out") && chk(W, (long)(a1 - a0) * v * vv, "pack_vvvv in")))
-    return hipErrorInvalidValue;
-  if (dry_run()) return hipSuccess;
-  dim3 grid((unsigned)std::min<long>((vv + kThreads - 1) / kThreads, 64), (a1 - a0) * v);
-  hipLaunchKernelGGL(pack_vvvv_kernel, grid, dim3(kThreads), 0, s, Vp, W, a0, v);
+  hipLaunchKernelGGL(unpack_rpm_kernel, grid, dim3(kThreads), 0, s, RL, Rplus, Rminus, ldr, o, v, nblk);
   return hipGetLastError();
 }
 
@@ -1223,14 +1396,15 @@ hipError_t pair_minus_rows(int* pm, int v, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t pack_full(double* V, const double* W, int a0, int a1, int v, hipStream_t s) {
+hipError_t pack_full(double* V, long ldv, const double* W, int a0, int a1, int v, hipStream_t s) {
   const long vv = (long)v * v;
   if (a1 <= a0) return hipSuccess;
-  if (bounds_checking() && !(chk(V, vv * vv, "pack_full out") && chk(W, (long)(a1 - a0) * v * vv, "pack_full in")))
+  if (ldv < vv) return hipErrorInvalidValue;
+  if (bounds_checking() && !(chk(V, vv * ldv, "pack_full out") && chk(W, (long)(a1 - a0) * v * vv, "pack_full in")))
     return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
   dim3 grid((unsigned)std::min<long>((vv + kThreads - 1) / kThreads, 64), (a1 - a0) * v);
-  hipLaunchKernelGGL(pack_full_kernel, grid, dim3(kThreads), 0, s, V, W, a0, v);
+  hipLaunchKernelGGL(pack_full_kernel, grid, dim3(kThreads), 0, s, V, ldv, W, a0, v);
   return hipGetLastError();
 }
 

@@ -16,10 +16,11 @@
 // Tile configurations: 128 x 128 (4 waves, two workgroups per CU), 256 x 128 and 192 x 192
 // (8 waves, one per CU), all with K staged 16 deep, chosen per call by how well whole rounds of 256 workgroups cover
 // the output; 64 x 64 and 32 x 32 for small outputs; 128 x 128 with split-K when a long K meets
-// too few tiles.  The particle-particle ladder has its own entry point (gemm_f64_ladder): 256-,
-// 224-, 208- or 128-row tiles, whichever pads the pair dimension least, and optionally the
+// too few tiles.  The particle-particle ladder has its own entry point (gemm_f64_ladder): tiles of a
+// height that fits the pair dimension, K split where one state leaves CUs idle, and optionally the
 // symmetric/antisymmetric vvvv combinations formed while staging from the stored full (ac|bd).
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 
 #include "internal.h"
@@ -41,6 +42,8 @@ struct GP {
   int tiles_m, tiles_n;
   int split, it_per_split;  // split-K: slices of the (nred x K-tile) iteration space
   double* part;             // partial tiles [split][nb1*nb2][M][N] when split > 1
+  int seq;                  // split > 1 without partial tiles: a workgroup runs all slices of its tile,
+                            // each added to C in turn (the sums of the partial tiles, in slice order)
   const int* pm;            // pair-combined B (ladder): second row of pair n
   const int* tab1;          // batch level 1: operand block of grid index z1 (nullptr: z1 itself)
   int lower;                // symmetric C: tiles on and below the diagonal only (tiles_m == tiles_n)
@@ -104,10 +107,8 @@ __global__ __launch_bounds__(256) void mirror_upper_kernel(GP p) {
   }
 }
 
-// PM: B is pair-combined (ladder against the full (ac|bd) in pair order): for batch z2 = 0 (+)
-// or 1 (-), B(k, n) = V[n][k] +- V[pm[n]][k] (rows of V at stride sbn).
 // MINB: workgroups per CU the register budget is sized for.
-template <int BM, int BN, int BK, int WM, int WN, int MINB, bool AMF, bool BNF, bool PM = false>
+template <int BM, int BN, int BK, int WM, int WN, int MINB, bool AMF, bool BNF>
 __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_f64_kernel(GP p) {
   constexpr int NT = WM * WN * 64;
   constexpr int TM = BM / WM, TN = BN / WN;
@@ -115,7 +116,6 @@ __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_f64_kernel(GP p) {
   constexpr int LA = BM * BK / NT, LB = BK * BN / NT;
   constexpr int PA = BM + 1, PB = BN + 1;  // +1 double: conflict-free transposing stores
   static_assert(RI >= 1 && RJ >= 1 && LA >= 1 && LB >= 1 && TM % 16 == 0 && TN % 16 == 0, "tile config");
-  static_assert(!PM || (!BNF && NT % BK == 0), "pair-combined B is staged k-fast");
   __shared__ double As[2][BK * PA];
   __shared__ double Bs[2][BK * PB];
 
@@ -125,15 +125,7 @@ __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_f64_kernel(GP p) {
 
   int tm, tn;
   const int ntiles = p.tiles_m * p.tiles_n;
-  int bid = blockIdx.x, z2 = blockIdx.y;
-  if constexpr (PM) {
-    // Both halves of a tile read the same V rows: they are dispatched back to back to the same
-    // XCD (workgroups b and b + 8 share an XCD), so the second one finds them in L2.
-    const int x = bid & 7, local = bid >> 3;
-    z2 = local & 1;
-    bid = ((local >> 1) << 3) | x;
-    if (bid >= ntiles) return;  // padding of the grid to whole groups of 8
-  }
+  const int bid = blockIdx.x, z2 = blockIdx.y;
   const int slice = bid / ntiles;
   tile_of(bid - slice * ntiles, p.tiles_m, p.tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
@@ -156,20 +148,6 @@ __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_f64_kernel(GP p) {
   const int it_end = min(nkt * p.nred, it_begin + p.it_per_split);
 
   double ra[LA], rb[LB];
-  double rw[PM ? LB : 1];  // pair-combined B: second row, combined with rb only when staged to LDS
-  // pair-combined B: the two V rows of each staged pair n are fixed for the whole K loop
-  const double* pva[PM ? LB : 1];
-  const double* pvb[PM ? LB : 1];
-  if constexpr (PM) {
-#pragma unroll
-    for (int l = 0; l < LB; ++l) {
-      const int gn = n0 + (tid + l * NT) / BK;
-      pva[l] = gn < p.N ? Bb + (long)gn * p.sbn : nullptr;
-      pvb[l] = gn < p.N ? Bb + (long)p.pm[gn] * p.sbn : nullptr;
-    }
-  }
-  const bool minus = PM && z2 == 1;
-  (void)rw;
   auto load = [&](int it) {
     const int r = it / nkt, k0 = (it % nkt) * BK;
     const double* Ar = Ab + r * p.sar;
@@ -182,24 +160,13 @@ __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_f64_kernel(GP p) {
       const int gm = m0 + m, gk = k0 + k;
       ra[l] = (gm < p.M && gk < p.K) ? Ar[gm * p.sam + gk * p.sak] : 0.0;
     }
-    if constexpr (PM) {
-      const int gk = k0 + tid % BK;  // the same k for every element this thread stages
 #pragma unroll
-      for (int l = 0; l < LB; ++l) {
-        const bool ok = pva[l] && gk < p.K;
-        rb[l] = ok ? pva[l][gk] : 0.0;
-        rw[l] = ok ? pvb[l][gk] : 0.0;
-      }
-      (void)Br;
-    } else {
-#pragma unroll
-      for (int l = 0; l < LB; ++l) {
-        const int e = tid + l * NT;
-        const int n = BNF ? (e % BN) : (e / BK);
-        const int k = BNF ? (e / BN) : (e % BK);
-        const int gn = n0 + n, gk = k0 + k;
-        rb[l] = (gn < p.N && gk < p.K) ? Br[gk * p.sbk + gn * p.sbn] : 0.0;
-      }
+    for (int l = 0; l < LB; ++l) {
+      const int e = tid + l * NT;
+      const int n = BNF ? (e % BN) : (e / BK);
+      const int k = BNF ? (e / BN) : (e % BK);
+      const int gn = n0 + n, gk = k0 + k;
+      rb[l] = (gn < p.N && gk < p.K) ? Br[gk * p.sbk + gn * p.sbn] : 0.0;
     }
   };
   auto store = [&](int buf) {
@@ -215,11 +182,7 @@ __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_f64_kernel(GP p) {
       const int e = tid + l * NT;
       const int n = BNF ? (e % BN) : (e / BK);
       const int k = BNF ? (e / BN) : (e % BK);
-      // the combination waits for the loads here, after the MFMAs, not where they are issued
-      if constexpr (PM)
-        Bs[buf][k * PB + n] = minus ? rb[l] - rw[l] : rb[l] + rw[l];
-      else
-        Bs[buf][k * PB + n] = rb[l];
+      Bs[buf][k * PB + n] = rb[l];
     }
   };
 
@@ -405,18 +368,22 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
   const int wm = wave / WN, wn = wave % WN;
   const int ntiles = p.tiles_m * p.tiles_n;
   int bid = blockIdx.x, z2 = blockIdx.y;
-  if constexpr (PM) {  // the + and - halves of a tile back to back on one XCD (see gemm_f64_kernel)
+  const int per = PM ? 2 * ((ntiles + 7) / 8 * 8) : p.lower ? gridDim.x : ntiles;  // workgroups of a slice
+  const int slice0 = bid / per, slice1 = p.seq ? p.split : slice0 + 1;  // split-K slices of this workgroup
+  bid -= slice0 * per;
+  if constexpr (PM) {
+    // Both halves of a tile read the same V rows: they are dispatched back to back to the same
+    // XCD (workgroups b and b + 8 share an XCD), so the second one finds them in L2.
     const int x = bid & 7, local = bid >> 3;
     z2 = local & 1;
     bid = ((local >> 1) << 3) | x;
-    if (bid >= ntiles) return;
+    if (bid >= ntiles) return;  // padding of the grid to whole groups of 8
   }
-  const int slice = PM ? 0 : bid / ntiles;  // split-K slice (never for PM)
   int tm, tn;
   if (!PM && p.lower)
     tile_of_lower(bid, p.tiles_m, tm, tn);
   else
-    tile_of(bid - slice * ntiles, p.tiles_m, p.tiles_n, tm, tn);
+    tile_of(bid, p.tiles_m, p.tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
   const int z1 = blockIdx.z;
   const int zs = p.tab1 ? p.tab1[z1] : z1;  // operand block of batch level 1
@@ -448,9 +415,6 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
       }
     }
   }
-  // stages [kt0, kt0 + nkt) of this slice
-  const int kt0 = slice * p.it_per_split;
-  const int nkt = min((p.K + KS - 1) / KS, kt0 + p.it_per_split) - kt0;
   auto issue1 = [&](int kt, int st, int j) {  // load instruction j of this wave for stage kt
     const int g = wave + NW * j;
     if (NPW * NW == NI || g < NI) {
@@ -479,10 +443,6 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
   };
 
   d4 acc[RI][RJ];
-#pragma unroll
-  for (int i = 0; i < RI; ++i)
-#pragma unroll
-    for (int j = 0; j < RJ; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
   const bool minus = PM && z2 == 1;
   const int l16 = lane & 15, q = lane >> 4;
   // Fragments are read one unit ahead of their MFMAs: a unit is one group of A fragment rows of one
@@ -518,72 +478,87 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
       for (int j = 0; j < RJ; ++j) fb[kk & 1][j] = minus ? fb[kk & 1][j] - fw[j] : fb[kk & 1][j] + fw[j];
     }
   };
+  for (int slice = slice0; slice < slice1; ++slice) {
 #pragma unroll
-  for (int st = 0; st < S; ++st)
-    if (st < nkt) issue(kt0 + st, st);
-  if (nkt > 0) {
-    if (S - 1 < nkt)
-      wait_stage<(S - 1) * NPWMIN>();
-    else
-      wait_stage<0>();
+    for (int i = 0; i < RI; ++i)
 #pragma unroll
-    for (int k = 0; k < NR; ++k) read1(T[0], 0, k);
-    combine(0);
-  }
-  for (int kt = 0; kt < nkt; ++kt) {  // kt counts stages of this slice
-    const int st = kt % S;
-    const bool more = kt + 1 < nkt, refill = kt + S < nkt;
+      for (int j = 0; j < RJ; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+    // stages [kt0, kt0 + nkt) of this slice
+    const int kt0 = slice * p.it_per_split;
+    const int nkt = min((p.K + KS - 1) / KS, kt0 + p.it_per_split) - kt0;
+    if (slice != slice0) wait_stage<0>();  // every wave is done with the slots of the slice before
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int kk = u / G, g = u % G;
-      const bool last = u + 1 == U;
-      const double* Tn = T[last ? (kt + 1) % S : st];
-      if (last && more) {
-        // stage kt + 1 has landed once no more than the later stages' loads of this wave are in
-        // flight; past the barrier it has for every wave, and every wave holds the last fragments of
-        // stage kt in registers, so its slot is refilled from here on
-        if (kt + S - 1 < nkt)
-          wait_stage<(S - 2) * NPWMIN>();
-        else
-          wait_stage<0>();
-      }
-      if (last && refill) mask_tail(kt0 + kt + S);
-      // the unit's products, with a fragment read or a refill load issued behind most of them
-      constexpr int NM = 2 * GI * RJ, LS = NR + 2 * NPW <= NM ? 2 : 1;
-      constexpr int ML = S == 2 ? 0 : LS == 2 ? NR : NM - NPW;  // two stages: the refill is due soonest
-      static_assert(NR <= NM && NPW <= NM, "one read and one load per product at most");
+    for (int st = 0; st < S; ++st)
+      if (st < nkt) issue(kt0 + st, st);
+    if (nkt > 0) {
+      if (S - 1 < nkt)
+        wait_stage<(S - 1) * NPWMIN>();
+      else
+        wait_stage<0>();
 #pragma unroll
-      for (int m = 0; m < NM; ++m) {
-        const int h = m / (GI * RJ), i = (m / RJ) % GI, j = m % RJ;
-        if (g * GI + i < RI)
-          acc[g * GI + i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[u & 1][i][h], fb[kk & 1][j][h],
-                                                                    acc[g * GI + i][j], 0, 0, 0);
-        if (m < NR && (!last || more)) read1(Tn, last ? 0 : u + 1, m);
-        if (last && refill && m >= ML && m < ML + LS * NPW && (m - ML) % LS == 0) issue1(kt0 + kt + S, st, (m - ML) / LS);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if (!last || more) combine(last ? 0 : u + 1);
+      for (int k = 0; k < NR; ++k) read1(T[0], 0, k);
+      combine(0);
     }
-  }
+    for (int kt = 0; kt < nkt; ++kt) {  // kt counts stages of this slice
+      const int st = kt % S;
+      const bool more = kt + 1 < nkt, refill = kt + S < nkt;
 #pragma unroll
-  for (int i = 0; i < RI; ++i)
+      for (int u = 0; u < U; ++u) {
+        const int kk = u / G, g = u % G;
+        const bool last = u + 1 == U;
+        const double* Tn = T[last ? (kt + 1) % S : st];
+        if (last && more) {
+          // stage kt + 1 has landed once no more than the later stages' loads of this wave are in
+          // flight; past the barrier it has for every wave, and every wave holds the last fragments of
+          // stage kt in registers, so its slot is refilled from here on
+          if (kt + S - 1 < nkt)
+            wait_stage<(S - 2) * NPWMIN>();
+          else
+            wait_stage<0>();
+        }
+        if (last && refill) mask_tail(kt0 + kt + S);
+        // the unit's products, with a fragment read or a refill load issued behind most of them
+        constexpr int NM = 2 * GI * RJ, LS = NR + 2 * NPW <= NM ? 2 : 1;
+        constexpr int ML = S == 2 ? 0 : LS == 2 ? NR : NM - NPW;  // two stages: the refill is due soonest
+        static_assert(NR <= NM && NPW <= NM, "one read and one load per product at most");
 #pragma unroll
-    for (int j = 0; j < RJ; ++j)
+        for (int m = 0; m < NM; ++m) {
+          const int h = m / (GI * RJ), i = (m / RJ) % GI, j = m % RJ;
+          if (g * GI + i < RI)
+            acc[g * GI + i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[u & 1][i][h], fb[kk & 1][j][h],
+                                                                      acc[g * GI + i][j], 0, 0, 0);
+          if (m < NR && (!last || more)) read1(Tn, last ? 0 : u + 1, m);
+          if (last && refill && m >= ML && m < ML + LS * NPW && (m - ML) % LS == 0) issue1(kt0 + kt + S, st, (m - ML) / LS);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!last || more) combine(last ? 0 : u + 1);
+      }
+    }
+    // the output addresses are formed here: hoisted out of the slice loop they would hold registers
+    // across it (a lane index hidden from the optimiser keeps them in place)
+    int ol = lane;
+    asm volatile("" : "+v"(ol));
+    const int oq = ol >> 4, o16 = ol & 15;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int gm = m0 + wm * TM + 16 * i + q + 4 * r;
-        const int gn = n0 + wn * TN + 16 * j + l16;
-        if (gm < p.M && gn < p.N) {
-          const double v = p.alpha * acc[i][j][r];
-          if (p.split > 1) {
-            const long zl = (long)z1 * gridDim.y + z2;
-            p.part[(((long)slice * gridDim.z * gridDim.y + zl) * p.M + gm) * p.N + gn] = v;
-          } else {
-            double* c = Cb + (long)gm * p.scm + (long)gn * p.scn;
-            *c = (p.beta == 0.0) ? v : v + p.beta * *c;
+    for (int i = 0; i < RI; ++i)
+#pragma unroll
+      for (int j = 0; j < RJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int gm = m0 + wm * TM + 16 * i + oq + 4 * r;
+          const int gn = n0 + wn * TN + 16 * j + o16;
+          if (gm < p.M && gn < p.N) {
+            const double v = p.alpha * acc[i][j][r];
+            if (p.part) {
+              const long zl = (long)z1 * p.nb2 + z2;
+              p.part[(((long)slice * gridDim.z * p.nb2 + zl) * p.M + gm) * p.N + gn] = v;
+            } else {
+              double* c = Cb + (long)gm * p.scm + (long)gn * p.scn;
+              *c = (slice != slice0) ? *c + v : (p.beta == 0.0) ? v : v + p.beta * *c;
+            }
           }
         }
-      }
+  }
 }
 
 // K-contiguous operands with 16-byte aligned rows and an even K (the loads move K-value pairs); the
@@ -595,33 +570,47 @@ bool dma_eligible(const GP& p) {
          p.sa1 % 2 == 0 && p.sa2 % 2 == 0 && p.sb1 % 2 == 0 && p.sb2 % 2 == 0 && al(p.A) && al(p.B);
 }
 
-// split > 1 (never with pm): K cut into `split` slices whose partial tiles go to ws, then summed
-// in a fixed order by splitk_reduce.
-template <int BM, int BN, int WM, int WN, int S>
-hipError_t launch_dma(GP p, int nb1, bool pm, int split, double* ws, hipStream_t s) {
-  constexpr int KS = kStageK;
+// C_z(m, n) = sum_s part[s][z][m][n], in slice order (the order of a workgroup that runs all slices).
+__global__ __launch_bounds__(256) void ordered_reduce(GP p, int nb1) {
+  const int n = blockIdx.x * 256 + threadIdx.x, zl = blockIdx.z;
+  if (n >= p.N) return;
+  const long nz = (long)nb1 * p.nb2, mn = (long)p.M * p.N;
+  const int z1 = zl / p.nb2, z2 = zl % p.nb2;
+  const int zs = p.tab1 ? p.tab1[z1] : z1;
+  double* C = p.C + zs * p.sc1 + z2 * p.sc2;
+  for (int m = blockIdx.y; m < p.M; m += gridDim.y) {
+    const double* x = p.part + zl * mn + (long)m * p.N + n;
+    double sum = *x;
+    for (int sl = 1; sl < p.split; ++sl) sum += x[sl * nz * mn];
+    C[m * p.scm + n * p.scn] = sum;
+  }
+}
+
+// split > 1: K cut into `split` slices whose partial tiles go to ws, then summed in a fixed order by
+// splitk_reduce; ordered: beta is 0 and they are summed in slice order, by ordered_reduce or, without
+// ws, by the workgroups themselves.
+template <int BM, int BN, int WM, int WN, int S, bool PM = false>
+hipError_t launch_dma(GP p, int nb1, int split, double* ws, bool ordered, hipStream_t s) {
   p.tiles_m = (p.M + BM - 1) / BM;
   p.tiles_n = (p.N + BN - 1) / BN;
-  const int nkt = (p.K + KS - 1) / KS;
+  const int nkt = (p.K + kStageK - 1) / kStageK;
   p.it_per_split = (nkt + split - 1) / split;
   p.split = (nkt + p.it_per_split - 1) / p.it_per_split;
   p.part = p.split > 1 ? ws : nullptr;
+  p.seq = ordered && p.split > 1 && !ws;
   const int tiles = p.lower ? p.tiles_m * (p.tiles_m + 1) / 2 : p.tiles_m * p.tiles_n;
-  if (p.lower && (p.split > 1 || pm || BM != BN || p.tiles_m != p.tiles_n)) return hipErrorInvalidValue;
-  if (pm) {  // both halves in grid.x, padded to whole groups of 8
-    if constexpr ((long)S * (BM + 2 * BN) * KS * 8 <= 160 * 1024) {
-      dim3 grid(2 * ((tiles + 7) / 8 * 8), 1, nb1);
-      hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, S, true>), grid, dim3(WM * WN * 64), 0, s, p);
-      return hipGetLastError();
-    } else {
-      return hipErrorInvalidValue;  // two B rows per pair do not fit this many stages
-    }
-  }
-  dim3 grid(tiles * p.split, p.nb2, nb1);
-  hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, S, false>), grid, dim3(WM * WN * 64), 0, s, p);
-  if (p.split > 1) {
+  if (p.lower && (p.split > 1 || PM || BM != BN || p.tiles_m != p.tiles_n)) return hipErrorInvalidValue;
+  if (p.split > 1 && !ws && !ordered) return hipErrorInvalidValue;
+  const int per = PM ? 2 * ((tiles + 7) / 8 * 8) : tiles;  // PM: both halves in grid.x, padded to groups of 8
+  dim3 grid(per * (p.seq ? 1 : p.split), PM ? 1 : p.nb2, nb1);
+  hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, S, PM>), grid, dim3(WM * WN * 64), 0, s, p);
+  if (p.part) {
     const long outs = (long)p.M * p.N * p.nb2 * nb1;
-    hipLaunchKernelGGL(splitk_reduce, dim3(splitk_blocks(outs)), dim3(256), 0, s, p, nb1, outs);
+    if (ordered)
+      hipLaunchKernelGGL(ordered_reduce, dim3((p.N + 255) / 256, std::min(p.M, 65535), p.nb2 * nb1), dim3(256),
+                         0, s, p, nb1);
+    else
+      hipLaunchKernelGGL(splitk_reduce, dim3(splitk_blocks(outs)), dim3(256), 0, s, p, nb1, outs);
   }
   return hipGetLastError();
 }
@@ -649,28 +638,77 @@ hipError_t launch_dma_auto(const GP& p, int nb1, int nb1d, double* ws, long ws_e
       best_split = sp;
     }
   }
-  if (best == 0) return launch_dma<192, 192, 2, 4, 3>(p, nb1, false, best_split, ws, s);
-  if (best == 1) return launch_dma<256, 128, 4, 2, 3>(p, nb1, false, best_split, ws, s);
-  return launch_dma<224, 128, 2, 4, 3>(p, nb1, false, best_split, ws, s);
+  if (best == 0) return launch_dma<192, 192, 2, 4, 3>(p, nb1, best_split, ws, false, s);
+  if (best == 1) return launch_dma<256, 128, 4, 2, 3>(p, nb1, best_split, ws, false, s);
+  return launch_dma<224, 128, 2, 4, 3>(p, nb1, best_split, ws, false, s);
 }
 
-// Ladder: BM x 128 tiles of 8 waves, both halves (grid.y = 2), no split-K, A/B staged k-fast.
-template <int BM, int WM>
-hipError_t launch_ladder(GP p, int nb1, bool pm, hipStream_t s) {
-  constexpr int BK = 16, WN = 8 / WM;
-  p.tiles_m = (p.M + BM - 1) / BM;
-  p.tiles_n = (p.N + 127) / 128;
-  p.split = 1;
-  p.it_per_split = (p.K + BK - 1) / BK;
-  p.part = nullptr;
-  const int tiles = p.tiles_m * p.tiles_n;
-  // pair-combined: the two halves interleave in grid.x (see the kernel), padded to groups of 8
-  dim3 grid(pm ? 2 * ((tiles + 7) / 8 * 8) : tiles, pm ? 1 : 2, nb1), block(512);
-  if (pm)
-    hipLaunchKernelGGL((gemm_f64_kernel<BM, 128, BK, WM, WN, 1, false, false, true>), grid, block, 0, s, p);
-  else
-    hipLaunchKernelGGL((gemm_f64_kernel<BM, 128, BK, WM, WN, 1, false, false, false>), grid, block, 0, s, p);
-  return hipGetLastError();
+// Ladder tiles: BM x 128, the eight waves side by side (BM / 16 fragment rows each).  Three stages, or
+// two where a stage with both rows of each pair leaves no room for a third.
+template <int BM, bool PM>
+hipError_t launch_ladder(const GP& p, int nb1, int split, double* ws, hipStream_t s) {
+  constexpr int S = 3L * (BM + (PM ? 256 : 128)) * kStageK * 8 <= 160 * 1024 ? 3 : 2;
+  return launch_dma<BM, 128, 1, 8, S, PM>(p, nb1, split, ws, true, s);
+}
+
+// Tile height and split-K count of a ladder of M rows (N columns, both halves).  Time of a launch: whole
+// rounds of 256 workgroups x stages of a slice (and about 6 to fill and drain) x (rows + 24 of B staging).
+// The split is that of one state's rows Mdec alone, so a state's sums do not depend on how many states
+// are stacked; it pays where one state leaves CUs idle: its partial tiles cost a pass over the outputs.
+struct LadderPlan {
+  int bm, split;
+};
+LadderPlan ladder_plan(long M, long Mdec, long N, long K) {
+  constexpr int kBM[] = {32, 48, 64, 80, 96, 112, 128, 144, 160, 176, 192, 208, 224, 240, 256};
+  const long nkt = (K + kStageK - 1) / kStageK, tn = (N + 127) / 128;
+  auto cost = [&](long m, int bm, int sp) {
+    const double wg = (double)((m + bm - 1) / bm * tn * 2 * sp);
+    const double stages = (double)((nkt + sp - 1) / sp + 6) * (bm + 24) * std::ceil(wg / 256);
+    return stages + (sp > 1 ? 400.0 + 2.0e-5 * (double)(sp + 1) * (double)m * (double)N * 2 : 0.0);
+  };
+  LadderPlan best{256, 1};
+  double least = -1;
+  for (int bm : kBM)
+    for (int sp = 1; sp <= 8 && (sp == 1 || nkt >= 16 * sp); ++sp) {
+      const double c = cost(Mdec, bm, sp);
+      if (least < 0 || c < least) {
+        least = c;
+        best = {bm, sp};
+      }
+    }
+  if (M != Mdec) {
+    least = -1;
+    for (int bm : kBM) {
+      const double c = std::ceil((double)((M + bm - 1) / bm * tn * 2) / 256) * (bm + 24);
+      if (least < 0 || c < least) {
+        least = c;
+        best.bm = bm;
+      }
+    }
+  }
+  return best;
+}
+
+template <bool PM>
+hipError_t launch_ladder_plan(const GP& p, int nb1, LadderPlan pl, double* ws, hipStream_t s) {
+  switch (pl.bm) {
+    case 32:  // (with pairs, more loads than products in a unit: the next height)
+      return launch_ladder<(PM ? 48 : 32), PM>(p, nb1, pl.split, ws, s);
+    case 48: return launch_ladder<48, PM>(p, nb1, pl.split, ws, s);
+    case 64: return launch_ladder<64, PM>(p, nb1, pl.split, ws, s);
+    case 80: return launch_ladder<80, PM>(p, nb1, pl.split, ws, s);
+    case 96: return launch_ladder<96, PM>(p, nb1, pl.split, ws, s);
+    case 112: return launch_ladder<112, PM>(p, nb1, pl.split, ws, s);
+    case 128: return launch_ladder<128, PM>(p, nb1, pl.split, ws, s);
+    case 144: return launch_ladder<144, PM>(p, nb1, pl.split, ws, s);
+    case 160: return launch_ladder<160, PM>(p, nb1, pl.split, ws, s);
+    case 176: return launch_ladder<176, PM>(p, nb1, pl.split, ws, s);
+    case 192: return launch_ladder<192, PM>(p, nb1, pl.split, ws, s);
+    case 208: return launch_ladder<208, PM>(p, nb1, pl.split, ws, s);
+    case 224: return launch_ladder<224, PM>(p, nb1, pl.split, ws, s);
+    case 240: return launch_ladder<240, PM>(p, nb1, pl.split, ws, s);
+    default: return launch_ladder<256, PM>(p, nb1, pl.split, ws, s);
+  }
 }
 
 }  // namespace
@@ -762,6 +800,7 @@ hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
   p.beta = g.beta;
   p.nb2 = g.nb2;
   p.nred = g.nred;
+  p.seq = 0;
   p.pm = nullptr;
   p.tab1 = g.tab1;
   p.lower = 0;
@@ -770,7 +809,7 @@ hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
     // upper triangle (each mirrored value sums the same products in the same K order); other
     // symmetric products (odd K, unaligned rows) take the full product below
     p.lower = 1;
-    hipError_t e = launch_dma<192, 192, 2, 4, 3>(p, g.nb1, false, 1, nullptr, s);
+    hipError_t e = launch_dma<192, 192, 2, 4, 3>(p, g.nb1, 1, nullptr, false, s);
     if (e != hipSuccess) return e;
     const long nbk = (g.M + 31) / 32;
     hipLaunchKernelGGL(mirror_upper_kernel, dim3((unsigned)(nbk * (nbk + 1) / 2), (unsigned)g.nb2, (unsigned)g.nb1),
@@ -814,75 +853,52 @@ hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
   return launch_cfg<32, 32, 16, 1, 1, 3>(p, amf, bnf, g.nb1, nb1d, g.ws, g.ws_elems, s);
 }
 
-hipError_t gemm_f64_ladder(int M, int Tv, const double* A, const double* V, long ldv, long vrows, const int* pm,
-                           double* C, hipStream_t s, const LadderBatch& lb) {
-  if (M <= 0 || Tv <= 0) return hipSuccess;
-  const bool pmode = pm != nullptr;
-  if (pmode && (ldv < Tv || vrows < Tv)) return hipErrorInvalidValue;
-  const long half = (long)M * Tv;
+hipError_t gemm_f64_ladder(const Ladder& L, hipStream_t s) {
+  if (L.M <= 0 || L.N <= 0) return hipSuccess;
+  const bool pmode = L.pm != nullptr;
+  const LadderBatch& lb = L.lb;
+  if (L.K <= 0 || lb.n > 65535 || L.Mdec <= 0 || L.M % L.Mdec) return hipErrorInvalidValue;
   if (bounds_checking()) {
-    const long vlast = pmode ? (vrows - 1) * ldv + Tv - 1 : 2L * Tv * Tv - 1;
     const long e1 = lb.tab ? lb.tab_max : lb.n - 1;  // last operand block of batch level 1
-    if (!(range_ok(A, 0, e1 * lb.sa + 2 * half - 1, sizeof(double), "ladder A") &&
-          range_ok(C, 0, e1 * lb.sc + 2 * half - 1, sizeof(double), "ladder C") &&
-          range_ok(V, 0, e1 * lb.sv + vlast, sizeof(double), "ladder V") &&
-          (!pmode || range_ok(pm, 0, Tv - 1, sizeof(int), "ladder pair rows"))))
+    const long vlast = pmode ? (L.vrows - 1) * L.ldv + L.K - 1 : L.sv2 + (L.N - 1L) * L.ldv + L.K - 1;
+    if (!(range_ok(L.A, 0, e1 * lb.sa + L.sa2 + (L.M - 1L) * L.lda + L.K - 1, sizeof(double), "ladder A") &&
+          range_ok(L.C, 0, e1 * lb.sc + L.sc2 + (L.M - 1L) * L.ldc + L.N - 1, sizeof(double), "ladder C") &&
+          range_ok(L.V, 0, e1 * lb.sv + vlast, sizeof(double), "ladder V") &&
+          (!pmode || range_ok(L.pm, 0, L.N - 1, sizeof(int), "ladder pair rows")) &&
+          (!L.ws || range_ok(L.ws, 0, L.ws_elems - 1, sizeof(double), "ladder split-K scratch"))))
       return hipErrorInvalidValue;
   }
   if (dry_run()) return hipSuccess;
   GP p{};
-  p.M = M;
-  p.N = Tv;
-  p.K = Tv;
-  p.A = A;
-  p.sam = Tv;
+  p.M = L.M;
+  p.N = L.N;
+  p.K = L.K;
+  p.A = L.A;
+  p.sam = L.lda;
   p.sak = 1;
-  p.sa2 = half;
-  p.B = V;
+  p.sa2 = L.sa2;
+  p.B = L.V;
   p.sbk = 1;
-  p.sbn = pmode ? ldv : Tv;
-  p.sb2 = pmode ? 0 : (long)Tv * Tv;
-  p.C = C;
-  p.scm = Tv;
+  p.sbn = L.ldv;
+  p.sb2 = pmode ? 0 : L.sv2;
+  p.C = L.C;
+  p.scm = L.ldc;
   p.scn = 1;
-  p.sc2 = half;
+  p.sc2 = L.sc2;
   p.alpha = 1.0;
   p.beta = 0.0;
   p.nb2 = 2;
   p.nred = 1;
-  p.pm = pm;
+  p.pm = L.pm;
   p.sa1 = lb.sa;
   p.sb1 = lb.sv;
   p.sc1 = lb.sc;
   p.tab1 = lb.tab;
-  // Row tiles of 256, 240, 224, 208 or 128 pair rows: the least padded M wins (each extra row is a full
-  // row of wasted products); on a tie the taller tile, which reads the vvvv operand fewer times.
-  // 208 rows (one wave column of 13 x 16 rows per wave) fit T(40) = 820 pairs in four tiles with
-  // 1.5 % padding where 224 rows pad by 9 %.
-  const long pad256 = (M + 255L) / 256 * 256, pad224 = (M + 223L) / 224 * 224, pad128 = (M + 127L) / 128 * 128;
-  const long pad208 = (M + 207L) / 208 * 208, pad240 = (M + 239L) / 240 * 240;
-  if (lb.n > 65535) return hipErrorInvalidValue;
-  if (dma_eligible(p)) {
-    // 240 rows (one wave column of 15 x 16 rows per wave) fit T(21) = 231 pairs with 4 % padding
-    // where 256 rows pad by 11 %, and sixteen stacked T(30) = 465 states exactly
-    const long best = std::min({pad256, pad240, pad224, pad208, pad128});
-    const int t = pad256 == best ? 0 : pad240 == best ? 4 : pad224 == best ? 1 : pad208 == best ? 2 : 3;
-    if (pmode) {  // two B rows per pair: two 16-deep stages
-      if (t == 0) return launch_dma<256, 128, 2, 4, 2>(p, lb.n, true, 1, nullptr, s);
-      if (t == 4) return launch_dma<240, 128, 1, 8, 2>(p, lb.n, true, 1, nullptr, s);
-      if (t == 1) return launch_dma<224, 128, 2, 4, 2>(p, lb.n, true, 1, nullptr, s);
-      if (t == 2) return launch_dma<208, 128, 1, 8, 2>(p, lb.n, true, 1, nullptr, s);
-      return launch_dma<128, 128, 2, 4, 2>(p, lb.n, true, 1, nullptr, s);
-    }
-    if (t == 0) return launch_dma<256, 128, 4, 2, 3>(p, lb.n, false, 1, nullptr, s);
-    if (t == 4) return launch_dma<240, 128, 1, 8, 3>(p, lb.n, false, 1, nullptr, s);
-    if (t == 1) return launch_dma<224, 128, 2, 4, 3>(p, lb.n, false, 1, nullptr, s);
-    if (t == 2) return launch_dma<208, 128, 1, 8, 3>(p, lb.n, false, 1, nullptr, s);
-    return launch_dma<128, 128, 2, 4, 3>(p, lb.n, false, 1, nullptr, s);
-  }
-  if (pad256 <= pad224 && pad256 <= pad128) return launch_ladder<256, 4>(p, lb.n, pmode, s);
-  if (pad224 <= pad128) return launch_ladder<224, 2>(p, lb.n, pmode, s);
-  return launch_ladder<128, 2>(p, lb.n, pmode, s);
+  if (!dma_eligible(p)) return hipErrorInvalidValue;  // the operands' rows are laid out for this kernel
+  const LadderPlan pl = ladder_plan(L.M, L.Mdec, L.N, L.K);
+  // one slice after another where the partial tiles do not fit the scratch: the same sums
+  double* ws = (long)pl.split * L.M * L.N * 2 * lb.n <= L.ws_elems ? L.ws : nullptr;
+  return pmode ? launch_ladder_plan<true>(p, lb.n, pl, ws, s) : launch_ladder_plan<false>(p, lb.n, pl, ws, s);
 }
 
 }  // namespace ascc

@@ -360,6 +360,30 @@ __global__ __launch_bounds__(256) void lowp_t_kernel(void* __restrict__ outp, lo
   }
 }
 
+// Low-precision shadow of [(kc|bd) | (kc|ld)]: row m = k*v + b (from kcbd[k][c][b][d]) or ov + k*o + l
+// (from kcld[k][c][l][d]), column c*v + d, zero padding up to ldo, laid out as to_lowp_2d lays out its rows.
+template <bool BF>
+__global__ __launch_bounds__(256) void lowp_gwz_kernel(void* __restrict__ outp, long ldo,
+                                                       const double* __restrict__ kcbd,
+                                                       const double* __restrict__ kcld, int o, int v) {
+  const long ov = (long)o * v, vv = (long)v * v, m = blockIdx.x;
+  const double* src = m < ov ? kcbd + m / v * v * vv + m % v * v : kcld + (m - ov) / o * v * ov + (m - ov) % o * v;
+  const long sc = m < ov ? vv : ov;
+  for (long x = blockIdx.y * 256L + threadIdx.x; x < ldo; x += (long)gridDim.y * 256) {
+    const long c = x / v;
+    const double d = x < vv ? src[c * sc + (x - c * v)] : 0.0;
+    if (BF) {
+      unsigned short* out = reinterpret_cast<unsigned short*>(outp);
+      const unsigned short h = bf16_rne((float)d);
+      const long q = m * 2 * ldo + (x >> 5) * 64 + (x & 31);
+      out[q] = h;
+      out[q + 32] = bf16_rne((float)(d - (double)bf16_to_f(h)));
+    } else {
+      reinterpret_cast<float*>(outp)[m * ldo + x] = (float)d;
+    }
+  }
+}
+
 // Low-precision shadow of the vvvv halves formed from the full (ac|bd) matrix in pair order (rows
 // at stride ldv): row r = h*Tv + n (h = 0: +, 1: -), column k < Tv, zero padding up to ldo; in FP64
 // x = V[n][k] +- V[pm[n]][k], then rounded and laid out as to_lowp_2d does (FP32, or interleaved bf16).
@@ -1296,6 +1320,23 @@ hipError_t gemm_lowp(const GemmLP& g, hipStream_t s) {
   if (sp.split > 1) to_partials(p);
   hipLaunchKernelGGL(gemm_lowp_kernel, dim3(p.tiles_m * p.tiles_n, nbz, sp.split), dim3(NT), 0, s, p);
   if (sp.split > 1) reduce(sp.split);
+  return hipGetLastError();
+}
+
+hipError_t to_lowp_gwz(int prec, float* out, long ldo, const double* kcbd, const double* kcld, int o, int v,
+                       hipStream_t s) {
+  const long ov = (long)o * v, vv = (long)v * v, rows = ov + (long)o * o;
+  if (ldo < vv || ldo % 32) return hipErrorInvalidValue;
+  if (bounds_checking() && !(range_ok(kcbd, 0, ov * vv - 1, 8, "Gwz shadow (kc|bd)") &&
+                             range_ok(kcld, 0, ov * ov - 1, 8, "Gwz shadow (kc|ld)") &&
+                             range_ok(out, 0, rows * ldo - 1, 4, "Gwz shadow")))
+    return hipErrorInvalidValue;
+  if (dry_run()) return hipSuccess;
+  const dim3 grid((unsigned)rows, (unsigned)std::min<long>((ldo + 255) / 256, 64));
+  if (prec == kPrecBF16x3)
+    hipLaunchKernelGGL(lowp_gwz_kernel<true>, grid, dim3(256), 0, s, out, ldo, kcbd, kcld, o, v);
+  else
+    hipLaunchKernelGGL(lowp_gwz_kernel<false>, grid, dim3(256), 0, s, out, ldo, kcbd, kcld, o, v);
   return hipGetLastError();
 }
 

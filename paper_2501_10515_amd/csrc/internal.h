@@ -90,14 +90,27 @@ Gemm gemm_rm(int M, int N, int K, double alpha, const double* A, long lda, bool 
 hipError_t gemm_f64(const Gemm& g, hipStream_t s);
 
 // Particle-particle ladder over pair indices, both halves h = 0 (+), 1 (-) in one launch:
-//   C[h][m][n] = sum_k A[h][m][k] * Vh(n, k),   m < M;  n, k < Tv
-// A and C are row-major [2][M][Tv].  pm == nullptr: Vh is stored, row-major [2][Tv][Tv] (V).
-// Otherwise V is the full (ac|bd) matrix in pair order (see pack_full), [vrows = v^2][ldv], and
-// Vh(n, k) = V[n][k] +- V[pm[n]][k] = (ac|bd) +- (ad|bc) for n = (a <= b), k = (c <= d) (on the
-// diagonal k = (c,c) this is twice the packed V+, so A carries half the diagonal t+).
-// No split-K, so every output is summed in the same order whatever M is.
-hipError_t gemm_f64_ladder(int M, int Tv, const double* A, const double* V, long ldv, long vrows, const int* pm,
-                           double* C, hipStream_t s, const LadderBatch& lb = LadderBatch());
+//   C_h[m][n] = sum_k A_h[m][k] * V_h(n, k),   m < M, n < N, k < K
+// A_h and C_h are rows at strides lda, ldc, the halves sa2, sc2 apart.  pm == nullptr: V_h is stored,
+// N rows at stride ldv, the halves sv2 apart.  Otherwise V is the full (ac|bd) matrix in pair order
+// (see pack_full), vrows rows at stride ldv, and V_h(n, k) = V[n][k] +- V[pm[n]][k] = (ac|bd) +- (ad|bc)
+// for n = (a <= b), k = (c <= d) (its diagonal columns hold (ac|bc) / 2, so V_+ is (ac|bc) there).
+// Rows are 16-byte aligned, K even (zero past T(v)).  A row's sums do not depend on M: K is cut into
+// slices as for Mdec rows (those of one state; M a multiple of it), summed in slice order.
+struct Ladder {
+  int M = 0, Mdec = 0, N = 0, K = 0;
+  const double* A = nullptr;
+  long lda = 0, sa2 = 0;
+  const double* V = nullptr;
+  long ldv = 0, sv2 = 0, vrows = 0;
+  const int* pm = nullptr;
+  double* C = nullptr;
+  long ldc = 0, sc2 = 0;
+  double* ws = nullptr;  // optional scratch for the slices' partial tiles
+  long ws_elems = 0;
+  LadderBatch lb;
+};
+hipError_t gemm_f64_ladder(const Ladder& L, hipStream_t s);
 
 // Low-precision contraction with FP64 result (gemm_lowp.hip):
 //   C_z(m,n) = alpha * sum_k A_z[m*lda + k] * B_z[n*ldb + k] + beta * C_z(m,n)
@@ -143,6 +156,10 @@ hipError_t gemm_lowp(const GemmLP& g, hipStream_t s);
 hipError_t to_lowp_2d(int prec, float* out, long ldo, const double* in, long ldi, long rows, long cols, hipStream_t s);
 // Transposed shadow: out row r (r < rows) = column r of in ([cols][ldi] FP64), padded to ldo.
 hipError_t to_lowp_t(int prec, float* out, long ldo, const double* in, long ldi, long rows, long cols, hipStream_t s);
+// Rows m = k*v + b: (kc|bd) = kcbd[k][c][b][d] and m = ov + k*o + l: (kc|ld) = kcld[k][c][l][d] over the
+// columns c*v + d (zero padded to ldo) in low precision.
+hipError_t to_lowp_gwz(int prec, float* out, long ldo, const double* kcbd, const double* kcld, int o, int v,
+                       hipStream_t s);
 // Packed vvvv halves [2][Tv][ldo] (zero padded) in low precision, formed from the full (ac|bd)
 // matrix in pair order [vrows][ldv] as gemm_f64_ladder forms them (V[n][k] +- V[pm[n]][k]).
 hipError_t to_lowp_pm(int prec, float* out, long ldo, const double* V, long ldv, long vrows, const int* pm, long Tv,
@@ -186,19 +203,30 @@ hipError_t permute4_strided(double* out, const long ostr[4], const int dims[4], 
                             int nin, hipStream_t s);
 
 // Assembly of the doubles residual from the ring, ladder and E-term pieces (formula at the kernel).
+// rminus: the ladders are pair rows rl = R+ and rminus = R- at stride ldr (unpack_rpm) instead of RL.
 hipError_t assemble_r2(double* r2, const double* g1, const double* rl, const double* em, const double* p1,
-                       const double* p2, int no, int nv, hipStream_t s);
+                       const double* p2, int no, int nv, hipStream_t s, const double* rminus = nullptr, long ldr = 0);
 
 // Pair packing of the particle-particle ladder (p(i,j) = row-major index of i <= j).
-// Full (ac|bd) storage in pair order R(a,b) (a <= b: p(a,b); a > b: T(v) + strict index of (b,a)):
-// pm[n] = R(b,a) for pair n = (a <= b); pack_full scatters W[a - a0][b][c][d] = (ac|bd), a0 <= a < a1,
-// to V[R(a,b)][R(c,d)].
+// Full (ac|bd) storage in pair order R(a,b) (a <= b: p(a,b); a > b: T(v) + strict index of (b,a)), rows at
+// stride ldv: pm[n] = R(b,a) for pair n = (a <= b); pack_full scatters W[a - a0][b][c][d] = (ac|bd),
+// a0 <= a < a1, to V[R(a,b)][R(c,d)], the diagonal columns c = d halved.
 hipError_t pair_minus_rows(int* pm, int v, hipStream_t s);
-hipError_t pack_full(double* V, const double* W, int a0, int a1, int v, hipStream_t s);
-// t+ rows -> tplus[T(o)][T(v)], t- rows -> tminus[T(o)][T(v)] (and back for R+-)
-hipError_t pack_tpm(double* tplus, double* tminus, const double* t2, int o, int v, double dscale, hipStream_t s);
-hipError_t unpack_rpm(double* RL, const double* Rplus, const double* Rminus, int o, int v, hipStream_t s);
-hipError_t pack_vvvv(double* Vp, const double* W, int a0, int a1, int v, hipStream_t s);  // rows a0 <= a < a1
+hipError_t pack_full(double* V, long ldv, const double* W, int a0, int a1, int v, hipStream_t s);
+// Pair rows (+ and - halves over the pairs c <= d, rows at stride ldo >= T(v), zero past T(v)):
+// t+-[T(o)], t+ = (t^cd + t^dc)/2, and V+-[T(v)] and G+-[ov + o^2], sums and differences of (ac|bd) and
+// (ad|bc), of (kc|bd) and (kd|bc) and of (kc|ld) and (kd|lc) (diagonal: the element itself, and 0).
+hipError_t pack_tpm(double* tplus, double* tminus, long ldo, const double* t2, int o, int v, hipStream_t s);
+hipError_t pack_vvvv(double* vplus, double* vminus, long ldo, const double* W, int a0, int a1, int v,
+                     hipStream_t s);  // rows a0 <= a < a1
+// (kc|bd) as kcbd[k][c][b][d], (kc|ld) as kcld[k][c][l][d]
+hipError_t pack_gwz(double* gplus, double* gminus, long ldo, const double* kcbd, const double* kcld, int o, int v,
+                    hipStream_t s);
+// W' and chi+- from the W/Z columns of the ladder's pair rows (formulas at the kernel)
+hipError_t wz_chi(double* wp, long ldw, double* chip, double* chim, const double* rp, const double* rm, long ldr,
+                  const double* g4, const double* foo, const double* t1, int o, int v, hipStream_t s);
+// RL[i][j][a][b] from the pair rows R+- (stride ldr)
+hipError_t unpack_rpm(double* RL, const double* Rplus, const double* Rminus, long ldr, int o, int v, hipStream_t s);
 
 // r1[i][a] += Fhat[no+a][i]
 hipError_t add_fvo(double* r1, const double* fhat, int no, int nv, hipStream_t s);
