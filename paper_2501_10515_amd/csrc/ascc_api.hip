@@ -175,7 +175,7 @@ struct ascc_ints {
   double* e0;     // [1] reference energy <phi_0|H|phi_0> = sum_i (h_ii + f_ii)
   double* Bov;    // [Q][o][v]
   double* BovT;   // [o][v][Q]: the same, K = Q contiguous
-  double* KL;     // [2][ov][ov]: (ib|ja), 2(ia|jb) - (ib|ja)
+  double* KL;     // [2][ov] rows at stride ldov: (ib|ja), 2(ia|jb) - (ib|ja)
   double* Lijab;  // [o][o][v][v]: 2(ia|jb) - (ib|ja)
   double* V;      // FULL: [v^2] rows at stride ldV, (ac|bd) at [R(a,b)][R(c,d)] (pair order: a <= b first,
                   // see pack_full).  PACKED: [2][T(v) + ov + o^2] rows at stride ldT: V+-, (ac|bd) +- (ad|bc)
@@ -185,7 +185,7 @@ struct ascc_ints {
   double* pairtab;  // FULL: int32 [T(v)]: row R(b,a) of V for pair p(a,b), a <= b
   double *Tp, *Rp;  // ladder operands: t+- [2][T(o)] rows at stride ldT (pack_tpm), and R+- with the W/Z
                     // pair rows behind each (unpack_rpm, wz_chi), [2][T(o)] rows at stride ldR
-  long ldT, ldV, ldR;
+  long ldT, ldV, ldR, ldov;
   // residual work arrays
   double* Bc;                    // [Q][n][o] T1 correction of the first o columns of B
   double* Bh;                    // [Q][n][n]
@@ -194,7 +194,8 @@ struct ascc_ints {
   double *J;                     // [Q]
   double *BvoTt, *Boo, *Bvv;     // [o][v][Q] (B^_ai at [i][a][Q]), [Q][o][o], [Q][v][v]
   double *G1, *G2, *G3, *G4;     // ovov, [k][i][a][c], ovov, [k][i][l][j]
-  double *TU, *Y, *XZ, *P;       // each [2][ov][ov]
+  double *TU, *XZ;               // [2][ov] rows at stride ldov: Tx | U, Xc | Zd
+  double *Y, *P;                 // [2][ov][ov]
   double *Nq;                    // [Q][o][v]
   double *WZ;                    // [o^2][ov + o^2] (FP64: W' in the first ov columns)
   double *chi;                   // [o^2][o^2] (FP64: chi+-, [2][T(o)][T(o)])
@@ -307,11 +308,11 @@ std::vector<std::pair<double* ascc_ints::*, long>> ints_plan(long o, long v, lon
   const long n = o + v, nn = n * n, ov = o * v, oo = o * o, vv = v * v, ovov = ov * ov;
   const long To = o * (o + 1) / 2, Tv = v * (v + 1) / 2;
   const bool full = (mode == ASCC_VVVV_FULL);
-  const long wzl = ov + oo, ldT = pad_line(Tv), ldR = pad_line(Tv + wzl);
+  const long wzl = ov + oo, ldT = pad_line(Tv), ldR = pad_line(Tv + wzl), ldov = pad_line(ov);
   return {
       {&ascc_ints::B, Q * nn},        {&ascc_ints::h, nn},           {&ascc_ints::eps, n},
       {&ascc_ints::fov, ov},          {&ascc_ints::e0, 1},
-      {&ascc_ints::Bov, Q * ov},      {&ascc_ints::KL, 2 * ovov},
+      {&ascc_ints::Bov, Q * ov},      {&ascc_ints::KL, 2 * ov * ldov},
       {&ascc_ints::Lijab, oo * vv},   {&ascc_ints::G, full ? 2 * wzl * ldT : 0},
       {&ascc_ints::BovT, ov * Q},
       {&ascc_ints::V, full ? vv * pad_line(vv) : 2 * (Tv + wzl) * ldT},
@@ -321,7 +322,7 @@ std::vector<std::pair<double* ascc_ints::*, long>> ints_plan(long o, long v, lon
       {&ascc_ints::Fh, nn},           {&ascc_ints::J, Q},            {&ascc_ints::BvoTt, Q * ov},
       {&ascc_ints::Boo, Q * oo},      {&ascc_ints::Bvv, Q * vv},     {&ascc_ints::G1, ovov},
       {&ascc_ints::G2, oo * vv},      {&ascc_ints::G3, ovov},        {&ascc_ints::G4, oo * oo},
-      {&ascc_ints::TU, 2 * ovov},     {&ascc_ints::Y, 2 * ovov},     {&ascc_ints::XZ, 2 * ovov},
+      {&ascc_ints::TU, 2 * ov * ldov}, {&ascc_ints::Y, 2 * ovov},    {&ascc_ints::XZ, 2 * ov * ldov},
       {&ascc_ints::P, 2 * ovov},      {&ascc_ints::Nq, Q * ov},      {&ascc_ints::WZ, oo * (ov + oo)},
       {&ascc_ints::chi, std::max(oo * oo, 2 * To * To)}, {&ascc_ints::RL, oo * vv},     {&ascc_ints::EM, oo * vv},
       {&ascc_ints::Abc, vv},          {&ascc_ints::Bkj, oo},         {&ascc_ints::Fvvp, vv},
@@ -633,6 +634,15 @@ hipError_t shadow(const ascc_ints* I, float* out, const double* in, long rows, l
   return hipSuccess;
 }
 
+// Low-precision shadow of [2][ov] rows at stride ldov (leading dimension lowp_ld(ov)).
+hipError_t shadow_ov(const ascc_ints* I, float* out, const double* in, hipStream_t s) {
+  EACH_SLOT {
+    const hipError_t e = to_lowp_2d(lowp_kind(I), S(out), lowp_ld(I->ov), S(in), I->ldov, 2 * I->ov, I->ov, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Low-precision shadow of `rows` rows of pairs at stride ldT.
 hipError_t shadow_pairs(const ascc_ints* I, float* out, const double* in, long rows, hipStream_t s) {
   const long Tv = (long)I->nv * (I->nv + 1) / 2;
@@ -700,7 +710,8 @@ int ladder_launch(ascc_ints* I, long S, const double* Tp, double* Rp, const Ladd
   return ASCC_OK;
 }
 
-// The ladders of S states on this integral set into the stacked rows Tp, Rp (Tpf in low precision).
+// The ladders of S states on this integral set into the stacked rows Tp, Rp (Tpf in low precision); t2s ==
+// nullptr: the t+- rows are there already.
 // Phases: pp_pack (pair packing and low-precision operands), pp_ladder (the contraction launch, nothing
 // else), pp_unpack (back to [i][j][a][b], where it is done).
 int pp_ladder_states(ascc_ints* I, int S, const double* const* t2s, double* Tp, double* Rp, float* Tpf,
@@ -711,7 +722,8 @@ int pp_ladder_states(ascc_ints* I, int S, const double* const* t2s, double* Tp, 
   const bool lowp = I->cur_prec != ASCC_PREC_FP64;
   const long ld = lowp_ld(Tv);
   phase_begin(I, PH_PACK, s);
-  for (int k = 0; k < S; ++k) HIPCHK(pack_tpm(Tp + k * To * ldT, Tp + (M + k * To) * ldT, ldT, t2s[k], o, v, s));
+  if (t2s)
+    for (int k = 0; k < S; ++k) HIPCHK(pack_tpm(Tp + k * To * ldT, Tp + (M + k * To) * ldT, ldT, t2s[k], o, v, s));
   if (lowp) HIPCHK(shadow_pairs(I, Tpf, Tp, 2 * M, s));
   phase_end(I, s);
   phase_begin(I, PH_LADDER, s);
@@ -728,15 +740,14 @@ int pp_ladder_states(ascc_ints* I, int S, const double* const* t2s, double* Tp, 
   return ASCC_OK;
 }
 
-// The ladder of every slot of a batch, each against its own integral set: the pair packing per
-// slot, one contraction launch over the slots.
-int pp_ladder_slots(ascc_ints* I, const double* t2, hipStream_t s) {
+// The ladder of every slot of a batch, each against its own integral set, one contraction launch over
+// the slots.
+int pp_ladder_slots(ascc_ints* I, hipStream_t s) {
   const int o = I->no, v = I->nv;
   const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2, M = To;
   const bool lowp = I->cur_prec != ASCC_PREC_FP64;
   const long ld = lowp_ld(Tv);
   phase_begin(I, PH_PACK, s);
-  EACH_SLOT HIPCHK(pack_tpm(S(I->Tp), S(I->Tp) + M * I->ldT, I->ldT, S(t2), o, v, s));
   if (lowp) EACH_SLOT HIPCHK(shadow_pairs(I, S(I->Tpf), S(I->Tp), 2 * M, s));
   phase_end(I, s);
   phase_begin(I, PH_LADDER, s);
@@ -760,9 +771,10 @@ int pp_ladder_slots(ascc_ints* I, const double* t2, hipStream_t s) {
   return ASCC_OK;
 }
 
-int pp_ladder(ascc_ints* I, const double* t2, hipStream_t s) {
-  if (nslots() > 1) return pp_ladder_slots(I, t2, s);
-  return pp_ladder_states(I, 1, &t2, I->Tp, I->Rp, I->Tpf, s);
+// The ladder of the amplitudes whose t+- rows amp_views has written.
+int pp_ladder(ascc_ints* I, hipStream_t s) {
+  if (nslots() > 1) return pp_ladder_slots(I, s);
+  return pp_ladder_states(I, 1, nullptr, I->Tp, I->Rp, I->Tpf, s);
 }
 
 size_t ints_footprint(long o, long v, long Q, int precision, int mode) {
@@ -805,7 +817,7 @@ int plascc_remove(ascc_ints* I, const double* t2, double* RL, hipStream_t s) {
   double* G = I->XZ;  // (kc|ld) at [k*o + l][c*v + d], from K[kd,lc] (the rings are done with XZ)
   {
     int d[4] = {o, o, v, v};
-    Perm4In x = pin(I->KL, (long)v * ov, v, 1, ov, 1.0);
+    Perm4In x = pin(I->KL, (long)v * I->ldov, v, 1, I->ldov, 1.0);
     HIPCHK(permute4(G, d, 0.0, &x, 1, s));
   }
   double* ZM = I->chi;
@@ -823,15 +835,16 @@ int plascc_remove(ascc_ints* I, const double* t2, double* RL, hipStream_t s) {
   // plA / plC for the E terms.
   const double kappa[2] = {0.5, -0.5};
   for (int z = 0; z < 2; ++z) {
-    const double* T = I->TU + z * ovov;
-    const double* K = I->KL + z * ovov;
+    const long ldk = I->ldov;
+    const double* T = I->TU + z * ov * ldk;
+    const double* K = I->KL + z * ov * ldk;
     const double* Y = I->Y + z * ovov;  // T K from the ring stage
     double* P = I->P + z * ovov;
-    HIPCHK(cross_gather_rows(I->plA, ov, T, ov, ov, ov, X, true, s));  // X rows of T^M
-    HIPCHK(cross_gather_cols(I->plC, mp, T, ov, ov, X, &X, s));         // C_p
-    HIPCHK(cross_gather_rows(I->plKr, ov, K, ov, ov, ov, X, false, s));
+    HIPCHK(cross_gather_rows(I->plA, ov, T, ldk, ov, ov, X, true, s));  // X rows of T^M
+    HIPCHK(cross_gather_cols(I->plC, mp, T, ldk, ov, X, &X, s));         // C_p
+    HIPCHK(cross_gather_rows(I->plKr, ov, K, ldk, ov, ov, X, false, s));
     HIPCHK(cross_gather_cols(I->plKpp, mp, I->plKr, ov, m, X, nullptr, s));  // K_pp
-    HIPCHK(cross_rows_without_corner(I->plYp, ov, Y, T, K, X, s));          // X rows of T^M K
+    HIPCHK(cross_rows_without_corner(I->plYp, ov, Y, T, K, ldk, X, s));          // X rows of T^M K
     HIPCHK(cross_gather_cols(I->plYpp, mp, I->plYp, ov, m, X, nullptr, s));
     // (X, X) block
     HIPCHK(mm(I, gemm_rm(m, m, ov, 1.0, I->plYp, ov, false, I->plA, ov, true, 0.0, I->plS, mp), s));
@@ -936,21 +949,16 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   }
 
   phase_end(I, s);
-  // --- permuted amplitude views: Tx[iajb] = t2[ijba], U[iajb] = 2 t2[ijab] - t2[ijba]
+  // --- amplitude views: Tx[iajb] = t2[ijba], U[iajb] = 2 t2[ijab] - t2[ijba], t+-
   phase_begin(I, PH_AMP, s);
-  double* Tx = I->TU;
-  double* U = I->TU + ovov;
-  EACH_SLOT {
-    int d[4] = {o, v, o, v};
-    const long si = (long)o * vv, sj = vv;
-    Perm4In x = pin(S(t2), si, 1, sj, v, 1.0);
-    HIPCHK(permute4(S(Tx), d, 0.0, &x, 1, s));
-    Perm4In y[2] = {pin(S(t2), si, v, sj, 1, 2.0), pin(S(t2), si, 1, sj, v, -1.0)};
-    HIPCHK(permute4(S(U), d, 0.0, y, 2, s));
-  }
+  const long ldov = I->ldov;
+  double* U = I->TU + ov * ldov;
+  // with the pair rows t+- where the ladder is computed here
+  EACH_SLOT HIPCHK(amp_views(S(I->TU), S(I->TU) + ov * ldov, ldov, lad ? nullptr : S(rows.Tp),
+                             lad ? nullptr : S(rows.Tp) + rows.st, I->ldT, S(t2), o, v, s));
   const bool lowp = I->cur_prec != ASCC_PREC_FP64;
   const long lov = lowp_ld(ov), lQ = lowp_ld(Q), loo = lowp_ld(oo);
-  if (lowp) HIPCHK(shadow(I, I->TUf, I->TU, 2 * ov, ov, s));  // Tx|U rows, K = ov
+  if (lowp) HIPCHK(shadow_ov(I, I->TUf, I->TU, s));  // Tx|U rows, K = ov
 
   phase_end(I, s);
   // --- density-fitted dressed integral blocks (K = naux)
@@ -974,7 +982,7 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     HIPCHK(mm(I, gemm_rm(oo, vv, Q, 1.0, I->Boo, oo, true, I->Bvv, vv, false, 0.0, I->G2, vv), s));    // g^_kiac
     HIPCHK(mm(I, gemm_rm(ov, ov, Q, 1.0, I->BvoTt, Q, false, I->BovT, Q, true, 0.0, I->G3, ov), s));   // g^_aikc
     // N_Q[k,a] = sum_lc B_Q,lc u_kl^ac (U is symmetric: its rows are its columns)
-    HIPCHK(mm(I, gemm_rm(Q, ov, ov, 1.0, I->Bov, ov, false, U, ov, true, 0.0, I->Nq, ov), s));
+    HIPCHK(mm(I, gemm_rm(Q, ov, ov, 1.0, I->Bov, ov, false, U, ldov, true, 0.0, I->Nq, ov), s));
   }
   HIPCHK(mm(I, gemm_rm(oo, oo, Q, 1.0, I->Boo, oo, true, I->Boo, oo, false, 0.0, I->G4, oo), s));      // g^_kilj
 
@@ -1029,7 +1037,7 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     phase_end(I, s);
   }
   // --- particle-particle ladder over the undressed (ac|bd) (with W/Z in FP64), plus the hole-hole ladder
-  if (!lad && (rc = pp_ladder(I, t2, s))) return rc;
+  if (!lad && (rc = pp_ladder(I, s))) return rc;
   const bool pairs = !lowp && I->pl_hole < 0;  // the assembly reads the ladders as pair rows
   if (lowp) {
     phase_begin(I, PH_UNPACK, s);
@@ -1071,34 +1079,26 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     HIPCHK(glp(lp_nt(I, ov, ov, ov, 2, I->TUf, ld, ov * ld, I->KLf, ld, ov * ld, I->Y, ov, ovov), s));
   } else {
     // K and L are symmetric, so B(k, n) = KL[n][k]: both operands K-contiguous
-    Gemm g = gemm_rm(ov, ov, ov, 1.0, I->TU, ov, false, I->KL, ov, true, 0.0, I->Y, ov);
-    g.sa2 = ovov;
-    g.sb2 = ovov;
+    Gemm g = gemm_rm(ov, ov, pad_even(ov), 1.0, I->TU, ldov, false, I->KL, ldov, true, 0.0, I->Y, ov);
+    g.sa2 = ov * ldov;
+    g.sb2 = ov * ldov;
     g.sc2 = ovov;
     g.nb2 = 2;
     HIPCHK(mm(I, g, s));
   }
   phase_end(I, s);
   phase_begin(I, PH_RING_XZ, s);
-  EACH_SLOT {
-    int d[4] = {o, v, o, v};  // (i, a, k, c)
-    const long si = vv, sa = v, sk = (long)o * vv, sc = 1;  // G2[k][i][a][c]
-    Perm4In x[2] = {pin(S(I->G2), si, sa, sk, sc, 1.0), pin(S(I->Y), (long)v * o * v, (long)o * v, v, 1, -0.5)};
-    HIPCHK(permute4(S(I->XZ), d, 0.0, x, 2, s));
-    Perm4In z[3] = {pin(S(I->G3), (long)v * o * v, (long)o * v, v, 1, 2.0), pin(S(I->G2), si, sa, sk, sc, -1.0),
-                    pin(S(I->Y) + ovov, (long)v * o * v, (long)o * v, v, 1, 0.5)};
-    HIPCHK(permute4(S(I->XZ) + ovov, d, 0.0, z, 3, s));
-  }
+  EACH_SLOT HIPCHK(ring_xz(S(I->XZ), S(I->XZ) + ov * ldov, ldov, S(I->G2), S(I->G3), S(I->Y), S(I->Y) + ovov, o, v, s));
   phase_end(I, s);
   phase_begin(I, PH_RING_P, s);
   if (lowp) {  // P1 = Tx Xc^T, P2 = U Zd^T
     const long ld = lowp_ld(ov);
-    HIPCHK(shadow(I, I->XZf, I->XZ, 2 * ov, ov, s));
+    HIPCHK(shadow_ov(I, I->XZf, I->XZ, s));
     HIPCHK(glp(lp_nt(I, ov, ov, ov, 2, I->TUf, ld, ov * ld, I->XZf, ld, ov * ld, I->P, ov, ovov), s));
   } else {
-    Gemm g = gemm_rm(ov, ov, ov, 1.0, I->TU, ov, false, I->XZ, ov, true, 0.0, I->P, ov);
-    g.sa2 = ovov;
-    g.sb2 = ovov;
+    Gemm g = gemm_rm(ov, ov, pad_even(ov), 1.0, I->TU, ldov, false, I->XZ, ldov, true, 0.0, I->P, ov);
+    g.sa2 = ov * ldov;
+    g.sb2 = ov * ldov;
     g.sc2 = ovov;
     g.nb2 = 2;
     HIPCHK(mm(I, g, s));
@@ -1208,7 +1208,7 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     g.N = 1;
     g.K = ov;
     g.A = U;
-    g.sam = ov;
+    g.sam = ldov;
     g.sak = 1;
     g.B = I->Fovh;
     g.sbk = 1;
@@ -1323,12 +1323,17 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
   {
     int d[4] = {o, v, o, v};
     const long si = (long)v * o * v, sa = (long)o * v, sj = v, sb = 1;
+    const long ldk = I->ldov, ostr[4] = {v * ldk, ldk, v, 1};
+    if (ldk != ov) {  // zero past ov
+      int dz[4] = {1, 1, (int)(2 * ov), (int)ldk};
+      HIPCHK(permute4(I->KL, dz, 0.0, nullptr, 0, s));
+    }
     Perm4In x = pin(Jov, si, sb, sj, sa, 1.0);  // (ib|ja)
-    HIPCHK(permute4(I->KL, d, 0.0, &x, 1, s));
+    HIPCHK(permute4_strided(I->KL, ostr, d, 0.0, &x, 1, s));
     Perm4In y[2] = {pin(Jov, si, sa, sj, sb, 2.0), pin(Jov, si, sb, sj, sa, -1.0)};
-    HIPCHK(permute4(I->KL + ovov, d, 0.0, y, 2, s));
+    HIPCHK(permute4_strided(I->KL + ov * ldk, ostr, d, 0.0, y, 2, s));
     int d2[4] = {o, o, v, v};  // (i, j, a, b) <- L[i][a][j][b]
-    Perm4In z = pin(I->KL + ovov, si, sj, sa, sb, 1.0);
+    Perm4In z = pin(I->KL + ov * ldk, v * ldk, sj, ldk, sb, 1.0);
     HIPCHK(permute4(I->Lijab, d2, 0.0, &z, 1, s));
   }
   // G+- (and its low-precision shadow, unpacked) from a temporary [(k,c)][(b,d)] product
@@ -1418,7 +1423,7 @@ int build_lowp_shadows(ascc_ints* I, hipStream_t s) {
     HIPCHK(shadow_pairs(I, I->Vf, I->V, Tv, s));
     HIPCHK(shadow_pairs(I, I->Vf + Tv * lowp_ld(Tv), I->V + (Tv + wzl) * I->ldT, Tv, s));
   }
-  HIPCHK(shadow(I, I->KLf, I->KL, 2 * ov, ov, s));
+  HIPCHK(shadow_ov(I, I->KLf, I->KL, s));
   const long Q = I->naux;
   HIPCHK(shadow(I, I->BovTf, I->BovT, ov, Q, s));      // B_kc (undressed by T1) as [kc][Q]
   HIPCHK(shadow(I, I->Bovf, I->Bov, Q, ov, s));         // and as [Q][kc]
@@ -1843,6 +1848,7 @@ static int build_ints_impl(const double* d_B, const double* d_fock, int fock_is_
   const long Tv = v * (v + 1) / 2;
   I->ldT = pad_line(Tv);
   I->ldV = pad_line(I->vv);
+  I->ldov = pad_line(I->ov);
   I->ldR = pad_line(Tv + I->ov + I->oo);
   if (ws) {
     if ((reinterpret_cast<uintptr_t>(ws) & (kAlign - 1)) != 0) {

@@ -703,6 +703,103 @@ __global__ __launch_bounds__(kThreads) void pack_halves_kernel(PackP p) {
   }
 }
 
+// The amplitude views of the contractions from t2 (t_ij^ab = t_ji^ba), one pair i <= j and 32 x 32 tile pair
+// (C <= D) of (a, b) per workgroup, each element of t2[ij] read once:
+//   Tx[ia][jb] = t_ij^ba, U[ia][jb] = 2 t_ij^ab - t_ij^ba (rows at stride ld, zero past o v)
+// and, where plus is given, the pair rows t+- (as pack_halves_kernel).  o20 v180: 125 + 36 us as three
+// passes, 75 us as one.
+__global__ __launch_bounds__(kThreads) void amp_views_kernel(double* __restrict__ Tx, double* __restrict__ U, long ld,
+                                                            double* __restrict__ plus, double* __restrict__ minus,
+                                                            long ldo, const double* __restrict__ t2, int o, int v) {
+  __shared__ double x1[32][33], x2[32][33];  // x1[c - c0][d - d0] = M(c, d), x2[d - d0][c - c0] = M(d, c), M = t2[ij]
+  const int nblk = (v + 31) / 32;
+  const long vv = (long)v * v, ov = (long)o * v, Tv = (long)v * (v + 1) / 2;
+  int i = 0, rem = blockIdx.x;
+  while (rem >= o - i) {
+    rem -= o - i;
+    ++i;
+  }
+  const int j = i + rem;
+  int C = 0, trem = blockIdx.y;
+  while (trem >= nblk - C) {
+    trem -= nblk - C;
+    ++C;
+  }
+  const int c0 = 32 * C, d0 = 32 * (C + trem);
+  const bool diag = trem == 0;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
+  const double* M = t2 + ((long)i * o + j) * vv;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int r = ty + 8 * k;
+    if (c0 + r < v && d0 + tx < v) x1[r][tx] = M[(long)(c0 + r) * v + d0 + tx];
+    if (d0 + r < v && c0 + tx < v) x2[r][tx] = M[(long)(d0 + r) * v + c0 + tx];
+  }
+  __syncthreads();
+  // row p, columns q of the views: m = M(a, b), t = M(b, a) with a the row's and b the column's virtual
+  auto put = [&](int p, int a, int q, int b, double m, double t) {
+    const long x = ((long)p * v + a) * ld + (long)q * v + b;
+    Tx[x] = t;
+    U[x] = 2.0 * m - t;
+  };
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int r = ty + 8 * k;
+    {
+      const int c = c0 + r, d = d0 + tx;  // along d
+      if (c < v && d < v) {
+        const double m = x1[r][tx], t = x2[tx][r];
+        put(i, c, j, d, m, t);
+        if (i != j) put(j, c, i, d, t, m);
+        if (plus && c <= d) {
+          const long q = blockIdx.x * ldo + pidx(c, d, v);
+          plus[q] = (c == d) ? m : 0.5 * (m + t);
+          minus[q] = (c == d) ? 0.0 : 0.5 * (m - t);
+        }
+      }
+    }
+    if (!diag) {
+      const int d = d0 + r, c = c0 + tx;  // along c
+      if (d < v && c < v) {
+        const double m = x2[r][tx], t = x1[tx][r];
+        put(i, d, j, c, m, t);
+        if (i != j) put(j, d, i, c, t, m);
+      }
+    }
+  }
+  if (plus && blockIdx.y == 0)
+    for (long x = Tv + threadIdx.x; x < ldo; x += kThreads) plus[blockIdx.x * ldo + x] = minus[blockIdx.x * ldo + x] = 0.0;
+  // the padding columns of the rows (i, a in C), written once: by the pair (i, i) and the tile pairs (C, C)
+  if (i == j && diag) {
+    const int pad = (int)(ld - ov);
+    for (int x = threadIdx.x; x < 32 * pad; x += kThreads) {
+      const int a = c0 + x / pad;
+      if (a < v) Tx[((long)i * v + a) * ld + ov + x % pad] = U[((long)i * v + a) * ld + ov + x % pad] = 0.0;
+    }
+  }
+}
+
+// Xc[ia][kc] = g^_kiac - Y1[ia][kc] / 2, Zd[ia][kc] = 2 g^_aikc - g^_kiac + Y2[ia][kc] / 2 (g2[k][i][a][c] = g^_kiac,
+// g3[ia][kc] = g^_aikc; Xc, Zd rows at stride ld, zero past o v): one workgroup per row ia, every array along c.
+__global__ __launch_bounds__(kThreads) void ring_xz_kernel(double* __restrict__ xc, double* __restrict__ zd, long ld,
+                                                          const double* __restrict__ g2, const double* __restrict__ g3,
+                                                          const double* __restrict__ y1, const double* __restrict__ y2,
+                                                          int o, int v) {
+  const long ia = blockIdx.x, ov = (long)o * v, row = ia * ov;
+  const double* g = g2 + ia * v;  // [i][a][.] of k = 0; k advances by o v^2
+  for (int x = threadIdx.x; x < ld; x += kThreads) {
+    double a = 0.0, b = 0.0;
+    if (x < ov) {
+      const int k = x / v, c = x - k * v;
+      const double q = g[(long)k * ov * v + c];
+      a = q - 0.5 * y1[row + x];
+      b = 2.0 * g3[row + x] - q + 0.5 * y2[row + x];
+    }
+    xc[ia * ld + x] = a;
+    zd[ia * ld + x] = b;
+  }
+}
+
 // From the pair rows Rw+-[p(i,j)][m] of W/Z (m = k*v + b: W_ij[k,b] = sum_cd (kc|bd) t_ij^cd, m = ov + k*o + l:
 // Z_ij[k,l] = sum_cd (kc|ld) t_ij^cd; X_ij = X+ + X-, X_ji = X+ - X-), with rows at stride ldr:
 //   wp[ij][k][b] = W_ij[k,b] - 1/2 sum_l Z_ij[k,l] t1[l][b]   (rows at stride ldw)
@@ -1122,17 +1219,17 @@ __global__ void cross_scatter_add_block_kernel(double* __restrict__ dst, long ld
   }
 }
 
-// dst[k][c] = Y[cross_row(k)][c] - [cross_row(k) == hp] T[hp][hp] K[hp][c]  (square ld x ld operands,
+// dst[k][c] = Y[cross_row(k)][c] - [cross_row(k) == hp] T[hp][hp] K[hp][c]  (ld x ld operands, T and K rows at ldk,
 // hp = h * nv + pa): the cross rows of (T with its corner entry removed) K, from Y = T K.
 __global__ void cross_rows_without_corner_kernel(double* __restrict__ dst, long ldd, const double* __restrict__ Y,
-                                                 const double* __restrict__ T, const double* __restrict__ K, long ld,
-                                                 Cross X) {
+                                                 const double* __restrict__ T, const double* __restrict__ K, long ldk,
+                                                 long ld, Cross X) {
   const long m = X.m(), total = m * ld, hp = (long)X.h * X.nv + X.pa;
-  const double thp = T[hp * ld + hp];
+  const double thp = T[hp * ldk + hp];
   for (long x = blockIdx.x * (long)blockDim.x + threadIdx.x; x < total; x += (long)gridDim.x * blockDim.x) {
     const long k = x / ld, c = x - k * ld;
     const long r = cross_row(X, k);
-    dst[k * ldd + c] = Y[r * ld + c] - (r == hp ? thp * K[hp * ld + c] : 0.0);
+    dst[k * ldd + c] = Y[r * ld + c] - (r == hp ? thp * K[hp * ldk + c] : 0.0);
   }
 }
 
@@ -1263,15 +1360,17 @@ hipError_t cross_scatter_add_block(double* dst, long ldd, const double* src, lon
 }
 
 hipError_t cross_rows_without_corner(double* dst, long ldd, const double* Y, const double* T, const double* K,
-                                     const Cross& X, hipStream_t s) {
+                                     long ldk, const Cross& X, hipStream_t s) {
   const long m = X.m(), ld = X.n();
-  if (!cross_ok(X) || ldd < ld) return hipErrorInvalidValue;
+  if (!cross_ok(X) || ldd < ld || ldk < ld) return hipErrorInvalidValue;
   if (bounds_checking() && !(range_ok(dst, 0, (m - 1) * ldd + ld - 1, 8, "cross rows dst") &&
-                             range_ok(Y, 0, ld * ld - 1, 8, "cross rows Y") && range_ok(T, 0, ld * ld - 1, 8, "cross rows T") &&
-                             range_ok(K, 0, ld * ld - 1, 8, "cross rows K")))
+                             range_ok(Y, 0, ld * ld - 1, 8, "cross rows Y") &&
+                             range_ok(T, 0, (ld - 1) * ldk + ld - 1, 8, "cross rows T") &&
+                             range_ok(K, 0, (ld - 1) * ldk + ld - 1, 8, "cross rows K")))
     return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
-  hipLaunchKernelGGL(cross_rows_without_corner_kernel, dim3(ew_grid(m * ld)), dim3(256), 0, s, dst, ldd, Y, T, K, ld, X);
+  hipLaunchKernelGGL(cross_rows_without_corner_kernel, dim3(ew_grid(m * ld)), dim3(256), 0, s, dst, ldd, Y, T, K, ldk, ld,
+                     X);
   return hipGetLastError();
 }
 
@@ -1358,6 +1457,31 @@ hipError_t pack_gwz(double* gplus, double* gminus, long ldo, const double* kcbd,
   const hipError_t e = pack_halves(kPackG, gplus, gminus, ldo, kcbd, o, v, 0, ov, 0, ov - 1, ov * v * v, s);
   if (e != hipSuccess) return e;
   return pack_halves(kPackGo, gplus, gminus, ldo, kcld, o, v, 0, oo, ov, ov + oo - 1, ov * ov, s);
+}
+
+hipError_t amp_views(double* Tx, double* U, long ld, double* tplus, double* tminus, long ldo, const double* t2, int o,
+                     int v, hipStream_t s) {
+  const long To = (long)o * (o + 1) / 2, ov = (long)o * v, nblk = (v + 31) / 32;
+  if (ld < ov || nblk * (nblk + 1) / 2 > 65535) return hipErrorInvalidValue;
+  if (bounds_checking() && !(chk(Tx, ov * ld, "views Tx") && chk(U, ov * ld, "views U") && chk(t2, ov * ov, "views t2") &&
+                             (!tplus || (chk(tplus, To * ldo, "views t+") && chk(tminus, To * ldo, "views t-")))))
+    return hipErrorInvalidValue;
+  if (dry_run()) return hipSuccess;
+  hipLaunchKernelGGL(amp_views_kernel, dim3((unsigned)To, (unsigned)(nblk * (nblk + 1) / 2)), dim3(kThreads), 0, s, Tx, U,
+                     ld, tplus, tminus, ldo, t2, o, v);
+  return hipGetLastError();
+}
+
+hipError_t ring_xz(double* xc, double* zd, long ld, const double* g2, const double* g3, const double* y1,
+                   const double* y2, int o, int v, hipStream_t s) {
+  const long ov = (long)o * v;
+  if (ld < ov) return hipErrorInvalidValue;
+  if (bounds_checking() && !(chk(xc, ov * ld, "ring Xc") && chk(zd, ov * ld, "ring Zd") && chk(g2, ov * ov, "ring g_kiac") &&
+                             chk(g3, ov * ov, "ring g_aikc") && chk(y1, ov * ov, "ring Y1") && chk(y2, ov * ov, "ring Y2")))
+    return hipErrorInvalidValue;
+  if (dry_run()) return hipSuccess;
+  hipLaunchKernelGGL(ring_xz_kernel, dim3((unsigned)ov), dim3(kThreads), 0, s, xc, zd, ld, g2, g3, y1, y2, o, v);
+  return hipGetLastError();
 }
 
 hipError_t wz_chi(double* wp, long ldw, double* chip, double* chim, const double* rp, const double* rm, long ldr,

@@ -46,7 +46,8 @@ struct GP {
                             // each added to C in turn (the sums of the partial tiles, in slice order)
   const int* pm;            // pair-combined B (ladder): second row of pair n
   const int* tab1;          // batch level 1: operand block of grid index z1 (nullptr: z1 itself)
-  int lower;                // symmetric C: tiles on and below the diagonal only (tiles_m == tiles_n)
+  int lower;                // symmetric C: tiles on and below the diagonal only (tiles_m == tiles_n), each
+                            // stored at its transposed place too
 };
 
 // Workgroup-to-tile map.  Workgroups are dispatched to the 8 XCDs round-robin; each XCD gets
@@ -79,32 +80,6 @@ __device__ __forceinline__ void tile_of_lower(int bid, int tiles, int& tm, int& 
   while (m * (m + 1) / 2 > t) --m;
   tm = m;
   tn = t - m * (m + 1) / 2;
-}
-
-// C_z(r, c) = C_z(c, r) for c > r: the strict upper triangle of a symmetric product copied from
-// its lower one through a 32 x 32 LDS tile (coalesced reads and writes).  grid.x enumerates the
-// 32 x 32 blocks on and above the diagonal, grid.y / grid.z the batch levels.
-__global__ __launch_bounds__(256) void mirror_upper_kernel(GP p) {
-  __shared__ double tile[32][33];
-  const int nb = (p.M + 31) / 32;
-  int by = (int)((sqrtf(8.f * (float)blockIdx.x + 1.f) - 1.f) * 0.5f);  // column block index
-  while ((by + 1) * (by + 2) / 2 <= (int)blockIdx.x) ++by;
-  while (by * (by + 1) / 2 > (int)blockIdx.x) --by;
-  const int bx = (int)blockIdx.x - by * (by + 1) / 2;  // row block, bx <= by
-  if (by >= nb) return;
-  const int zs = p.tab1 ? p.tab1[blockIdx.z] : (int)blockIdx.z;
-  double* C = p.C + zs * p.sc1 + (long)blockIdx.y * p.sc2;
-  const int r0 = bx * 32, c0 = by * 32;  // destination rows r0.., columns c0.. (upper side)
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int i = ty; i < 32; i += 8) {  // source C(c, r): rows c0 + i, columns r0 + tx
-    const int c = c0 + i, r = r0 + tx;
-    if (c < p.M && r < p.M) tile[i][tx] = C[(long)c * p.scm + (long)r * p.scn];
-  }
-  __syncthreads();
-  for (int i = ty; i < 32; i += 8) {
-    const int r = r0 + i, c = c0 + tx;
-    if (r < p.M && c < p.M && c > r) C[(long)r * p.scm + (long)c * p.scn] = tile[tx][i];
-  }
 }
 
 // MINB: workgroups per CU the register budget is sized for.
@@ -348,7 +323,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const double* base, 
   return __builtin_amdgcn_make_buffer_rsrc(ub, (short)0, __builtin_amdgcn_readfirstlane((int)(rows * ld * 8)), 0x00020000);
 }
 
-template <int BM, int BN, int WM, int WN, int S, bool PM>
+// RED: nred products of K-values each (K a multiple of 16) run through one K loop, product r at strides
+// sar, sbr.
+template <int BM, int BN, int WM, int WN, int S, bool PM, bool RED>
 __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
   typedef double dd2 __attribute__((ext_vector_type(2)));
   typedef double d4 __attribute__((ext_vector_type(4)));
@@ -396,8 +373,12 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
   // read as zero; the advance along K is a scalar offset), pair rows of a pair-combined B, which lie
   // anywhere in the stored matrix, as addresses (kZero16 past N).
   constexpr int J2 = (IA + IB) / NW;  // first instruction of a wave that can hold pair rows
-  const __amdgpu_buffer_rsrc_t ra = tile_rsrc(Ab + (long)m0 * p.sam, min(BM, p.M - m0), p.sam);
-  const __amdgpu_buffer_rsrc_t rb = tile_rsrc(Bb + (long)n0 * p.sbn, min(BN, p.N - n0), p.sbn);
+  const double* At = Ab + (long)m0 * p.sam;
+  const double* Bt = Bb + (long)n0 * p.sbn;
+  const int rows_a = min(BM, p.M - m0), rows_b = min(BN, p.N - n0);
+  __amdgpu_buffer_rsrc_t ra = tile_rsrc(At, rows_a, p.sam), rb = tile_rsrc(Bt, rows_b, p.sbn);
+  const int nk1 = (p.K + KS - 1) / KS;  // stages of one product
+  int k_red = 0;                         // RED: stages before the current product
   uint32_t off[NPW];
   const double* src2[PM ? NPW - J2 : 1];
   (void)src2;
@@ -421,7 +402,7 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
       lds_void_t* dst = (lds_void_t*)&T[st][g * 128];
       if (!PM || g < IA + IB) {
         const uint32_t o = off[j];
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(g < IA ? ra : rb, dst, 16, o, kt * KS * 8, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(g < IA ? ra : rb, dst, 16, o, (kt - k_red) * KS * 8, 0, 0);
       } else {
         const double* x = src2[PM && j >= J2 ? j - J2 : 0];
         const double* a = (x && kt * KS + ck < p.K) ? x + kt * KS : kZero16;
@@ -429,15 +410,21 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
       }
     }
   };
-  // before the loads of the last stage of an uneven K (no stage follows it): chunks past K read as zero
-  auto mask_tail = [&](int kt) {
-    if ((kt + 1) * KS > p.K && kt * KS + ck >= p.K) {
+  // before the loads of stage kt: RED: the descriptors of its product; otherwise, on the last stage of an
+  // uneven K (no stage follows it), chunks past K read as zero
+  auto begin_stage = [&](int kt) {
+    if constexpr (RED) {
+      const int r = kt / nk1;
+      k_red = r * nk1;
+      ra = tile_rsrc(At + r * p.sar, rows_a, p.sam);
+      rb = tile_rsrc(Bt + r * p.sbr, rows_b, p.sbn);
+    } else if ((kt + 1) * KS > p.K && kt * KS + ck >= p.K) {
 #pragma unroll
       for (int j = 0; j < NPW; ++j) off[j] = 0x80000000u;  // past the range of every descriptor
     }
   };
   auto issue = [&](int kt, int st) {
-    mask_tail(kt);
+    begin_stage(kt);
 #pragma unroll
     for (int j = 0; j < NPW; ++j) issue1(kt, st, j);
   };
@@ -485,7 +472,7 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
       for (int j = 0; j < RJ; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
     // stages [kt0, kt0 + nkt) of this slice
     const int kt0 = slice * p.it_per_split;
-    const int nkt = min((p.K + KS - 1) / KS, kt0 + p.it_per_split) - kt0;
+    const int nkt = min(RED ? nk1 * p.nred : nk1, kt0 + p.it_per_split) - kt0;
     if (slice != slice0) wait_stage<0>();  // every wave is done with the slots of the slice before
 #pragma unroll
     for (int st = 0; st < S; ++st)
@@ -516,7 +503,7 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
           else
             wait_stage<0>();
         }
-        if (last && refill) mask_tail(kt0 + kt + S);
+        if (last && refill) begin_stage(kt0 + kt + S);
         // the unit's products, with a fragment read or a refill load issued behind most of them
         constexpr int NM = 2 * GI * RJ, LS = NR + 2 * NPW <= NM ? 2 : 1;
         constexpr int ML = S == 2 ? 0 : LS == 2 ? NR : NM - NPW;  // two stages: the refill is due soonest
@@ -555,18 +542,21 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
             } else {
               double* c = Cb + (long)gm * p.scm + (long)gn * p.scn;
               *c = (slice != slice0) ? *c + v : (p.beta == 0.0) ? v : v + p.beta * *c;
+              if (!PM && !RED && BM == BN && p.lower && tm != tn) Cb[(long)gn * p.scm + (long)gm * p.scn] = v;
             }
           }
         }
   }
 }
 
-// K-contiguous operands with 16-byte aligned rows and an even K (the loads move K-value pairs); the
-// rows of a tile (256 at most) lie within the 2 GiB range of a buffer descriptor.
+// K-contiguous operands with 16-byte aligned rows and an even K (the loads move K-value pairs; whole
+// stages when several products are summed); the rows of a tile (256 at most) do not overlap and lie
+// within the 2 GiB range of a buffer descriptor.
 bool dma_eligible(const GP& p) {
   auto al = [](const void* x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
-  auto near = [](long ld) { return ld >= 0 && ld < (1L << 20); };
-  return near(p.sam) && near(p.sbn) && p.sak == 1 && p.sbk == 1 && p.nred == 1 && p.K % 2 == 0 && p.sam % 2 == 0 && p.sbn % 2 == 0 &&
+  auto near = [&](long ld) { return ld >= p.K && ld < (1L << 20); };
+  return near(p.sam) && near(p.sbn) && p.sak == 1 && p.sbk == 1 && p.K % (p.nred > 1 ? kStageK : 2) == 0 &&
+         p.sar % 2 == 0 && p.sbr % 2 == 0 && p.sam % 2 == 0 && p.sbn % 2 == 0 &&
          p.sa1 % 2 == 0 && p.sa2 % 2 == 0 && p.sb1 % 2 == 0 && p.sb2 % 2 == 0 && al(p.A) && al(p.B);
 }
 
@@ -589,11 +579,12 @@ __global__ __launch_bounds__(256) void ordered_reduce(GP p, int nb1) {
 // split > 1: K cut into `split` slices whose partial tiles go to ws, then summed in a fixed order by
 // splitk_reduce; ordered: beta is 0 and they are summed in slice order, by ordered_reduce or, without
 // ws, by the workgroups themselves.
-template <int BM, int BN, int WM, int WN, int S, bool PM = false>
+template <int BM, int BN, int WM, int WN, int S, bool PM = false, bool RED = false>
 hipError_t launch_dma(GP p, int nb1, int split, double* ws, bool ordered, hipStream_t s) {
   p.tiles_m = (p.M + BM - 1) / BM;
   p.tiles_n = (p.N + BN - 1) / BN;
-  const int nkt = (p.K + kStageK - 1) / kStageK;
+  const int nkt = (p.K + kStageK - 1) / kStageK * (RED ? p.nred : 1);
+  if (!RED && p.nred != 1) return hipErrorInvalidValue;
   p.it_per_split = (nkt + split - 1) / split;
   p.split = (nkt + p.it_per_split - 1) / p.it_per_split;
   p.part = p.split > 1 ? ws : nullptr;
@@ -603,7 +594,7 @@ hipError_t launch_dma(GP p, int nb1, int split, double* ws, bool ordered, hipStr
   if (p.split > 1 && !ws && !ordered) return hipErrorInvalidValue;
   const int per = PM ? 2 * ((tiles + 7) / 8 * 8) : tiles;  // PM: both halves in grid.x, padded to groups of 8
   dim3 grid(per * (p.seq ? 1 : p.split), PM ? 1 : p.nb2, nb1);
-  hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, S, PM>), grid, dim3(WM * WN * 64), 0, s, p);
+  hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, S, PM, RED>), grid, dim3(WM * WN * 64), 0, s, p);
   if (p.part) {
     const long outs = (long)p.M * p.N * p.nb2 * nb1;
     if (ordered)
@@ -615,32 +606,71 @@ hipError_t launch_dma(GP p, int nb1, int split, double* ws, bool ordered, hipStr
   return hipGetLastError();
 }
 
-// Direct-to-LDS launch for a non-pair-combined contraction: the tile (192 x 192, 256 x 128 or
-// 224 x 128) and split-K count with the least estimated time = whole rounds of 256 workgroups x
-// tile area x K-stages per slice; split-K only with scratch, when the tiles cannot fill one round.
-hipError_t launch_dma_auto(const GP& p, int nb1, int nb1d, double* ws, long ws_elems, hipStream_t s) {
-  const long nbatch = (long)p.nb2 * nb1d, outs = (long)p.M * p.N * p.nb2 * nb1;
-  const int nkt = (p.K + 7) / 8;
+// Direct-to-LDS launch of a general contraction: the tile and split-K count with the least estimated time,
+//   6 us + (stages of a slice + 2) x max(tiles per CU x t, t1) + 5 us and the partial tiles' traffic if split
+// with t the time of one stage of one tile on a busy CU and t1 its latency alone (us, measured: sweeps of tile
+// and split over 100..3600 squared outputs; the choice stays within 10 % of the best of them).  Where the
+// outputs are few, small tiles with K split keep every CU busy: 1521 x 1521 x 1522 twice 450 -> 254 us,
+// 576 x 576 x 240 75 -> 17 us, 390 x 1521 x 1522 70 -> 55 us against 192- to 256-row tiles.
+// nb1d: the outer batch count the choice is made for; where the partial tiles of all blocks do not fit the
+// scratch, the blocks run in several launches, so that a block's sums never depend on the batch.
+hipError_t launch_dma_auto(const GP& p0, int nb1, int nb1d, double* ws, long ws_elems, hipStream_t s) {
+  struct Cfg {
+    int bm, bn;
+    double t, t1;
+  };
+  constexpr Cfg kCfg[] = {{192, 192, 4.19, 4.19}, {256, 128, 3.80, 3.80}, {224, 128, 3.45, 3.45}, {128, 128, 1.93, 1.93},
+                          {96, 96, 1.31, 1.45},   {64, 64, 0.58, 0.70},   {32, 32, 0.185, 0.50}};
+  const bool red = p0.nred > 1;
+  const long nbatch = (long)p0.nb2 * nb1d, outs = (long)p0.M * p0.N * nbatch;  // of the deciding batch
+  const long nkt = (long)((p0.K + kStageK - 1) / kStageK) * p0.nred;
   int best = -1, best_split = 1;
-  double best_cost = 0.0;
-  const int bms[3] = {192, 256, 224}, bns[3] = {192, 128, 128};
-  for (int c = 0; c < 3; ++c) {
-    const long tiles = (long)((p.M + bms[c] - 1) / bms[c]) * ((p.N + bns[c] - 1) / bns[c]) * nbatch;
-    int sp = 1;
-    if (ws && tiles < 192 && nkt >= 32) {
-      sp = (int)std::min<long>({256 / tiles, (long)nkt / 16, 256L, ws_elems / std::max<long>(outs, 1)});
-      sp = std::max(sp, 1);
-    }
-    const double cost = (double)((tiles * sp + 255) / 256) * bms[c] * bns[c] * ((nkt + sp - 1) / sp);
-    if (best < 0 || cost < best_cost) {
-      best = c;
-      best_cost = cost;
-      best_split = sp;
+  double least = 0.0;
+  for (int c = 0; c < (int)(sizeof kCfg / sizeof kCfg[0]); ++c) {
+    const Cfg& f = kCfg[c];
+    if ((red && f.bm > 64) || (p0.lower && f.bm != f.bn)) continue;
+    const long tm = (p0.M + f.bm - 1) / f.bm, tn = (p0.N + f.bn - 1) / f.bn;
+    const long tiles = (p0.lower ? tm * (tm + 1) / 2 : tm * tn) * nbatch;
+    for (long sp = 1; sp <= 256; sp += sp < 4 ? 1 : sp / 2) {
+      if (sp > 1 && (p0.lower || !ws || tiles * sp > 1536 || nkt < 4 * sp || sp * outs > ws_elems)) break;
+      const double per = std::max((double)((tiles * sp + 255) / 256) * f.t, f.t1);
+      const double us = 6.0 + (double)((nkt + sp - 1) / sp + 2) * per + (sp > 1 ? 5.0 + (double)((sp + 1) * outs) * 2.7e-6 : 0.0);
+      if (best < 0 || us < least) {
+        best = c;
+        best_split = (int)sp;
+        least = us;
+      }
     }
   }
-  if (best == 0) return launch_dma<192, 192, 2, 4, 3>(p, nb1, best_split, ws, false, s);
-  if (best == 1) return launch_dma<256, 128, 4, 2, 3>(p, nb1, best_split, ws, false, s);
-  return launch_dma<224, 128, 2, 4, 3>(p, nb1, best_split, ws, false, s);
+  const long fit = best_split > 1 ? std::max<long>(1, ws_elems / (best_split * (outs / nb1d))) : nb1;
+  for (long z0 = 0; z0 < nb1; z0 += fit) {
+    GP p = p0;
+    const int n = (int)std::min<long>(fit, nb1 - z0);
+    if (p.tab1) {
+      p.tab1 += z0;
+    } else {
+      p.A += z0 * p.sa1;
+      p.B += z0 * p.sb1;
+      p.C += z0 * p.sc1;
+    }
+    hipError_t e;
+    switch (best) {
+      case 0: e = launch_dma<192, 192, 2, 4, 3>(p, n, best_split, ws, false, s); break;
+      case 1: e = launch_dma<256, 128, 4, 2, 3>(p, n, best_split, ws, false, s); break;
+      case 2: e = launch_dma<224, 128, 2, 4, 3>(p, n, best_split, ws, false, s); break;
+      case 3: e = launch_dma<128, 128, 2, 4, 3>(p, n, best_split, ws, false, s); break;
+      case 4: e = launch_dma<96, 96, 2, 2, 3>(p, n, best_split, ws, false, s); break;
+      case 5:
+        e = red ? launch_dma<64, 64, 2, 2, 3, false, true>(p, n, best_split, ws, false, s)
+                : launch_dma<64, 64, 2, 2, 3>(p, n, best_split, ws, false, s);
+        break;
+      default:
+        e = red ? launch_dma<32, 32, 1, 1, 3, false, true>(p, n, best_split, ws, false, s)
+                : launch_dma<32, 32, 1, 1, 3>(p, n, best_split, ws, false, s);
+    }
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // Ladder tiles: BM x 128, the eight waves side by side (BM / 16 fragment rows each).  Three stages, or
@@ -654,11 +684,13 @@ hipError_t launch_ladder(const GP& p, int nb1, int split, double* ws, hipStream_
 // Tile height and split-K count of a ladder of M rows (N columns, both halves).  Time of a launch: whole
 // rounds of 256 workgroups x stages of a slice (and about 6 to fill and drain) x (rows + 24 of B staging).
 // The split is that of one state's rows Mdec alone, so a state's sums do not depend on how many states
-// are stacked; it pays where one state leaves CUs idle: its partial tiles cost a pass over the outputs.
+// are stacked, and takes only counts whose partial tiles fit the scratch; it pays where one state leaves CUs
+// idle: its partial tiles cost a pass over the outputs.  Against the best of all heights and splits, us:
+// o8 v72 48 / 45, o10 v90 108 / 104, o12 v108 252 / 243, o15 v135 881 / 853, o20 v180 4266 / 4259.
 struct LadderPlan {
   int bm, split;
 };
-LadderPlan ladder_plan(long M, long Mdec, long N, long K) {
+LadderPlan ladder_plan(long M, long Mdec, long N, long K, long ws_elems) {
   constexpr int kBM[] = {32, 48, 64, 80, 96, 112, 128, 144, 160, 176, 192, 208, 224, 240, 256};
   const long nkt = (K + kStageK - 1) / kStageK, tn = (N + 127) / 128;
   auto cost = [&](long m, int bm, int sp) {
@@ -669,7 +701,7 @@ LadderPlan ladder_plan(long M, long Mdec, long N, long K) {
   LadderPlan best{256, 1};
   double least = -1;
   for (int bm : kBM)
-    for (int sp = 1; sp <= 8 && (sp == 1 || nkt >= 16 * sp); ++sp) {
+    for (int sp = 1; sp <= 8 && (sp == 1 || (nkt >= 16 * sp && 2 * sp * Mdec * N <= ws_elems)); ++sp) {
       const double c = cost(Mdec, bm, sp);
       if (least < 0 || c < least) {
         least = c;
@@ -804,17 +836,9 @@ hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
   p.pm = nullptr;
   p.tab1 = g.tab1;
   p.lower = 0;
-  if (g.lower && g.M == g.N && g.beta == 0.0 && dma_eligible(p)) {
-    // symmetric C: the 192 x 192 tiles on and below the diagonal, then the mirror of the strict
-    // upper triangle (each mirrored value sums the same products in the same K order); other
-    // symmetric products (odd K, unaligned rows) take the full product below
-    p.lower = 1;
-    hipError_t e = launch_dma<192, 192, 2, 4, 3>(p, g.nb1, 1, nullptr, false, s);
-    if (e != hipSuccess) return e;
-    const long nbk = (g.M + 31) / 32;
-    hipLaunchKernelGGL(mirror_upper_kernel, dim3((unsigned)(nbk * (nbk + 1) / 2), (unsigned)g.nb2, (unsigned)g.nb1),
-                       dim3(256), 0, s, p);
-    return hipGetLastError();
+  if (dma_eligible(p)) {
+    p.lower = g.lower && g.M == g.N && g.beta == 0.0 && g.nred == 1;
+    return launch_dma_auto(p, g.nb1, nb1d, g.ws, g.ws_elems, s);
   }
   // Global-load order: an operand whose m (n) stride is 1 is read m-fast (n-fast).
   const bool amf = (g.sam == 1 && g.sak != 1);
@@ -830,8 +854,6 @@ hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
       return (double)((t + 255) / 256) * bm * bn / rate;
     };
     const double e128 = est(128, 128, 59.5), e256 = est(256, 128, 60.0), e192 = est(192, 192, 61.5);
-    // direct-to-LDS tiles sustain ~67-68 TFLOP/s on full rounds
-    if (dma_eligible(p)) return launch_dma_auto(p, g.nb1, nb1d, g.ws, g.ws_elems, s);
     if (e192 < e128 && e192 <= e256) return launch_cfg<192, 192, 16, 2, 4, 1>(p, amf, bnf, g.nb1, nb1d, nullptr, 0, s);
     if (e256 < e128) return launch_cfg<256, 128, 16, 4, 2, 1>(p, amf, bnf, g.nb1, nb1d, nullptr, 0, s);
     return launch_cfg<128, 128, 16, 2, 2, 2>(p, amf, bnf, g.nb1, nb1d, g.ws, g.ws_elems, s);
@@ -840,7 +862,6 @@ hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
   // to 32 slices, a long K still leaves each slice enough iterations to hide its reduction)
   const bool long_k = g.ws && (long)g.K * g.nred >= 2048 && tiles128 >= 16;
   if (g.M >= 96 && g.N >= 96 && long_k) {
-    if (dma_eligible(p)) return launch_dma_auto(p, g.nb1, nb1d, g.ws, g.ws_elems, s);
     return launch_cfg<128, 128, 16, 2, 2, 2>(p, amf, bnf, g.nb1, nb1d, g.ws, g.ws_elems, s);
   }
   const long tiles64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * nbatch;
@@ -895,7 +916,7 @@ hipError_t gemm_f64_ladder(const Ladder& L, hipStream_t s) {
   p.sc1 = lb.sc;
   p.tab1 = lb.tab;
   if (!dma_eligible(p)) return hipErrorInvalidValue;  // the operands' rows are laid out for this kernel
-  const LadderPlan pl = ladder_plan(L.M, L.Mdec, L.N, L.K);
+  const LadderPlan pl = ladder_plan(L.M, L.Mdec, L.N, L.K, L.ws ? L.ws_elems : 0);
   // one slice after another where the partial tiles do not fit the scratch: the same sums
   double* ws = (long)pl.split * L.M * L.N * 2 * lb.n <= L.ws_elems ? L.ws : nullptr;
   return pmode ? launch_ladder_plan<true>(p, lb.n, pl, ws, s) : launch_ladder_plan<false>(p, lb.n, pl, ws, s);

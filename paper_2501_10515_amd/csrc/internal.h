@@ -67,8 +67,8 @@ struct Gemm {
   // each block whatever nb1 is, as long as the split-K scratch holds the partials of every block)
   bool per_block = false;
   // C = A B with B(k, n) = A(n, k) is symmetric: when M == N, beta == 0 and the rows qualify for
-  // the direct-to-LDS kernel, only the tiles on and below the diagonal are computed and the strict
-  // upper triangle is copied from the lower one (otherwise the full product)
+  // the direct-to-LDS kernel, only the tiles on and below the diagonal are computed, each stored
+  // at its transposed place too (otherwise the full product)
   bool lower = false;
 };
 
@@ -222,6 +222,12 @@ hipError_t pack_vvvv(double* vplus, double* vminus, long ldo, const double* W, i
 // (kc|bd) as kcbd[k][c][b][d], (kc|ld) as kcld[k][c][l][d]
 hipError_t pack_gwz(double* gplus, double* gminus, long ldo, const double* kcbd, const double* kcld, int o, int v,
                     hipStream_t s);
+// Tx, U (rows at stride ld, zero past o v) and, with tplus given, t+- from t2; Xc and Zd of the rings
+// (formulas at the kernels)
+hipError_t amp_views(double* Tx, double* U, long ld, double* tplus, double* tminus, long ldo, const double* t2, int o,
+                     int v, hipStream_t s);
+hipError_t ring_xz(double* xc, double* zd, long ld, const double* g2, const double* g3, const double* y1,
+                   const double* y2, int o, int v, hipStream_t s);
 // W' and chi+- from the W/Z columns of the ladder's pair rows (formulas at the kernel)
 hipError_t wz_chi(double* wp, long ldw, double* chip, double* chim, const double* rp, const double* rm, long ldr,
                   const double* g4, const double* foo, const double* t1, int o, int v, hipStream_t s);
@@ -254,8 +260,8 @@ struct Cross {
 //                      rows r that are members of *zero_rows written as 0.
 //   cross_scatter_add_rows / _cols / _block: the inverse placements, dst += alpha * src.
 //   cross_rows_without_corner: dst[k][c] = Y[row k][c] - [row k == hp] T[hp][hp] K[hp][c] for
-//                      square X.n() x X.n() operands (the cross rows of T' K, T' = T minus its
-//                      corner entry, from Y = T K).
+//                      X.n() x X.n() operands, T and K rows at stride ldk (the cross rows of T' K,
+//                      T' = T minus its corner entry, from Y = T K).
 //   em_cross_column:   EM[ij][a][b] += tc[ij][v + a - [a > pa]] * A[b][pa] for a != pa.
 // mixed_doubles: dst = src on the mixed doubles (index set holds h or pa, not all primary), else 0.
 hipError_t cross_gather_rows(double* dst, long ldd, const double* src, long lds, long src_rows, long ncols,
@@ -269,7 +275,7 @@ hipError_t cross_scatter_add_cols(double* dst, long ldd, long nrows, const doubl
 hipError_t cross_scatter_add_block(double* dst, long ldd, const double* src, long lds, double alpha, const Cross& X,
                                    hipStream_t s);
 hipError_t cross_rows_without_corner(double* dst, long ldd, const double* Y, const double* T, const double* K,
-                                     const Cross& X, hipStream_t s);
+                                     long ldk, const Cross& X, hipStream_t s);
 hipError_t em_cross_column(double* em, const double* tc, long ldt, const double* A, int o, int v, int pa,
                            hipStream_t s);
 hipError_t mixed_doubles(double* dst, const double* src, int o, int v, int h, int pa, hipStream_t s);
