@@ -168,13 +168,13 @@ struct ascc_ints {
   long ov, oo, vv, ovov, oovv;
   Pool pool;
   // constant integrals
-  double* B;      // [Q][n][n]
+  double* B;      // [n][n] rows of ldQ fitting values
   double* h;      // [n][n] core Hamiltonian
   double* eps;    // [n] Fock diagonal
   double* fov;    // [o][v] reference Fock, occupied-virtual block
   double* e0;     // [1] reference energy <phi_0|H|phi_0> = sum_i (h_ii + f_ii)
-  double* Bov;    // [Q][o][v]
-  double* BovT;   // [o][v][Q]: the same, K = Q contiguous
+  double* Bov;    // [ldQ] rows at stride ldov (zero past naux): B_Q,kc at [Q][k*v+c]
+  double* BovT;   // [o][v] rows at stride ldQ: the same, Q contiguous
   double* KL;     // [2][ov] rows at stride ldov: (ib|ja), 2(ia|jb) - (ib|ja)
   double* Lijab;  // [o][o][v][v]: 2(ia|jb) - (ib|ja)
   double* V;      // FULL: [v^2] rows at stride ldV, (ac|bd) at [R(a,b)][R(c,d)] (pair order: a <= b first,
@@ -185,22 +185,19 @@ struct ascc_ints {
   double* pairtab;  // FULL: int32 [T(v)]: row R(b,a) of V for pair p(a,b), a <= b
   double *Tp, *Rp;  // ladder operands: t+- [2][T(o)] rows at stride ldT (pack_tpm), and R+- with the W/Z
                     // pair rows behind each (unpack_rpm, wz_chi), [2][T(o)] rows at stride ldR
-  long ldT, ldV, ldR, ldov;
+  long ldT, ldV, ldR, ldov, ldQ;  // row strides: whole 128-byte lines, zero past the row
   // residual work arrays
-  double* Bc;                    // [Q][n][o] T1 correction of the first o columns of B
-  double* Bh;                    // [Q][n][n]
-  double* hc;                    // [n][o]
-  double* Fh;                    // [n][n]
-  double *J;                     // [Q]
-  double *BvoTt, *Boo, *Bvv;     // [o][v][Q] (B^_ai at [i][a][Q]), [Q][o][o], [Q][v][v]
+  double* D;                     // [o][n] rows at stride ldQ: (B Y^T)_pk at [k][p]
+  double* Fh;                    // [n][n] X^-1 F^ Y^-T (build: scratch)
+  double *BvoTt, *Boo, *Bvv;     // B^ rows at stride ldQ: B^_ai at [i][a], B^_ki at [k][i], B^_ac at [a][c]
   double *G1, *G2, *G3, *G4;     // ovov, [k][i][a][c], ovov, [k][i][l][j]
   double *TU, *XZ;               // [2][ov] rows at stride ldov: Tx | U, Xc | Zd
   double *Y, *P;                 // [2][ov][ov]
-  double *Nq;                    // [Q][o][v]
+  double *Nq;                    // [o][v] rows at stride ldQ: N_Q[k,a] at [k][a]
   double *WZ;                    // [o^2][ov + o^2] (FP64: W' in the first ov columns)
   double *chi;                   // [o^2][o^2] (FP64: chi+-, [2][T(o)][T(o)])
   double *RL, *EM;               // [o^2][v^2]
-  double *Abc, *Bkj, *Fvvp, *Foop, *Fovh;  // small
+  double *Abc, *Bkj, *Fvvp, *Foop, *Fovh;  // small (Abc, Bkj: PLASCC)
   double *partial;               // reduction scratch
   double *splitk;                // split-K partial tiles of small-output contractions
   // FP32 shadows of the large-contraction operands (only for a low-precision integral set)
@@ -308,22 +305,21 @@ std::vector<std::pair<double* ascc_ints::*, long>> ints_plan(long o, long v, lon
   const long n = o + v, nn = n * n, ov = o * v, oo = o * o, vv = v * v, ovov = ov * ov;
   const long To = o * (o + 1) / 2, Tv = v * (v + 1) / 2;
   const bool full = (mode == ASCC_VVVV_FULL);
-  const long wzl = ov + oo, ldT = pad_line(Tv), ldR = pad_line(Tv + wzl), ldov = pad_line(ov);
+  const long wzl = ov + oo, ldT = pad_line(Tv), ldR = pad_line(Tv + wzl), ldov = pad_line(ov), ldQ = pad_line(Q);
   return {
-      {&ascc_ints::B, Q * nn},        {&ascc_ints::h, nn},           {&ascc_ints::eps, n},
+      {&ascc_ints::B, nn * ldQ},      {&ascc_ints::h, nn},           {&ascc_ints::eps, n},
       {&ascc_ints::fov, ov},          {&ascc_ints::e0, 1},
-      {&ascc_ints::Bov, Q * ov},      {&ascc_ints::KL, 2 * ov * ldov},
+      {&ascc_ints::Bov, ldQ * ldov},  {&ascc_ints::KL, 2 * ov * ldov},
       {&ascc_ints::Lijab, oo * vv},   {&ascc_ints::G, full ? 2 * wzl * ldT : 0},
-      {&ascc_ints::BovT, ov * Q},
+      {&ascc_ints::BovT, ov * ldQ},
       {&ascc_ints::V, full ? vv * pad_line(vv) : 2 * (Tv + wzl) * ldT},
       {&ascc_ints::pairtab, full ? Tv : 0},
       {&ascc_ints::Tp, 2 * To * ldT}, {&ascc_ints::Rp, 2 * To * ldR},
-      {&ascc_ints::Bc, Q * n * o},    {&ascc_ints::Bh, Q * nn},      {&ascc_ints::hc, n * o},
-      {&ascc_ints::Fh, nn},           {&ascc_ints::J, Q},            {&ascc_ints::BvoTt, Q * ov},
-      {&ascc_ints::Boo, Q * oo},      {&ascc_ints::Bvv, Q * vv},     {&ascc_ints::G1, ovov},
+      {&ascc_ints::D, o * n * ldQ},   {&ascc_ints::Fh, nn},          {&ascc_ints::BvoTt, ov * ldQ},
+      {&ascc_ints::Boo, oo * ldQ},    {&ascc_ints::Bvv, vv * ldQ},   {&ascc_ints::G1, ovov},
       {&ascc_ints::G2, oo * vv},      {&ascc_ints::G3, ovov},        {&ascc_ints::G4, oo * oo},
       {&ascc_ints::TU, 2 * ov * ldov}, {&ascc_ints::Y, 2 * ovov},    {&ascc_ints::XZ, 2 * ov * ldov},
-      {&ascc_ints::P, 2 * ovov},      {&ascc_ints::Nq, Q * ov},      {&ascc_ints::WZ, oo * (ov + oo)},
+      {&ascc_ints::P, 2 * ovov},      {&ascc_ints::Nq, ov * ldQ},    {&ascc_ints::WZ, oo * (ov + oo)},
       {&ascc_ints::chi, std::max(oo * oo, 2 * To * To)}, {&ascc_ints::RL, oo * vv},     {&ascc_ints::EM, oo * vv},
       {&ascc_ints::Abc, vv},          {&ascc_ints::Bkj, oo},         {&ascc_ints::Fvvp, vv},
       {&ascc_ints::Foop, oo},         {&ascc_ints::Fovh, ov},        {&ascc_ints::partial, 8192},
@@ -507,80 +503,23 @@ inline hipError_t glp(GemmLP g, hipStream_t s) {
   return gemm_lowp(g, s);
 }
 
-// T1 dressing of `nb` stacked n x n matrices, dst = X src Y^T with X = 1 - F, Y^T = 1 + F and
-// F[o + a][i] = t1[i][a]: one GEMM for the correction of the first o columns, tc = src[:, o:n] t1^T,
-// then one streaming pass (dress_apply) that forms dst from src and tc.
-int dress(const ascc_ints* I, const double* src, double* tc, double* dst, const double* t1, int o, int v, int nb,
-          hipStream_t s) {
-  const long n = o + v, nn = n * n;
-  Gemm g;
-  g.M = (int)n;
-  g.N = o;
-  g.K = v;
-  g.A = src + o;
-  g.sam = n;
-  g.sak = 1;
-  g.sa2 = nn;
-  g.B = t1;
-  g.sbk = 1;
-  g.sbn = v;
-  g.C = tc;
-  g.scm = o;
-  g.scn = 1;
-  g.sc2 = n * o;
-  g.nb2 = nb;
-  HIPCHK(mm(I, g, s));
-  EACH_SLOT HIPCHK(dress_apply(S(dst), S(src), S(tc), S(t1), o, v, nb, s));
-  return ASCC_OK;
+// sum over k < o and Q of rows A[m][k] and B[n][k], each a row of ldQ fitting values: C = alpha (...) + beta C.
+// am, ak: strides of m and k in A; bn, bk in B.
+Gemm sum_kq(const ascc_ints* I, int M, int N, int nk, double alpha, const double* A, long am, long ak, const double* B,
+            long bn, long bk, double beta, double* C, long ldc) {
+  Gemm g = gemm_rm(M, N, (int)I->ldQ, alpha, A, am, false, B, bn, true, beta, C, ldc);
+  g.nred = nk;
+  g.sar = ak;
+  g.sbr = bk;
+  return g;
 }
 
-// F += sign * (2 sum_Q J_Q B_Q - sum_Q B_Q[:,0:o] B_Q[0:o,:]),  J_Q = sum_k B_Q[k][k]
-int add_two_electron_fock(const ascc_ints* I, double* F, const double* Bq, double* J, int o, int v, int Q, double sign,
-                          hipStream_t s) {
-  const long n = o + v, nn = n * n;
-  EACH_SLOT HIPCHK(diag_trace(S(J), S(Bq), Q, n, o, s));
-  {
-    Gemm g;
-    g.M = 1;
-    g.N = nn;
-    g.K = Q;
-    g.A = J;
-    g.sam = 0;
-    g.sak = 1;
-    g.B = Bq;
-    g.sbk = nn;
-    g.sbn = 1;
-    g.C = F;
-    g.scm = 0;
-    g.scn = 1;
-    g.alpha = 2.0 * sign;
-    g.beta = 1.0;
-    HIPCHK(mm(I, g, s));
-  }
-  {
-    Gemm g;
-    g.M = n;
-    g.N = n;
-    g.K = o;
-    g.A = Bq;
-    g.sam = n;
-    g.sak = 1;
-    g.sar = nn;
-    g.B = Bq;
-    g.sbk = n;
-    g.sbn = 1;
-    g.sbr = nn;
-    g.C = F;
-    g.scm = n;
-    g.scn = 1;
-    g.alpha = -sign;
-    g.beta = 1.0;
-    g.nred = Q;
-    HIPCHK(mm(I, g, s));
-  }
+// f -= sign sum_kQ D[p][k] B[k][q] (the exchange part; dm, dk: strides of p and k in D)
+int subtract_exchange(const ascc_ints* I, double* f, const double* D, long dm, long dk, double sign, hipStream_t s) {
+  const int n = I->n;
+  HIPCHK(mm(I, sum_kq(I, n, n, I->no, -sign, D, dm, dk, I->B, I->ldQ, n * I->ldQ, 1.0, f, n), s));
   return ASCC_OK;
 }
-
 
 // C_z[m][n] = sum_k A_z[m][k] B_z[n][k] in the handle's current low precision (FP64 result).
 GemmLP lp_nt(const ascc_ints* I, long M, long N, long K, int nb, const float* A, long lda, long sa2, const float* B,
@@ -638,6 +577,15 @@ hipError_t shadow(const ascc_ints* I, float* out, const double* in, long rows, l
 hipError_t shadow_ov(const ascc_ints* I, float* out, const double* in, hipStream_t s) {
   EACH_SLOT {
     const hipError_t e = to_lowp_2d(lowp_kind(I), S(out), lowp_ld(I->ov), S(in), I->ldov, 2 * I->ov, I->ov, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// Low-precision shadow of `rows` rows of fitting values at stride ldQ (leading dimension lowp_ld(naux)).
+hipError_t shadow_q(const ascc_ints* I, float* out, const double* in, long rows, hipStream_t s) {
+  EACH_SLOT {
+    const hipError_t e = to_lowp_2d(lowp_kind(I), S(out), lowp_ld(I->naux), S(in), I->ldQ, rows, I->naux, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -806,7 +754,7 @@ size_t ints_footprint(long o, long v, long Q, int precision, int mode) {
 // rows outside X.  Runs after the rings and E terms, in G2, chi, Abc and Bkj, which those are
 // done with, and in the compact buffers of ascc_set_plascc.
 int plascc_remove(ascc_ints* I, const double* t2, double* RL, hipStream_t s) {
-  const int o = I->no, v = I->nv, Q = I->naux, h = I->pl_hole, pa = I->pl_pa;
+  const int o = I->no, v = I->nv, h = I->pl_hole, pa = I->pl_pa;
   const long ov = I->ov, oo = I->oo, vv = I->vv, ovov = I->ovov;
   const Cross X{o, v, h, pa}, Xo{o, o, h, h}, Xv{v, v, pa, pa};
   const long m = X.m(), mp = pad_even(m), mo = Xo.m(), mop = pad_even(mo), mvp = pad_even(Xv.m());
@@ -858,14 +806,15 @@ int plascc_remove(ascc_ints* I, const double* t2, double* RL, hipStream_t s) {
     HIPCHK(mm(I, gemm_rm(ov, m, m, 1.0, I->plC, mp, false, I->plKpp, mp, false, 0.0, I->plW, mp), s));
     HIPCHK(mm(I, gemm_rm(ov, ov, mp, kappa[z], I->plW, mp, false, I->plC, mp, true, 1.0, P, ov), s));
   }
-  // --- E terms.  N^M[Q][r] = sum_c B_Q,c U^M[r][c]: columns outside X from C_p, X columns from the
-  // X rows of U^M
-  HIPCHK(cross_gather_cols(I->plBp, mp, I->Bov, ov, Q, X, nullptr, s));
-  HIPCHK(mm(I, gemm_rm(Q, ov, mp, 1.0, I->plBp, mp, false, I->plC, mp, true, 0.0, I->plN, ov), s));
-  HIPCHK(mm(I, gemm_rm(Q, m, ov, 1.0, I->Bov, ov, false, I->plA, ov, true, 0.0, I->plNw, mp), s));
-  HIPCHK(cross_scatter_add_cols(I->plN, ov, Q, I->plNw, mp, 1.0, X, s));
+  // --- E terms.  N^M[r][Q] = sum_c U^M[r][c] B_Q,c: columns c in X from C_p, the X rows' other columns from
+  // the X rows of U^M
+  const long lq = I->ldQ, ldov = I->ldov;
+  HIPCHK(cross_gather_cols(I->plBp, mp, I->Bov, ldov, lq, X, nullptr, s));
+  HIPCHK(mm(I, gemm_rm(ov, lq, mp, 1.0, I->plC, mp, false, I->plBp, mp, true, 0.0, I->plN, lq), s));
+  HIPCHK(mm(I, gemm_rm(m, lq, ov, 1.0, I->plA, ov, false, I->Bov, ldov, true, 0.0, I->plNw, lq), s));
+  HIPCHK(cross_scatter_add_rows(I->plN, lq, ov, I->plNw, lq, lq, 1.0, X, s));
   // A^M[b][c] = sum_Qk N^M_Q[k,b] B_Q,kc;  EM[ij][a][b] += sum_c t^M_ij^ac A^M[b][c]
-  HIPCHK(mm(I, gemm_rm(v, v, (long)Q * o, 1.0, I->plN, v, true, I->Bov, v, false, 0.0, I->Abc, v), s));
+  HIPCHK(mm(I, sum_kq(I, v, v, o, 1.0, I->plN, lq, v * lq, I->BovT, lq, v * lq, 0.0, I->Abc, v), s));
   HIPCHK(mm(I, gemm_rm(mo * v, v, v, 1.0, I->plTa, v, false, I->Abc, v, true, 0.0, I->plEc, v), s));
   HIPCHK(cross_scatter_add_rows(I->EM, vv, oo, I->plEc, vv, vv, 1.0, Xo, s));
   {  // rows outside the occupied cross, a = pa: EM[ij][pa][b] += sum_c t^M_ij^{pa c} A^M[b][c]
@@ -873,25 +822,8 @@ int plascc_remove(ascc_ints* I, const double* t2, double* RL, hipStream_t s) {
     HIPCHK(mm(I, g, s));
   }
   HIPCHK(em_cross_column(I->EM, I->plTc, mvp, I->Abc, o, v, pa, s));  // ... and a != pa, c = pa
-  {  // B^M[k][j] = sum_Qd B_Q,kd N^M_Q[j,d]
-    Gemm g;
-    g.M = o;
-    g.N = o;
-    g.K = v;
-    g.A = I->Bov;
-    g.sam = v;
-    g.sak = 1;
-    g.sar = ov;
-    g.B = I->plN;
-    g.sbk = 1;
-    g.sbn = v;
-    g.sbr = ov;
-    g.C = I->Bkj;
-    g.scm = o;
-    g.scn = 1;
-    g.nred = Q;
-    HIPCHK(mm(I, g, s));
-  }
+  // B^M[k][j] = sum_Qd B_Q,kd N^M_Q[j,d]
+  HIPCHK(mm(I, sum_kq(I, o, o, v, 1.0, I->BovT, v * lq, lq, I->plN, v * lq, lq, 0.0, I->Bkj, o), s));
   {  // EM[i][j][ab] += sum_k B^M[k][j] t^M_ik^ab   (batched over i)
     Gemm g;
     g.M = o;
@@ -926,28 +858,14 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   const long wzl = ov + oo;  // row length of WZ
   int rc;
 
-  // --- T1 dressing of B and of the one-electron operator, dressed Fock matrix
+  // --- T1 dressing: the dressed blocks of B, and the dressed Fock matrix: F^ = X (h + 2 sum_Q J_Q B - sum_kQ D B) Y^T
+  // (D = B Y^T for the occupied columns), F^_vo into r1
+  const long lq = I->ldQ;
   phase_begin(I, PH_DRESS, s);
-  if ((rc = dress(I, I->B, I->Bc, I->Bh, t1, o, v, Q, s))) return rc;
-  if ((rc = dress(I, I->h, I->hc, I->Fh, t1, o, v, 1, s))) return rc;
-  if ((rc = add_two_electron_fock(I, I->Fh, I->Bh, I->J, o, v, Q, 1.0, s))) return rc;
-
-  // --- contiguous dressed blocks
-  EACH_SLOT {
-    int d[4] = {o, v, Q, 1};
-    Perm4In x = pin(S(I->Bh) + o * n, 1, n, nn, 0, 1.0);  // B^_ai -> [i][a][Q]
-    HIPCHK(permute4(S(I->BvoTt), d, 0.0, &x, 1, s));
-    int d2[4] = {Q, o, o, 1};
-    x = pin(S(I->Bh), nn, n, 1, 0, 1.0);
-    HIPCHK(permute4(S(I->Boo), d2, 0.0, &x, 1, s));
-    int d3[4] = {Q, v, v, 1};
-    x = pin(S(I->Bh) + o * n + o, nn, n, 1, 0, 1.0);
-    HIPCHK(permute4(S(I->Bvv), d3, 0.0, &x, 1, s));
-    int d4[4] = {o, v, 1, 1};
-    x = pin(S(I->Fh) + o, n, 1, 0, 0, 1.0);  // F^_kc
-    HIPCHK(permute4(S(I->Fovh), d4, 0.0, &x, 1, s));
-  }
-
+  EACH_SLOT HIPCHK(dress_right(S(I->D), S(I->B), S(t1), o, v, lq, s));
+  EACH_SLOT HIPCHK(dress_left(S(I->Bvv), S(I->BvoTt), S(I->Boo), S(I->Fh), S(I->B), S(I->D), S(t1), S(I->h), o, v, lq, s));
+  if ((rc = subtract_exchange(I, I->Fh, I->D, lq, n * lq, 1.0, s))) return rc;
+  EACH_SLOT HIPCHK(fock_finish(S(I->Fvvp), S(I->Foop), S(r1), S(I->Fovh), S(I->Fh), S(t1), o, v, s));
   phase_end(I, s);
   // --- amplitude views: Tx[iajb] = t2[ijba], U[iajb] = 2 t2[ijab] - t2[ijba], t+-
   phase_begin(I, PH_AMP, s);
@@ -966,57 +884,42 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   // g^_aibj enters R2 unmultiplied by amplitudes: always FP64, so the low-precision residual's
   // rounding floor stays proportional to the amplitudes
   {  // g^_aibj: a symmetric product, its lower triangle computed and mirrored
-    Gemm g = gemm_rm(ov, ov, Q, 1.0, I->BvoTt, Q, false, I->BvoTt, Q, true, 0.0, I->G1, ov);
+    Gemm g = gemm_rm(ov, ov, pad_even(Q), 1.0, I->BvoTt, lq, false, I->BvoTt, lq, true, 0.0, I->G1, ov);
     g.lower = true;
     HIPCHK(mm(I, g, s));
   }
-  if (lowp) {  // the same products on K-contiguous low-precision shadows (B^_kc ones are constant)
-    HIPCHK(shadow(I, I->BvoTtf, I->BvoTt, ov, Q, s));
-    HIPCHK(shadow_t(I, I->BooTf, I->Boo, oo, oo, Q, s));
-    HIPCHK(shadow_t(I, I->BvvTf, I->Bvv, vv, vv, Q, s));
+  // N_Q[k,a] = sum_lc B_Q,lc u_kl^ac (U is a symmetric ov x ov matrix: its rows are its columns), Q contiguous
+  if (lowp) {  // the same products on low-precision shadows (B^_kc ones are constant)
+    HIPCHK(shadow_q(I, I->BvoTtf, I->BvoTt, ov, s));
+    HIPCHK(shadow_q(I, I->BooTf, I->Boo, oo, s));
+    HIPCHK(shadow_q(I, I->BvvTf, I->Bvv, vv, s));
     HIPCHK(glp(lp_nt(I, oo, vv, Q, 1, I->BooTf, lQ, 0, I->BvvTf, lQ, 0, I->G2, vv, 0), s));    // g^_kiac
     HIPCHK(glp(lp_nt(I, ov, ov, Q, 1, I->BvoTtf, lQ, 0, I->BovTf, lQ, 0, I->G3, ov, 0), s));   // g^_aikc
-    // N_Q[k,a] = sum_lc B_Q,lc u_kl^ac: U is a symmetric ov x ov matrix, so its rows are its columns
-    HIPCHK(glp(lp_nt(I, Q, ov, ov, 1, I->Bovf, lov, 0, I->TUf + ov * lov, lov, 0, I->Nq, ov, 0), s));
+    GemmLP g = lp_nt(I, Q, ov, ov, 1, I->Bovf, lov, 0, I->TUf + ov * lov, lov, 0, I->Nq, 1, 0);
+    g.scn = lq;
+    HIPCHK(glp(g, s));
+    if (lq != Q) EACH_SLOT {  // the rows' padding
+      int d[4] = {1, 1, (int)ov, (int)(lq - Q)};
+      const long os[4] = {0, 0, lq, 1};
+      HIPCHK(permute4_strided(S(I->Nq) + Q, os, d, 0.0, nullptr, 0, s));
+    }
   } else {
-    HIPCHK(mm(I, gemm_rm(oo, vv, Q, 1.0, I->Boo, oo, true, I->Bvv, vv, false, 0.0, I->G2, vv), s));    // g^_kiac
-    HIPCHK(mm(I, gemm_rm(ov, ov, Q, 1.0, I->BvoTt, Q, false, I->BovT, Q, true, 0.0, I->G3, ov), s));   // g^_aikc
-    // N_Q[k,a] = sum_lc B_Q,lc u_kl^ac (U is symmetric: its rows are its columns)
-    HIPCHK(mm(I, gemm_rm(Q, ov, ov, 1.0, I->Bov, ov, false, U, ldov, true, 0.0, I->Nq, ov), s));
+    const long kq = pad_even(Q);
+    HIPCHK(mm(I, gemm_rm(oo, vv, kq, 1.0, I->Boo, lq, false, I->Bvv, lq, true, 0.0, I->G2, vv), s));    // g^_kiac
+    HIPCHK(mm(I, gemm_rm(ov, ov, kq, 1.0, I->BvoTt, lq, false, I->BovT, lq, true, 0.0, I->G3, ov), s));  // g^_aikc
+    HIPCHK(mm(I, gemm_rm(ov, lq, pad_even(ov), 1.0, U, ldov, false, I->Bov, ldov, true, 0.0, I->Nq, lq), s));
   }
-  HIPCHK(mm(I, gemm_rm(oo, oo, Q, 1.0, I->Boo, oo, true, I->Boo, oo, false, 0.0, I->G4, oo), s));      // g^_kilj
+  {  // g^_kilj
+    Gemm g = gemm_rm(oo, oo, pad_even(Q), 1.0, I->Boo, lq, false, I->Boo, lq, true, 0.0, I->G4, oo);
+    g.lower = true;
+    HIPCHK(mm(I, g, s));
+  }
 
   phase_end(I, s);
   // --- E-term intermediates F'_bc = F^_bc - sum_Qk N_Q[k,b] B_Q,kc ; F''_kj = F^_kj + sum_Qd B_Q,kd N_Q[j,d]
   phase_begin(I, PH_N5, s);
-  HIPCHK(mm(I, gemm_rm(v, v, (long)Q * o, 1.0, I->Nq, v, true, I->Bov, v, false, 0.0, I->Abc, v), s));
-  {
-    Gemm g;
-    g.M = o;
-    g.N = o;
-    g.K = v;
-    g.A = I->Bov;
-    g.sam = v;
-    g.sak = 1;
-    g.sar = ov;
-    g.B = I->Nq;
-    g.sbk = 1;
-    g.sbn = v;
-    g.sbr = ov;
-    g.C = I->Bkj;
-    g.scm = o;
-    g.scn = 1;
-    g.nred = Q;
-    HIPCHK(mm(I, g, s));
-  }
-  EACH_SLOT {
-    int d[4] = {v, v, 1, 1};
-    Perm4In x[2] = {pin(S(I->Fh) + o * n + o, n, 1, 0, 0, 1.0), pin(S(I->Abc), v, 1, 0, 0, -1.0)};
-    HIPCHK(permute4(S(I->Fvvp), d, 0.0, x, 2, s));
-    int d2[4] = {o, o, 1, 1};
-    Perm4In y[2] = {pin(S(I->Fh), n, 1, 0, 0, 1.0), pin(S(I->Bkj), o, 1, 0, 0, 1.0)};
-    HIPCHK(permute4(S(I->Foop), d2, 0.0, y, 2, s));
-  }
+  HIPCHK(mm(I, sum_kq(I, v, v, o, -1.0, I->Nq, lq, v * lq, I->BovT, lq, v * lq, 1.0, I->Fvvp, v), s));
+  HIPCHK(mm(I, sum_kq(I, o, o, v, 1.0, I->BovT, v * lq, lq, I->Nq, v * lq, lq, 1.0, I->Foop, o), s));
   phase_end(I, s);
 
   if (lowp) {
@@ -1181,27 +1084,9 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   }
   phase_begin(I, PH_N5, s);
   // --- singles
-  {  // r1[i][a] = sum_Qd N_Q[i,d] B^_Q,ad
-    Gemm g;
-    g.M = o;
-    g.N = v;
-    g.K = v;
-    g.A = I->Nq;
-    g.sam = v;
-    g.sak = 1;
-    g.sar = ov;
-    g.B = I->Bvv;
-    g.sbk = 1;
-    g.sbn = v;
-    g.sbr = vv;
-    g.C = r1;
-    g.scm = v;
-    g.scn = 1;
-    g.nred = Q;
-    HIPCHK(mm(I, g, s));
-  }
-  // r1 -= sum_Qk B^_Q,ki N_Q[k,a]
-  HIPCHK(mm(I, gemm_rm(o, v, (long)Q * o, -1.0, I->Boo, o, true, I->Nq, v, false, 1.0, r1, v), s));
+  // r1[i][a] = F^_ai + sum_dQ N_Q[i,d] B^_Q,ad - sum_kQ B^_Q,ki N_Q[k,a]
+  HIPCHK(mm(I, sum_kq(I, o, v, v, 1.0, I->Nq, v * lq, lq, I->Bvv, v * lq, lq, 1.0, r1, v), s));
+  HIPCHK(mm(I, sum_kq(I, o, v, o, -1.0, I->Boo, lq, o * lq, I->Nq, lq, v * lq, 1.0, r1, v), s));
   {  // r1[(ia)] += sum_kc U[(ia),(kc)] F^_kc
     Gemm g;
     g.M = ov;
@@ -1219,8 +1104,6 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     g.beta = 1.0;
     HIPCHK(mm(I, g, s));
   }
-  EACH_SLOT HIPCHK(add_fvo(S(r1), S(I->Fh), o, v, s));
-
   phase_end(I, s);
   // --- doubles assembly and energy
   phase_begin(I, PH_ASSEMBLE, s);
@@ -1264,7 +1147,17 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
   const int o = I->no, v = I->nv, Q = I->naux;
   const long n = I->n, nn = n * n, ov = I->ov, oo = I->oo, vv = I->vv, ovov = I->ovov;
   const long wzl = ov + oo;
-  HIPCHK(d_copy(I->B, Bsrc, sizeof(double) * Q * nn, hipMemcpyDeviceToDevice, s));
+  const long lq = I->ldQ;
+  {  // B[Q][p][q] -> rows [p][q] of fitting values, zero past naux
+    int d[4] = {1, 1, (int)nn, Q};
+    const long os[4] = {0, 0, lq, 1};
+    Perm4In x = pin(Bsrc, 0, 0, 1, nn, 1.0);
+    HIPCHK(permute4_strided(I->B, os, d, 0.0, &x, 1, s));
+    if (lq != Q) {
+      int dz[4] = {1, 1, (int)nn, (int)(lq - Q)};
+      HIPCHK(permute4_strided(I->B + Q, os, dz, 0.0, nullptr, 0, s));
+    }
+  }
   // Fock matrix -> h (start), eps, fov
   if (fock_is_diag) {
     HIPCHK(d_copy(I->eps, fock, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
@@ -1287,14 +1180,15 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
     HIPCHK(permute4(I->fov, d, 0.0, &x, 1, s));
   }
   // h = f - sum_k (2 (pq|kk) - (pk|kq))
-  int rc = add_two_electron_fock(I, I->h, I->B, I->J, o, v, Q, -1.0, s);
+  HIPCHK(coulomb(I->h, I->h, I->B, -2.0, o, (int)n, lq, s));
+  int rc = subtract_exchange(I, I->h, I->B, n * lq, lq, -1.0, s);
   if (rc) return rc;
   if (hole >= 0) {
     const double c = s_sign / std::sqrt(2.0);
-    HIPCHK(onebody_transform(I->B, Q, (int)n, hole, particle, c, s));
-    HIPCHK(onebody_transform(I->h, 1, (int)n, hole, particle, c, s));
-    HIPCHK(d_copy(I->Fh, I->h, sizeof(double) * nn, hipMemcpyDeviceToDevice, s));
-    if ((rc = add_two_electron_fock(I, I->Fh, I->B, I->J, o, v, Q, 1.0, s))) return rc;  // fbar
+    HIPCHK(onebody_transform(I->B, (int)n, lq, Q, hole, particle, c, s));
+    HIPCHK(onebody_transform(I->h, (int)n, 1, 1, hole, particle, c, s));
+    HIPCHK(coulomb(I->Fh, I->h, I->B, 2.0, o, (int)n, lq, s));
+    if ((rc = subtract_exchange(I, I->Fh, I->B, n * lq, lq, 1.0, s))) return rc;  // fbar
     int d[4] = {o, v, 1, 1};
     Perm4In x = pin(I->Fh + o, n, 1, 0, 0, 1.0);
     HIPCHK(permute4(I->fov, d, 0.0, &x, 1, s));
@@ -1304,22 +1198,21 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
     HIPCHK(reference_energy(I->e0, I->h, n + 1, nn, I->eps, 1, n, o, s));
   }
 
-  // B_ov and the undressed B_vv, the latter as [a][c][Q] (K = Q contiguous, into the work array Bvv,
-  // which every residual overwrites with the dressed [Q][a][c])
+  // B_ov, with Q contiguous and, with zero rows past naux and zero columns past o v, with kc contiguous
   {
-    int d[4] = {Q, o, v, 1};
-    Perm4In x = pin(I->B + o, nn, n, 1, 0, 1.0);
-    HIPCHK(permute4(I->Bov, d, 0.0, &x, 1, s));
-    int dt[4] = {o, v, Q, 1};
-    Perm4In xt = pin(I->B + o, n, 1, nn, 0, 1.0);  // B_kc -> [k][c][Q]
-    HIPCHK(permute4(I->BovT, dt, 0.0, &xt, 1, s));
-    int d2[4] = {v, v, Q, 1};
-    Perm4In y = pin(I->B + o * n + o, n, 1, nn, 0, 1.0);
-    HIPCHK(permute4(I->Bvv, d2, 0.0, &y, 1, s));
+    int d[4] = {o, v, 1, (int)lq};
+    Perm4In x = pin(I->B + o * lq, n * lq, lq, 0, 1, 1.0);
+    HIPCHK(permute4(I->BovT, d, 0.0, &x, 1, s));
+    int dz[4] = {1, 1, (int)lq, (int)I->ldov};
+    if (I->ldov != ov || lq != Q) HIPCHK(permute4(I->Bov, dz, 0.0, nullptr, 0, s));
+    int dt[4] = {1, 1, Q, (int)ov};
+    const long os[4] = {0, 0, I->ldov, 1};
+    Perm4In y = pin(I->BovT, 0, 0, 1, lq, 1.0);
+    HIPCHK(permute4_strided(I->Bov, os, dt, 0.0, &y, 1, s));
   }
   // J = (ia|jb) into G1 (work), then K and L
   double* Jov = I->G1;
-  HIPCHK(mm(I, gemm_rm(ov, ov, Q, 1.0, I->BovT, Q, false, I->BovT, Q, true, 0.0, Jov, ov), s));
+  HIPCHK(mm(I, gemm_rm(ov, ov, pad_even(Q), 1.0, I->BovT, lq, false, I->BovT, lq, true, 0.0, Jov, ov), s));
   {
     int d[4] = {o, v, o, v};
     const long si = (long)v * o * v, sa = (long)o * v, sj = v, sb = 1;
@@ -1344,7 +1237,11 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
     Pool tmp_alloc = sub_pool(I->pool);
     int rc2 = dalloc(tmp_alloc, &tmp, (size_t)ov * vv);
     if (rc2) return rc2;
-    hipError_t e = mm(I, gemm_rm(ov, vv, Q, 1.0, I->BovT, Q, false, I->Bvv, Q, true, 0.0, tmp, vv), s);
+    Gemm g = gemm_rm(ov, v, pad_even(Q), 1.0, I->BovT, lq, false, I->B + (o * n + o) * lq, lq, true, 0.0, tmp, vv);
+    g.sb2 = n * lq;  // batched over b
+    g.sc2 = v;
+    g.nb2 = v;
+    hipError_t e = mm(I, g, s);
     if (e == hipSuccess) {
       double* gp = full ? I->G : I->V + Tv * I->ldT;
       e = pack_gwz(gp, gp + (full ? wzl * I->ldT : vhalf), I->ldT, tmp, Jov, o, v, s);
@@ -1360,7 +1257,7 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
     }
   }
   // V[a][b][c][d] = (ac|bd) = sum_Q B_Q,ac B_Q,bd, batched over (a, b), in chunks of a.  Both
-  // operands are rows of the [a][c][Q] B_vv: K-contiguous.  The packed halves read only the slabs
+  // operands are rows of B: K-contiguous.  The packed halves read only the slabs
   // with b >= a (V[a][b][d][c] = (ad|bc) is the same slab), so a packed build starts b at the
   // chunk's first a; the full matrix needs every b.
   auto vslab = [&](int a0, int na, double* dst) -> hipError_t {
@@ -1368,15 +1265,15 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
     Gemm g;
     g.M = v;
     g.N = v;
-    g.K = Q;
-    g.A = I->Bvv + (long)a0 * v * Q;
-    g.sam = Q;
+    g.K = (int)pad_even(Q);
+    g.A = I->B + ((o + a0) * n + o) * lq;
+    g.sam = lq;
     g.sak = 1;
-    g.sa1 = (long)v * Q;
-    g.B = I->Bvv + (long)b0 * v * Q;
+    g.sa1 = n * lq;
+    g.B = I->B + ((o + b0) * n + o) * lq;
     g.sbk = 1;
-    g.sbn = Q;
-    g.sb2 = (long)v * Q;
+    g.sbn = lq;
+    g.sb2 = n * lq;
     g.C = dst + (long)b0 * vv;
     g.scm = v;
     g.scn = 1;
@@ -1425,8 +1322,8 @@ int build_lowp_shadows(ascc_ints* I, hipStream_t s) {
   }
   HIPCHK(shadow_ov(I, I->KLf, I->KL, s));
   const long Q = I->naux;
-  HIPCHK(shadow(I, I->BovTf, I->BovT, ov, Q, s));      // B_kc (undressed by T1) as [kc][Q]
-  HIPCHK(shadow(I, I->Bovf, I->Bov, Q, ov, s));         // and as [Q][kc]
+  HIPCHK(shadow_q(I, I->BovTf, I->BovT, ov, s));  // B_kc (undressed by T1) as [kc][Q]
+  HIPCHK(to_lowp_2d(lowp_kind(I), I->Bovf, lowp_ld(ov), I->Bov, I->ldov, Q, ov, s));  // and as [Q][kc]
   return ASCC_OK;
 }
 
@@ -1579,8 +1476,8 @@ std::vector<std::pair<double* ascc_ints::*, long>> plascc_plan(long o, long v, l
       {&ascc_ints::plA, m * ov},    {&ascc_ints::plC, ov * mp},   {&ascc_ints::plKr, m * ov},
       {&ascc_ints::plKpp, m * mp},  {&ascc_ints::plYp, m * ov},   {&ascc_ints::plYpp, m * mp},
       {&ascc_ints::plS, m * mp},    {&ascc_ints::plZ, m * ov},    {&ascc_ints::plZt, ov * mp},
-      {&ascc_ints::plW, ov * mp},   {&ascc_ints::plN, Q * ov},    {&ascc_ints::plBp, Q * mp},
-      {&ascc_ints::plNw, Q * mp},   {&ascc_ints::plTa, mo * vv},  {&ascc_ints::plTc, oo * mvp},
+      {&ascc_ints::plW, ov * mp},   {&ascc_ints::plN, ov * pad_line(Q)}, {&ascc_ints::plBp, pad_line(Q) * mp},
+      {&ascc_ints::plNw, m * pad_line(Q)}, {&ascc_ints::plTa, mo * vv},  {&ascc_ints::plTc, oo * mvp},
       {&ascc_ints::plGc, oo * mvp}, {&ascc_ints::plZo, mo * oo},  {&ascc_ints::plZh, oo * mop},
       {&ascc_ints::plRc, oo * mvp}, {&ascc_ints::plEc, mo * vv},
   };
@@ -1849,6 +1746,7 @@ static int build_ints_impl(const double* d_B, const double* d_fock, int fock_is_
   I->ldT = pad_line(Tv);
   I->ldV = pad_line(I->vv);
   I->ldov = pad_line(I->ov);
+  I->ldQ = pad_line(Q);
   I->ldR = pad_line(Tv + I->ov + I->oo);
   if (ws) {
     if ((reinterpret_cast<uintptr_t>(ws) & (kAlign - 1)) != 0) {

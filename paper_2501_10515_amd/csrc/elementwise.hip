@@ -184,110 +184,253 @@ __global__ __launch_bounds__(kThreads) void assemble_r2_kernel(double* __restric
   }
 }
 
-__global__ void add_fvo_kernel(double* r1, const double* F, int o, int v) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < o * v) {
-    const int i = idx / v, a = idx % v;
-    r1[idx] += F[(long)(o + a) * (o + v) + i];
-  }
-}
-
-// T1 dressing applied from the column correction: for each of the stacked n x n matrices,
-//   b(x, q) = S[x][q] + (q < o ? Tc[x][q] : 0)   with Tc[x][i] = sum_a S[x][o + a] t1[i][a],
-//   D[p][q] = b(p, q) - [p >= o] sum_{i < o} t1[i][p - o] b(i, q).
-// One thread per column q of a 32-row chunk of one matrix: b(i, q) is read once per i and applied to
-// all 32 rows; the t1 coefficients depend on the row only, so they are wave-uniform (scalar loads).
-__global__ __launch_bounds__(kThreads) void dress_apply_kernel(double* __restrict__ D, const double* __restrict__ S,
-                                                               const double* __restrict__ Tc,
-                                                               const double* __restrict__ t1, int o, int v) {
-  constexpr int RC = 32;
-  const int n = o + v;
-  const long nn = (long)n * n;
-  const int z = blockIdx.z, r0 = blockIdx.x * RC, q = blockIdx.y * kThreads + threadIdx.x;
-  if (q >= n) return;
-  const double* Sz = S + z * nn;
-  const double* Tz = Tc + (long)z * n * o;
-  double* Dz = D + z * nn;
-  const bool qlo = q < o;
-  double acc[RC];
+// ---------------------------------------------------------------------------------------
+// T1 dressing B^ = X B Y^T with X = 1 - t1 (virtual-occupied block) and Y^T = 1 + t1 (virtual-occupied), every
+// array with the fitting index Q last (rows of ldq values, zero past naux), so that the dressed blocks are
+// written in the layout that the contractions over Q read, in two passes over B (o20 v180 Q600, with the Fock
+// matrix: 0.53 ms as products, block copies and traces of [Q][p][q] arrays, 0.2 ms so).
+//
+// Right side: D[k][p] = B[p][k] + sum_c B[p][o + c] t1[k][c], all p, k < o.  One thread per Q column of one p
+// and KC values of k: B's virtual columns are read once per KC, coalesced.
+constexpr int kDressCols = 128, kDressC = 32;
+template <int KC>
+__global__ __launch_bounds__(kDressCols) void dress_right_kernel(double* __restrict__ D, const double* __restrict__ B,
+                                                                 const double* __restrict__ t1, int o, int v, long ldq) {
+  __shared__ double t[kDressC][KC];
+  const int n = o + v, p = blockIdx.y, k0 = blockIdx.z * KC;
+  const long q = blockIdx.x * (long)kDressCols + threadIdx.x;
+  const bool in = q < ldq;
+  const double* Bp = B + (long)p * n * ldq + q;
+  double acc[KC];
 #pragma unroll
-  for (int r = 0; r < RC; ++r) {
-    const int p = r0 + r;
-    acc[r] = p < n ? Sz[(long)p * n + q] + (qlo ? Tz[(long)p * o + q] : 0.0) : 0.0;
-  }
-  if (r0 + RC > o) {  // the chunk has rows p >= o
-    for (int i = 0; i < o; ++i) {
-      const double b = Sz[(long)i * n + q] + (qlo ? Tz[(long)i * o + q] : 0.0);
-      const double* ti = t1 + (long)i * v;
+  for (int r = 0; r < KC; ++r) acc[r] = (in && k0 + r < o) ? Bp[(k0 + r) * ldq] : 0.0;
+  for (int c0 = 0; c0 < v; c0 += kDressC) {
+    const int nc = min(kDressC, v - c0);
+    __syncthreads();
+    for (int x = threadIdx.x; x < kDressC * KC; x += kDressCols) {
+      const int r = x / kDressC, c = x % kDressC;
+      t[c][r] = (c < nc && k0 + r < o) ? t1[(long)(k0 + r) * v + c0 + c] : 0.0;
+    }
+    __syncthreads();
+    if (in) {
+      const double* b = Bp + (long)(o + c0) * ldq;
+#pragma unroll 4
+      for (int c = 0; c < nc; ++c) {
+        const double x = b[c * ldq];
 #pragma unroll
-      for (int r = 0; r < RC; ++r) {
-        const int p = r0 + r;
-        if (p >= o && p < n) acc[r] -= ti[p - o] * b;
+        for (int r = 0; r < KC; ++r) acc[r] += t[c][r] * x;
       }
     }
   }
+  if (!in) return;
 #pragma unroll
-  for (int r = 0; r < RC; ++r) {
-    const int p = r0 + r;
-    if (p < n) Dz[(long)p * n + q] = acc[r];
+  for (int r = 0; r < KC; ++r)
+    if (k0 + r < o) D[((long)(k0 + r) * n + p) * ldq + q] = acc[r];
+}
+
+// Wave sum over the 64 lanes, every lane gets it (a fixed order).
+__device__ __forceinline__ double wave_all(double x) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+  return x;
+}
+
+// Left side: out[a][x] = in[a][x] - sum_k t1[k][a] w[k][x] for the columns x
+//   x = c < v:       bvv[a][c] = B[o+a][o+c] - sum_k t1[k][a] B[k][o+c]
+//   x = v + i:       bvo[i][a] = D[i][o+a]   - sum_k t1[k][a] D[i][k],  and boo[k][i] = D[i][k]
+// and the Coulomb part of the Fock matrix, f[p][q] = h[p][q] + 2 sum_Q J_Q B[p][q], J_Q = sum_k D[k][k]: its
+// virtual-virtual rows from the same reads, the others by the workgroups behind the columns.
+// A workgroup holds one column x and 32 values of a (eight per wave) and walks the Q in chunks of 64 with the
+// chunk's w rows in LDS.
+constexpr int kDressA = 32, kDressK = 128;
+struct DressP {
+  const double *B, *D, *t1, *h;
+  double *bvv, *bvo, *boo, *f;
+  int o, v;
+  long ldq;
+};
+__global__ __launch_bounds__(kThreads) void dress_left_kernel(DressP p) {
+  extern __shared__ double sh[];  // of kDressK k at a time: w [.][64], t1 [.][kDressA]; J parts [4][64]
+  const int o = p.o, v = p.v, n = o + v, tid = threadIdx.x, lane = tid & 63, ok = min(o, kDressK);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const long ldq = p.ldq;
+  double* w = sh;
+  double* t = sh + ok * 64;
+  double* jp = t + ok * kDressA;
+  // J of one chunk of 64 Q, for this lane
+  auto trace = [&](long q0) -> double {
+    double s = 0.0;
+    if (q0 + lane < ldq)
+      for (int k = wave; k < o; k += 4) s += p.D[((long)k * n + k) * ldq + q0 + lane];
+    __syncthreads();
+    jp[wave * 64 + lane] = s;
+    __syncthreads();
+    return ((jp[lane] + jp[64 + lane]) + jp[128 + lane]) + jp[192 + lane];
+  };
+  const int x = blockIdx.x, a0 = blockIdx.y * kDressA;
+  if (x >= n) {  // Coulomb rows (p, q) with p or q occupied: 32 per workgroup
+    const long nrow = (long)n * n - (long)v * v, r0 = ((long)(x - n) * gridDim.y + blockIdx.y) * 32;
+    if (r0 >= nrow) return;
+    double dot[8];
+    long row[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const long y = r0 + wave * 8 + r;  // rows of the occupied p first, then (o + a, k)
+      row[r] = y >= nrow ? -1 : y < (long)o * n ? y : (o + (y - (long)o * n) / o) * n + (y - (long)o * n) % o;
+      dot[r] = 0.0;
+    }
+    for (long q0 = 0; q0 < ldq; q0 += 64) {
+      const double j = trace(q0);
+      if (q0 + lane < ldq) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+          if (row[r] >= 0) dot[r] += j * p.B[row[r] * ldq + q0 + lane];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const double s = wave_all(dot[r]);
+      if (lane == 0 && row[r] >= 0) p.f[row[r]] = p.h[row[r]] + 2.0 * s;
+    }
+    return;
+  }
+  const bool vv = x < v;
+  const int i = x - v;
+  const double* in = vv ? p.B + ((long)o * n + o + x) * ldq : p.D + ((long)i * n + o) * ldq;  // of a = 0
+  const long sin = vv ? n * ldq : ldq;
+  const double* wsrc = vv ? p.B + (long)(o + x) * ldq : p.D + (long)i * n * ldq;  // of k = 0
+  const long sw = vv ? n * ldq : ldq;
+  double* out = vv ? p.bvv + (long)x * ldq : p.bvo + (long)i * v * ldq;
+  const long sout = vv ? v * ldq : ldq;
+  double dot[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) dot[r] = 0.0;
+  const int ab = a0 + wave * 8;
+  for (long q0 = 0; q0 < ldq; q0 += 64) {
+    const double j = vv ? trace(q0) : 0.0;
+    const long q = q0 + lane;
+    double acc[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      acc[r] = (q < ldq && ab + r < v) ? in[(ab + r) * sin + q] : 0.0;
+      dot[r] += j * acc[r];
+    }
+    for (int k0 = 0; k0 < o; k0 += kDressK) {
+      const int nk = min(kDressK, o - k0);
+      __syncthreads();
+      if (q0 == 0 || o > kDressK)
+        for (int y = tid; y < nk * kDressA; y += kThreads) {
+          const int a = a0 + y % kDressA;
+          t[y] = a < v ? p.t1[(long)(k0 + y / kDressA) * v + a] : 0.0;
+        }
+      for (int y = tid; y < nk * 64; y += kThreads) {
+        const long k = k0 + (y >> 6), qy = q0 + (y & 63);
+        const double z = qy < ldq ? wsrc[k * sw + qy] : 0.0;
+        w[y] = z;
+        if (!vv && blockIdx.y == 0 && qy < ldq) p.boo[(k * o + i) * ldq + qy] = z;
+      }
+      __syncthreads();
+      for (int k = 0; k < nk; ++k) {
+        const double z = w[k * 64 + lane];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) acc[r] -= t[k * kDressA + wave * 8 + r] * z;
+      }
+    }
+    if (q < ldq) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+        if (ab + r < v) out[(ab + r) * sout + q] = acc[r];
+    }
+  }
+  if (!vv) return;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const double s = wave_all(dot[r]);
+    const long row = (long)(o + ab + r) * n + o + x;
+    if (lane == 0 && ab + r < v) p.f[row] = p.h[row] + 2.0 * s;
   }
 }
 
-// The same dressing with the chunk's t1 coefficients staged in LDS first: for fixed i the 32
-// coefficients t1[i][p - o] of the chunk's rows are contiguous, zero for rows p < o or p >= n, so
-// the inner loop is branch-free and reads them as LDS broadcasts instead of one dependent scalar
-// load per (i, row).
-constexpr int kDressRows = 32;
-__global__ __launch_bounds__(kThreads) void dress_apply_lds_kernel(double* __restrict__ D, const double* __restrict__ S,
-                                                                   const double* __restrict__ Tc,
-                                                                   const double* __restrict__ t1, int o, int v) {
-  extern __shared__ double coef[];  // [o][kDressRows]
-  const int n = o + v;
-  const long nn = (long)n * n;
-  const int z = blockIdx.z, r0 = blockIdx.x * kDressRows, q = blockIdx.y * kThreads + threadIdx.x;
-  const bool lower = r0 + kDressRows > o;  // the chunk has rows p >= o
-  if (lower) {
-    for (int x = threadIdx.x; x < o * kDressRows; x += kThreads) {
-      const int i = x / kDressRows, p = r0 + (x - i * kDressRows);
-      coef[x] = (p >= o && p < n) ? t1[(long)i * v + (p - o)] : 0.0;
+// f[row] = f0[row] + alpha sum_Q J_Q B[row], J_Q = sum_k B[k][k], for all n^2 rows, 32 per workgroup.
+__global__ __launch_bounds__(kThreads) void coulomb_kernel(double* __restrict__ f, const double* __restrict__ f0,
+                                                          const double* __restrict__ B, double alpha, int o, int n,
+                                                          long ldq) {
+  __shared__ double J[64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long nn = (long)n * n, row = blockIdx.x * 32L + wave * 8;
+  double dot[8] = {};
+  for (long q0 = 0; q0 < ldq; q0 += 64) {
+    const long q = q0 + lane;
+    __syncthreads();
+    if (wave == 0) {
+      double s = 0.0;
+      if (q < ldq)
+        for (int k = 0; k < o; ++k) s += B[((long)k * n + k) * ldq + q];
+      J[lane] = s;
     }
     __syncthreads();
-  }
-  if (q >= n) return;
-  const double* Sz = S + z * nn;
-  const double* Tz = Tc + (long)z * n * o;
-  double* Dz = D + z * nn;
-  const bool qlo = q < o;
-  double acc[kDressRows];
+    if (q < ldq) {
 #pragma unroll
-  for (int r = 0; r < kDressRows; ++r) {
-    const int p = r0 + r;
-    acc[r] = p < n ? Sz[(long)p * n + q] + (qlo ? Tz[(long)p * o + q] : 0.0) : 0.0;
-  }
-  if (lower) {
-    for (int i = 0; i < o; ++i) {
-      const double b = Sz[(long)i * n + q] + (qlo ? Tz[(long)i * o + q] : 0.0);
-      const double* ci = coef + i * kDressRows;
-#pragma unroll
-      for (int r = 0; r < kDressRows; ++r) acc[r] -= ci[r] * b;
+      for (int r = 0; r < 8; ++r)
+        if (row + r < nn) dot[r] += J[lane] * B[(row + r) * ldq + q];
     }
   }
 #pragma unroll
-  for (int r = 0; r < kDressRows; ++r) {
-    const int p = r0 + r;
-    if (p < n) Dz[(long)p * n + q] = acc[r];
+  for (int r = 0; r < 8; ++r) {
+    const double s = wave_all(dot[r]);
+    if (lane == 0 && row + r < nn) f[row + r] = f0[row + r] + alpha * s;
   }
 }
 
-// x -> (1 + c E_hp) x (1 - c E_hp) on each of nb stacked n x n matrices (E_hp: the unit matrix with a
-// one at row h, column p): row h += c row p, then column p -= c column h of the result.  One
-// workgroup per matrix; the two steps touch disjoint rows / columns of their own step.
-__global__ __launch_bounds__(kThreads) void onebody_transform_kernel(double* __restrict__ X, int n, int h, int p,
-                                                                     double c) {
-  double* Xz = X + (long)blockIdx.x * n * n;
-  for (int q = threadIdx.x; q < n; q += kThreads) Xz[(long)h * n + q] += c * Xz[(long)p * n + q];
+// Dressed Fock blocks F^ = X f Y^T: fvv [v][v], foo [o][o], fvo as r1[i][a] = F^_ai, fov [o][v] = f_ov.  The
+// first v workgroups form the rows b of fvv, the others the columns j < o (g(x) = f[x][j] + sum_c f[x][o+c] t1[j][c]).
+__global__ __launch_bounds__(512) void fock_finish_kernel(double* __restrict__ fvv, double* __restrict__ foo,
+                                                         double* __restrict__ r1, double* __restrict__ fov,
+                                                         const double* __restrict__ f, const double* __restrict__ t1,
+                                                         int o, int v) {
+  extern __shared__ double g[];  // [o + v]
+  const int n = o + v;
+  if ((int)blockIdx.x < v) {
+    const int b = blockIdx.x;
+    for (int k = threadIdx.x; k < o; k += 512) g[k] = t1[(long)k * v + b];
+    __syncthreads();
+    for (int c = threadIdx.x; c < v; c += 512) {
+      double s = f[(long)(o + b) * n + o + c];
+      for (int k = 0; k < o; ++k) s -= g[k] * f[(long)k * n + o + c];
+      fvv[(long)b * v + c] = s;
+    }
+    return;
+  }
+  const int j = blockIdx.x - v, lane = threadIdx.x & 63;
+  for (int x = threadIdx.x >> 6; x < n; x += 8) {
+    double s = 0.0;
+    for (int c = lane; c < v; c += 64) s += f[(long)x * n + o + c] * t1[(long)j * v + c];
+    s = wave_all(s);
+    if (lane == 0) g[x] = f[(long)x * n + j] + s;
+  }
   __syncthreads();
-  for (int r = threadIdx.x; r < n; r += kThreads) Xz[(long)r * n + p] -= c * Xz[(long)r * n + h];
+  for (int k = threadIdx.x; k < o; k += 512) foo[(long)k * o + j] = g[k];
+  for (int a = threadIdx.x; a < v; a += 512) {
+    double s = g[o + a];
+    for (int k = 0; k < o; ++k) s -= t1[(long)k * v + a] * g[k];
+    r1[(long)j * v + a] = s;
+    fov[(long)j * v + a] = f[(long)j * n + o + a];
+  }
+}
+
+// x -> (1 + c E_hp) x (1 - c E_hp) on an n x n matrix of rows of len values (stride ld): row h += c row p, then
+// column p -= c column h of the result; element (r, s) of either step is one workgroup row of len values.
+__global__ __launch_bounds__(kThreads) void onebody_row_kernel(double* __restrict__ X, int n, long ld, long len, int h,
+                                                               int p, double c) {
+  double* d = X + ((long)h * n + blockIdx.x) * ld;
+  const double* s = X + ((long)p * n + blockIdx.x) * ld;
+  for (long q = threadIdx.x; q < len; q += kThreads) d[q] += c * s[q];
+}
+__global__ __launch_bounds__(kThreads) void onebody_col_kernel(double* __restrict__ X, int n, long ld, long len, int h,
+                                                               int p, double c) {
+  double* d = X + ((long)blockIdx.x * n + p) * ld;
+  const double* s = X + ((long)blockIdx.x * n + h) * ld;
+  for (long q = threadIdx.x; q < len; q += kThreads) d[q] -= c * s[q];
 }
 
 // t1 = 0 except t1[h][a] = s1; t2 = 0 except t2[h][h][a][a] = s2.
@@ -299,16 +442,6 @@ __global__ __launch_bounds__(kThreads) void initial_guess_kernel(double* __restr
       t1[x] = (x == k1) ? s1 : 0.0;
     else
       t2[x - len1] = (x - len1 == k2) ? s2 : 0.0;
-  }
-}
-
-__global__ void diag_trace_kernel(double* J, const double* Bh, int naux, int n, int no) {
-  const int Q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (Q < naux) {
-    const double* b = Bh + (long)Q * n * n;
-    double s = 0.0;
-    for (int k = 0; k < no; ++k) s += b[(long)k * n + k];
-    J[Q] = s;
   }
 }
 
@@ -1104,42 +1237,73 @@ hipError_t assemble_r2(double* r2, const double* g1, const double* rl, const dou
   return hipGetLastError();
 }
 
-hipError_t add_fvo(double* r1, const double* fhat, int no, int nv, hipStream_t s) {
-  const int total = no * nv;
-  const long n = no + nv;
-  if (bounds_checking() && !(range_ok(r1, 0, total - 1, 8, "add_fvo r1") && range_ok(fhat, 0, n * n - 1, 8, "add_fvo F")))
-    return hipErrorInvalidValue;
-  if (dry_run()) return hipSuccess;
-  hipLaunchKernelGGL(add_fvo_kernel, dim3((total + 255) / 256), dim3(256), 0, s, r1, fhat, no, nv);
-  return hipGetLastError();
-}
+static bool chk(const void* p, long n, const char* what) { return range_ok(p, 0, n - 1, 8, what); }
 
-hipError_t dress_apply(double* D, const double* S, const double* Tc, const double* t1, int o, int v, int nb,
-                       hipStream_t s) {
+hipError_t dress_right(double* D, const double* B, const double* t1, int o, int v, long ldq, hipStream_t s) {
   const long n = o + v;
-  if (o < 1 || v < 1 || nb < 1 || nb > 65535) return hipErrorInvalidValue;
-  if (bounds_checking() && !(range_ok(D, 0, nb * n * n - 1, 8, "dress D") && range_ok(S, 0, nb * n * n - 1, 8, "dress S") &&
-                             range_ok(Tc, 0, nb * n * o - 1, 8, "dress Tc") && range_ok(t1, 0, (long)o * v - 1, 8, "dress t1")))
+  if (o < 1 || v < 1 || ldq < 1 || n > 65535) return hipErrorInvalidValue;
+  if (bounds_checking() && !(chk(D, o * n * ldq, "dress D") && chk(B, n * n * ldq, "dress B") && chk(t1, (long)o * v, "dress t1")))
     return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
-  if (o <= 256) {  // coefficients of one chunk: o * 32 doubles of LDS, 64 KB at most
-    hipLaunchKernelGGL(dress_apply_lds_kernel,
-                       dim3((unsigned)((n + kDressRows - 1) / kDressRows), (unsigned)((n + kThreads - 1) / kThreads),
-                            (unsigned)nb),
-                       dim3(kThreads), (size_t)o * kDressRows * sizeof(double), s, D, S, Tc, t1, o, v);
-    return hipGetLastError();
+  // sums per thread: the multiple of 8 that holds o in the fewest passes over B (at most 40)
+  const int passes = (o + 39) / 40, kc = ((o + passes - 1) / passes + 7) / 8 * 8;
+  const dim3 grid((unsigned)((ldq + kDressCols - 1) / kDressCols), (unsigned)n, (unsigned)((o + kc - 1) / kc));
+  switch (kc) {
+    case 8: hipLaunchKernelGGL(dress_right_kernel<8>, grid, dim3(kDressCols), 0, s, D, B, t1, o, v, ldq); break;
+    case 16: hipLaunchKernelGGL(dress_right_kernel<16>, grid, dim3(kDressCols), 0, s, D, B, t1, o, v, ldq); break;
+    case 24: hipLaunchKernelGGL(dress_right_kernel<24>, grid, dim3(kDressCols), 0, s, D, B, t1, o, v, ldq); break;
+    case 32: hipLaunchKernelGGL(dress_right_kernel<32>, grid, dim3(kDressCols), 0, s, D, B, t1, o, v, ldq); break;
+    default: hipLaunchKernelGGL(dress_right_kernel<40>, grid, dim3(kDressCols), 0, s, D, B, t1, o, v, ldq);
   }
-  hipLaunchKernelGGL(dress_apply_kernel, dim3((unsigned)((n + 31) / 32), (unsigned)((n + kThreads - 1) / kThreads), (unsigned)nb),
-                     dim3(kThreads), 0, s, D, S, Tc, t1, o, v);
   return hipGetLastError();
 }
 
-hipError_t onebody_transform(double* X, long nb, int n, int h, int p, double c, hipStream_t s) {
-  if (nb < 1 || n < 1) return hipSuccess;
-  if (h < 0 || h >= n || p < 0 || p >= n || h == p || nb > 0x7fffffffL) return hipErrorInvalidValue;
-  if (bounds_checking() && !range_ok(X, 0, nb * n * n - 1, 8, "one-body transform")) return hipErrorInvalidValue;
+hipError_t dress_left(double* bvv, double* bvo, double* boo, double* f, const double* B, const double* D,
+                      const double* t1, const double* h, int o, int v, long ldq, hipStream_t s) {
+  const long n = o + v, oo = (long)o * o, ov = (long)o * v, vv = (long)v * v;
+  if (o < 1 || v < 1 || o > 256 || ldq < 1) return hipErrorInvalidValue;
+  if (bounds_checking() && !(chk(bvv, vv * ldq, "dress B^vv") && chk(bvo, ov * ldq, "dress B^vo") && chk(boo, oo * ldq, "dress B^oo") &&
+                             chk(f, n * n, "dress f") && chk(B, n * n * ldq, "dress B") && chk(D, o * n * ldq, "dress D") &&
+                             chk(t1, ov, "dress t1") && chk(h, n * n, "dress h")))
+    return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
-  hipLaunchKernelGGL(onebody_transform_kernel, dim3((unsigned)nb), dim3(kThreads), 0, s, X, n, h, p, c);
+  const long ga = (v + kDressA - 1) / kDressA, rest = (n * n - vv + 31) / 32;  // a blocks; Coulomb workgroups
+  const size_t lds = ((size_t)std::min(o, kDressK) * (64 + kDressA) + 256) * sizeof(double);
+  if (lds > 64 * 1024 &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(dress_left_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(dress_left_kernel, dim3((unsigned)(n + (rest + ga - 1) / ga), (unsigned)ga), dim3(kThreads), lds, s,
+                     DressP{B, D, t1, h, bvv, bvo, boo, f, o, v, ldq});
+  return hipGetLastError();
+}
+
+hipError_t coulomb(double* f, const double* f0, const double* B, double alpha, int o, int n, long ldq, hipStream_t s) {
+  const long nn = (long)n * n;
+  if (bounds_checking() && !(chk(f, nn, "Coulomb f") && chk(f0, nn, "Coulomb f0") && chk(B, nn * ldq, "Coulomb B")))
+    return hipErrorInvalidValue;
+  if (dry_run()) return hipSuccess;
+  hipLaunchKernelGGL(coulomb_kernel, dim3((unsigned)((nn + 31) / 32)), dim3(kThreads), 0, s, f, f0, B, alpha, o, n, ldq);
+  return hipGetLastError();
+}
+
+hipError_t fock_finish(double* fvv, double* foo, double* r1, double* fov, const double* f, const double* t1, int o,
+                       int v, hipStream_t s) {
+  const long n = o + v, ov = (long)o * v;
+  if (bounds_checking() && !(chk(fvv, (long)v * v, "F^vv") && chk(foo, (long)o * o, "F^oo") && chk(r1, ov, "F^vo") &&
+                             chk(fov, ov, "F^ov") && chk(f, n * n, "Fock f") && chk(t1, ov, "Fock t1")))
+    return hipErrorInvalidValue;
+  if (dry_run()) return hipSuccess;
+  hipLaunchKernelGGL(fock_finish_kernel, dim3((unsigned)n), dim3(512), n * sizeof(double), s, fvv, foo, r1, fov, f, t1, o, v);
+  return hipGetLastError();
+}
+
+hipError_t onebody_transform(double* X, int n, long ld, long len, int h, int p, double c, hipStream_t s) {
+  if (n < 1 || len < 1 || ld < len) return hipErrorInvalidValue;
+  if (h < 0 || h >= n || p < 0 || p >= n || h == p) return hipErrorInvalidValue;
+  if (bounds_checking() && !chk(X, ((long)n * n - 1) * ld + len, "one-body transform")) return hipErrorInvalidValue;
+  if (dry_run()) return hipSuccess;
+  hipLaunchKernelGGL(onebody_row_kernel, dim3((unsigned)n), dim3(kThreads), 0, s, X, n, ld, len, h, p, c);
+  hipLaunchKernelGGL(onebody_col_kernel, dim3((unsigned)n), dim3(kThreads), 0, s, X, n, ld, len, h, p, c);
   return hipGetLastError();
 }
 
@@ -1398,15 +1562,6 @@ hipError_t mixed_doubles(double* dst, const double* src, int o, int v, int h, in
   return hipGetLastError();
 }
 
-hipError_t diag_trace(double* J, const double* Bh, int naux, int n, int no, hipStream_t s) {
-  if (bounds_checking() && !(range_ok(J, 0, naux - 1, 8, "trace J") &&
-                             range_ok(Bh, 0, (long)naux * n * n - 1, 8, "trace B")))
-    return hipErrorInvalidValue;
-  if (dry_run()) return hipSuccess;
-  hipLaunchKernelGGL(diag_trace_kernel, dim3((naux + 255) / 256), dim3(256), 0, s, J, Bh, naux, n, no);
-  return hipGetLastError();
-}
-
 hipError_t energy(double* e, double* partial, const double* t1, const double* t2, const double* Lijab,
                   const double* fov, int no, int nv, hipStream_t s) {
   const long total = (long)no * no * nv * nv;
@@ -1421,8 +1576,6 @@ hipError_t energy(double* e, double* partial, const double* t1, const double* t2
   return hipGetLastError();
 }
 
-
-static bool chk(const void* p, long n, const char* what) { return range_ok(p, 0, n - 1, 8, what); }
 
 static hipError_t pack_halves(int mode, double* plus, double* minus, long ldo, const double* src, int o, int v, int a0,
                               long rows, long out_lo, long out_hi, long src_len, hipStream_t s) {

@@ -550,11 +550,11 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
 }
 
 // K-contiguous operands with 16-byte aligned rows and an even K (the loads move K-value pairs; whole
-// stages when several products are summed); the rows of a tile (256 at most) do not overlap and lie
-// within the 2 GiB range of a buffer descriptor.
+// stages when several products are summed); the rows of a tile do not overlap and lie within the 2 GiB range of a
+// buffer descriptor (32 rows here, taller tiles are checked where they are chosen).
 bool dma_eligible(const GP& p) {
   auto al = [](const void* x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
-  auto near = [&](long ld) { return ld >= p.K && ld < (1L << 20); };
+  auto near = [&](long ld) { return ld >= p.K && ld < (1L << 23); };
   return near(p.sam) && near(p.sbn) && p.sak == 1 && p.sbk == 1 && p.K % (p.nred > 1 ? kStageK : 2) == 0 &&
          p.sar % 2 == 0 && p.sbr % 2 == 0 && p.sam % 2 == 0 && p.sbn % 2 == 0 &&
          p.sa1 % 2 == 0 && p.sa2 % 2 == 0 && p.sb1 % 2 == 0 && p.sb2 % 2 == 0 && al(p.A) && al(p.B);
@@ -629,6 +629,7 @@ hipError_t launch_dma_auto(const GP& p0, int nb1, int nb1d, double* ws, long ws_
   for (int c = 0; c < (int)(sizeof kCfg / sizeof kCfg[0]); ++c) {
     const Cfg& f = kCfg[c];
     if ((red && f.bm > 64) || (p0.lower && f.bm != f.bn)) continue;
+    if (std::max(p0.sam, p0.sbn) * f.bm >= 1L << 28) continue;  // rows past a descriptor's 2 GiB
     const long tm = (p0.M + f.bm - 1) / f.bm, tn = (p0.N + f.bn - 1) / f.bn;
     const long tiles = (p0.lower ? tm * (tm + 1) / 2 : tm * tn) * nbatch;
     for (long sp = 1; sp <= 256; sp += sp < 4 ? 1 : sp / 2) {
@@ -915,7 +916,7 @@ hipError_t gemm_f64_ladder(const Ladder& L, hipStream_t s) {
   p.sb1 = lb.sv;
   p.sc1 = lb.sc;
   p.tab1 = lb.tab;
-  if (!dma_eligible(p)) return hipErrorInvalidValue;  // the operands' rows are laid out for this kernel
+  if (!dma_eligible(p) || std::max(p.sam, p.sbn) >= 1L << 20) return hipErrorInvalidValue;  // rows laid out for this kernel
   const LadderPlan pl = ladder_plan(L.M, L.Mdec, L.N, L.K, L.ws ? L.ws_elems : 0);
   // one slice after another where the partial tiles do not fit the scratch: the same sums
   double* ws = (long)pl.split * L.M * L.N * 2 * lb.n <= L.ws_elems ? L.ws : nullptr;

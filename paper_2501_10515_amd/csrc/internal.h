@@ -234,16 +234,22 @@ hipError_t wz_chi(double* wp, long ldw, double* chip, double* chim, const double
 // RL[i][j][a][b] from the pair rows R+- (stride ldr)
 hipError_t unpack_rpm(double* RL, const double* Rplus, const double* Rminus, long ldr, int o, int v, hipStream_t s);
 
-// r1[i][a] += Fhat[no+a][i]
-hipError_t add_fvo(double* r1, const double* fhat, int no, int nv, hipStream_t s);
+// T1 dressing and the dressed Fock matrix (formulas at the kernels).  B is [p][q] rows of ldq fitting values
+// (zero past naux), likewise D [o][n], bvv [v][v], bvo [o][v] (B^_ai at [i][a]) and boo [o][o]:
+//   dress_right  D[k][p] = (B Y^T)_pk
+//   dress_left   bvv, bvo, boo and f = h + 2 sum_Q J_Q B, J_Q = sum_k D[k][k]
+//   coulomb      f = f0 + alpha sum_Q J_Q B, J_Q = sum_k B[k][k]
+//   fock_finish  F^ = X f Y^T: fvv [v][v], foo [o][o], r1 = F^_ai at [i][a], fov [o][v]
+hipError_t dress_right(double* D, const double* B, const double* t1, int o, int v, long ldq, hipStream_t s);
+hipError_t dress_left(double* bvv, double* bvo, double* boo, double* f, const double* B, const double* D,
+                      const double* t1, const double* h, int o, int v, long ldq, hipStream_t s);
+hipError_t coulomb(double* f, const double* f0, const double* B, double alpha, int o, int n, long ldq, hipStream_t s);
+hipError_t fock_finish(double* fvv, double* foo, double* r1, double* fov, const double* f, const double* t1, int o,
+                       int v, hipStream_t s);
 
-// T1 dressing of nb stacked n x n matrices S (n = o + v) given Tc[z][x][i] = sum_a S[z][x][o+a] t1[i][a]:
-//   D[p][q] = b(p, q) - [p >= o] sum_{i<o} t1[i][p-o] b(i, q),  b(x, q) = S[x][q] + [q < o] Tc[x][q].
-hipError_t dress_apply(double* D, const double* S, const double* Tc, const double* t1, int o, int v, int nb,
-                       hipStream_t s);
-
-// x -> (1 + c E_hp) x (1 - c E_hp) in place on nb stacked n x n matrices (E_hp: one at row h, column p).
-hipError_t onebody_transform(double* X, long nb, int n, int h, int p, double c, hipStream_t s);
+// x -> (1 + c E_hp) x (1 - c E_hp) in place on an n x n matrix of rows of len values at stride ld (E_hp: one at
+// row h, column p).
+hipError_t onebody_transform(double* X, int n, long ld, long len, int h, int p, double c, hipStream_t s);
 // A cross index set: over the n = no * nv indices r = i * nv + a, the members with i == h or
 // a == pa (m = no + nv - 1 of them), listed compactly as (h, 0 .. nv-1), then (i, pa) for i != h
 // ascending.  With (no, nv, h, pa) = (o, v, hole, particle) it is the set of (i, a) rows of an
@@ -284,9 +290,6 @@ hipError_t reference_energy(double* e0, const double* h, long hs, long hlen, con
                             int o, hipStream_t s);
 // t1 = 0, t2 = 0 except t1[h][a] = s1 and t2[h][h][a][a] = s2.
 hipError_t initial_guess(double* t1, double* t2, int no, int nv, int h, int a, double s1, double s2, hipStream_t s);
-
-// J[Q] = sum_k Bh[Q][k][k]
-hipError_t diag_trace(double* J, const double* Bh, int naux, int n, int no, hipStream_t s);
 
 // Deterministic two-stage energy reduction:
 //   e = sum_{ijab} (t2 + t1_ia t1_jb) L[ijab] + 2 sum_ia f_ia t1_ia
