@@ -322,7 +322,7 @@ std::vector<std::pair<double* ascc_ints::*, long>> ints_plan(long o, long v, lon
       {&ascc_ints::P, 2 * ovov},      {&ascc_ints::Nq, ov * ldQ},    {&ascc_ints::WZ, oo * (ov + oo)},
       {&ascc_ints::chi, std::max(oo * oo, 2 * To * To)}, {&ascc_ints::RL, oo * vv},     {&ascc_ints::EM, oo * vv},
       {&ascc_ints::Abc, vv},          {&ascc_ints::Bkj, oo},         {&ascc_ints::Fvvp, vv},
-      {&ascc_ints::Foop, oo},         {&ascc_ints::Fovh, ov},        {&ascc_ints::partial, 8192},
+      {&ascc_ints::Foop, oo},         {&ascc_ints::Fovh, ldov},        {&ascc_ints::partial, 8192},
       {&ascc_ints::splitk, kSplitKElems},
   };
 }
@@ -467,8 +467,8 @@ T* S(T* p) {
 }
 #define EACH_SLOT for (g_slot = 0; g_slot < nslots(); ++g_slot)
 
-// FP64 contraction with the integral set's split-K scratch (shared by the slots of a batch).
-inline hipError_t mm(const ascc_ints* I, Gemm g, hipStream_t s) {
+// A contraction with the integral set's split-K scratch (shared by the slots of a batch), over the slots.
+inline hipError_t over_slots(const ascc_ints* I, Gemm& g) {
   g.ws = I->splitk;
   g.ws_elems = kSplitKElems;
   if (nslots() > 1) {
@@ -483,8 +483,26 @@ inline hipError_t mm(const ascc_ints* I, Gemm g, hipStream_t s) {
     g.tab1_max = g_sb->tab_max;
     g.per_block = true;  // each slot sums in the order it would alone
   }
-  return gemm_f64(g, s);
+  return hipSuccess;
 }
+
+// FP64 contraction.
+inline hipError_t mm(const ascc_ints* I, Gemm g, hipStream_t s) {
+  const hipError_t e = over_slots(I, g);
+  return e != hipSuccess ? e : gemm_f64(g, s);
+}
+
+// Independent FP64 contractions, small ones as one launch.
+hipError_t mm_group(const ascc_ints* I, std::vector<Gemm> gs, hipStream_t s) {
+  for (Gemm& g : gs) {
+    const hipError_t e = over_slots(I, g);
+    if (e != hipSuccess) return e;
+  }
+  return gemm_f64_group(gs.data(), (int)gs.size(), s);
+}
+
+// Whether mm would run it on small tiles (then it joins a group).
+bool mm_small(const ascc_ints* I, Gemm g) { return over_slots(I, g) == hipSuccess && gemm_f64_small(g); }
 
 // Low-precision contraction, one launch over the slots of a batch.
 inline hipError_t glp(GemmLP g, hipStream_t s) {
@@ -515,10 +533,9 @@ Gemm sum_kq(const ascc_ints* I, int M, int N, int nk, double alpha, const double
 }
 
 // f -= sign sum_kQ D[p][k] B[k][q] (the exchange part; dm, dk: strides of p and k in D)
-int subtract_exchange(const ascc_ints* I, double* f, const double* D, long dm, long dk, double sign, hipStream_t s) {
+Gemm exchange(const ascc_ints* I, double* f, const double* D, long dm, long dk, double sign) {
   const int n = I->n;
-  HIPCHK(mm(I, sum_kq(I, n, n, I->no, -sign, D, dm, dk, I->B, I->ldQ, n * I->ldQ, 1.0, f, n), s));
-  return ASCC_OK;
+  return sum_kq(I, n, n, I->no, -sign, D, dm, dk, I->B, I->ldQ, n * I->ldQ, 1.0, f, n);
 }
 
 // C_z[m][n] = sum_k A_z[m][k] B_z[n][k] in the handle's current low precision (FP64 result).
@@ -861,34 +878,66 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   // --- T1 dressing: the dressed blocks of B, and the dressed Fock matrix: F^ = X (h + 2 sum_Q J_Q B - sum_kQ D B) Y^T
   // (D = B Y^T for the occupied columns), F^_vo into r1
   const long lq = I->ldQ;
+  const bool lowp = I->cur_prec != ASCC_PREC_FP64;
+  const long lov = lowp_ld(ov), lQ = lowp_ld(Q), loo = lowp_ld(oo);
+  const long ldov = I->ldov, kq = pad_even(Q);
+  const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2;
   phase_begin(I, PH_DRESS, s);
   EACH_SLOT HIPCHK(dress_right(S(I->D), S(I->B), S(t1), o, v, lq, s));
   EACH_SLOT HIPCHK(dress_left(S(I->Bvv), S(I->BvoTt), S(I->Boo), S(I->Fh), S(I->B), S(I->D), S(t1), S(I->h), o, v, lq, s));
-  if ((rc = subtract_exchange(I, I->Fh, I->D, lq, n * lq, 1.0, s))) return rc;
-  EACH_SLOT HIPCHK(fock_finish(S(I->Fvvp), S(I->Foop), S(r1), S(I->Fovh), S(I->Fh), S(t1), o, v, s));
   phase_end(I, s);
-  // --- amplitude views: Tx[iajb] = t2[ijba], U[iajb] = 2 t2[ijab] - t2[ijba], t+-
+  // --- amplitude views: Tx[iajb] = t2[ijba], U[iajb] = 2 t2[ijab] - t2[ijba] and, where the ladder is computed
+  // here, its pair rows t+-
   phase_begin(I, PH_AMP, s);
-  const long ldov = I->ldov;
   double* U = I->TU + ov * ldov;
-  // with the pair rows t+- where the ladder is computed here
   EACH_SLOT HIPCHK(amp_views(S(I->TU), S(I->TU) + ov * ldov, ldov, lad ? nullptr : S(rows.Tp),
                              lad ? nullptr : S(rows.Tp) + rows.st, I->ldT, S(t2), o, v, s));
-  const bool lowp = I->cur_prec != ASCC_PREC_FP64;
-  const long lov = lowp_ld(ov), lQ = lowp_ld(Q), loo = lowp_ld(oo);
   if (lowp) HIPCHK(shadow_ov(I, I->TUf, I->TU, s));  // Tx|U rows, K = ov
-
   phase_end(I, s);
-  // --- density-fitted dressed integral blocks (K = naux)
+
+  // --- products of the dressed blocks and views: the exchange part of the Fock matrix, the density-fitted
+  // integral blocks (K = naux), N_Q[k,a] = sum_lc B_Q,lc u_kl^ac (U is a symmetric ov x ov matrix: its rows are
+  // its columns), and where they are small the rings' Y1 = Tx K, Y2 = U L (K and L are symmetric, so
+  // B(k, n) = KL[n][k]) and a short ladder
   phase_begin(I, PH_DF, s);
-  // g^_aibj enters R2 unmultiplied by amplitudes: always FP64, so the low-precision residual's
-  // rounding floor stays proportional to the amplitudes
-  {  // g^_aibj: a symmetric product, its lower triangle computed and mirrored
-    Gemm g = gemm_rm(ov, ov, pad_even(Q), 1.0, I->BvoTt, lq, false, I->BvoTt, lq, true, 0.0, I->G1, ov);
+  std::vector<Gemm> first;
+  first.push_back(exchange(I, I->Fh, I->D, lq, n * lq, 1.0));
+  {  // g^_aibj: a symmetric product.  It enters R2 unmultiplied by amplitudes: always FP64, so the low-precision
+     // residual's rounding floor stays proportional to the amplitudes
+    Gemm g = gemm_rm(ov, ov, kq, 1.0, I->BvoTt, lq, false, I->BvoTt, lq, true, 0.0, I->G1, ov);
     g.lower = true;
-    HIPCHK(mm(I, g, s));
+    first.push_back(g);
   }
-  // N_Q[k,a] = sum_lc B_Q,lc u_kl^ac (U is a symmetric ov x ov matrix: its rows are its columns), Q contiguous
+  {  // g^_kilj
+    Gemm g = gemm_rm(oo, oo, kq, 1.0, I->Boo, lq, false, I->Boo, lq, true, 0.0, I->G4, oo);
+    g.lower = true;
+    first.push_back(g);
+  }
+  Gemm ring_y = gemm_rm(ov, ov, pad_even(ov), 1.0, I->TU, ldov, false, I->KL, ldov, true, 0.0, I->Y, ov);
+  ring_y.sa2 = ov * ldov;
+  ring_y.sb2 = ov * ldov;
+  ring_y.sc2 = ovov;
+  ring_y.nb2 = 2;
+  bool ring_y_done = false, ladder_done = lad != nullptr;
+  if (!lowp) {
+    first.push_back(gemm_rm(oo, vv, kq, 1.0, I->Boo, lq, false, I->Bvv, lq, true, 0.0, I->G2, vv));    // g^_kiac
+    first.push_back(gemm_rm(ov, ov, kq, 1.0, I->BvoTt, lq, false, I->BovT, lq, true, 0.0, I->G3, ov));  // g^_aikc
+    first.push_back(gemm_rm(ov, lq, pad_even(ov), 1.0, U, ldov, false, I->Bov, ldov, true, 0.0, I->Nq, lq));
+    ring_y_done = mm_small(I, ring_y);
+    if (ring_y_done) first.push_back(ring_y);
+    // a ladder whose K is too short to be cut (ladder_plan) is summed whole by every kernel, stacked or not
+    if (!lad && I->vvvv_mode == ASCC_VVVV_PACKED && Tv <= kLadderWhole) {
+      Gemm g = gemm_rm(To, Tv + wzl, pad_even(Tv), 1.0, rows.Tp, I->ldT, false, I->V, I->ldT, true, 0.0, rows.Rp, I->ldR);
+      g.sa2 = rows.st;
+      g.sb2 = (Tv + wzl) * I->ldT;
+      g.sc2 = rows.sr;
+      g.nb2 = 2;
+      g.fixed = true;
+      ladder_done = mm_small(I, g);
+      if (ladder_done) first.push_back(g);
+    }
+  }
+  HIPCHK(mm_group(I, first, s));
   if (lowp) {  // the same products on low-precision shadows (B^_kc ones are constant)
     HIPCHK(shadow_q(I, I->BvoTtf, I->BvoTt, ov, s));
     HIPCHK(shadow_q(I, I->BooTf, I->Boo, oo, s));
@@ -903,23 +952,46 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
       const long os[4] = {0, 0, lq, 1};
       HIPCHK(permute4_strided(S(I->Nq) + Q, os, d, 0.0, nullptr, 0, s));
     }
-  } else {
-    const long kq = pad_even(Q);
-    HIPCHK(mm(I, gemm_rm(oo, vv, kq, 1.0, I->Boo, lq, false, I->Bvv, lq, true, 0.0, I->G2, vv), s));    // g^_kiac
-    HIPCHK(mm(I, gemm_rm(ov, ov, kq, 1.0, I->BvoTt, lq, false, I->BovT, lq, true, 0.0, I->G3, ov), s));  // g^_aikc
-    HIPCHK(mm(I, gemm_rm(ov, lq, pad_even(ov), 1.0, U, ldov, false, I->Bov, ldov, true, 0.0, I->Nq, lq), s));
   }
-  {  // g^_kilj
-    Gemm g = gemm_rm(oo, oo, pad_even(Q), 1.0, I->Boo, lq, false, I->Boo, lq, true, 0.0, I->G4, oo);
-    g.lower = true;
-    HIPCHK(mm(I, g, s));
-  }
-
   phase_end(I, s);
-  // --- E-term intermediates F'_bc = F^_bc - sum_Qk N_Q[k,b] B_Q,kc ; F''_kj = F^_kj + sum_Qd B_Q,kd N_Q[j,d]
+  phase_begin(I, PH_DRESS, s);
+  EACH_SLOT HIPCHK(fock_finish(S(I->Fvvp), S(I->Foop), S(r1), S(I->Fovh), ldov, S(I->Fh), S(t1), o, v, s));
+  phase_end(I, s);
+
+  // --- rings: Y1, Y2 (batched pair), then Xc and Zd
+  phase_begin(I, PH_RING_Y, s);
+  if (lowp) {  // K and L are symmetric matrices, so B[n][k] = B[k][n]
+    HIPCHK(glp(lp_nt(I, ov, ov, ov, 2, I->TUf, lov, ov * lov, I->KLf, lov, ov * lov, I->Y, ov, ovov), s));
+  } else if (!ring_y_done) {
+    HIPCHK(mm(I, ring_y, s));
+  }
+  phase_end(I, s);
+  phase_begin(I, PH_RING_XZ, s);
+  EACH_SLOT HIPCHK(ring_xz(S(I->XZ), S(I->XZ) + ov * ldov, ldov, S(I->G2), S(I->G3), S(I->Y), S(I->Y) + ovov, o, v, s));
+  phase_end(I, s);
+
+  // --- products of N_Q: F'_bc = F^_bc - sum_Qk N_Q[k,b] B_Q,kc, F''_kj = F^_kj + sum_Qd B_Q,kd N_Q[j,d] (E term) and
+  // r1[i][a] = F^_ai + sum_dQ N_Q[i,d] B^_Q,ad - sum_kQ B^_Q,ki N_Q[k,a] + sum_kc U[ia][kc] F^_kc; where they are
+  // small also the rings' P1 = Tx Xc^T, P2 = U Zd^T
   phase_begin(I, PH_N5, s);
-  HIPCHK(mm(I, sum_kq(I, v, v, o, -1.0, I->Nq, lq, v * lq, I->BovT, lq, v * lq, 1.0, I->Fvvp, v), s));
-  HIPCHK(mm(I, sum_kq(I, o, o, v, 1.0, I->BovT, v * lq, lq, I->Nq, v * lq, lq, 1.0, I->Foop, o), s));
+  Gemm ring_p = gemm_rm(ov, ov, pad_even(ov), 1.0, I->TU, ldov, false, I->XZ, ldov, true, 0.0, I->P, ov);
+  ring_p.sa2 = ov * ldov;
+  ring_p.sb2 = ov * ldov;
+  ring_p.sc2 = ovov;
+  ring_p.nb2 = 2;
+  std::vector<Gemm> second;
+  second.push_back(sum_kq(I, v, v, o, -1.0, I->Nq, lq, v * lq, I->BovT, lq, v * lq, 1.0, I->Fvvp, v));
+  second.push_back(sum_kq(I, o, o, v, 1.0, I->BovT, v * lq, lq, I->Nq, v * lq, lq, 1.0, I->Foop, o));
+  second.push_back(sum_kq(I, o, v, v, 1.0, I->Nq, v * lq, lq, I->Bvv, v * lq, lq, 1.0, r1, v));
+  second.push_back(sum_kq(I, o, v, o, -1.0, I->Boo, lq, o * lq, I->Nq, lq, v * lq, 1.0, r1, v));
+  {
+    Gemm g = gemm_rm(ov, 1, pad_even(ov), 1.0, U, ldov, false, I->Fovh, ldov, true, 1.0, r1, 1);
+    second.push_back(g);
+  }
+  for (int k = 2; k < 5; ++k) second[k].acc = 0;
+  const bool ring_p_done = !lowp && mm_small(I, ring_p);
+  if (ring_p_done) second.push_back(ring_p);
+  HIPCHK(mm_group(I, second, s));
   phase_end(I, s);
 
   if (lowp) {
@@ -940,7 +1012,7 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     phase_end(I, s);
   }
   // --- particle-particle ladder over the undressed (ac|bd) (with W/Z in FP64), plus the hole-hole ladder
-  if (!lad && (rc = pp_ladder(I, s))) return rc;
+  if (!ladder_done && (rc = pp_ladder(I, s))) return rc;
   const bool pairs = !lowp && I->pl_hole < 0;  // the assembly reads the ladders as pair rows
   if (lowp) {
     phase_begin(I, PH_UNPACK, s);
@@ -957,7 +1029,6 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   } else {
     // W', chi+- with F'' in it, and R+- += chi+- t+- over the pairs k <= l: a quarter of the products of
     // the full sum over k, l (and the F'' t2 product rides along)
-    const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2;
     phase_begin(I, PH_HH, s);
     EACH_SLOT HIPCHK(wz_chi(S(I->WZ), wzl, S(I->chi), S(I->chi) + To * To, S(rows.Rp) + Tv, S(rows.Rp) + rows.sr + Tv,
                             I->ldR, S(I->G4), S(I->Foop), S(t1), o, v, s));
@@ -975,38 +1046,14 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     }
   }
 
-  // --- rings: Y1 = Tx K, Y2 = U L (batched pair)
-  phase_begin(I, PH_RING_Y, s);
-  if (lowp) {  // K and L are symmetric matrices, so B[n][k] = B[k][n]
-    const long ld = lov;
-    HIPCHK(glp(lp_nt(I, ov, ov, ov, 2, I->TUf, ld, ov * ld, I->KLf, ld, ov * ld, I->Y, ov, ovov), s));
-  } else {
-    // K and L are symmetric, so B(k, n) = KL[n][k]: both operands K-contiguous
-    Gemm g = gemm_rm(ov, ov, pad_even(ov), 1.0, I->TU, ldov, false, I->KL, ldov, true, 0.0, I->Y, ov);
-    g.sa2 = ov * ldov;
-    g.sb2 = ov * ldov;
-    g.sc2 = ovov;
-    g.nb2 = 2;
-    HIPCHK(mm(I, g, s));
-  }
-  phase_end(I, s);
-  phase_begin(I, PH_RING_XZ, s);
-  EACH_SLOT HIPCHK(ring_xz(S(I->XZ), S(I->XZ) + ov * ldov, ldov, S(I->G2), S(I->G3), S(I->Y), S(I->Y) + ovov, o, v, s));
-  phase_end(I, s);
+  // --- rings: P1 = Tx Xc^T, P2 = U Zd^T (batched pair)
   phase_begin(I, PH_RING_P, s);
-  if (lowp) {  // P1 = Tx Xc^T, P2 = U Zd^T
-    const long ld = lowp_ld(ov);
+  if (lowp) {
     HIPCHK(shadow_ov(I, I->XZf, I->XZ, s));
-    HIPCHK(glp(lp_nt(I, ov, ov, ov, 2, I->TUf, ld, ov * ld, I->XZf, ld, ov * ld, I->P, ov, ovov), s));
-  } else {
-    Gemm g = gemm_rm(ov, ov, pad_even(ov), 1.0, I->TU, ldov, false, I->XZ, ldov, true, 0.0, I->P, ov);
-    g.sa2 = ov * ldov;
-    g.sb2 = ov * ldov;
-    g.sc2 = ovov;
-    g.nb2 = 2;
-    HIPCHK(mm(I, g, s));
+    HIPCHK(glp(lp_nt(I, ov, ov, ov, 2, I->TUf, lov, ov * lov, I->XZf, lov, ov * lov, I->P, ov, ovov), s));
+  } else if (!ring_p_done) {
+    HIPCHK(mm(I, ring_p, s));
   }
-
   phase_end(I, s);
   phase_begin(I, PH_N5, s);
   // EM = sum_c t_ij^ac F'_bc
@@ -1082,29 +1129,6 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     if ((rc = plascc_remove(I, t2, RL, s))) return rc;
     phase_end(I, s);
   }
-  phase_begin(I, PH_N5, s);
-  // --- singles
-  // r1[i][a] = F^_ai + sum_dQ N_Q[i,d] B^_Q,ad - sum_kQ B^_Q,ki N_Q[k,a]
-  HIPCHK(mm(I, sum_kq(I, o, v, v, 1.0, I->Nq, v * lq, lq, I->Bvv, v * lq, lq, 1.0, r1, v), s));
-  HIPCHK(mm(I, sum_kq(I, o, v, o, -1.0, I->Boo, lq, o * lq, I->Nq, lq, v * lq, 1.0, r1, v), s));
-  {  // r1[(ia)] += sum_kc U[(ia),(kc)] F^_kc
-    Gemm g;
-    g.M = ov;
-    g.N = 1;
-    g.K = ov;
-    g.A = U;
-    g.sam = ldov;
-    g.sak = 1;
-    g.B = I->Fovh;
-    g.sbk = 1;
-    g.sbn = 0;
-    g.C = r1;
-    g.scm = 1;
-    g.scn = 0;
-    g.beta = 1.0;
-    HIPCHK(mm(I, g, s));
-  }
-  phase_end(I, s);
   // --- doubles assembly and energy
   phase_begin(I, PH_ASSEMBLE, s);
   EACH_SLOT HIPCHK(assemble_r2(S(r2), S(I->G1), pairs ? S(rows.Rp) : S(RL), S(I->EM), S(I->P), S(I->P) + ovov, o, v, s,
@@ -1181,14 +1205,13 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
   }
   // h = f - sum_k (2 (pq|kk) - (pk|kq))
   HIPCHK(coulomb(I->h, I->h, I->B, -2.0, o, (int)n, lq, s));
-  int rc = subtract_exchange(I, I->h, I->B, n * lq, lq, -1.0, s);
-  if (rc) return rc;
+  HIPCHK(mm(I, exchange(I, I->h, I->B, n * lq, lq, -1.0), s));
   if (hole >= 0) {
     const double c = s_sign / std::sqrt(2.0);
     HIPCHK(onebody_transform(I->B, (int)n, lq, Q, hole, particle, c, s));
     HIPCHK(onebody_transform(I->h, (int)n, 1, 1, hole, particle, c, s));
     HIPCHK(coulomb(I->Fh, I->h, I->B, 2.0, o, (int)n, lq, s));
-    if ((rc = subtract_exchange(I, I->Fh, I->B, n * lq, lq, 1.0, s))) return rc;  // fbar
+    HIPCHK(mm(I, exchange(I, I->Fh, I->B, n * lq, lq, 1.0), s));  // fbar
     int d[4] = {o, v, 1, 1};
     Perm4In x = pin(I->Fh + o, n, 1, 0, 0, 1.0);
     HIPCHK(permute4(I->fov, d, 0.0, &x, 1, s));

@@ -382,10 +382,10 @@ __global__ __launch_bounds__(kThreads) void coulomb_kernel(double* __restrict__ 
   }
 }
 
-// Dressed Fock blocks F^ = X f Y^T: fvv [v][v], foo [o][o], fvo as r1[i][a] = F^_ai, fov [o][v] = f_ov.  The
+// Dressed Fock blocks F^ = X f Y^T: fvv [v][v], foo [o][o], fvo as r1[i][a] = F^_ai, fov [o][v] = f_ov (zero to ldf).  The
 // first v workgroups form the rows b of fvv, the others the columns j < o (g(x) = f[x][j] + sum_c f[x][o+c] t1[j][c]).
 __global__ __launch_bounds__(512) void fock_finish_kernel(double* __restrict__ fvv, double* __restrict__ foo,
-                                                         double* __restrict__ r1, double* __restrict__ fov,
+                                                         double* __restrict__ r1, double* __restrict__ fov, long ldf,
                                                          const double* __restrict__ f, const double* __restrict__ t1,
                                                          int o, int v) {
   extern __shared__ double g[];  // [o + v]
@@ -416,6 +416,8 @@ __global__ __launch_bounds__(512) void fock_finish_kernel(double* __restrict__ f
     r1[(long)j * v + a] = s;
     fov[(long)j * v + a] = f[(long)j * n + o + a];
   }
+  if (j == 0)
+    for (long x = (long)o * v + threadIdx.x; x < ldf; x += 512) fov[x] = 0.0;
 }
 
 // x -> (1 + c E_hp) x (1 - c E_hp) on an n x n matrix of rows of len values (stride ld): row h += c row p, then
@@ -1286,14 +1288,15 @@ hipError_t coulomb(double* f, const double* f0, const double* B, double alpha, i
   return hipGetLastError();
 }
 
-hipError_t fock_finish(double* fvv, double* foo, double* r1, double* fov, const double* f, const double* t1, int o,
-                       int v, hipStream_t s) {
+hipError_t fock_finish(double* fvv, double* foo, double* r1, double* fov, long ldf, const double* f, const double* t1,
+                       int o, int v, hipStream_t s) {
   const long n = o + v, ov = (long)o * v;
   if (bounds_checking() && !(chk(fvv, (long)v * v, "F^vv") && chk(foo, (long)o * o, "F^oo") && chk(r1, ov, "F^vo") &&
-                             chk(fov, ov, "F^ov") && chk(f, n * n, "Fock f") && chk(t1, ov, "Fock t1")))
+                             chk(fov, std::max(ldf, ov), "F^ov") && chk(f, n * n, "Fock f") && chk(t1, ov, "Fock t1")))
     return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
-  hipLaunchKernelGGL(fock_finish_kernel, dim3((unsigned)n), dim3(512), n * sizeof(double), s, fvv, foo, r1, fov, f, t1, o, v);
+  hipLaunchKernelGGL(fock_finish_kernel, dim3((unsigned)n), dim3(512), n * sizeof(double), s, fvv, foo, r1, fov, ldf, f, t1, o,
+                     v);
   return hipGetLastError();
 }
 

@@ -41,6 +41,7 @@ struct GP {
   int nb2, nred;
   int tiles_m, tiles_n;
   int split, it_per_split;  // split-K: slices of the (nred x K-tile) iteration space
+  int per;                  // direct-to-LDS: workgroups of one slice
   double* part;             // partial tiles [split][nb1*nb2][M][N] when split > 1
   int seq;                  // split > 1 without partial tiles: a workgroup runs all slices of its tile,
                             // each added to C in turn (the sums of the partial tiles, in slice order)
@@ -323,10 +324,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const double* base, 
   return __builtin_amdgcn_make_buffer_rsrc(ub, (short)0, __builtin_amdgcn_readfirstlane((int)(rows * ld * 8)), 0x00020000);
 }
 
-// RED: nred products of K-values each (K a multiple of 16) run through one K loop, product r at strides
-// sar, sbr.
+// One workgroup's tile (and slices): bid numbers the workgroups of p (tiles x slices), z2 and z1 are its batch
+// levels (nz1 operand blocks).  RED: nred products of K-values each (K a multiple of 16 if there are several)
+// run through one K loop, product r at strides sar, sbr.
 template <int BM, int BN, int WM, int WN, int S, bool PM, bool RED>
-__global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
+__device__ __forceinline__ void dma_tile(const GP& p, int bid, int z2, const int z1, const int nz1) {
   typedef double dd2 __attribute__((ext_vector_type(2)));
   typedef double d4 __attribute__((ext_vector_type(4)));
   constexpr int NW = WM * WN;
@@ -344,10 +346,8 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int ntiles = p.tiles_m * p.tiles_n;
-  int bid = blockIdx.x, z2 = blockIdx.y;
-  const int per = PM ? 2 * ((ntiles + 7) / 8 * 8) : p.lower ? gridDim.x : ntiles;  // workgroups of a slice
-  const int slice0 = bid / per, slice1 = p.seq ? p.split : slice0 + 1;  // split-K slices of this workgroup
-  bid -= slice0 * per;
+  const int slice0 = bid / p.per, slice1 = p.seq ? p.split : slice0 + 1;  // split-K slices of this workgroup
+  bid -= slice0 * p.per;
   if constexpr (PM) {
     // Both halves of a tile read the same V rows: they are dispatched back to back to the same
     // XCD (workgroups b and b + 8 share an XCD), so the second one finds them in L2.
@@ -362,7 +362,6 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
   else
     tile_of(bid, p.tiles_m, p.tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
-  const int z1 = blockIdx.z;
   const int zs = p.tab1 ? p.tab1[z1] : z1;  // operand block of batch level 1
   const double* Ab = p.A + zs * p.sa1 + z2 * p.sa2;
   const double* Bb = p.B + zs * p.sb1 + z2 * p.sb2;
@@ -413,7 +412,7 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
   // before the loads of stage kt: RED: the descriptors of its product; otherwise, on the last stage of an
   // uneven K (no stage follows it), chunks past K read as zero
   auto begin_stage = [&](int kt) {
-    if constexpr (RED) {
+    if (RED && p.nred > 1) {
       const int r = kt / nk1;
       k_red = r * nk1;
       ra = tile_rsrc(At + r * p.sar, rows_a, p.sam);
@@ -538,15 +537,64 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
             const double v = p.alpha * acc[i][j][r];
             if (p.part) {
               const long zl = (long)z1 * p.nb2 + z2;
-              p.part[(((long)slice * gridDim.z * p.nb2 + zl) * p.M + gm) * p.N + gn] = v;
+              p.part[(((long)slice * nz1 * p.nb2 + zl) * p.M + gm) * p.N + gn] = v;
             } else {
               double* c = Cb + (long)gm * p.scm + (long)gn * p.scn;
               *c = (slice != slice0) ? *c + v : (p.beta == 0.0) ? v : v + p.beta * *c;
-              if (!PM && !RED && BM == BN && p.lower && tm != tn) Cb[(long)gn * p.scm + (long)gm * p.scn] = v;
+              if (!PM && BM == BN && p.lower && tm != tn) Cb[(long)gn * p.scm + (long)gm * p.scn] = v;
             }
           }
         }
   }
+}
+
+template <int BM, int BN, int WM, int WN, int S, bool PM, bool RED>
+__global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
+  dma_tile<BM, BN, WM, WN, S, PM, RED>(p, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z);
+}
+
+// Several independent contractions as one launch: problem i takes the workgroups start[i] .. start[i + 1] - 1
+// (batch level 2, slices and tiles), every problem the same batch level 1 in grid.z.
+constexpr int kMaxGroup = 8;
+struct GroupP {
+  int n, start[kMaxGroup + 1];
+  GP p[kMaxGroup];
+};
+template <int BT, int W>
+__global__ __launch_bounds__(W* W * 64, 1) void gemm_f64_group_kernel(GroupP g) {
+  int i = 0;
+  while (i + 1 < g.n && (int)blockIdx.x >= g.start[i + 1]) ++i;
+  const GP& p = g.p[i];
+  const int local = (int)blockIdx.x - g.start[i], per2 = p.per * p.split, z2 = local / per2;
+  dma_tile<BT, BT, W, W, 3, false, true>(p, local - z2 * per2, z2, blockIdx.z, gridDim.z);
+}
+
+// The partial tiles of a group: job i sums slices of outs values per operand block (as splitk_reduce) and takes
+// the workgroups start[i] .. start[i + 1] - 1.  The slices of several problems with one output follow one another.
+struct GroupR {
+  int n, start[kMaxGroup + 1];
+  int slices[kMaxGroup];
+  GP p[kMaxGroup];
+};
+__global__ __launch_bounds__(256) void group_reduce_kernel(GroupR g) {
+  __shared__ double red[4][64];
+  int i = 0;
+  while (i + 1 < g.n && (int)blockIdx.x >= g.start[i + 1]) ++i;
+  const GP& p = g.p[i];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, z1 = blockIdx.z, ns = g.slices[i];
+  const long mn = (long)p.M * p.N, outs = mn * p.nb2, x = ((int)blockIdx.x - g.start[i]) * 64L + lane;
+  const int s0 = (int)((long)ns * w / 4), s1 = (int)((long)ns * (w + 1) / 4);
+  double acc = 0.0;
+  if (x < outs)
+    for (int sl = s0; sl < s1; ++sl) acc += p.part[((long)sl * gridDim.z + z1) * outs + x];
+  red[w][lane] = acc;
+  __syncthreads();
+  if (w != 0 || x >= outs) return;
+  const double sum = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+  const int z2 = (int)(x / mn), gm = (int)(x % mn / p.N), gn = (int)(x % p.N);
+  const int zs = p.tab1 ? p.tab1[z1] : z1;
+  double* c = p.C + zs * p.sc1 + z2 * p.sc2 + gm * p.scm + gn * p.scn;
+  *c = (p.beta == 0.0) ? sum : sum + p.beta * *c;
 }
 
 // K-contiguous operands with 16-byte aligned rows and an even K (the loads move K-value pairs; whole
@@ -592,8 +640,8 @@ hipError_t launch_dma(GP p, int nb1, int split, double* ws, bool ordered, hipStr
   const int tiles = p.lower ? p.tiles_m * (p.tiles_m + 1) / 2 : p.tiles_m * p.tiles_n;
   if (p.lower && (p.split > 1 || PM || BM != BN || p.tiles_m != p.tiles_n)) return hipErrorInvalidValue;
   if (p.split > 1 && !ws && !ordered) return hipErrorInvalidValue;
-  const int per = PM ? 2 * ((tiles + 7) / 8 * 8) : tiles;  // PM: both halves in grid.x, padded to groups of 8
-  dim3 grid(per * (p.seq ? 1 : p.split), PM ? 1 : p.nb2, nb1);
+  p.per = PM ? 2 * ((tiles + 7) / 8 * 8) : tiles;  // PM: both halves in grid.x, padded to groups of 8
+  dim3 grid(p.per * (p.seq ? 1 : p.split), PM ? 1 : p.nb2, nb1);
   hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, S, PM, RED>), grid, dim3(WM * WN * 64), 0, s, p);
   if (p.part) {
     const long outs = (long)p.M * p.N * p.nb2 * nb1;
@@ -614,46 +662,62 @@ hipError_t launch_dma(GP p, int nb1, int split, double* ws, bool ordered, hipStr
 // 576 x 576 x 240 75 -> 17 us, 390 x 1521 x 1522 70 -> 55 us against 192- to 256-row tiles.
 // nb1d: the outer batch count the choice is made for; where the partial tiles of all blocks do not fit the
 // scratch, the blocks run in several launches, so that a block's sums never depend on the batch.
-hipError_t launch_dma_auto(const GP& p0, int nb1, int nb1d, double* ws, long ws_elems, hipStream_t s) {
-  struct Cfg {
-    int bm, bn;
-    double t, t1;
-  };
-  constexpr Cfg kCfg[] = {{192, 192, 4.19, 4.19}, {256, 128, 3.80, 3.80}, {224, 128, 3.45, 3.45}, {128, 128, 1.93, 1.93},
-                          {96, 96, 1.31, 1.45},   {64, 64, 0.58, 0.70},   {32, 32, 0.185, 0.50}};
+struct DmaCfg {
+  int bm, bn;
+  double t, t1;
+};
+constexpr DmaCfg kDmaCfg[] = {{192, 192, 4.19, 4.19}, {256, 128, 3.80, 3.80}, {224, 128, 3.45, 3.45}, {128, 128, 1.93, 1.93},
+                              {96, 96, 1.31, 1.45},   {64, 64, 0.58, 0.70},   {32, 32, 0.185, 0.50}};
+struct DmaPlan {
+  int cfg, split;
+  double us;
+};
+long dma_tiles(const GP& p, int bm, int bn) {  // of one operand block
+  const long tm = (p.M + bm - 1) / bm, tn = (p.N + bn - 1) / bn;
+  return p.lower ? tm * (tm + 1) / 2 : tm * tn;
+}
+inline long dma_stages(const GP& p) { return (long)((p.K + kStageK - 1) / kStageK) * p.nred; }
+DmaPlan plan_dma(const GP& p0, int nb1d, bool ws, long ws_elems) {
   const bool red = p0.nred > 1;
   const long nbatch = (long)p0.nb2 * nb1d, outs = (long)p0.M * p0.N * nbatch;  // of the deciding batch
-  const long nkt = (long)((p0.K + kStageK - 1) / kStageK) * p0.nred;
-  int best = -1, best_split = 1;
-  double least = 0.0;
-  for (int c = 0; c < (int)(sizeof kCfg / sizeof kCfg[0]); ++c) {
-    const Cfg& f = kCfg[c];
+  const long nkt = dma_stages(p0);
+  DmaPlan best{-1, 1, 0.0};
+  for (int c = 0; c < (int)(sizeof kDmaCfg / sizeof kDmaCfg[0]); ++c) {
+    const DmaCfg& f = kDmaCfg[c];
     if ((red && f.bm > 64) || (p0.lower && f.bm != f.bn)) continue;
     if (std::max(p0.sam, p0.sbn) * f.bm >= 1L << 28) continue;  // rows past a descriptor's 2 GiB
-    const long tm = (p0.M + f.bm - 1) / f.bm, tn = (p0.N + f.bn - 1) / f.bn;
-    const long tiles = (p0.lower ? tm * (tm + 1) / 2 : tm * tn) * nbatch;
+    const long tiles = dma_tiles(p0, f.bm, f.bn) * nbatch;
     for (long sp = 1; sp <= 256; sp += sp < 4 ? 1 : sp / 2) {
       if (sp > 1 && (p0.lower || !ws || tiles * sp > 1536 || nkt < 4 * sp || sp * outs > ws_elems)) break;
       const double per = std::max((double)((tiles * sp + 255) / 256) * f.t, f.t1);
       const double us = 6.0 + (double)((nkt + sp - 1) / sp + 2) * per + (sp > 1 ? 5.0 + (double)((sp + 1) * outs) * 2.7e-6 : 0.0);
-      if (best < 0 || us < least) {
-        best = c;
-        best_split = (int)sp;
-        least = us;
-      }
+      if (best.cfg < 0 || us < best.us) best = {c, (int)sp, us};
     }
   }
+  return best;
+}
+
+// p advanced to operand block z0 of batch level 1
+GP at_block(GP p, long z0) {
+  if (p.tab1) {
+    p.tab1 += z0;
+  } else {
+    p.A += z0 * p.sa1;
+    p.B += z0 * p.sb1;
+    p.C += z0 * p.sc1;
+  }
+  return p;
+}
+
+hipError_t launch_dma_auto(const GP& p0, int nb1, int nb1d, double* ws, long ws_elems, hipStream_t s) {
+  const bool red = p0.nred > 1;
+  const long outs = (long)p0.M * p0.N * p0.nb2 * nb1d;
+  const DmaPlan pl = plan_dma(p0, nb1d, ws != nullptr, ws_elems);
+  const int best = pl.cfg, best_split = pl.split;
   const long fit = best_split > 1 ? std::max<long>(1, ws_elems / (best_split * (outs / nb1d))) : nb1;
   for (long z0 = 0; z0 < nb1; z0 += fit) {
-    GP p = p0;
+    const GP p = at_block(p0, z0);
     const int n = (int)std::min<long>(fit, nb1 - z0);
-    if (p.tab1) {
-      p.tab1 += z0;
-    } else {
-      p.A += z0 * p.sa1;
-      p.B += z0 * p.sb1;
-      p.C += z0 * p.sc1;
-    }
     hipError_t e;
     switch (best) {
       case 0: e = launch_dma<192, 192, 2, 4, 3>(p, n, best_split, ws, false, s); break;
@@ -702,7 +766,7 @@ LadderPlan ladder_plan(long M, long Mdec, long N, long K, long ws_elems) {
   LadderPlan best{256, 1};
   double least = -1;
   for (int bm : kBM)
-    for (int sp = 1; sp <= 8 && (sp == 1 || (nkt >= 16 * sp && 2 * sp * Mdec * N <= ws_elems)); ++sp) {
+    for (int sp = 1; sp <= 8 && (sp == 1 || (K > kLadderWhole && nkt >= 16 * sp && 2 * sp * Mdec * N <= ws_elems)); ++sp) {
       const double c = cost(Mdec, bm, sp);
       if (least < 0 || c < least) {
         least = c;
@@ -800,15 +864,8 @@ static bool gemm_in_bounds(const Gemm& g) {
   return !g.ws || range_ok(g.ws, 0, g.ws_elems - 1, sizeof(double), "gemm split-K scratch");
 }
 
-hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
-  if (g.M <= 0 || g.N <= 0 || g.nb1 <= 0 || g.nb2 <= 0) return hipSuccess;
-  if (bounds_checking() && !gemm_in_bounds(g)) return hipErrorInvalidValue;
-  if (dry_run()) return hipSuccess;
-  if (g.nb1 > 65535 || g.nb2 > 65535) return hipErrorInvalidValue;
-  // tile and split-K choices: for the whole batch, or as for one block of the outer level
-  const int nb1d = g.per_block ? 1 : g.nb1, nbatch = nb1d * g.nb2;
-  if (g.K <= 0 || g.nred <= 0) return hipErrorInvalidValue;  // callers never pass an empty contraction
-  GP p;
+static GP to_gp(const Gemm& g) {
+  GP p{};
   p.M = g.M;
   p.N = g.N;
   p.K = g.K;
@@ -837,10 +894,20 @@ hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
   p.pm = nullptr;
   p.tab1 = g.tab1;
   p.lower = 0;
-  if (dma_eligible(p)) {
-    p.lower = g.lower && g.M == g.N && g.beta == 0.0 && g.nred == 1;
-    return launch_dma_auto(p, g.nb1, nb1d, g.ws, g.ws_elems, s);
-  }
+  p.lower = g.lower && g.M == g.N && g.beta == 0.0 && g.nred == 1 && dma_eligible(p);
+  return p;
+}
+
+hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0 || g.nb1 <= 0 || g.nb2 <= 0) return hipSuccess;
+  if (bounds_checking() && !gemm_in_bounds(g)) return hipErrorInvalidValue;
+  if (dry_run()) return hipSuccess;
+  if (g.nb1 > 65535 || g.nb2 > 65535) return hipErrorInvalidValue;
+  // tile and split-K choices: for the whole batch, or as for one block of the outer level
+  const int nb1d = g.per_block ? 1 : g.nb1, nbatch = nb1d * g.nb2;
+  if (g.K <= 0 || g.nred <= 0) return hipErrorInvalidValue;  // callers never pass an empty contraction
+  GP p = to_gp(g);
+  if (dma_eligible(p)) return launch_dma_auto(p, g.nb1, nb1d, g.fixed ? nullptr : g.ws, g.ws_elems, s);
   // Global-load order: an operand whose m (n) stride is 1 is read m-fast (n-fast).
   const bool amf = (g.sam == 1 && g.sak != 1);
   const bool bnf = (g.sbn == 1) || (g.sbk != 1);
@@ -873,6 +940,129 @@ hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
   if (g.ws && g.M >= 16 && g.N >= 16 && (long)g.K * g.nred >= 2048 && tiles64 < 192)
     return launch_cfg<64, 64, 16, 2, 2, 2>(p, amf, bnf, g.nb1, nb1d, g.ws, g.ws_elems, s);
   return launch_cfg<32, 32, 16, 1, 1, 3>(p, amf, bnf, g.nb1, nb1d, g.ws, g.ws_elems, s);
+}
+
+bool gemm_f64_small(const Gemm& g) {
+  const GP p = to_gp(g);
+  if (g.M <= 0 || g.N <= 0 || g.K <= 0 || !dma_eligible(p)) return false;
+  const DmaPlan pl = plan_dma(p, g.per_block ? 1 : g.nb1, g.ws && !g.fixed, g.ws_elems);
+  return pl.cfg >= 0 && kDmaCfg[pl.cfg].bm <= 64;
+}
+
+hipError_t gemm_f64_group(const Gemm* all, int count, hipStream_t s) {
+  // Estimated as plan_dma estimates a launch, with one launch overhead and one reduction for all; a unit is one
+  // slice of one tile, sliced to about the same number of stages in every problem.  Contractions that take
+  // larger tiles go by themselves (those that share an output stay together).
+  const int nb1 = count > 0 ? all[0].nb1 : 1;
+  Gemm gs[kMaxGroup];
+  GP p[kMaxGroup];
+  int n = 0;
+  auto joins_group = [&](const Gemm& g) {
+    return !dry_run() && g.nb1 == nb1 && nb1 <= 65535 && g.ws && g.ws == all[0].ws && gemm_f64_small(g);
+  };
+  bool together = true;
+  for (int i = 0; i < count; ++i)
+    if (all[i].acc >= 0) together = together && joins_group(all[i]);
+  double solo = 0.0;
+  for (int i = 0; i < count; ++i) {
+    const Gemm& g = all[i];
+    if (n == kMaxGroup || (g.acc >= 0 ? !together : !joins_group(g))) {
+      const hipError_t e = gemm_f64(g, s);
+      if (e != hipSuccess) return e;
+      continue;
+    }
+    if (bounds_checking() && !gemm_in_bounds(g)) return hipErrorInvalidValue;
+    gs[n] = g;
+    p[n++] = to_gp(g);
+    if (!g.fixed) solo += plan_dma(p[n - 1], g.per_block ? 1 : g.nb1, true, g.ws_elems).us;
+  }
+  const bool group = n > 1;
+  struct Choice {
+    int bt = 0;
+    long unit = 0;
+    double us = 0.0;
+  } best;
+  auto split_of = [&](int i, long unit) {
+    const long nkt = dma_stages(p[i]);
+    if (gs[i].fixed || p[i].lower) return 1L;
+    return std::max(1L, std::min({(nkt + unit - 1) / unit, nkt / 4, 64L}));
+  };
+  for (int bt : {64, 32}) {
+    if (!group) break;
+    const double t = bt == 64 ? 0.58 : 0.185, t1 = bt == 64 ? 0.70 : 0.50;
+    for (long unit : {8L, 12L, 16L, 24L, 32L, 48L, 64L, 128L, 1L << 40}) {
+      double work = 0.0, units = 0.0, parts = 0.0;
+      long longest = 0;
+      for (int i = 0; i < n; ++i) {
+        if (gs[i].fixed) continue;  // the choice does not depend on these
+        const long sp = split_of(i, unit), st = (dma_stages(p[i]) + sp - 1) / sp, tl = dma_tiles(p[i], bt, bt) * p[i].nb2;
+        work += (double)(tl * sp) * (double)(st + 2);
+        units += (double)(tl * sp);
+        longest = std::max(longest, st);
+        if (sp > 1 || gs[i].acc >= 0) parts += (double)sp * p[i].M * p[i].N * p[i].nb2;
+      }
+      if (parts > (double)gs[0].ws_elems) continue;
+      const double on = std::min(std::ceil(units / 256.0), bt == 64 ? 3.0 : 6.0);  // units sharing a CU
+      const double us = 6.0 + std::max(work * t / 256.0, (double)(longest + 2) * std::max(t1, on * t)) +
+                        (parts > 0 ? 5.0 + parts * 2.7e-6 : 0.0);
+      if (best.bt == 0 || us < best.us) best = {bt, unit, us};
+    }
+  }
+  if (!group || best.bt == 0 || best.us >= solo) {
+    for (int i = 0; i < n; ++i) {
+      const hipError_t e = gemm_f64(gs[i], s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  // slices, scratch and launch order (problems that share an output: their slices follow one another)
+  long parts = 0;
+  for (int i = 0; i < n; ++i) {
+    const long sp = split_of(i, best.unit);
+    p[i].tiles_m = (p[i].M + best.bt - 1) / best.bt;
+    p[i].tiles_n = (p[i].N + best.bt - 1) / best.bt;
+    p[i].per = (int)dma_tiles(p[i], best.bt, best.bt);
+    const long nkt = dma_stages(p[i]);
+    p[i].it_per_split = (int)((nkt + sp - 1) / sp);
+    p[i].split = (int)((nkt + p[i].it_per_split - 1) / p[i].it_per_split);
+    if (p[i].split > 1 || gs[i].acc >= 0) parts += (long)p[i].split * p[i].M * p[i].N * p[i].nb2;
+  }
+  const long fit = parts ? std::max(1L, std::min<long>(nb1, gs[0].ws_elems / parts)) : nb1;
+  for (long z0 = 0; z0 < nb1; z0 += fit) {
+    const int nz = (int)std::min<long>(fit, nb1 - z0);
+    GroupP gp{};
+    GroupR gr{};
+    double* ws = gs[0].ws;
+    gp.n = n;
+    for (int i = 0; i < n; ++i) {
+      GP q = at_block(p[i], z0);
+      const bool joins = gs[i].acc >= 0 && i > 0 && gs[i - 1].acc == gs[i].acc;  // adds to the job before it
+      if (q.split > 1 || gs[i].acc >= 0) {
+        q.part = ws;
+        ws += (long)q.split * q.M * q.N * q.nb2 * nz;
+        if (joins) {
+          gr.slices[gr.n - 1] += q.split;
+        } else {
+          gr.p[gr.n] = q;
+          gr.slices[gr.n] = q.split;
+          gr.start[gr.n + 1] = gr.start[gr.n] + (int)(((long)q.M * q.N * q.nb2 + 63) / 64);
+          ++gr.n;
+        }
+      }
+      gp.p[i] = q;
+      gp.start[i + 1] = gp.start[i] + q.per * q.split * q.nb2;
+    }
+    const dim3 grid((unsigned)gp.start[n], 1, (unsigned)nz);
+    if (best.bt == 64)
+      hipLaunchKernelGGL((gemm_f64_group_kernel<64, 2>), grid, dim3(256), 0, s, gp);
+    else
+      hipLaunchKernelGGL((gemm_f64_group_kernel<32, 1>), grid, dim3(64), 0, s, gp);
+    if (gr.n)
+      hipLaunchKernelGGL(group_reduce_kernel, dim3((unsigned)gr.start[gr.n], 1, (unsigned)nz), dim3(256), 0, s, gr);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t gemm_f64_ladder(const Ladder& L, hipStream_t s) {

@@ -70,6 +70,10 @@ struct Gemm {
   // the direct-to-LDS kernel, only the tiles on and below the diagonal are computed, each stored
   // at its transposed place too (otherwise the full product)
   bool lower = false;
+  // In a group (gemm_f64_group): consecutive contractions with the same acc >= 0 add to one output (the same
+  // C, M x N elements in the same order, beta = 1); fixed: K is summed whole by any launch.
+  int acc = -1;
+  bool fixed = false;
 };
 
 // Batch level of the particle-particle ladder: n operand blocks (A, V and C offset by sa, sv, sc
@@ -88,6 +92,12 @@ Gemm gemm_rm(int M, int N, int K, double alpha, const double* A, long lda, bool 
              bool tb, double beta, double* C, long ldc);
 
 hipError_t gemm_f64(const Gemm& g, hipStream_t s);
+// Independent contractions in order (each output read and written by one of them, or added to by several with
+// the same acc): small ones as one launch where that is estimated to take less time than their own launches, a
+// choice made from the shapes of one operand block (not from those marked fixed).
+hipError_t gemm_f64_group(const Gemm* gs, int n, hipStream_t s);
+// Whether a contraction would take small direct-to-LDS tiles (64 x 64 or 32 x 32) by itself.
+bool gemm_f64_small(const Gemm& g);
 
 // Particle-particle ladder over pair indices, both halves h = 0 (+), 1 (-) in one launch:
 //   C_h[m][n] = sum_k A_h[m][k] * V_h(n, k),   m < M, n < N, k < K
@@ -110,6 +120,7 @@ struct Ladder {
   long ws_elems = 0;
   LadderBatch lb;
 };
+constexpr int kLadderWhole = 31 * 16;  // K up to this is never cut
 hipError_t gemm_f64_ladder(const Ladder& L, hipStream_t s);
 
 // Low-precision contraction with FP64 result (gemm_lowp.hip):
@@ -239,13 +250,13 @@ hipError_t unpack_rpm(double* RL, const double* Rplus, const double* Rminus, lon
 //   dress_right  D[k][p] = (B Y^T)_pk
 //   dress_left   bvv, bvo, boo and f = h + 2 sum_Q J_Q B, J_Q = sum_k D[k][k]
 //   coulomb      f = f0 + alpha sum_Q J_Q B, J_Q = sum_k B[k][k]
-//   fock_finish  F^ = X f Y^T: fvv [v][v], foo [o][o], r1 = F^_ai at [i][a], fov [o][v]
+//   fock_finish  F^ = X f Y^T: fvv [v][v], foo [o][o], r1 = F^_ai at [i][a], fov [o][v] (zero to ldf elements)
 hipError_t dress_right(double* D, const double* B, const double* t1, int o, int v, long ldq, hipStream_t s);
 hipError_t dress_left(double* bvv, double* bvo, double* boo, double* f, const double* B, const double* D,
                       const double* t1, const double* h, int o, int v, long ldq, hipStream_t s);
 hipError_t coulomb(double* f, const double* f0, const double* B, double alpha, int o, int n, long ldq, hipStream_t s);
-hipError_t fock_finish(double* fvv, double* foo, double* r1, double* fov, const double* f, const double* t1, int o,
-                       int v, hipStream_t s);
+hipError_t fock_finish(double* fvv, double* foo, double* r1, double* fov, long ldf, const double* f, const double* t1,
+                       int o, int v, hipStream_t s);
 
 // x -> (1 + c E_hp) x (1 - c E_hp) in place on an n x n matrix of rows of len values at stride ld (E_hp: one at
 // row h, column p).
