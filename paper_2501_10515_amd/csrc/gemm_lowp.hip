@@ -6,11 +6,10 @@
 // rounded to nearest even by the conversion kernels); C is FP64 with general strides.  Two
 // arithmetic policies:
 //
-//   FP32   : v_mfma_f32_16x16x4_f32 on FP32 shadows (256 x 256 direct-to-LDS tiles for large
-//            products, 128 x 128 register-staged ones for small).
+//   FP32   : v_mfma_f32_16x16x4_f32 on FP32 shadows.
 //   BF16X3 : the shadows are two bf16 planes, x = hi + lo with hi = RNE_bf16(x),
-//            lo = RNE_bf16(x - hi); v_mfma_f32_16x16x32_bf16 forms lo*hi + hi*lo + hi*hi (the
-//            lo*lo term, relative size 2^-16, is dropped).
+//            lo = RNE_bf16(x - hi); v_mfma_f32_16x16x32_bf16 or 32x32x16 forms
+//            lo*hi + hi*lo + hi*hi (the lo*lo term, relative size 2^-16, is dropped).
 //
 // Both accumulate in FP32 inside a K chunk and add each chunk's partial sum into the FP64 C tile
 // (which the workgroup owns for the whole K range), so accumulation across chunks is FP64.
@@ -22,7 +21,8 @@
 // C(8(q/4) + 4(l/32) + q%4, l%32).
 #include <algorithm>
 #include <cstdint>
-#include <cstdlib>
+#include <type_traits>
+#include <utility>
 
 #include "internal.h"
 
@@ -32,32 +32,12 @@ namespace {
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
-struct LP {
-  int M, N, K;
-  const float* A;
-  long lda, sa2;
-  const float* B;
-  long ldb, sb2;
-  double* C;
-  long scm, scn, sc2;
-  double alpha, beta;
-  int tiles_m, tiles_n;
-  int chunk;    // K-tiles per FP32 accumulation chunk
-  int ktps;     // K-tiles per split-K slice (blockIdx.z); the whole K when not split
-  long cslice;  // C offset between slices (partial tiles of a split launch), 0 otherwise
-  // batch: blockIdx.y = z1 * nb + z; z1 selects operand block tab1[z1] (or z1) at strides
-  // sa1, sb1, sc1 (partial tiles of a split launch: block z1 itself)
-  int nb, part;
-  const int* tab1;
-  long sa1, sb1, sc1;
-};
-
-// The eight-wave split-BF16x3 kernel adds a later FP32 chunk's partial sum into the FP64 result with
+// The 32 x 32 split-BF16x3 fragments add a later FP32 chunk's partial sum into the FP64 result with
 // a non-returning FP64 atomic add, performed at L2: the old value is never read into registers
-// (2.8 % of the o40 v360 split-BF16x3 step; the FP32 kernels' 16 x 16 output layout, four rows per
-// instruction, made the same change twice as slow there, so they keep the load-add-store).  Each
+// (2.8 % of the o40 v360 split-BF16x3 step; the 16 x 16 output layout, four rows per
+// instruction, made the same change twice as slow there, so it keeps the load-add-store).  Each
 // element has one writer (the lane that owns it) and its chunks arrive in order, so the sums are
-// those of a load-add-store; the first chunk's plain stores are waited for before any add follows.
+// those of a load-add-store; the stores of a chunk are waited for before any add follows.
 __device__ __forceinline__ void add_to(double* p, double v) { unsafeAtomicAdd(p, v); }
 
 // Round-to-nearest-even FP32 -> bf16 bits (finite inputs; NaN stays NaN).
@@ -69,17 +49,7 @@ __device__ __forceinline__ unsigned short bf16_rne(float f) {
 }
 __device__ __forceinline__ float bf16_to_f(unsigned short h) { return __uint_as_float(((uint32_t)h) << 16); }
 
-// ASCC_NO_TAIL_TILES=1 (read once per process) keeps a last row tile of at most 64 rows in the
-// full-tile launch instead of the tail launch; both give the same rows bit for bit.
-bool tail_tiles_enabled() {
-  static const bool on = [] {
-    const char* e = std::getenv("ASCC_NO_TAIL_TILES");
-    return !(e && e[0] == '1');
-  }();
-  return on;
-}
-
-// Same, walked in groups of 8 M-tiles (M fastest inside a group): the workgroups resident on one
+// Workgroup to tile, walked in groups of 8 M-tiles (M fastest inside a group): the workgroups resident on one
 // XCD at a time cover a compact block of C and share A and B slices in its L2.
 __device__ __forceinline__ void tile_of_grouped(int bid, int tiles_m, int tiles_n, int& tm, int& tn) {
   constexpr int GM = 8;
@@ -93,145 +63,6 @@ __device__ __forceinline__ void tile_of_grouped(int bid, int tiles_m, int tiles_
   const int r = t - g * per;
   tm = first + r % gs;
   tn = r / gs;
-}
-
-__device__ __forceinline__ void tile_of_lp(int bid, int tiles_m, int total, int& tm, int& tn) {
-  const int q = total >> 3, rem = total & 7;
-  const int x = bid & 7, local = bid >> 3;
-  const int tile = x * q + min(x, rem) + local;
-  tm = tile % tiles_m;
-  tn = tile / tiles_m;
-}
-
-constexpr int BM = 128, BN = 128, NT = 256;
-
-// FP32 policy: 128 x 128 tiles, four 64 x 64 waves, v_mfma_f32_16x16x4_f32.
-__global__ __launch_bounds__(NT, 1) void gemm_lowp_kernel(LP p) {
-  // K depth per LDS stage and row pitch of the staged tiles (elements)
-  constexpr int BK = 32;
-  constexpr int PITCH = BK + 4;
-  // per stage each thread moves 4 float4 of A and 4 of B (128 x 32 floats each)
-  constexpr int LQ = BM * BK / 4 / NT;
-  static_assert(LQ == 4, "tile config");
-  __shared__ __attribute__((aligned(16))) float As[2][BM * PITCH];
-  __shared__ __attribute__((aligned(16))) float Bs[2][BN * PITCH];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;  // 2 x 2 waves of 64 x 64
-  int tm, tn;
-  tile_of_lp(blockIdx.x, p.tiles_m, p.tiles_m * p.tiles_n, tm, tn);
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int z = blockIdx.y % p.nb, z1 = blockIdx.y / p.nb;
-  const int zs = __builtin_amdgcn_readfirstlane(p.tab1 ? p.tab1[z1] : z1);  // uniform: scalar buffer descriptors
-  const float* Ab = p.A + z * p.sa2 + zs * p.sa1;
-  const float* Bb = p.B + z * p.sb2 + zs * p.sb1;
-  double* Cb = p.C + z * p.sc2 + (p.part ? z1 : zs) * p.sc1 + blockIdx.z * p.cslice;
-
-  f4 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-
-  // K-tiles [kt0, nkt) of this split-K slice
-  const int kt0 = blockIdx.z * p.ktps, nkt = min((p.K + BK - 1) / BK, kt0 + p.ktps);
-  f4 ra[LQ], rb[LQ];
-  // chunk c = tid + NT*l of the tile: row c/8, k offset 4*(c%8)
-  auto load = [&](int kt) {
-    const int k0 = kt * BK;
-#pragma unroll
-    for (int l = 0; l < LQ; ++l) {
-      const int c = tid + l * NT;
-      const int r = c >> 3, kq = (c & 7) * 4;
-      const int gk = k0 + kq;
-      const int gm = m0 + r, gn = n0 + r;
-      f4 va = f4{0.f, 0.f, 0.f, 0.f}, vb = va;
-      if (gm < p.M) {
-        const float* src = Ab + gm * p.lda + gk;
-        if (gk + 3 < p.K && ((reinterpret_cast<uintptr_t>(src) & 15) == 0)) {
-          va = *reinterpret_cast<const f4*>(src);
-        } else {
-#pragma unroll
-          for (int t = 0; t < 4; ++t)
-            if (gk + t < p.K) va[t] = src[t];
-        }
-      }
-      if (gn < p.N) {
-        const float* src = Bb + gn * p.ldb + gk;
-        if (gk + 3 < p.K && ((reinterpret_cast<uintptr_t>(src) & 15) == 0)) {
-          vb = *reinterpret_cast<const f4*>(src);
-        } else {
-#pragma unroll
-          for (int t = 0; t < 4; ++t)
-            if (gk + t < p.K) vb[t] = src[t];
-        }
-      }
-      ra[l] = va;
-      rb[l] = vb;
-    }
-  };
-  auto store = [&](int buf) {
-#pragma unroll
-    for (int l = 0; l < LQ; ++l) {
-      const int c = tid + l * NT;
-      const int r = c >> 3, kq = (c & 7) * 4;
-      *reinterpret_cast<f4*>(&As[buf][r * PITCH + kq]) = ra[l];
-      *reinterpret_cast<f4*>(&Bs[buf][r * PITCH + kq]) = rb[l];
-    }
-  };
-
-  auto flush = [&](bool first) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int gm = m0 + wm * 64 + i * 16 + 4 * (lane >> 4) + r;
-          const int gn = n0 + wn * 64 + j * 16 + (lane & 15);
-          if (gm < p.M && gn < p.N) {
-            double* c = Cb + gm * p.scm + gn * p.scn;
-            const double v = p.alpha * (double)acc[i][j][r];
-            if (first)
-              *c = (p.beta == 0.0) ? v : v + p.beta * *c;
-            else
-              *c += v;
-          }
-          acc[i][j][r] = 0.f;
-        }
-  };
-
-  const int lr = lane & 15, lg = lane >> 4;
-  if (kt0 < nkt) {
-    load(kt0);
-    store(0);
-  }
-  __syncthreads();
-  for (int kc = kt0; kc < nkt; kc += p.chunk) {
-  const int kend = min(nkt, kc + p.chunk);
-  for (int kt = kc; kt < kend; ++kt) {
-    const int cur = (kt - kt0) & 1;
-    if (kt + 1 < nkt) load(kt + 1);
-    const float* as = As[cur];
-    const float* bs = Bs[cur];
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 4) {
-      float xa[4], xb[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) xa[i] = as[(wm * 64 + i * 16 + lr) * PITCH + kk + lg];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) xb[j] = bs[(wn * 64 + j * 16 + lr) * PITCH + kk + lg];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[i], xb[j], acc[i][j], 0, 0, 0);
-    }
-    if (kt + 1 < nkt) store(cur ^ 1);
-    __syncthreads();
-  }
-  flush(kc == kt0);
-  }
-  if (kt0 >= nkt) flush(true);
 }
 
 // Row-padded conversions: out row r holds in row r (cols values) then zeros up to ldo.
@@ -415,652 +246,252 @@ __global__ __launch_bounds__(256) void lowp_pm_kernel(unsigned short* __restrict
 
 
 // ---------------------------------------------------------------------------------------
-// Split-BF16x3 on pre-split operands: each row of A and B holds, per K-block of 32, the 32 hi
-// values then the 32 lo values (bf16; row stride lda/ldb a multiple of 64, zero padding), so one
-// K-step of a row is one 128-byte line, every staging load is one 16-byte chunk and no
-// conversion happens in the kernel.
+// The contraction kernel.  A stage is 32 K-values of every tile row, which both policies keep in one 128-byte line
+// (32 FP32 values, or the hi 32 | lo 32 of a split).  The lines go straight from memory to LDS (eight rows per
+// 1 KB load; lane l of a load writes LDS bytes 16l .. 16l + 15), S stages deep, with one barrier per stage; rows past M or N
+// read as zero through the range of the tile's buffer descriptor, and the K padding of a shadow is zero.  The 16-byte chunk c
+// of row r sits at slot c ^ ((r >> 1) & 7): sixteen rows of one chunk cover all 64 LDS banks.
 //
-// LDS tiles hold 32 K-values per row (64 bytes) with no padding; the 16-byte chunk c of row r is
-// stored at slot c ^ ((r >> 1) & 3).  Measured on gfx950 (bank-conflict counters), this makes both
-// the fragment reads of v_mfma_f32_16x16x32_bf16 (row = lane % 16, chunk = lane / 16) and the
-// four-lanes-per-row staging stores conflict-free; padded 80-byte rows conflict 2-way on both.
+// Fragments are read one unit ahead of their MFMAs (a unit is one group of A fragments of one K step), reads and refill
+// loads spread between the MFMAs.  Of the three arithmetic orders below every tile shape gives the same bits,
+// so the tile is free to follow the sizes and the batch.
 //
-// Two kernels: 256 x 128 tiles of eight 64 x 64 waves with register-staged loads (small
-// contractions: fewer than 128 tiles of 256 x 256, or 64 with split-K scratch), and 256 x 256 tiles
-// of eight 128 x 64 waves whose operands are loaded straight into LDS by buffer_load ... lds,
-// double-buffered (the rest, K split into slices to fill a round when the tiles are too few: half
-// the LDS traffic per MFMA and no staging registers).
-__device__ __forceinline__ int lds_slot(int r, int c) { return r * 32 + ((c ^ ((r >> 1) & 3)) << 3); }
+//   kF32Seq  v_mfma_f32_16x16x4_f32, MFMA t of 16 K-values takes K = 4t .. 4t + 3
+//   kF32Str  the same, MFMA t takes K = t, t + 4, t + 8, t + 12 (one 16-byte read per fragment)
+//   kBf16    v_mfma_f32_16x16x32_bf16: lo hi, hi lo, hi hi of 32 K-values
+//   kBf32    v_mfma_f32_32x32x16_bf16: the same, of 16 K-values
+enum { kF32Seq, kF32Str, kBf16, kBf32 };
+constexpr int kChunk = 256;  // stages per FP32 accumulation chunk (even: a chunk starts with the first fragment buffers)
 
-struct LPB {
+struct LP {
   int M, N, K;
-  const unsigned short* A;
+  const char* A;  // strides of the operands in bytes
   long lda, sa2;
-  const unsigned short* B;
+  const char* B;
   long ldb, sb2;
   double* C;
   long scm, scn, sc2;
   double alpha, beta;
   int tiles_m, tiles_n;
-  int chunk;
-  int ktps;
-  long cslice;
-  int nb, part;  // batch levels as in LP
+  int ktps;     // stages per split-K slice (blockIdx.z); the whole K when not split
+  long cslice;  // C offset between slices (partial tiles of a split launch), 0 otherwise
+  // batch: blockIdx.y = z1 * nb + z; z1 selects operand block tab1[z1] (or z1) at strides
+  // sa1, sb1, sc1 (partial tiles of a split launch: block z1 itself)
+  int nb, part;
   const int* tab1;
   long sa1, sb1, sc1;
 };
 
-constexpr int BM2 = 256, BN2 = 128, BK2 = 32, NT2 = 512;
-typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-
-__global__ __launch_bounds__(NT2, 1) void gemm_bf16x3_kernel(LPB p) {
-  __shared__ __attribute__((aligned(16))) unsigned short As[2][2][BM2 * BK2];
-  __shared__ __attribute__((aligned(16))) unsigned short Bs[2][2][BN2 * BK2];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;  // 4 x 2 waves of 64 x 64
-  int tm, tn;
-  tile_of_lp(blockIdx.x, p.tiles_m, p.tiles_m * p.tiles_n, tm, tn);
-  const int m0 = tm * BM2, n0 = tn * BN2;
-  const int z = blockIdx.y % p.nb, z1 = blockIdx.y / p.nb;
-  const int zs = __builtin_amdgcn_readfirstlane(p.tab1 ? p.tab1[z1] : z1);  // uniform: scalar buffer descriptors
-  const unsigned short* Ab = p.A + z * p.sa2 + zs * p.sa1;
-  const unsigned short* Bb = p.B + z * p.sb2 + zs * p.sb1;
-  double* Cb = p.C + z * p.sc2 + (p.part ? z1 : zs) * p.sc1 + blockIdx.z * p.cslice;
-
-  f4 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-
-  const int kt0 = blockIdx.z * p.ktps, nkt = min((p.K + BK2 - 1) / BK2, kt0 + p.ktps);
-  u4 ra[4], rb[2];
-  // Workgroup-uniform bases (scalar registers) plus 32-bit per-lane element offsets keep the
-  // address arithmetic out of the vector register budget.
-  const unsigned short* Arow = Ab + (long)m0 * p.lda;
-  const unsigned short* Brow = Bb + (long)n0 * p.ldb;
-  const int lda = (int)p.lda, ldb = (int)p.ldb, kpad = lda / 2;  // lda == ldb for these operands
-  // A: 256 rows x 4 chunks x 2 planes = 2048 chunks (4 per thread); B: 1024 chunks (2 per thread)
-  auto load = [&](int kt) {
-    const int k0 = kt * BK2;
-#pragma unroll
-    for (int l = 0; l < 4; ++l) {
-      const int c = tid + l * NT2;
-      const int plane = c >> 10, rem = c & 1023, row = rem >> 2, kc = (rem & 3) * 8;
-      const int gk = k0 + kc;
-      u4 v = u4{0u, 0u, 0u, 0u};
-      if (m0 + row < p.M && gk < kpad)
-        v = *reinterpret_cast<const u4*>(Arow + (unsigned)(row * lda + 2 * k0 + plane * 32 + kc));
-      ra[l] = v;
-    }
-#pragma unroll
-    for (int l = 0; l < 2; ++l) {
-      const int c = tid + l * NT2;
-      const int plane = c >> 9, rem = c & 511, row = rem >> 2, kc = (rem & 3) * 8;
-      const int gk = k0 + kc;
-      u4 v = u4{0u, 0u, 0u, 0u};
-      if (n0 + row < p.N && gk < kpad)
-        v = *reinterpret_cast<const u4*>(Brow + (unsigned)(row * ldb + 2 * k0 + plane * 32 + kc));
-      rb[l] = v;
-    }
-  };
-  auto store = [&](int buf) {
-#pragma unroll
-    for (int l = 0; l < 4; ++l) {
-      const int c = tid + l * NT2;
-      const int plane = c >> 10, rem = c & 1023, row = rem >> 2, kc = (rem & 3) * 8;
-      *reinterpret_cast<u4*>(&As[buf][plane][lds_slot(row, kc >> 3)]) = ra[l];
-    }
-#pragma unroll
-    for (int l = 0; l < 2; ++l) {
-      const int c = tid + l * NT2;
-      const int plane = c >> 9, rem = c & 511, row = rem >> 2, kc = (rem & 3) * 8;
-      *reinterpret_cast<u4*>(&Bs[buf][plane][lds_slot(row, kc >> 3)]) = rb[l];
-    }
-  };
-  double* Cw = Cb + (long)(m0 + wm * 64) * p.scm + (long)(n0 + wn * 64) * p.scn;  // wave-uniform
-  const int scm = (int)p.scm, scn = (int)p.scn;
-  auto flush = [&](bool first) {
-    int lx = lane;  // opaque to the compiler: the addresses below are not hoisted out of the K loop
-    asm volatile("" : "+v"(lx));
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int lm = i * 16 + 4 * (lx >> 4) + r, ln = j * 16 + (lx & 15);
-          if (m0 + wm * 64 + lm < p.M && n0 + wn * 64 + ln < p.N) {
-            double* c = Cw + (lm * scm + ln * scn);
-            const double v = p.alpha * (double)acc[i][j][r];
-            if (first)
-              *c = (p.beta == 0.0) ? v : v + p.beta * *c;
-            else
-              *c += v;
-          }
-          acc[i][j][r] = 0.f;
-        }
-  };
-
-  const int lr = lane & 15, lg = lane >> 4;
-  if (kt0 < nkt) {
-    load(kt0);
-    store(0);
-  }
-  __syncthreads();
-  for (int kc = kt0; kc < nkt; kc += p.chunk) {
-    const int kend = min(nkt, kc + p.chunk);
-    for (int kt = kc; kt < kend; ++kt) {
-      const int cur = (kt - kt0) & 1;
-      if (kt + 1 < nkt) load(kt + 1);
-      // all A fragments stay in registers; B fragments are loaded one 16-column panel at a time
-      bf8 xa[4][2];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int off = lds_slot(wm * 64 + i * 16 + lr, lg);
-        xa[i][0] = *reinterpret_cast<const bf8*>(&As[cur][0][off]);
-        xa[i][1] = *reinterpret_cast<const bf8*>(&As[cur][1][off]);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int off = lds_slot(wn * 64 + j * 16 + lr, lg);
-        const bf8 bh = *reinterpret_cast<const bf8*>(&Bs[cur][0][off]);
-        const bf8 bl = *reinterpret_cast<const bf8*>(&Bs[cur][1][off]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[i][1], bh, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[i][0], bl, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[i][0], bh, acc[i][j], 0, 0, 0);
-        }
-      }
-      if (kt + 1 < nkt) store(cur ^ 1);
-      __syncthreads();
-    }
-    flush(kc == kt0);
-  }
-  if (kt0 >= nkt) flush(true);
-}
-
 // Buffer descriptor of a wave-uniform range (base, bytes), built from scalar registers: every
 // component goes through readfirstlane, so the buffer loads take it straight from SGPRs (left to
 // itself the compiler kept parts of it in VGPRs and wrapped each load in a waterfall loop).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const void* base, int bytes) {
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const void* base, uint32_t bytes) {
   const uintptr_t b = reinterpret_cast<uintptr_t>(base);
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
   void* ub = reinterpret_cast<void*>(((uintptr_t)hi << 32) | lo);
-  return __builtin_amdgcn_make_buffer_rsrc(ub, (short)0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc(ub, (short)0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
 }
 
-// 256 x 256 tiles, eight waves of 128 x 64 (two per SIMD, so one wave's fragment reads and barrier
-// wait overlap the other's MFMAs), v_mfma_f32_32x32x16_bf16 (4 x 2 fragments of 32 x 32 per wave).
-// Each wave stages 64 rows of one operand per K-step as whole 128-byte lines (a row's K-block holds
-// hi 32 | lo 32) with eight buffer_load_dwordx4 ... lds (lane l of an instruction writes LDS bytes
-// 16l .. 16l + 15, so lanes pick the global chunk that belongs at their swizzled slot; staged as two
-// 64-byte planes, each line was fetched by two waves and the step took 3-4 % longer); rows past M
-// or N and K-blocks past the padded row read as zero through the buffer range check.  Per K-step:
-// wait for this wave's part of the stage, barrier, issue the next stage into the other buffer, then
-// two K = 16 halves of fragment reads and 24 MFMAs.  The buffer refilled after a step's barrier was
-// read in the step before, whose fragments every wave consumed before reaching that barrier, so one
-// barrier per step suffices.  Measured at o40 v360 (ring products 14400^3, ladder 820 x 64980 x 64980, W/Z 1600 x
-// 16000 x 129600): 0.49 / 0.41 / 0.40 of the split-BF16x3 peak, against 0.37 / 0.31 / 0.29 with four
-// waves of 128 x 128 (one per SIMD); with eight waves the kernel is bound by the rate at which the
-// operand stages reach LDS (a copy of it without MFMAs takes as long), not by the matrix cores.
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef __attribute__((address_space(3))) char lds_char_t;
-typedef float f16v __attribute__((ext_vector_type(16)));
-constexpr int BM3 = 256, BN3 = 256, NT3 = 512;
+// Waits until at most N loads of this wave are in flight and its LDS reads have arrived, then for the other waves.
+template <int N>
+__device__ __forceinline__ void wait_stage() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x070 | (N & 15) | ((N >> 4) << 14));  // vmcnt(N) lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 
-__global__ __launch_bounds__(NT3, 1) void gemm_bf16x3_dma_kernel(LPB p) {
-  // [stage][operand][row][64 bf16]: a row's whole K-block (hi 32 | lo 32, one 128-byte line), its
-  // eight 16-byte chunks c at slots c ^ ((row >> 1) & 7)
-  __shared__ __attribute__((aligned(1024))) unsigned short T[2][2][256 * 64];
+typedef __attribute__((address_space(3))) void lds_void_t;
+
+// f(0), ..., f(N - 1) with compile-time arguments (the K loop's body is beyond what the unroller takes on).
+#define INLINE __attribute__((always_inline))
+template <int I>
+using Int = std::integral_constant<int, I>;
+template <class Fn, int... I>
+__device__ __forceinline__ void unrolled_(Fn f, std::integer_sequence<int, I...>) {
+  (f(Int<I>()), ...);
+}
+// of n things spread over the slots 0 .. slots - 1: those before slot x
+constexpr int upto(int x, int n, int slots) { return x <= 0 ? 0 : x >= slots ? n : x * n / slots; }
+template <int N, class Fn>
+__device__ __forceinline__ void unrolled(Fn f) {
+  unrolled_(f, std::make_integer_sequence<int, N>());
+}
+
+template <int KIND, int BM, int BN, int WM, int WN, int S>
+__global__ __launch_bounds__(WM* WN * 64, 1) void gemm_lowp_kernel(LP p) {
+  constexpr bool BF = KIND == kBf16 || KIND == kBf32;
+  constexpr int F = KIND == kBf32 ? 32 : 16;       // fragment edge
+  constexpr int NH = KIND == kBf16 ? 1 : 2;        // K steps of a stage
+  constexpr int NP = BF ? 2 : 1, NA = F * F / 64;  // 16-byte parts of a fragment, accumulator values of a lane
+  constexpr int NR1 = KIND == kF32Seq ? 4 : NP;    // LDS reads of a fragment
+  constexpr int NT1 = BF ? 3 : 4;                  // MFMAs of a fragment pair and K step
+  constexpr int NW = WM * WN, TM = BM / WM, TN = BN / WN, RI = TM / F, RJ = TN / F;
+  constexpr int IA = BM / 8, NI = (BM + BN) / 8, NPW = (NI + NW - 1) / NW, NPWMIN = NI / NW;  // 1 KB loads of a stage
+  constexpr int G = RI * NP >= 8 ? 2 : 1, GI = (RI + G - 1) / G, U = G * NH;  // groups of A fragments, units of a stage
+  static_assert(BM % (F * WM) == 0 && BN % (F * WN) == 0 && S >= 2 && NPWMIN >= 1, "tile config");
+  typedef float fa_t __attribute__((ext_vector_type(NA)));
+  __shared__ __attribute__((aligned(1024))) char T[S][(BM + BN) * 128];
+
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 2, wn = wave & 3;  // this wave's 128 x 64 block of the tile
+  const int wm = wave / WN, wn = wave % WN;
   int tm, tn;
   tile_of_grouped(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
-  const int m0 = tm * BM3, n0 = tn * BN3;
+  const int m0 = tm * BM, n0 = tn * BN;
   const int z = blockIdx.y % p.nb, z1 = blockIdx.y / p.nb;
   const int zs = __builtin_amdgcn_readfirstlane(p.tab1 ? p.tab1[z1] : z1);  // uniform: scalar buffer descriptors
-  const int lop = wave >> 2, lq = wave & 3;  // staging: operand (A, B), rows 64 lq .. 64 lq + 63
-  const bool isA = lop == 0;
-  const unsigned short* base = isA ? p.A + z * p.sa2 + zs * p.sa1 + (long)m0 * p.lda
-                                   : p.B + z * p.sb2 + zs * p.sb1 + (long)n0 * p.ldb;
-  const int ld = isA ? (int)p.lda : (int)p.ldb;  // row stride (bf16): K-blocks of [hi 32 | lo 32]
-  const int rows = min(256, isA ? p.M - m0 : p.N - n0);
-  const __amdgpu_buffer_rsrc_t rs = uniform_rsrc(base, rows * ld * 2);
-  // lane l of a load writes row l / 8 of an 8-row group, slot l % 8; the chunk that belongs there
-  // differs by 4 between even and odd groups (the swizzle's (row >> 1) & 4 term)
-  const int r8 = lane >> 3, c0 = (lane & 7) ^ (r8 >> 1);
-  const unsigned off_even = (unsigned)(((64 * lq + r8) * ld + c0 * 8) * 2);
-  const unsigned off_odd = (unsigned)(((64 * lq + r8) * ld + (c0 ^ 4) * 8) * 2);
-  auto issue = [&](int kt, int stage) {
-    unsigned oe = off_even, oo = off_odd;
-    asm volatile("" : "+v"(oe), "+v"(oo));  // two offset registers across the loop, not one per load
-    lds_char_t* dst = (lds_char_t*)(lds_void_t*)&T[stage][lop][64 * lq * 64];
+  const char* At = p.A + z * p.sa2 + zs * p.sa1 + (long)m0 * p.lda;
+  const char* Bt = p.B + z * p.sb2 + zs * p.sb1 + (long)n0 * p.ldb;
+  double* Cb = p.C + z * p.sc2 + (p.part ? z1 : zs) * p.sc1 + blockIdx.z * p.cslice;
+  const uint32_t bytes_a = (uint32_t)(min(BM, p.M - m0) * p.lda), bytes_b = (uint32_t)(min(BN, p.N - n0) * p.ldb);
+  uint32_t off[NPW];  // this lane's source in each load its wave issues: byte offset in the tile's rows
 #pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      const unsigned uni = (unsigned)((8 * g * ld + kt * 64) * 2);  // wave-uniform
-      const unsigned off = kt * 64 < ld ? ((g & 1) ? oo : oe) + uni : 0x80000000u;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + g * 1024), 16, off, 0, 0, 0);
+  for (int j = 0; j < NPW; ++j) {
+    const int g = wave + NW * j, r = 8 * g + (lane >> 3);
+    const uint32_t ck = 16 * ((lane & 7) ^ ((r >> 1) & 7));
+    off[j] = (g < IA ? (uint32_t)(r * p.lda) : (uint32_t)((r - BM) * p.ldb)) + ck;
+  }
+  // stages [kt0, kt0 + nkt) of this slice; loads past the last one have an empty range (they fetch nothing and write
+  // zeros nobody reads), so the K loop runs without branches and counts the same loads in every stage
+  const int kt0 = blockIdx.z * p.ktps, nkt = min((p.K + 31) / 32, kt0 + p.ktps) - kt0;
+  __amdgpu_buffer_rsrc_t ra, rb;
+  auto begin_stage = [&](int kt) INLINE {
+    ra = uniform_rsrc(At, kt < nkt ? bytes_a : 0u);
+    rb = uniform_rsrc(Bt, kt < nkt ? bytes_b : 0u);
+  };
+  auto issue1 = [&](int kt, int st, int j) INLINE {  // load j of this wave for stage kt
+    const int g = wave + NW * j;
+    if (NPW * NW == NI || g < NI) {
+      const uint32_t o = off[j];
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(g < IA ? ra : rb, (lds_void_t*)&T[st][g * 1024], 16, o, (kt0 + kt) * 128, 0, 0);
     }
   };
-  double* Cb = p.C + z * p.sc2 + (p.part ? z1 : zs) * p.sc1 + blockIdx.z * p.cslice;
-  f16v acc[4][2];
+
+  fa_t acc[RI][RJ];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < RI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < RJ; ++j)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-  // 32 x 32 fragment: register q of lane l holds C(8 (q / 4) + 4 (l / 32) + q % 4, l % 32)
-  auto flush = [&](bool first) {
+      for (int q = 0; q < NA; ++q) acc[i][j][q] = 0.f;
+  auto flush = [&](bool first, bool last) INLINE {
     // addresses formed here, from a lane index the compiler cannot see through: hoisted out of the
     // K loop they would hold registers across it (and spill)
     int ln = lane;
     asm volatile("" : "+v"(ln));
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < RI; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < RJ; ++j)
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          const int gm = m0 + wm * 128 + i * 32 + 8 * (q >> 2) + 4 * (ln >> 5) + (q & 3);
-          const int gn = n0 + wn * 64 + j * 32 + (ln & 31);
+        for (int q = 0; q < NA; ++q) {
+          const int fm = F == 32 ? 8 * (q >> 2) + 4 * (ln >> 5) + (q & 3) : 4 * (ln >> 4) + q;
+          const int gm = m0 + wm * TM + i * F + fm, gn = n0 + wn * TN + j * F + (ln & (F - 1));
           if (gm < p.M && gn < p.N) {
-            double* cp = Cb + (long)gm * p.scm + (long)gn * p.scn;
+            double* c = Cb + (long)gm * p.scm + (long)gn * p.scn;
             const double v = p.alpha * (double)acc[i][j][q];
             if (first)
-              *cp = (p.beta == 0.0) ? v : v + p.beta * *cp;
+              *c = (p.beta == 0.0) ? v : v + p.beta * *c;
+            else if (F == 32)
+              add_to(c, v);
             else
-              add_to(cp, v);
+              *c += v;
           }
           acc[i][j][q] = 0.f;
         }
-    if (first) __builtin_amdgcn_s_waitcnt(0xF70);  // the stores have reached L2
+    if (!last) __builtin_amdgcn_s_waitcnt(0xF70);  // the stores have reached L2
   };
-  const int kt0 = blockIdx.z * p.ktps, nkt = min((p.K + 31) / 32, kt0 + p.ktps);
-  const int fr = lane & 31, fc = lane >> 5;  // fragment row, K-chunk within a K = 16 half
-  const int sw = (fr >> 1) & 7;                // the slot swizzle of every row this lane reads
-  if (kt0 < nkt) issue(kt0, 0);
-  for (int kc = kt0; kc < nkt; kc += p.chunk) {
-    const int kend = min(nkt, kc + p.chunk);
-    for (int kt = kc; kt < kend; ++kt) {
-      const int cur = (kt - kt0) & 1;
-      __builtin_amdgcn_s_waitcnt(0xF70);  // vmcnt(0): this wave's part of stage kt has landed
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();  // every wave's has, and every wave has read stage cur ^ 1
-      asm volatile("" ::: "memory");  // (its fragments fed the MFMAs of the previous step)
-      if (kt + 1 < nkt) issue(kt + 1, cur ^ 1);
-#pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
-        // hi chunk q = 2 sub + fc at slot q ^ sw, lo chunk 4 + q at (q ^ sw) ^ 4 (sw depends on fr only)
-        const int hs = ((2 * sub + fc) ^ sw) * 8, ls = hs ^ 32;
-        bf8 xa[4][2], xb[2][2];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = (wm * 128 + i * 32 + fr) * 64;
-          xa[i][0] = *reinterpret_cast<const bf8*>(&T[cur][0][row + hs]);
-          xa[i][1] = *reinterpret_cast<const bf8*>(&T[cur][0][row + ls]);
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int row = (wn * 64 + j * 32 + fr) * 64;
-          xb[j][0] = *reinterpret_cast<const bf8*>(&T[cur][1][row + hs]);
-          xb[j][1] = *reinterpret_cast<const bf8*>(&T[cur][1][row + ls]);
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[i][1], xb[j][0], acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[i][0], xb[j][1], acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[i][0], xb[j][0], acc[i][j], 0, 0, 0);
-          }
-      }
-    }
-    flush(kc == kt0);
-  }
-  if (kt0 >= nkt) flush(true);
-}
 
-
-// The last rows of M (at most 64, the part of a 256-row tile that would be padding) against 256-column
-// tiles of B: eight waves of 64 x 32 (both 32-row fragments of one 32-column block each).  A stage
-// holds 64 A rows and 256 B rows in the layout of the eight-wave kernel (40 KB of loads instead of
-// 64 KB: each wave issues one A and four B loads), and every output element sees the MFMA sequence
-// and chunk flushes of that kernel, so the rows it computes are bit for bit the same.
-__global__ __launch_bounds__(NT3, 1) void gemm_bf16x3_dma_tail_kernel(LPB p) {
-  __shared__ __attribute__((aligned(1024))) unsigned short T[2][2][256 * 64];  // A uses rows 0..63
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  int tm, tn;
-  tile_of_grouped(blockIdx.x, 1, p.tiles_n, tm, tn);
-  const int n0 = tn * BN3;
-  const int z = blockIdx.y % p.nb, z1 = blockIdx.y / p.nb;
-  const int zs = __builtin_amdgcn_readfirstlane(p.tab1 ? p.tab1[z1] : z1);
-  const unsigned short* abase = p.A + z * p.sa2 + zs * p.sa1;
-  const unsigned short* bbase = p.B + z * p.sb2 + zs * p.sb1 + (long)n0 * p.ldb;
-  const int arows = min(64, p.M), brows = min(256, p.N - n0);
-  const __amdgpu_buffer_rsrc_t ra = uniform_rsrc(abase, arows * (int)p.lda * 2);
-  const __amdgpu_buffer_rsrc_t rb = uniform_rsrc(bbase, brows * (int)p.ldb * 2);
-  // whole 128-byte lines in the layout of the eight-wave kernel: a stage is 8 groups of 8 A rows and
-  // 32 of 8 B rows; wave w loads A group w and B groups w, w + 8, w + 16, w + 24, all of the parity
-  // of w, so one chunk choice per lane serves every load of the wave
-  const int r8 = lane >> 3, c = (lane & 7) ^ (r8 >> 1) ^ ((wave & 1) << 2);
-  const unsigned a_off = (unsigned)((r8 * (int)p.lda + c * 8) * 2), b_off = (unsigned)((r8 * (int)p.ldb + c * 8) * 2);
-  auto issue = [&](int kt, int stage) {
-    unsigned ao = a_off, bo = b_off;
-    asm volatile("" : "+v"(ao), "+v"(bo));
-    const bool have = kt * 64 < (int)p.lda;  // the K-block exists (lda == ldb)
-    {
-      const unsigned uni = (unsigned)((8 * wave * (int)p.lda + kt * 64) * 2);
-      lds_char_t* dst = (lds_char_t*)(lds_void_t*)&T[stage][0][8 * wave * 64];
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t*)dst, 16, have ? ao + uni : 0x80000000u, 0, 0, 0);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int gb = wave + 8 * j;
-      const unsigned uni = (unsigned)((8 * gb * (int)p.ldb + kt * 64) * 2);
-      lds_char_t* dst = (lds_char_t*)(lds_void_t*)&T[stage][1][8 * gb * 64];
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void_t*)dst, 16, have ? bo + uni : 0x80000000u, 0, 0, 0);
+  // fragments: rows of the lane at l128 within a fragment's rows, chunk c at (c ^ sw) * 16
+  const int fr = lane & (F - 1), fg = lane / F, sw = (fr >> 1) & 7;
+  f4 fa[2][GI][NP], fb[2][RJ][NP];
+  auto read_part = [&](const char* row, int h, int k, f4* x) INLINE {
+    if constexpr (KIND == kF32Seq) {
+      x[0][k] = *reinterpret_cast<const float*>(row + (((4 * h + k) ^ sw) << 4) + 4 * fg);
+    } else {
+      const int c = KIND == kF32Str ? 4 * h + fg : KIND == kBf16 ? 4 * k + fg : 4 * k + 2 * h + fg;
+      x[k] = *reinterpret_cast<const f4*>(row + ((c ^ sw) << 4));
     }
   };
-  double* Cb = p.C + z * p.sc2 + (p.part ? z1 : zs) * p.sc1 + blockIdx.z * p.cslice;
-  f16v acc[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int q = 0; q < 16; ++q) acc[i][q] = 0.f;
-  auto flush = [&](bool first) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int gm = i * 32 + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
-        const int gn = n0 + wave * 32 + (lane & 31);
-        if (gm < p.M && gn < p.N) {
-          double* cp = Cb + (long)gm * p.scm + (long)gn * p.scn;
-          const double v = p.alpha * (double)acc[i][q];
-          if (first)
-            *cp = (p.beta == 0.0) ? v : v + p.beta * *cp;
-          else
-            add_to(cp, v);
-        }
-        acc[i][q] = 0.f;
-      }
-    if (first) __builtin_amdgcn_s_waitcnt(0xF70);  // the stores have reached L2
-  };
-  const int kt0 = blockIdx.z * p.ktps, nkt = min((p.K + 31) / 32, kt0 + p.ktps);
-  const int fr = lane & 31, fc = lane >> 5;
-  const int sw = (fr >> 1) & 7;  // the slot swizzle of every row this lane reads
-  if (kt0 < nkt) issue(kt0, 0);
-  for (int kc = kt0; kc < nkt; kc += p.chunk) {
-    const int kend = min(nkt, kc + p.chunk);
-    for (int kt = kc; kt < kend; ++kt) {
-      const int cur = (kt - kt0) & 1;
-      __builtin_amdgcn_s_waitcnt(0xF70);  // vmcnt(0): this wave's part of stage kt has landed
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();  // every wave's has, and every wave has read stage cur ^ 1
-      asm volatile("" ::: "memory");
-      if (kt + 1 < nkt) issue(kt + 1, cur ^ 1);
-#pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
-        const int hs = ((2 * sub + fc) ^ sw) * 8, ls = hs ^ 32;  // hi and lo chunk slots
-        bf8 xa[2][2], xb[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const int row = (i * 32 + fr) * 64;
-          xa[i][0] = *reinterpret_cast<const bf8*>(&T[cur][0][row + hs]);
-          xa[i][1] = *reinterpret_cast<const bf8*>(&T[cur][0][row + ls]);
-        }
-        const int rowb = (wave * 32 + fr) * 64;
-        xb[0] = *reinterpret_cast<const bf8*>(&T[cur][1][rowb + hs]);
-        xb[1] = *reinterpret_cast<const bf8*>(&T[cur][1][rowb + ls]);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[i][1], xb[0], acc[i], 0, 0, 0);
-          acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[i][0], xb[1], acc[i], 0, 0, 0);
-          acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[i][0], xb[0], acc[i], 0, 0, 0);
-        }
-      }
-    }
-    flush(kc == kt0);
-  }
-  if (kt0 >= nkt) flush(true);
-}
-
-
-// FP32, direct to LDS: 256 x 256 tiles, eight waves of 128 x 64 (two per SIMD), v_mfma_f32_16x16x4_f32.
-// A stage holds 16 K-values of every tile row (64 bytes; the 16-byte chunk c of row r at slot
-// c ^ ((r >> 1) & 3), the 64-byte-row layout of the FP64 direct-to-LDS kernel), four stages (three in flight),
-// one barrier per stage after a per-wave vmcnt wait.  Each wave loads 64 rows of one operand per
-// stage (four 1 KB buffer_load ... lds; rows past M or N read as zero through the buffer range
-// check, the K padding of the shadows is zero).  Each fragment read returns four K-values of a row
-// and feeds four MFMAs: lane group g = l / 16 supplies K = 4g + t to MFMA t, identically for A and B.
-// FP32 accumulation within K chunks, FP64 across them; split-K slices as in the other kernels.
-constexpr int BM4 = 256, BN4 = 256, NT4 = 512, S4 = 4;
-
-__global__ __launch_bounds__(NT4, 1) void gemm_f32_dma_kernel(LP p) {
-  __shared__ __attribute__((aligned(1024))) float T[S4][(BM4 + BN4) * 16];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 2, wn = wave & 3;  // this wave's 128 x 64 block of the tile
-  int tm, tn;
-  tile_of_grouped(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
-  const int m0 = tm * BM4, n0 = tn * BN4;
-  const int z = blockIdx.y % p.nb, z1 = blockIdx.y / p.nb;
-  const int zs = __builtin_amdgcn_readfirstlane(p.tab1 ? p.tab1[z1] : z1);  // uniform: scalar buffer descriptors
-  // staging: waves 0-3 load rows 64 w .. 64 w + 63 of the A tile, waves 4-7 the same of the B tile
-  const bool isA = wave < 4;
-  const int r0 = 64 * (wave & 3);
-  const float* base = isA ? p.A + z * p.sa2 + zs * p.sa1 + (long)(m0 + r0) * p.lda
-                          : p.B + z * p.sb2 + zs * p.sb1 + (long)(n0 + r0) * p.ldb;
-  const int ld = isA ? (int)p.lda : (int)p.ldb;  // row stride (floats), a multiple of 32 covering K
-  const int rows = max(0, min(64, (isA ? p.M - m0 : p.N - n0) - r0));
-  const __amdgpu_buffer_rsrc_t rs = uniform_rsrc(base, rows * ld * 4);
-  const int lr = lane >> 2, c = (lane & 3) ^ ((lr >> 1) & 3);  // row in a 16-row block, chunk loaded
-  const int lrow0 = (isA ? 0 : BM4) + r0;                         // first LDS row of this wave's rows
-  auto issue = [&](int ks, int stage) {
-    lds_char_t* dst = (lds_char_t*)(lds_void_t*)&T[stage][lrow0 * 16];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const unsigned off = (unsigned)(((g * 16 + lr) * ld + ks * 16 + c * 4) * 4);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + g * 1024), 16, off, 0, 0, 0);
+  // read k of the fragments of unit u (buffers of parity P): the B fragments of a new K step, then the A fragments
+  constexpr int RB = RJ * NR1, NR = RB + GI * NR1;
+  auto read1 = [&](const char* Ts, auto P, auto u, auto kc) INLINE {
+    constexpr int h = u() / G, g = u() % G, k = kc();
+    if constexpr (k < RB) {
+      if constexpr (g == 0)
+        read_part(Ts + (BM + wn * TN + (k / NR1) * F + fr) * 128, h, k % NR1, fb[(P() * NH + h) & 1][k / NR1]);
+    } else {
+      constexpr int i = (k - RB) / NR1;
+      if constexpr (g * GI + i < RI)
+        read_part(Ts + (wm * TM + (g * GI + i) * F + fr) * 128, h, k % NR1, fa[(P() * U + u()) & 1][i]);
     }
   };
-  double* Cb = p.C + z * p.sc2 + (p.part ? z1 : zs) * p.sc1 + blockIdx.z * p.cslice;
-  f4 acc[8][4];
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-  auto flush = [&](bool first) {
-    // addresses formed here from an opaque lane index (hoisted, they would spill)
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int gm = m0 + wm * 128 + i * 16 + 4 * (ln >> 4) + r;
-          const int gn = n0 + wn * 64 + j * 16 + (ln & 15);
-          if (gm < p.M && gn < p.N) {
-            double* cp = Cb + (long)gm * p.scm + (long)gn * p.scn;
-            const double v = p.alpha * (double)acc[i][j][r];
-            if (first)
-              *cp = (p.beta == 0.0) ? v : v + p.beta * *cp;
-            else
-              *cp += v;
-          }
-          acc[i][j][r] = 0.f;
-        }
-  };
-  // stages of 16 K-values [ks0, nks) of this split-K slice (ktps and chunk count 32-wide K-tiles)
-  const int ks0 = blockIdx.z * 2 * p.ktps, nks = min((p.K + 15) / 16, ks0 + 2 * p.ktps);
-  const int chunk = 2 * p.chunk;
-  const int l16 = lane & 15, q = lane >> 4;
-#pragma unroll
-  for (int st = 0; st < S4 - 1; ++st)
-    if (ks0 + st < nks) issue(ks0 + st, st);
-  for (int kc = ks0; kc < nks; kc += chunk) {
-    const int kend = min(nks, kc + chunk);
-    for (int ks = kc; ks < kend; ++ks) {
-      const int st = (ks - ks0) % S4;
-      // stage ks has landed once no more than the later stages' loads (four per stage) of this
-      // wave are in flight
-      const int ahead = min(S4 - 2, nks - 1 - ks);
-      if (ahead >= 2)
-        __builtin_amdgcn_s_waitcnt(0xF78);  // vmcnt(8)
-      else if (ahead == 1)
-        __builtin_amdgcn_s_waitcnt(0xF74);  // vmcnt(4)
+  auto product = [&](const f4* a, const f4* b, int t, fa_t& c) INLINE {
+    if constexpr (BF) {
+      const bf8 x = __builtin_bit_cast(bf8, a[t == 0 ? 1 : 0]), y = __builtin_bit_cast(bf8, b[t == 1 ? 1 : 0]);
+      if constexpr (F == 32)
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, c, 0, 0, 0);
       else
-        __builtin_amdgcn_s_waitcnt(0xF70);  // vmcnt(0)
-      __builtin_amdgcn_s_barrier();
-      const float* Ts = T[st];
-      f4 fa[8], fb[4];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int r = wm * 128 + i * 16 + l16;
-        fa[i] = *reinterpret_cast<const f4*>(Ts + r * 16 + 4 * (q ^ ((r >> 1) & 3)));
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int r = BM4 + wn * 64 + j * 16 + l16;
-        fb[j] = *reinterpret_cast<const f4*>(Ts + r * 16 + 4 * (q ^ ((r >> 1) & 3)));
-      }
-      // the stage refilled now was last read in the previous iteration, before this barrier
-      if (ks + S4 - 1 < nks) issue(ks + S4 - 1, (ks - ks0 + S4 - 1) % S4);
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][t], fb[j][t], acc[i][j], 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, c, 0, 0, 0);
+    } else {
+      c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0][t], b[0][t], c, 0, 0, 0);
     }
-    flush(kc == ks0);
-  }
-  if (ks0 >= nks) flush(true);
-}
+  };
 
-// The last rows of M (at most 64) for the FP32 kernel above: 64 x 256 tiles, eight waves of 64 x 32
-// (four 16-row by two 16-column fragments each), stages of 64 A rows and 256 B rows (20 KB; each
-// wave loads two 16-row blocks of B, waves 0-3 also one of A), four stages.  Every output element
-// sees the MFMA sequence and chunk flushes of that kernel, so its rows are bit for bit the same.
-__global__ __launch_bounds__(NT4, 1) void gemm_f32_dma_tail_kernel(LP p) {
-  __shared__ __attribute__((aligned(1024))) float T[S4][(64 + BN4) * 16];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  int tm, tn;
-  tile_of_grouped(blockIdx.x, 1, p.tiles_n, tm, tn);
-  const int n0 = tn * BN4;
-  const int z = blockIdx.y % p.nb, z1 = blockIdx.y / p.nb;
-  const int zs = __builtin_amdgcn_readfirstlane(p.tab1 ? p.tab1[z1] : z1);
-  const float* abase = p.A + z * p.sa2 + zs * p.sa1;
-  const float* bbase = p.B + z * p.sb2 + zs * p.sb1 + (long)n0 * p.ldb;
-  const __amdgpu_buffer_rsrc_t ra = uniform_rsrc(abase, min(64, p.M) * (int)p.lda * 4);
-  const __amdgpu_buffer_rsrc_t rb = uniform_rsrc(bbase, min(256, p.N - n0) * (int)p.ldb * 4);
-  const int lr = lane >> 2, c = (lane & 3) ^ ((lr >> 1) & 3);  // row in a 16-row block, chunk loaded
-  const bool loadsA = wave < 4;                                   // three loads per stage, else two
-  auto issue = [&](int ks, int stage) {
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      const int blk = 2 * wave + g;
-      const unsigned off = (unsigned)(((blk * 16 + lr) * (int)p.ldb + ks * 16 + c * 4) * 4);
-      lds_char_t* dst = (lds_char_t*)(lds_void_t*)&T[stage][(64 + blk * 16) * 16];
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void_t*)dst, 16, off, 0, 0, 0);
-    }
-    if (loadsA) {
-      const unsigned off = (unsigned)(((wave * 16 + lr) * (int)p.lda + ks * 16 + c * 4) * 4);
-      lds_char_t* dst = (lds_char_t*)(lds_void_t*)&T[stage][(wave * 16) * 16];
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t*)dst, 16, off, 0, 0, 0);
-    }
+  unrolled<S>([&](auto st) INLINE {
+    begin_stage(st());
+    unrolled<NPW>([&](auto j) INLINE { issue1(st(), st(), j()); });
+  });
+  wait_stage<(S - 1) * NPWMIN>();
+  unrolled<NR>([&](auto k) INLINE { read1(T[0], Int<0>(), Int<0>(), k); });
+  // one stage, in slot st; P: parity of the fragment buffers its first unit uses (those of the next stage's follow)
+  auto stage = [&](int kt, int st, int st1, auto P) INLINE {
+    unrolled<U>([&](auto uc) INLINE {
+      constexpr int u = uc(), h = u / G, g = u % G, NM = NT1 * GI * RJ;
+      constexpr int MR = BF ? NM : (NM + 1) / 2, ML = BF ? 0 : MR;  // reads go in slots 0 .. MR - 1, loads from ML on
+      constexpr bool last = u + 1 == U;
+      const char* Tn = T[last ? st1 : st];
+      if constexpr (last) {
+        // stage kt + 1 has landed once no more than the later stages' loads of this wave are in flight; past the
+        // barrier it has for every wave, and every wave holds the last fragments of stage kt in registers,
+        // so its slot is refilled from here on
+        wait_stage<(S - 2) * NPWMIN>();
+        begin_stage(kt + S);
+      }
+      unrolled<NM>([&](auto mc) INLINE {
+        constexpr int m = mc(), t = m / (GI * RJ), i = m / RJ % GI, j = m % RJ;
+        if constexpr (g * GI + i < RI)
+          product(fa[(P() * U + u) & 1][i], fb[(P() * NH + h) & 1][j], t, acc[g * GI + i][j]);
+        constexpr int k0 = upto(m, NR, MR), k1 = upto(m + 1, NR, MR);
+        constexpr int l0 = upto(m - ML, NPW, NM - ML), l1 = upto(m + 1 - ML, NPW, NM - ML);
+        unrolled<k1 - k0>([&](auto k) INLINE {
+          read1(Tn, Int<last ? P() ^ 1 : P()>(), Int<last ? 0 : u + 1>(), Int<k0 + k()>());
+        });
+        if constexpr (last) unrolled<l1 - l0>([&](auto k) INLINE { issue1(kt + S, st, l0 + k()); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
   };
-  double* Cb = p.C + z * p.sc2 + (p.part ? z1 : zs) * p.sc1 + blockIdx.z * p.cslice;
-  f4 acc[4][2];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-  auto flush = [&](bool first) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int gm = i * 16 + 4 * (lane >> 4) + r;
-          const int gn = n0 + wave * 32 + j * 16 + (lane & 15);
-          if (gm < p.M && gn < p.N) {
-            double* cp = Cb + (long)gm * p.scm + (long)gn * p.scn;
-            const double v = p.alpha * (double)acc[i][j][r];
-            if (first)
-              *cp = (p.beta == 0.0) ? v : v + p.beta * *cp;
-            else
-              *cp += v;
-          }
-          acc[i][j][r] = 0.f;
-        }
-  };
-  const int ks0 = blockIdx.z * 2 * p.ktps, nks = min((p.K + 15) / 16, ks0 + 2 * p.ktps);
-  const int chunk = 2 * p.chunk;
-  const int l16 = lane & 15, q = lane >> 4;
-#pragma unroll
-  for (int st = 0; st < S4 - 1; ++st)
-    if (ks0 + st < nks) issue(ks0 + st, st);
-  for (int kc = ks0; kc < nks; kc += chunk) {
-    const int kend = min(nks, kc + chunk);
-    for (int ks = kc; ks < kend; ++ks) {
-      const int st = (ks - ks0) % S4;
-      // stage ks has landed once no more than the later stages' loads of this wave are in flight
-      const int ahead = min(S4 - 2, nks - 1 - ks);
-      if (loadsA) {
-        if (ahead >= 2)
-          __builtin_amdgcn_s_waitcnt(0xF76);  // vmcnt(6)
-        else if (ahead == 1)
-          __builtin_amdgcn_s_waitcnt(0xF73);  // vmcnt(3)
-        else
-          __builtin_amdgcn_s_waitcnt(0xF70);  // vmcnt(0)
-      } else {
-        if (ahead >= 2)
-          __builtin_amdgcn_s_waitcnt(0xF74);  // vmcnt(4)
-        else if (ahead == 1)
-          __builtin_amdgcn_s_waitcnt(0xF72);  // vmcnt(2)
-        else
-          __builtin_amdgcn_s_waitcnt(0xF70);  // vmcnt(0)
-      }
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      const float* Ts = T[st];
-      f4 fa[4], fb[2];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = i * 16 + l16;
-        fa[i] = *reinterpret_cast<const f4*>(Ts + r * 16 + 4 * (q ^ ((r >> 1) & 3)));
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int r = 64 + wave * 32 + j * 16 + l16;
-        fb[j] = *reinterpret_cast<const f4*>(Ts + r * 16 + 4 * (q ^ ((r >> 1) & 3)));
-      }
-      // the stage refilled now was last read in the previous iteration, before this barrier
-      if (ks + S4 - 1 < nks) issue(ks + S4 - 1, (ks - ks0 + S4 - 1) % S4);
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][t], fb[j][t], acc[i][j], 0, 0, 0);
+  for (int kc = 0, st = 0; kc < nkt; kc += kChunk) {
+    const int kend = min(nkt, kc + kChunk);
+    auto next = [](int x) { return x + 1 == S ? 0 : x + 1; };
+    int kt = kc;
+    for (; kt < kend; ++kt) {
+      int st1 = next(st);
+      stage(kt, st, st1, Int<0>());
+      st = st1;
+      if (++kt == kend) break;
+      st1 = next(st);
+      stage(kt, st, st1, Int<1>());
+      st = st1;
     }
-    flush(kc == ks0);
+    flush(kc == 0, kend == nkt);
   }
-  if (ks0 >= nks) flush(true);
+  if (nkt <= 0) flush(true, true);
+  __builtin_amdgcn_s_waitcnt(0xF70);  // no load may reach LDS after the workgroup has left
 }
 
 // C_z(m,n) = beta * C_z(m,n) + sum_s part[s][z][m][n], summed in slice order.
@@ -1096,6 +527,35 @@ SplitPlan plan_split(const GemmLP& g, long tiles, int nkt) {
   sp.split = (nkt + sp.ktps - 1) / sp.ktps;
   return sp;
 }
+
+// Tile shapes.  A launch of c = ceil(workgroups / 256) tiles per CU and k stages is taken as f + k max(t1, c ts) + c e:
+// t1 is the stage of a workgroup with a CU to itself (load and LDS latency), ts that of one among many
+// (MFMA and load rate), e the store of a tile; us, fitted (6 % rms) to 50 contractions of o4 v36 to o40 v130 systems, over
+// which the choice comes within 1 % of the best shape in the mean.  All shapes of an order give the same bits.
+// Measured there against register-staged 256 x 128 / 128 x 128 tiles (kBf16, kF32Seq) and 256 x 256 direct-to-LDS
+// ones: 2.2 and 2.05 times as fast, 1.2 (kBf32) and 1.4 (kF32Str).  Split-BF16x3, o8 v72: ladder 36 x 2628 x 2628 108 -> 22 us,
+// rings 576^3 30 -> 8.8 us; o20 v180: ladder 210 x 16290 x 16290 910 -> 643 us, rings 3600^3 460 -> 423 us.  FP32,
+// o17 v131: ladder 153 x 8646 x 8646 1.42 -> 0.62 ms, rings 2227^3 535 -> 360 us.
+struct Shape {
+  int kind, bm, bn, threads;
+  double t1, ts, f, e;
+  void (*kernel)(LP);
+};
+#define SHAPE(KIND, BM, BN, WM, WN, S, T1, TS, F, E) \
+  { KIND, BM, BN, WM * WN * 64, T1, TS, F, E, gemm_lowp_kernel<KIND, BM, BN, WM, WN, S> }
+const Shape kShapes[] = {
+    SHAPE(kBf16, 64, 64, 2, 2, 3, 0.219, 0.238, 4.0, 0.0),    SHAPE(kBf16, 64, 64, 2, 2, 4, 0.169, 0.236, 3.6, 0.54),
+    SHAPE(kBf16, 96, 96, 2, 2, 3, 0.415, 0.374, 3.9, 1.28),   SHAPE(kBf16, 128, 64, 2, 2, 3, 0.373, 0.365, 4.4, 0.63),
+    SHAPE(kBf16, 128, 128, 2, 2, 4, 0.043, 0.565, 1.6, 5.44), SHAPE(kBf16, 256, 128, 4, 2, 3, 0.910, 0.867, 6.9, 0.0),
+    SHAPE(kBf32, 64, 128, 2, 2, 3, 1.0, 0.386, 0.0, 1.57),    SHAPE(kBf32, 128, 256, 2, 4, 3, 1.240, 1.042, 0.0, 8.87),
+    SHAPE(kBf32, 192, 192, 2, 2, 3, 1.239, 1.156, 0.0, 11.8), SHAPE(kBf32, 256, 128, 4, 2, 3, 1.231, 1.025, 0.0, 8.55),
+    SHAPE(kBf32, 192, 256, 2, 4, 2, 0.339, 1.563, 0.0, 9.75), SHAPE(kBf32, 256, 256, 2, 4, 2, 0.798, 1.849, 0.0, 15.0),
+    SHAPE(kF32Seq, 64, 64, 2, 2, 3, 0.706, 0.561, 3.1, 1.17), SHAPE(kF32Seq, 64, 64, 2, 2, 4, 0.691, 0.583, 2.7, 1.72),
+    SHAPE(kF32Seq, 96, 96, 2, 2, 3, 1.526, 1.243, 1.1, 4.38), SHAPE(kF32Seq, 128, 64, 2, 2, 3, 1.204, 1.031, 2.3, 2.89),
+    SHAPE(kF32Str, 64, 64, 2, 2, 3, 0.706, 0.499, 6.3, 0.78), SHAPE(kF32Str, 128, 256, 2, 4, 3, 3.731, 3.665, 1.0, 8.94),
+    SHAPE(kF32Str, 224, 192, 2, 4, 3, 4.9, 4.938, 1.0, 10.2), SHAPE(kF32Str, 256, 256, 2, 4, 2, 7.1, 7.135, 5.9, 10.4),
+};
+#undef SHAPE
 
 }  // namespace
 
@@ -1135,56 +595,89 @@ hipError_t gemm_lowp(const GemmLP& g, hipStream_t s) {
   if (g.K <= 0 || (long)g.nb * g.nb1 > 65535 || (g.prec != kPrecFP32 && g.prec != kPrecBF16x3))
     return hipErrorInvalidValue;
   const bool bf = (g.prec == kPrecBF16x3);
-  // bf16: interleaved rows; the row strides are equal multiples of 64 and cover K
-  if (bf && (((g.lda | g.ldb | g.sa2 | g.sb2 | g.sa1 | g.sb1) & 63) || g.lda != g.ldb || g.lda / 2 < g.K))
+  // whole stages: rows of K padded to 32 values (128 bytes), 16-byte aligned (bf16: interleaved K-blocks)
+  const int nkt = (g.K + 31) / 32;
+  const long unit = bf ? 64 : 32, el = bf ? 2 : 4, row = unit * nkt;
+  auto al16 = [](const void* x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
+  if (((g.lda | g.ldb | g.sa2 | g.sb2 | g.sa1 | g.sb1) & (unit - 1)) || g.lda < row || g.ldb < row || !al16(g.A) || !al16(g.B))
     return hipErrorInvalidValue;
   const long nz1 = g.tab1 ? g.tab1_max + 1 : g.nb1;  // operand blocks of the outer batch level
   if (bounds_checking()) {
-    // bf16: every staged chunk stays inside its padded row
-    const long la = (long)(g.M - 1) * g.lda + (bf ? g.lda - 1 : g.K - 1) + (long)(g.nb - 1) * g.sa2 + (nz1 - 1) * g.sa1;
-    const long lb = (long)(g.N - 1) * g.ldb + (bf ? g.ldb - 1 : g.K - 1) + (long)(g.nb - 1) * g.sb2 + (nz1 - 1) * g.sb1;
+    const long la = (long)(g.M - 1) * g.lda + row - 1 + (long)(g.nb - 1) * g.sa2 + (nz1 - 1) * g.sa1;
+    const long lb = (long)(g.N - 1) * g.ldb + row - 1 + (long)(g.nb - 1) * g.sb2 + (nz1 - 1) * g.sb1;
     long lo = 0, hi = 0;
     const long dc[4] = {(long)(g.M - 1) * g.scm, (long)(g.N - 1) * g.scn, (long)(g.nb - 1) * g.sc2, (nz1 - 1) * g.sc1};
     for (long d : dc) {
       if (d < 0) lo += d; else hi += d;
     }
-    const size_t el = bf ? 2 : 4;
     if (!(range_ok(g.A, 0, la, el, "lowp A") && range_ok(g.B, 0, lb, el, "lowp B") && range_ok(g.C, lo, hi, 8, "lowp C") &&
           (!g.ws || range_ok(g.ws, 0, g.ws_elems - 1, 8, "lowp split-K scratch"))))
       return hipErrorInvalidValue;
   }
   if (dry_run()) return hipSuccess;
-  // 8192 of K per FP32 chunk in both modes (2048 for FP32 measured 15 % slower at o40 v360 for no
-  // change in the refined solves; the flush of the FP64 tile is the cost)
-  const int chunk = g.chunk_ktiles > 0 ? g.chunk_ktiles : 256;
-  const int nbz = g.nb * g.nb1;                       // grid.y
-  const int nbd = g.per_block ? g.nb : nbz;            // the batch the kernel and split choices see
-  // the batch and output fields shared by both parameter blocks
-  auto common = [&](auto& p) {
-    p.M = g.M;
-    p.N = g.N;
-    p.K = g.K;
-    p.lda = g.lda;
-    p.sa2 = g.sa2;
-    p.ldb = g.ldb;
-    p.sb2 = g.sb2;
-    p.C = g.C;
-    p.scm = g.scm;
-    p.scn = g.scn;
-    p.sc2 = g.sc2;
-    p.alpha = g.alpha;
-    p.beta = g.beta;
-    p.chunk = chunk;
-    p.cslice = 0;
-    p.nb = g.nb;
-    p.part = 0;
-    p.tab1 = g.tab1;
-    p.sa1 = g.sa1;
-    p.sb1 = g.sb1;
-    p.sc1 = g.sc1;
-  };
-  // split launches write partial tiles [split][nb1][nb][M][N] into the scratch
-  auto to_partials = [&](auto& p) {
+  const int nbz = g.nb * g.nb1;              // grid.y
+  const int nbd = g.per_block ? g.nb : nbz;  // the batch the order and the slices are chosen for
+  const int mdec = g.m_dec > 0 ? g.m_dec : g.M;
+  // The order and the slices, which the bits of a result depend on, follow from the shape of one state alone: the wide
+  // orders (32 x 32 products, one read per FP32 fragment) from half a round of 256 x 256 tiles on, or a quarter with
+  // scratch, K cut so that all slices fill one round; the others in slices of at least 512.
+  const long t2 = (long)((mdec + 255) / 256) * ((g.N + 255) / 256) * nbd;
+  int kind = bf ? kBf16 : kF32Seq, ktps = nkt;
+  if (t2 >= 128) {
+    kind = bf ? kBf32 : kF32Str;
+  } else {
+    const long outs = (long)g.M * g.N * g.nb * g.nb1;
+    const long n = (g.ws && t2 >= 64) ? std::min<long>({256 / t2, (long)nkt / 16, g.ws_elems / std::max<long>(outs, 1)}) : 0;
+    if (n >= 2) {
+      kind = bf ? kBf32 : kF32Str;
+      ktps = (int)((nkt + n - 1) / n);
+    } else {
+      const long bm = bf ? 256 : 128;
+      ktps = plan_split(g, ((g.M + bm - 1) / bm) * ((g.N + 127) / 128) * nbd, nkt).ktps;
+    }
+  }
+  const int split = (nkt + ktps - 1) / ktps;
+  const Shape* best = nullptr;
+  double best_us = 0.0;
+  for (const Shape& f : kShapes) {
+    // a tile's rows lie within the 4 GiB range of a buffer descriptor
+    if (f.kind != kind || std::min(f.bm, g.M) * g.lda * el >= (1L << 32) || std::min(f.bn, g.N) * g.ldb * el >= (1L << 32)) continue;
+    const long tiles = (long)((g.M + f.bm - 1) / f.bm) * ((g.N + f.bn - 1) / f.bn);
+    const double c = (double)((tiles * nbz * split + 255) / 256);
+    const double us = f.f + ktps * std::max(f.t1, c * f.ts) + c * f.e;
+    if (!best || us < best_us) {
+      best = &f;
+      best_us = us;
+    }
+  }
+  if (!best) return hipErrorInvalidValue;
+  LP p;
+  p.M = g.M;
+  p.N = g.N;
+  p.K = g.K;
+  p.A = reinterpret_cast<const char*>(g.A);
+  p.lda = g.lda * el;
+  p.sa2 = g.sa2 * el;
+  p.B = reinterpret_cast<const char*>(g.B);
+  p.ldb = g.ldb * el;
+  p.sb2 = g.sb2 * el;
+  p.C = g.C;
+  p.scm = g.scm;
+  p.scn = g.scn;
+  p.sc2 = g.sc2;
+  p.alpha = g.alpha;
+  p.beta = g.beta;
+  p.tiles_m = (g.M + best->bm - 1) / best->bm;
+  p.tiles_n = (g.N + best->bn - 1) / best->bn;
+  p.ktps = ktps;
+  p.cslice = 0;
+  p.nb = g.nb;
+  p.part = 0;
+  p.tab1 = g.tab1;
+  p.sa1 = g.sa1 * el;
+  p.sb1 = g.sb1 * el;
+  p.sc1 = g.sc1;
+  if (split > 1) {  // partial tiles [split][nb1][nb][M][N] in the scratch
     p.C = g.ws;
     p.scm = g.N;
     p.scn = 1;
@@ -1193,133 +686,13 @@ hipError_t gemm_lowp(const GemmLP& g, hipStream_t s) {
     p.cslice = (long)g.M * g.N * nbz;
     p.beta = 0.0;
     p.part = 1;
-  };
-  auto reduce = [&](int split) {
+  }
+  hipLaunchKernelGGL(best->kernel, dim3(p.tiles_m * p.tiles_n, nbz, split), dim3(best->threads), 0, s, p);
+  if (split > 1) {
     const long total = (long)g.M * g.N * nbz;
     hipLaunchKernelGGL(lowp_splitk_reduce, dim3((unsigned)std::min<long>((total + 255) / 256, 4096)), dim3(256), 0, s,
                        g.C, g.scm, g.scn, g.sc2, g.sc1, g.nb, g.tab1, g.beta, g.ws, g.M, g.N, total, split);
-  };
-  if (bf) {
-    LPB p;
-    common(p);
-    p.A = reinterpret_cast<const unsigned short*>(g.A);
-    p.B = reinterpret_cast<const unsigned short*>(g.B);
-    const int nkt = (g.K + 31) / 32;
-    // buffer descriptors cover one tile's rows: 256 * ld bf16 must stay below 2^31 bytes
-    const int mdec = g.m_dec > 0 ? g.m_dec : g.M;
-    const long t3 = (long)((mdec + BM3 - 1) / BM3) * ((g.N + BN3 - 1) / BN3) * nbd;
-    const bool dma_ok = 512L * g.lda < (1L << 31);
-    // from 128 tiles on (half a round) the eight-wave kernel beats the register-staged one even
-    // with the round partly idle; from 64 tiles with scratch, K is cut into slices so that the
-    // tiles of all slices fill one round (partial tiles summed in slice order)
-    int dsplit = 0;
-    if (dma_ok && t3 >= 128) {
-      dsplit = 1;
-    } else if (dma_ok && g.ws && t3 >= 64) {
-      const long outs = (long)g.M * g.N * g.nb * g.nb1;
-      const long n = std::min<long>({256 / t3, (long)nkt / 16, g.ws_elems / std::max<long>(outs, 1)});
-      if (n >= 2) dsplit = (int)n;
-    }
-    if (dsplit > 0) {
-      p.tiles_m = (g.M + BM3 - 1) / BM3;
-      p.tiles_n = (g.N + BN3 - 1) / BN3;
-      p.ktps = (nkt + dsplit - 1) / dsplit;
-      const int split = (nkt + p.ktps - 1) / p.ktps;
-      const int mtail = g.M % BM3;
-      if (tail_tiles_enabled() && split == 1 && mtail > 0 && mtail <= 64 && g.M > BM3) {
-        // the last, mostly padding, row tile as 64-row tail tiles of 40 KB stages (about 5/8 of a
-        // full workgroup's time) after the full row tiles, when that takes fewer rounds of 256
-        const long full = (long)(g.M / BM3) * p.tiles_n * nbz, tail = (long)p.tiles_n * nbz;
-        const double r_all = (double)((full + tail + 255) / 256);
-        const double r_split = (double)((full + 255) / 256) + 0.625 * (double)((tail + 255) / 256);
-        if (r_split < r_all) {
-          LPB pt = p;
-          p.M = g.M - mtail;
-          p.tiles_m = p.M / BM3;
-          pt.A += (long)p.M * g.lda;
-          pt.C += (long)p.M * g.scm;
-          pt.M = mtail;
-          pt.tiles_m = 1;
-          hipLaunchKernelGGL(gemm_bf16x3_dma_kernel, dim3(p.tiles_m * p.tiles_n, nbz, 1), dim3(NT3), 0, s, p);
-          hipLaunchKernelGGL(gemm_bf16x3_dma_tail_kernel, dim3(pt.tiles_n, nbz, 1), dim3(NT3), 0, s, pt);
-          return hipGetLastError();
-        }
-      }
-      if (split > 1) to_partials(p);
-      hipLaunchKernelGGL(gemm_bf16x3_dma_kernel, dim3(p.tiles_m * p.tiles_n, nbz, split), dim3(NT3), 0, s, p);
-      if (split > 1) reduce(split);
-      return hipGetLastError();
-    }
-    p.tiles_m = (g.M + BM2 - 1) / BM2;
-    p.tiles_n = (g.N + BN2 - 1) / BN2;
-    const SplitPlan sp = plan_split(g, (long)p.tiles_m * p.tiles_n * nbd, nkt);
-    p.ktps = sp.ktps;
-    if (sp.split > 1) to_partials(p);
-    hipLaunchKernelGGL(gemm_bf16x3_kernel, dim3(p.tiles_m * p.tiles_n, nbz, sp.split), dim3(NT2), 0, s, p);
-    if (sp.split > 1) reduce(sp.split);
-    return hipGetLastError();
   }
-  LP p;
-  common(p);
-  p.A = g.A;
-  p.B = g.B;
-  {
-    // the direct-to-LDS kernel for the same sizes as the split-BF16x3 one (16-byte aligned rows,
-    // zero-padded to whole K stages of 16)
-    const int mdec = g.m_dec > 0 ? g.m_dec : g.M;
-    const long t4 = (long)((mdec + BM4 - 1) / BM4) * ((g.N + BN4 - 1) / BN4) * nbd;
-    const int nkt = (g.K + 31) / 32;
-    const long k16 = (g.K + 15L) / 16 * 16;
-    auto al16 = [](const void* x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
-    const bool dma_ok = al16(g.A) && al16(g.B) && ((g.lda | g.ldb | g.sa2 | g.sb2 | g.sa1 | g.sb1) & 3) == 0 &&
-                        g.lda >= k16 && g.ldb >= k16 && 256L * std::max(g.lda, g.ldb) < (1L << 31);
-    int dsplit = 0;
-    if (dma_ok && t4 >= 128) {
-      dsplit = 1;
-    } else if (dma_ok && g.ws && t4 >= 64) {
-      const long outs = (long)g.M * g.N * g.nb * g.nb1;
-      const long n = std::min<long>({256 / t4, (long)nkt / 16, g.ws_elems / std::max<long>(outs, 1)});
-      if (n >= 2) dsplit = (int)n;
-    }
-    if (dsplit > 0) {
-      p.tiles_m = (g.M + BM4 - 1) / BM4;
-      p.tiles_n = (g.N + BN4 - 1) / BN4;
-      p.ktps = (nkt + dsplit - 1) / dsplit;
-      const int split = (nkt + p.ktps - 1) / p.ktps;
-      const int mtail = g.M % BM4;
-      // (the tail kernel's B range spans 256 rows of one buffer descriptor)
-      if (tail_tiles_enabled() && split == 1 && mtail > 0 && mtail <= 64 && g.M > BM4 && 1024L * g.ldb < (1L << 31)) {
-        // the last row tile as 64-row tail tiles, as for split-BF16x3 (20 KB stages: about 5/8 of
-        // a full workgroup's time)
-        const long full = (long)(g.M / BM4) * p.tiles_n * nbz, tail = (long)p.tiles_n * nbz;
-        const double r_all = (double)((full + tail + 255) / 256);
-        const double r_split = (double)((full + 255) / 256) + 0.625 * (double)((tail + 255) / 256);
-        if (r_split < r_all) {
-          LP pt = p;
-          p.M = g.M - mtail;
-          p.tiles_m = p.M / BM4;
-          pt.A += (long)p.M * g.lda;
-          pt.C += (long)p.M * g.scm;
-          pt.M = mtail;
-          pt.tiles_m = 1;
-          hipLaunchKernelGGL(gemm_f32_dma_kernel, dim3(p.tiles_m * p.tiles_n, nbz, 1), dim3(NT4), 0, s, p);
-          hipLaunchKernelGGL(gemm_f32_dma_tail_kernel, dim3(pt.tiles_n, nbz, 1), dim3(NT4), 0, s, pt);
-          return hipGetLastError();
-        }
-      }
-      if (split > 1) to_partials(p);
-      hipLaunchKernelGGL(gemm_f32_dma_kernel, dim3(p.tiles_m * p.tiles_n, nbz, split), dim3(NT4), 0, s, p);
-      if (split > 1) reduce(split);
-      return hipGetLastError();
-    }
-  }
-  p.tiles_m = (g.M + BM - 1) / BM;
-  p.tiles_n = (g.N + BN - 1) / BN;
-  const SplitPlan sp = plan_split(g, (long)p.tiles_m * p.tiles_n * nbd, (g.K + 31) / 32);
-  p.ktps = sp.ktps;
-  if (sp.split > 1) to_partials(p);
-  hipLaunchKernelGGL(gemm_lowp_kernel, dim3(p.tiles_m * p.tiles_n, nbz, sp.split), dim3(NT), 0, s, p);
-  if (sp.split > 1) reduce(sp.split);
   return hipGetLastError();
 }
 

@@ -126,8 +126,7 @@ hipError_t gemm_f64_ladder(const Ladder& L, hipStream_t s);
 // Low-precision contraction with FP64 result (gemm_lowp.hip):
 //   C_z(m,n) = alpha * sum_k A_z[m*lda + k] * B_z[n*ldb + k] + beta * C_z(m,n)
 // A, B are FP32 (K contiguous); prec selects FP32 MFMA or split-BF16x3 MFMA; FP32 accumulation
-// inside chunks of chunk_ktiles K-tiles (32 wide; 0 = the default of the precision: 64 for FP32,
-// 256 for split-BF16x3), FP64 accumulation across chunks.
+// inside chunks of 8192 K-values, FP64 accumulation across chunks.
 constexpr int kPrecFP64 = 0, kPrecFP32 = 1, kPrecBF16x3 = 2;
 struct GemmLP {
   int M = 0, N = 0, K = 0, nb = 1;
@@ -139,9 +138,8 @@ struct GemmLP {
   long scm = 0, scn = 1, sc2 = 0;
   double alpha = 1.0, beta = 0.0;
   int prec = kPrecFP32;
-  int chunk_ktiles = 0;
-  // BF16X3: A and B are interleaved splits (see to_lowp_2d); lda, ldb, sa2, sb2 count bf16
-  // elements (lda == ldb, multiples of 64, lda / 2 >= K)
+  // rows zero-padded to whole K-blocks of 32; BF16X3: interleaved splits (see to_lowp_2d), lda, ldb,
+  // sa2, sb2 count bf16 elements
   // Optional split-K scratch: an output with too few tiles to fill the chip has its K range cut
   // into slices (each at least 512 of K, each FP32 chunk starting at its slice's start) whose
   // FP64 partial tiles land here and are then summed in slice order (deterministic).

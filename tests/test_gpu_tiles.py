@@ -1,0 +1,60 @@
+"""Residuals at sizes around the edges of the contractions' tiles, slices and padded rows, alone and batched."""
+import numpy as np
+import pytest
+
+from gen.synth_df import make_system, random_amplitudes
+
+pytestmark = pytest.mark.gpu
+
+# FP64: a residual element is a sum of at most about 3000 products of the integrals and amplitudes, each product chain
+# rounded a few times: 3000 u = 3e-13 of the largest term, which is no larger than max|R| times ten here.
+# FP32 and split-BF16x3: as in test_gpu_lowp.py.
+REL = {"fp64": 3e-12, "fp32": 2e-6, "bf16x3": 4e-5}
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
+@pytest.mark.parametrize("mode", ["full", "packed"])
+@pytest.mark.parametrize("o,v,Q", [
+    (1, 2, 3),     # one pair, rows shorter than a padded line
+    (2, 8, 16),    # ov = one stage of K
+    (4, 16, 32),   # ov = 64: whole tiles
+    (5, 13, 17),   # ov = 65: one row past a tile; T(v) odd
+    (8, 12, 33),   # ov = 96, o^2 = 64
+    (9, 11, 40),   # ov = 99, T(v) = 66
+    (13, 15, 48),  # ov = 195: one 192-row tile and three rows
+    (16, 17, 64),  # o^2 = 256, T(o) = 136
+])
+def test_tile_edges(o, v, Q, mode, prec):
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2501_10515_amd as P
+    from oracle import cs_ccsd
+
+    from .gpu_util import dev, gpu_residual, host
+
+    S = 3
+    print(f"case o={o} v={v} Q={Q} vvvv={mode} prec={prec}", flush=True)
+    B, eps = make_system(o, v, Q, 17, sigma=0.1)
+    amps = [random_amplitudes(o, v, 500 + k, 0.05, 0.05) for k in range(S)]
+    pc = {"fp64": P.ASCC_PREC_FP64, "fp32": P.ASCC_PREC_FP32, "bf16x3": P.ASCC_PREC_BF16X3}[prec]
+    vm = P.ASCC_VVVV_FULL if mode == "full" else P.ASCC_VVVV_PACKED
+    ints = P.ascc_build_ints(dev(B), dev(eps), o, precision=pc, vvvv_mode=vm)
+    alone = [gpu_residual(P, ints, *a) for a in amps]
+    r1, r2 = cs_ccsd.residual(B, np.diag(eps), *amps[0])
+    scale = max(np.abs(r1).max(), np.abs(r2).max())
+    err = max(np.abs(alone[0][0] - r1).max(), np.abs(alone[0][1] - r2).max())
+    print(f"  max|dR| = {err:.3e}  (max|R| = {scale:.3e})", flush=True)
+    assert err <= REL[prec] * scale
+    # the tiles of a batch are chosen for all its states; its bits are those of each state alone
+    P.ascc_batch_reserve(ints, S)
+    t1, t2 = [dev(a[0]) for a in amps], [dev(a[1]) for a in amps]
+    b1, b2 = [torch.empty_like(t) for t in t1], [torch.empty_like(t) for t in t2]
+    e = torch.empty(S, dtype=torch.float64, device="cuda")
+    P.ascc_residual_batch(ints, t1, t2, b1, b2, e)
+    torch.cuda.synchronize()
+    ints.close()
+    for k in range(S):
+        assert np.array_equal(host(b1[k]), alone[k][0]) and np.array_equal(host(b2[k]), alone[k][1])
+        assert float(host(e)[k]) == alone[k][2]
