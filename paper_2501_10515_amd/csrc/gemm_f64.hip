@@ -375,7 +375,7 @@ __device__ __forceinline__ void dma_tile(const GP& p, int bid, int z2, const int
   const double* At = Ab + (long)m0 * p.sam;
   const double* Bt = Bb + (long)n0 * p.sbn;
   const int rows_a = min(BM, p.M - m0), rows_b = min(BN, p.N - n0);
-  __amdgpu_buffer_rsrc_t ra = tile_rsrc(At, rows_a, p.sam), rb = tile_rsrc(Bt, rows_b, p.sbn);
+  __amdgpu_buffer_rsrc_t ra, rb;
   const int nk1 = (p.K + KS - 1) / KS;  // stages of one product
   int k_red = 0;                         // RED: stages before the current product
   uint32_t off[NPW];
@@ -409,15 +409,17 @@ __device__ __forceinline__ void dma_tile(const GP& p, int bid, int z2, const int
       }
     }
   };
-  // before the loads of stage kt: RED: the descriptors of its product; otherwise, on the last stage of an
-  // uneven K (no stage follows it), chunks past K read as zero
+  // before the loads of stage kt (the slice ends before kend): the descriptors, of its product where several are
+  // summed; with an empty range past the slice (its loads fetch nothing and write zeros nobody reads), so that
+  // the K loop runs without branches and counts the same loads in every stage; on the last stage of an uneven
+  // K (no stage follows it) chunks past K read as zero
+  int kend = 0;
   auto begin_stage = [&](int kt) {
-    if (RED && p.nred > 1) {
-      const int r = kt / nk1;
-      k_red = r * nk1;
-      ra = tile_rsrc(At + r * p.sar, rows_a, p.sam);
-      rb = tile_rsrc(Bt + r * p.sbr, rows_b, p.sbn);
-    } else if ((kt + 1) * KS > p.K && kt * KS + ck >= p.K) {
+    const int r = RED && p.nred > 1 ? kt / nk1 : 0;
+    if (RED) k_red = r * nk1;
+    ra = tile_rsrc(At + r * p.sar, kt < kend ? rows_a : 0, p.sam);
+    rb = tile_rsrc(Bt + r * p.sbr, kt < kend ? rows_b : 0, p.sbn);
+    if (!(RED && p.nred > 1) && kt < kend && (kt + 1) * KS > p.K && kt * KS + ck >= p.K) {
 #pragma unroll
       for (int j = 0; j < NPW; ++j) off[j] = 0x80000000u;  // past the range of every descriptor
     }
@@ -473,36 +475,27 @@ __device__ __forceinline__ void dma_tile(const GP& p, int bid, int z2, const int
     const int kt0 = slice * p.it_per_split;
     const int nkt = min(RED ? nk1 * p.nred : nk1, kt0 + p.it_per_split) - kt0;
     if (slice != slice0) wait_stage<0>();  // every wave is done with the slots of the slice before
+    kend = kt0 + nkt;
 #pragma unroll
-    for (int st = 0; st < S; ++st)
-      if (st < nkt) issue(kt0 + st, st);
-    if (nkt > 0) {
-      if (S - 1 < nkt)
-        wait_stage<(S - 1) * NPWMIN>();
-      else
-        wait_stage<0>();
+    for (int st = 0; st < S; ++st) issue(kt0 + st, st);
+    wait_stage<(S - 1) * NPWMIN>();
 #pragma unroll
-      for (int k = 0; k < NR; ++k) read1(T[0], 0, k);
-      combine(0);
-    }
-    for (int kt = 0; kt < nkt; ++kt) {  // kt counts stages of this slice
-      const int st = kt % S;
-      const bool more = kt + 1 < nkt, refill = kt + S < nkt;
+    for (int k = 0; k < NR; ++k) read1(T[0], 0, k);
+    combine(0);
+    for (int kt = 0, st = 0; kt < nkt; ++kt) {  // kt counts stages of this slice, st is its slot
+      const int st1 = st + 1 == S ? 0 : st + 1;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int kk = u / G, g = u % G;
         const bool last = u + 1 == U;
-        const double* Tn = T[last ? (kt + 1) % S : st];
-        if (last && more) {
+        const double* Tn = T[last ? st1 : st];
+        if (last) {
           // stage kt + 1 has landed once no more than the later stages' loads of this wave are in
           // flight; past the barrier it has for every wave, and every wave holds the last fragments of
           // stage kt in registers, so its slot is refilled from here on
-          if (kt + S - 1 < nkt)
-            wait_stage<(S - 2) * NPWMIN>();
-          else
-            wait_stage<0>();
+          wait_stage<(S - 2) * NPWMIN>();
+          begin_stage(kt0 + kt + S);
         }
-        if (last && refill) begin_stage(kt0 + kt + S);
         // the unit's products, with a fragment read or a refill load issued behind most of them
         constexpr int NM = 2 * GI * RJ, LS = NR + 2 * NPW <= NM ? 2 : 1;
         constexpr int ML = S == 2 ? 0 : LS == 2 ? NR : NM - NPW;  // two stages: the refill is due soonest
@@ -513,13 +506,15 @@ __device__ __forceinline__ void dma_tile(const GP& p, int bid, int z2, const int
           if (g * GI + i < RI)
             acc[g * GI + i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[u & 1][i][h], fb[kk & 1][j][h],
                                                                       acc[g * GI + i][j], 0, 0, 0);
-          if (m < NR && (!last || more)) read1(Tn, last ? 0 : u + 1, m);
-          if (last && refill && m >= ML && m < ML + LS * NPW && (m - ML) % LS == 0) issue1(kt0 + kt + S, st, (m - ML) / LS);
+          if (m < NR) read1(Tn, last ? 0 : u + 1, m);
+          if (last && m >= ML && m < ML + LS * NPW && (m - ML) % LS == 0) issue1(kt0 + kt + S, st, (m - ML) / LS);
           __builtin_amdgcn_sched_barrier(0);
         }
-        if (!last || more) combine(last ? 0 : u + 1);
+        combine(last ? 0 : u + 1);
       }
+      st = st1;
     }
+    __builtin_amdgcn_s_waitcnt(0xF70);  // no load may reach LDS after the workgroup has left
     // the output addresses are formed here: hoisted out of the slice loop they would hold registers
     // across it (a lane index hidden from the optimiser keeps them in place)
     int ol = lane;
