@@ -345,13 +345,18 @@ std::vector<std::pair<float* ascc_ints::*, long>> lowp_plan(long o, long v, long
   };
 }
 
-// Bytes of the (kc|bd) temporary and of one chunk of the packed-vvvv build (freed after the build).
+// Elements of the (kc|bd) temporary or of one chunk of the (ac|bd) build (freed after the build), at most about 2 GB.  A
+// packed set needs the slabs with b >= a and computes those with b >= the chunk's first a: n chunks cost (1 + 1/n)/2 of
+// all products (6 v^5 flops with naux = 3 v, at 70 TFLOP/s) and two launches each, least near n = sqrt(time / 20 us); more
+// than 16 gain nothing (chunks that fit the last-level cache pack 20 % faster, but their products run at 52 instead of
+// 62 TFLOP/s: o18 v162 15.6 instead of 14.7 ms).
 long build_temp_elems(long o, long v, int mode, long* chunk_a) {
   const long vvv = v * v * v;
-  long ac = std::max<long>(1, std::min<long>(v, (256L << 20) / std::max<long>(vvv, 1)));  // about 2 GB
-  // a packed set needs the (ac|bd) slabs with b >= a only and computes those with b >= the chunk's
-  // first a: chunks of at most v/16 values of a keep that within about 3 % of the a <= b triangle
-  if (mode == ASCC_VVVV_PACKED) ac = std::min<long>(ac, std::max<long>(1, (v + 15) / 16));
+  long ac = std::max<long>(1, std::min<long>(v, (256L << 20) / std::max<long>(vvv, 1)));
+  if (mode == ASCC_VVVV_PACKED) {
+    const long n = std::lround(std::sqrt(6.0 * (double)vvv * v * v / 70e12 / 20e-6));
+    ac = std::min<long>(ac, (v + std::clamp<long>(n, 1, 16) - 1) / std::clamp<long>(n, 1, 16));
+  }
   if (chunk_a) *chunk_a = ac;
   const long wtmp = o * v * v * v;
   return std::max(wtmp, ac * vvv);
@@ -1252,6 +1257,11 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
     Perm4In z = pin(I->KL + ov * ldk, v * ldk, sj, ldk, sb, 1.0);
     HIPCHK(permute4(I->Lijab, d2, 0.0, &z, 1, s));
   }
+  {  // B_vv as rows [p][q] one after another (the dressed block of a residual takes its place)
+    int d[4] = {v, v, 1, (int)lq};
+    Perm4In x = pin(I->B + (o * n + o) * lq, n * lq, lq, 0, 1, 1.0);
+    HIPCHK(permute4(I->Bvv, d, 0.0, &x, 1, s));
+  }
   // G+- (and its low-precision shadow, unpacked) from a temporary [(k,c)][(b,d)] product
   const bool full = I->vvvv_mode == ASCC_VVVV_FULL;
   const long Tv = (long)v * (v + 1) / 2, vhalf = (Tv + wzl) * I->ldT;  // packed: elements of one half
@@ -1260,10 +1270,7 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
     Pool tmp_alloc = sub_pool(I->pool);
     int rc2 = dalloc(tmp_alloc, &tmp, (size_t)ov * vv);
     if (rc2) return rc2;
-    Gemm g = gemm_rm(ov, v, pad_even(Q), 1.0, I->BovT, lq, false, I->B + (o * n + o) * lq, lq, true, 0.0, tmp, vv);
-    g.sb2 = n * lq;  // batched over b
-    g.sc2 = v;
-    g.nb2 = v;
+    const Gemm g = gemm_rm(ov, vv, pad_even(Q), 1.0, I->BovT, lq, false, I->Bvv, lq, true, 0.0, tmp, vv);
     hipError_t e = mm(I, g, s);
     if (e == hipSuccess) {
       double* gp = full ? I->G : I->V + Tv * I->ldT;
@@ -1279,34 +1286,17 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
       return ASCC_E_HIP;
     }
   }
-  // V[a][b][c][d] = (ac|bd) = sum_Q B_Q,ac B_Q,bd, batched over (a, b), in chunks of a.  Both
-  // operands are rows of B: K-contiguous.  The packed halves read only the slabs
-  // with b >= a (V[a][b][d][c] = (ad|bc) is the same slab), so a packed build starts b at the
-  // chunk's first a; the full matrix needs every b.
+  // W[a][c][b][d] = (ac|bd) = sum_Q B_Q,ac B_Q,bd, rows (a, c) of a chunk of a against rows (b, d) of B_vv as one product
+  // (batched over a and b in tiles of v x v, o18 v162 reached 40 TFLOP/s: 162 of 192 rows and columns).  The packed
+  // halves read only the slabs with b >= a ((ad|bc) is in the same slab), so a packed build starts b at the chunk's first
+  // a; the full matrix needs every b.
   auto vslab = [&](int a0, int na, double* dst) -> hipError_t {
-    const int b0 = full ? 0 : a0;
-    Gemm g;
-    g.M = v;
-    g.N = v;
-    g.K = (int)pad_even(Q);
-    g.A = I->B + ((o + a0) * n + o) * lq;
-    g.sam = lq;
-    g.sak = 1;
-    g.sa1 = n * lq;
-    g.B = I->B + ((o + b0) * n + o) * lq;
-    g.sbk = 1;
-    g.sbn = lq;
-    g.sb2 = n * lq;
-    g.C = dst + (long)b0 * vv;
-    g.scm = v;
-    g.scn = 1;
-    g.sc1 = (long)v * vv;
-    g.sc2 = vv;
-    g.nb1 = na;
-    g.nb2 = v - b0;
-    return mm(I, g, s);
+    const long b0 = full ? 0 : a0, nbd = (v - b0) * v;
+    return mm(I, gemm_rm(na * (long)v, nbd, pad_even(Q), 1.0, I->Bvv + a0 * v * lq, lq, false, I->Bvv + b0 * v * lq, lq, true, 0.0,
+                         dst, nbd), s);
   };
   // in chunks of a through a temporary: scattered to the full matrix in pair order, or packed
+  const bool lowp = I->precision != ASCC_PREC_FP64;
   if (full) HIPCHK(pair_minus_rows(pair_minus(I), v, s));
   long ac = 1;
   const long elems = build_temp_elems(o, v, I->vvvv_mode, &ac);

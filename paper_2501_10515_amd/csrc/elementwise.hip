@@ -768,11 +768,12 @@ __global__ __launch_bounds__(kThreads) void update_stage3(double* t1, double* t2
 // sc: plus[p(c,d)] = f (M(c,d) + M(d,c)), minus[p(c,d)] = f (M(c,d) - M(d,c)) for c < d, and M(c,c), 0 on
 // the diagonal; columns T(v) .. ldo - 1 are zeroed.  The block of grid column x and its output row:
 //   kPackT   t+-: the pairs i <= j of t2 (f = 1/2), row p(i,j)
-//   kPackV   V+-: W[a - a0][b][.][.] of (ac|bd) for a in [a0, a1), b >= a, row p(a,b)
+//   kPackV   V+-: W[a - a0][c][b - a0][d] of (ac|bd) for a in [a0, a1), b >= a, row p(a,b)
 //   kPackG   G+-: (kc|bd) = W[k][c][b][d], row k*v + b of the rows behind V+-
 //   kPackGo  G+-: (kc|ld) = W[k][c][l][d], row ov + k*o + l of the same
-// One workgroup per block row and 32 x 32 tile pair (C <= D): both tiles are read along their rows, the
-// transposed one through LDS, and both outputs written along theirs (o20 v180: t+- 48 -> 15 us).
+// One workgroup per block row and 32 x 32 tile pair (C <= D), or all pairs of one C where the rows are many: both
+// tiles are read along their rows, the transposed one through LDS, and both outputs written along theirs (o20 v180:
+// t+- 48 -> 15 us; all pairs of one C keep the unaligned ends of 32-value pieces in one L2: V+- of o18 v162 2.2 -> 1.7 ms).
 enum { kPackT, kPackV, kPackG, kPackGo };
 struct PackP {
   double *plus, *minus;
@@ -781,7 +782,7 @@ struct PackP {
   int mode, o, v, a0;
 };
 __global__ __launch_bounds__(kThreads) void pack_halves_kernel(PackP p) {
-  __shared__ double tile[32][33];
+  __shared__ double tile[2][32][33];
   const int o = p.o, v = p.v, nblk = (v + 31) / 32;
   const long vv = (long)v * v, Tv = (long)v * (v + 1) / 2, y = blockIdx.x;
   long base, sc = v, row;
@@ -797,7 +798,8 @@ __global__ __launch_bounds__(kThreads) void pack_halves_kernel(PackP p) {
   } else if (p.mode == kPackV) {
     const int a = p.a0 + (int)(y / v), b = (int)(y % v);
     if (b < a) return;
-    base = y * vv;
+    sc = (long)(v - p.a0) * v;
+    base = y / v * v * sc + (long)(b - p.a0) * v;
     row = pidx(a, b, v);
   } else if (p.mode == kPackG) {
     base = y / v * v * vv + y % v * v;
@@ -813,28 +815,36 @@ __global__ __launch_bounds__(kThreads) void pack_halves_kernel(PackP p) {
   double* minus = p.minus + row * p.ldo;
   if (blockIdx.y == 0)
     for (long x = Tv + threadIdx.x; x < p.ldo; x += kThreads) plus[x] = minus[x] = 0.0;
-  int C = 0, rem = blockIdx.y;  // tile pair (C, D), C <= D
-  while (rem >= nblk - C) {
-    rem -= nblk - C;
-    ++C;
+  int C = blockIdx.y, D0 = C, D1 = nblk;  // tile pairs (C, D), D0 <= D < D1
+  if (p.mode == kPackT) {
+    int rem = blockIdx.y;
+    for (C = 0; rem >= nblk - C; ++C) rem -= nblk - C;
+    D0 = C + rem;
+    D1 = D0 + 1;
   }
-  const int c0 = 32 * C, d0 = 32 * (C + rem);
+  const int c0 = 32 * C;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int d = d0 + ty + 8 * k, c = c0 + tx;
-    if (d < v && c < v) tile[ty + 8 * k][tx] = M[d * sc + c];
-  }
-  __syncthreads();
   const double f = p.mode == kPackT ? 0.5 : 1.0;
+  for (int D = D0; D < D1; ++D) {
+    const int d0 = 32 * D;
+    double(*t)[33] = tile[D & 1];  // the other one may still be read
+    double x[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int c = c0 + ty + 8 * k, d = d0 + tx;
-    if (c > d || d >= v) continue;
-    const double a = M[c * sc + d], b = tile[tx][ty + 8 * k];
-    const long q = pidx(c, d, v);
-    plus[q] = (c == d) ? a : f * (a + b);
-    minus[q] = (c == d) ? 0.0 : f * (a - b);
+    for (int k = 0; k < 4; ++k) {
+      const int r = ty + 8 * k;
+      if (d0 + r < v && c0 + tx < v) t[r][tx] = M[(d0 + r) * sc + c0 + tx];
+      x[k] = (c0 + r < v && d0 + tx < v) ? M[(c0 + r) * sc + d0 + tx] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int c = c0 + ty + 8 * k, d = d0 + tx;
+      if (c > d || d >= v) continue;
+      const double a = x[k], b = t[tx][ty + 8 * k];
+      const long q = pidx(c, d, v);
+      plus[q] = (c == d) ? a : f * (a + b);
+      minus[q] = (c == d) ? 0.0 : f * (a - b);
+    }
   }
 }
 
@@ -1082,19 +1092,20 @@ __global__ __launch_bounds__(kThreads) void pair_minus_rows_kernel(int* __restri
   for (int b = a; b < v; ++b) pm[pidx(a, b, v)] = (int)pair_order(b, a, v);
 }
 
-// Full (ac|bd) in pair order, rows at stride ldv: V[R(a,b)][R(c,d)] = W[a - a0][b][c][d] for a in [a0, a1),
+// Full (ac|bd) in pair order, rows at stride ldv: V[R(a,b)][R(c,d)] = W[a - a0][c][b][d] for a in [a0, a1),
 // the diagonal columns c = d halved, so that V[R(a,b)] +- V[R(b,a)] are the packed halves there too.
 __global__ __launch_bounds__(kThreads) void pack_full_kernel(double* __restrict__ V, long ldv,
                                                             const double* __restrict__ W, int a0, int v) {
   const int a = a0 + blockIdx.y / v, b = blockIdx.y % v;
   const long vv = (long)v * v;
-  const double* src = W + ((long)(a - a0) * v + b) * vv;
+  const double* src = W + (long)(a - a0) * v * vv + (long)b * v;
   double* dst = V + pair_order(a, b, v) * ldv;
   if (blockIdx.x == 0)
     for (long x = vv + threadIdx.x; x < ldv; x += kThreads) dst[x] = 0.0;
   for (long x = blockIdx.x * (long)blockDim.x + threadIdx.x; x < vv; x += (long)gridDim.x * blockDim.x) {
     const int c = x / v, d = x % v;
-    dst[pair_order(c, d, v)] = (c == d) ? 0.5 * src[x] : src[x];
+    const double w = src[c * vv + d];
+    dst[pair_order(c, d, v)] = (c == d) ? 0.5 * w : w;
   }
 }
 
@@ -1580,39 +1591,37 @@ hipError_t energy(double* e, double* partial, const double* t1, const double* t2
 }
 
 
-static hipError_t pack_halves(int mode, double* plus, double* minus, long ldo, const double* src, int o, int v, int a0,
-                              long rows, long out_lo, long out_hi, long src_len, hipStream_t s) {
-  const long Tv = (long)v * (v + 1) / 2, nblk = (v + 31) / 32;
+static hipError_t pack_halves(const PackP& p, long rows, long out_lo, long out_hi, long src_len, hipStream_t s) {
+  const long Tv = (long)p.v * (p.v + 1) / 2, nblk = (p.v + 31) / 32, ny = p.mode == kPackT ? nblk * (nblk + 1) / 2 : nblk;
   if (rows <= 0) return hipSuccess;
-  if (ldo < Tv || rows > 0x7fffffffL || nblk * (nblk + 1) / 2 > 65535) return hipErrorInvalidValue;
-  if (bounds_checking() && !(range_ok(plus, out_lo * ldo, (out_hi + 1) * ldo - 1, 8, "pair packing plus") &&
-                             range_ok(minus, out_lo * ldo, (out_hi + 1) * ldo - 1, 8, "pair packing minus") &&
-                             chk(src, src_len, "pair packing input")))
+  if (p.ldo < Tv || rows > 0x7fffffffL || ny > 65535) return hipErrorInvalidValue;
+  if (bounds_checking() && !(range_ok(p.plus, out_lo * p.ldo, (out_hi + 1) * p.ldo - 1, 8, "pair packing plus") &&
+                             range_ok(p.minus, out_lo * p.ldo, (out_hi + 1) * p.ldo - 1, 8, "pair packing minus") &&
+                             chk(p.src, src_len, "pair packing input")))
     return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
-  hipLaunchKernelGGL(pack_halves_kernel, dim3((unsigned)rows, (unsigned)(nblk * (nblk + 1) / 2)), dim3(kThreads), 0, s,
-                     PackP{plus, minus, ldo, src, mode, o, v, a0});
+  hipLaunchKernelGGL(pack_halves_kernel, dim3((unsigned)rows, (unsigned)ny), dim3(kThreads), 0, s, p);
   return hipGetLastError();
 }
 
 hipError_t pack_tpm(double* tplus, double* tminus, long ldo, const double* t2, int o, int v, hipStream_t s) {
   const long To = (long)o * (o + 1) / 2;
-  return pack_halves(kPackT, tplus, tminus, ldo, t2, o, v, 0, To, 0, To - 1, (long)o * o * v * v, s);
+  return pack_halves({tplus, tminus, ldo, t2, kPackT, o, v, 0}, To, 0, To - 1, (long)o * o * v * v, s);
 }
 
 hipError_t pack_vvvv(double* vplus, double* vminus, long ldo, const double* W, int a0, int a1, int v, hipStream_t s) {
   if (a1 <= a0) return hipSuccess;
   auto row = [&](long a) { return a * v - a * (a - 1) / 2; };  // p(a, a)
-  return pack_halves(kPackV, vplus, vminus, ldo, W, 1, v, a0, (long)(a1 - a0) * v, row(a0), row(a1) - 1,
-                     (long)(a1 - a0) * v * v * v, s);
+  return pack_halves({vplus, vminus, ldo, W, kPackV, 1, v, a0}, (long)(a1 - a0) * v, row(a0), row(a1) - 1,
+                     (long)(a1 - a0) * v * v * (v - a0), s);
 }
 
 hipError_t pack_gwz(double* gplus, double* gminus, long ldo, const double* kcbd, const double* kcld, int o, int v,
                     hipStream_t s) {
   const long ov = (long)o * v, oo = (long)o * o;
-  const hipError_t e = pack_halves(kPackG, gplus, gminus, ldo, kcbd, o, v, 0, ov, 0, ov - 1, ov * v * v, s);
+  const hipError_t e = pack_halves({gplus, gminus, ldo, kcbd, kPackG, o, v, 0}, ov, 0, ov - 1, ov * v * v, s);
   if (e != hipSuccess) return e;
-  return pack_halves(kPackGo, gplus, gminus, ldo, kcld, o, v, 0, oo, ov, ov + oo - 1, ov * ov, s);
+  return pack_halves({gplus, gminus, ldo, kcld, kPackGo, o, v, 0}, oo, ov, ov + oo - 1, ov * ov, s);
 }
 
 hipError_t amp_views(double* Tx, double* U, long ld, double* tplus, double* tminus, long ldo, const double* t2, int o,

@@ -218,7 +218,7 @@ hipError_t assemble_r2(double* r2, const double* g1, const double* rl, const dou
 
 // Pair packing of the particle-particle ladder (p(i,j) = row-major index of i <= j).
 // Full (ac|bd) storage in pair order R(a,b) (a <= b: p(a,b); a > b: T(v) + strict index of (b,a)), rows at
-// stride ldv: pm[n] = R(b,a) for pair n = (a <= b); pack_full scatters W[a - a0][b][c][d] = (ac|bd),
+// stride ldv: pm[n] = R(b,a) for pair n = (a <= b); pack_full scatters W[a - a0][c][b][d] = (ac|bd),
 // a0 <= a < a1, to V[R(a,b)][R(c,d)], the diagonal columns c = d halved.
 hipError_t pair_minus_rows(int* pm, int v, hipStream_t s);
 hipError_t pack_full(double* V, long ldv, const double* W, int a0, int a1, int v, hipStream_t s);
@@ -226,8 +226,8 @@ hipError_t pack_full(double* V, long ldv, const double* W, int a0, int a1, int v
 // t+-[T(o)], t+ = (t^cd + t^dc)/2, and V+-[T(v)] and G+-[ov + o^2], sums and differences of (ac|bd) and
 // (ad|bc), of (kc|bd) and (kd|bc) and of (kc|ld) and (kd|lc) (diagonal: the element itself, and 0).
 hipError_t pack_tpm(double* tplus, double* tminus, long ldo, const double* t2, int o, int v, hipStream_t s);
-hipError_t pack_vvvv(double* vplus, double* vminus, long ldo, const double* W, int a0, int a1, int v,
-                     hipStream_t s);  // rows a0 <= a < a1
+// rows a0 <= a < a1 from W[a - a0][c][b - a0][d] = (ac|bd)
+hipError_t pack_vvvv(double* vplus, double* vminus, long ldo, const double* W, int a0, int a1, int v, hipStream_t s);
 // (kc|bd) as kcbd[k][c][b][d], (kc|ld) as kcld[k][c][l][d]
 hipError_t pack_gwz(double* gplus, double* gminus, long ldo, const double* kcbd, const double* kcld, int o, int v,
                     hipStream_t s);
