@@ -1971,8 +1971,9 @@ void ascc_diis_free(ascc_diis* D) {
   delete D;
 }
 
-int ascc_update(ascc_ints* I, ascc_diis* D, double* t1, double* t2, const double* r1, const double* r2,
-                const double* e, double level_shift, double* stats, void* stream) {
+// ascc_update from the amplitudes t1i, t2i (t1, t2 themselves, or other arrays, which are left as they are).
+static int update_impl(ascc_ints* I, ascc_diis* D, const double* t1i, const double* t2i, double* t1, double* t2,
+                       const double* r1, const double* r2, const double* e, double level_shift, double* stats, void* stream) {
   if (!I || !D || !t1 || !t2 || !r1 || !r2 || !e || !stats) return fail(ASCC_E_ARG, "NULL argument to ascc_update");
   if (D->no != I->no || D->nv != I->nv) return fail(ASCC_E_STATE, "DIIS state and integrals differ in shape");
   if (!(level_shift >= 0.0)) return fail(ASCC_E_ARG, "level_shift must be >= 0");
@@ -1984,6 +1985,8 @@ int ascc_update(ascc_ints* I, ascc_diis* D, double* t1, double* t2, const double
   user.add(e, sizeof(double));
   user.add(stats, 8 * sizeof(double));
   UpdateArgs u;
+  u.t1i = t1i;
+  u.t2i = t2i;
   u.t1 = t1;
   u.t2 = t2;
   u.r1 = r1;
@@ -2006,6 +2009,11 @@ int ascc_update(ascc_ints* I, ascc_diis* D, double* t1, double* t2, const double
   phase_end(I, static_cast<hipStream_t>(stream));
   D->calls += 1;
   return ASCC_OK;
+}
+
+int ascc_update(ascc_ints* I, ascc_diis* D, double* t1, double* t2, const double* r1, const double* r2,
+                const double* e, double level_shift, double* stats, void* stream) {
+  return update_impl(I, D, t1, t2, t1, t2, r1, r2, e, level_shift, stats, stream);
 }
 
 }  // extern "C"
@@ -2078,9 +2086,11 @@ size_t solve_workspace_bytes(long o, long v, int diis_size) {
   return align_up(off);
 }
 
-// The solve loop of ascc_solve.  ws == nullptr: the DIIS state and work arrays are allocated here and
+// The solve loop of ascc_solve.  ws == nullptr: one block for the DIIS state and work arrays is allocated here and
 // the statistics are read through pinned host memory; otherwise everything is carved from
-// [ws, ws + ws_bytes) (>= solve_workspace_bytes) and no allocation is made.
+// [ws, ws + ws_bytes) (>= solve_workspace_bytes) and no allocation is made.  Each update goes from the current amplitudes
+// to the other of two sets, which become the current ones when it is accepted (copies to and fro took four launches of an
+// iteration's 27 at o5 v20); the caller's set has them in the end.
 int solve_impl(ascc_ints* I, const ascc_opts* opts, double* t1, double* t2, ascc_result* res, void* stream,
                char* ws, size_t ws_bytes) {
   if (!I || !opts || !t1 || !t2 || !res) return fail(ASCC_E_ARG, "NULL argument to ascc_solve");
@@ -2090,20 +2100,23 @@ int solve_impl(ascc_ints* I, const ascc_opts* opts, double* t1, double* t2, ascc
   std::memset(res, 0, sizeof(*res));
   const int prec0 = I->cur_prec;
   bool lowp_phase = (prec0 != ASCC_PREC_FP64);
-  size_t dbytes = 0;
-  if (ws) {
-    dbytes = diis_footprint(I->no, I->nv, opts->diis_size);
-    if (ws_bytes < solve_workspace_bytes(I->no, I->nv, opts->diis_size))
-      return fail(ASCC_E_NOMEM, "solver workspace too small");
+  const size_t dbytes = diis_footprint(I->no, I->nv, opts->diis_size), need = solve_workspace_bytes(I->no, I->nv, opts->diis_size);
+  if (ws && ws_bytes < need) return fail(ASCC_E_NOMEM, "solver workspace too small");
+  Pool block;
+  const bool pinned = !ws;
+  int rc = ASCC_OK;
+  if (!ws) {
+    if ((rc = dalloc(block, &ws, need))) return rc;
+    ws_bytes = need;
   }
   ascc_diis* D = nullptr;
-  int rc = diis_create_impl(I, opts->diis_size, opts->diis_start, ws, dbytes, &D);
-  if (rc) return rc;
-  Pool work;
-  if (ws) {
-    work.base = ws + dbytes;
-    work.size = ws_bytes - dbytes;
+  if ((rc = diis_create_impl(I, opts->diis_size, opts->diis_start, ws, dbytes, &D))) {
+    free_all(block);
+    return rc;
   }
+  Pool work;
+  work.base = ws + dbytes;
+  work.size = ws_bytes - dbytes;
   double *r1 = nullptr, *r2 = nullptr, *e = nullptr, *stats = nullptr, *t1s = nullptr, *t2s = nullptr;
   rc = dalloc(work, &r1, I->ov);
   if (!rc) rc = dalloc(work, &r2, I->oovv);
@@ -2116,7 +2129,7 @@ int solve_impl(ascc_ints* I, const ascc_opts* opts, double* t1, double* t2, ascc
   double local_stats[8];
   if (dry_run()) {
     hstats = dry_stats;  // a dry run reports zeros: converged after one iteration
-  } else if (ws) {
+  } else if (!pinned) {
     hstats = local_stats;  // pageable: the copy completes before the stream synchronisation returns
   } else if (!rc && hipHostMalloc((void**)&hstats, 8 * sizeof(double), 0) != hipSuccess) {
     rc = fail(ASCC_E_NOMEM, "pinned host allocation failed");
@@ -2125,21 +2138,17 @@ int solve_impl(ascc_ints* I, const ascc_opts* opts, double* t1, double* t2, ascc
   user.add(t1, sizeof(double) * I->ov);
   user.add(t2, sizeof(double) * I->oovv);
   int status = ASCC_E_NOT_CONVERGED;
+  double *c1 = t1, *c2 = t2, *n1 = t1s, *n2 = t2s;  // current amplitudes, trial ones
   int lowp_iters = 0;
   LowpStall stall;
   bool confirm = false;  // the next evaluation is the first FP64 one after a hand-over
   double handover_de = 0.0;
   for (int it = 0; !rc && it < opts->maxiter; ++it) {
-    rc = residual_fp64(I, t1, t2, r1, r2, e, s);
+    rc = residual_fp64(I, c1, c2, r1, r2, e, s);
     if (rc) break;
-    // statistics of the residual at the current amplitudes, without changing them: run the
-    // update on a copy (the copy also carries the DIIS bookkeeping of this iteration)
-    if (d_copy(t1s, t1, sizeof(double) * I->ov, hipMemcpyDeviceToDevice, s) != hipSuccess ||
-        d_copy(t2s, t2, sizeof(double) * I->oovv, hipMemcpyDeviceToDevice, s) != hipSuccess) {
-      rc = fail(ASCC_E_HIP, "copy of amplitudes failed");
-      break;
-    }
-    rc = ascc_update(I, D, t1s, t2s, r1, r2, e, opts->level_shift, stats, stream);
+    // statistics of the residual at the current amplitudes, without changing them (the update also
+    // carries the DIIS bookkeeping of this iteration)
+    rc = update_impl(I, D, c1, c2, n1, n2, r1, r2, e, opts->level_shift, stats, stream);
     if (rc) break;
     if (d_copy(hstats, stats, 8 * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess || d_sync(s) != hipSuccess) {
       rc = fail(ASCC_E_HIP, "reading iteration statistics failed");
@@ -2186,28 +2195,24 @@ int solve_impl(ascc_ints* I, const ascc_opts* opts, double* t1, double* t2, ascc
         // low-precision pairs carry the rounding of those contractions), and the update is redone
         confirm = false;
         if ((rc = ascc_diis_reset(D, stream))) break;
-        if (d_copy(t1s, t1, sizeof(double) * I->ov, hipMemcpyDeviceToDevice, s) != hipSuccess ||
-            d_copy(t2s, t2, sizeof(double) * I->oovv, hipMemcpyDeviceToDevice, s) != hipSuccess) {
-          rc = fail(ASCC_E_HIP, "copy of amplitudes failed");
-          break;
-        }
-        if ((rc = ascc_update(I, D, t1s, t2s, r1, r2, e, opts->level_shift, stats, stream))) break;
+        if ((rc = update_impl(I, D, c1, c2, n1, n2, r1, r2, e, opts->level_shift, stats, stream))) break;
       }
     }
     // accept the update, except after the last evaluation: a solve that ends unconverged returns the
     // amplitudes its reported energy and residual norms were evaluated at
     if (it + 1 == opts->maxiter) break;
-    if (d_copy(t1, t1s, sizeof(double) * I->ov, hipMemcpyDeviceToDevice, s) != hipSuccess ||
-        d_copy(t2, t2s, sizeof(double) * I->oovv, hipMemcpyDeviceToDevice, s) != hipSuccess) {
-      rc = fail(ASCC_E_HIP, "copy of amplitudes failed");
-      break;
-    }
+    std::swap(c1, n1);
+    std::swap(c2, n2);
   }
+  if (c1 != t1 && (d_copy(t1, c1, sizeof(double) * I->ov, hipMemcpyDeviceToDevice, s) != hipSuccess ||
+                   d_copy(t2, c2, sizeof(double) * I->oovv, hipMemcpyDeviceToDevice, s) != hipSuccess) && !rc)
+    rc = fail(ASCC_E_HIP, "copy of amplitudes failed");
   I->cur_prec = prec0;
   (void)d_sync(s);
-  if (hstats && !dry_run() && !ws) (void)hipHostFree(hstats);
+  if (hstats && !dry_run() && pinned) (void)hipHostFree(hstats);
   free_all(work);
   ascc_diis_free(D);
+  free_all(block);
   if (rc) return rc;
   if (status == ASCC_E_NOT_CONVERGED) {
     // near convergence: the energy no longer moves at the energy test's precision and every

@@ -14,7 +14,7 @@ namespace ascc {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kRedBlocks = 1024;  // first-stage blocks of every reduction
+constexpr int kRedBlocks = 1024;  // first-stage blocks of a reduction at most
 
 struct P4 {
   double* out;
@@ -232,6 +232,11 @@ __global__ __launch_bounds__(kDressCols) void dress_right_kernel(double* __restr
 __device__ __forceinline__ double wave_all(double x) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+  return x;
+}
+__device__ __forceinline__ double wave_max(double x) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) x = fmax(x, __shfl_xor(x, off, 64));
   return x;
 }
 
@@ -452,11 +457,6 @@ __device__ __forceinline__ double wave_sum(double x) {
   for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
   return x;
 }
-__device__ __forceinline__ double wave_max(double x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x = fmax(x, __shfl_down(x, off, 64));
-  return x;
-}
 
 // Block sum of one value per thread; result valid in thread 0.
 __device__ double block_sum(double x, double* sh) {
@@ -470,18 +470,6 @@ __device__ double block_sum(double x, double* sh) {
     for (int k = 0; k < (int)(blockDim.x >> 6); ++k) s += sh[k];
   return s;
 }
-__device__ double block_max(double x, double* sh) {
-  x = wave_max(x);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) sh[w] = x;
-  __syncthreads();
-  double s = 0.0;
-  if (threadIdx.x == 0)
-    for (int k = 0; k < (int)(blockDim.x >> 6); ++k) s = fmax(s, sh[k]);
-  return s;
-}
-
 __global__ __launch_bounds__(kThreads) void energy_stage1(double* partial, const double* __restrict__ t1,
                                                          const double* __restrict__ t2,
                                                          const double* __restrict__ L, int o, int v, long total) {
@@ -529,6 +517,8 @@ __device__ __forceinline__ double denom(long x, int o, int v, const double* eps,
 }
 
 struct UK {
+  const double* t1i;  // the amplitudes the step starts from (t1, t2 themselves in place)
+  const double* t2i;
   double* t1;
   double* t2;
   const double* r1;
@@ -554,6 +544,8 @@ __device__ __forceinline__ T* in_slot(T* p, long k, long ss) {
 __global__ __launch_bounds__(kThreads) void update_stage1(UK p) {
   if (p.ss) {  // this grid row's slot
     const long k = p.tab ? p.tab[blockIdx.y] : blockIdx.y;
+    p.t1i = in_slot(p.t1i, k, p.ss);
+    p.t2i = in_slot(p.t2i, k, p.ss);
     p.t1 = in_slot(p.t1, k, p.ss);
     p.t2 = in_slot(p.t2, k, p.ss);
     p.r1 = in_slot(p.r1, k, p.ss);
@@ -564,7 +556,7 @@ __global__ __launch_bounds__(kThreads) void update_stage1(UK p) {
     p.partial = in_slot(p.partial, k, p.ss);
     p.st = in_slot(p.st, k, p.ss);
   }
-  __shared__ double sh[kThreads / 64];
+  __shared__ double sh[kThreads / 64][3 + kMaxDiis];
   const int head = p.st->head;
   const bool store = p.st->calls >= p.start;  // decided on the device, so a captured graph replays it
   bool valid[kMaxDiis];
@@ -575,10 +567,9 @@ __global__ __launch_bounds__(kThreads) void update_stage1(UK p) {
   const long ov = (long)p.o * p.v;
   for (long x = blockIdx.x * (long)blockDim.x + threadIdx.x; x < p.len; x += (long)gridDim.x * blockDim.x) {
     const double r = (x < ov) ? p.r1[x] : p.r2[x - ov];
-    double* tp = (x < ov) ? (p.t1 + x) : (p.t2 + (x - ov));
     const double s = r / denom(x, p.o, p.v, p.eps, p.shift);
-    const double tn = *tp + s;
-    *tp = tn;
+    const double tn = ((x < ov) ? p.t1i[x] : p.t2i[x - ov]) + s;
+    *((x < ov) ? (p.t1 + x) : (p.t2 + (x - ov))) = tn;
     rr += r * r;
     rmax = fmax(rmax, fabs(r));
     if (!isfinite(r)) bad += 1.0;
@@ -589,74 +580,98 @@ __global__ __launch_bounds__(kThreads) void update_stage1(UK p) {
       p.hist_e[(long)head * p.len + x] = s;
     }
   }
-  double* out = p.partial + (long)blockIdx.x * p.nstat;
-  double v = block_sum(rr, sh);
-  if (threadIdx.x == 0) out[0] = v;
-  v = block_max(rmax, sh);
-  if (threadIdx.x == 0) out[1] = v;
-  v = block_sum(bad, sh);
-  if (threadIdx.x == 0) out[2] = v;
-  for (int k = 0; k < p.m; ++k) {
-    v = block_sum(dots[k], sh);
-    if (threadIdx.x == 0) out[3 + k] = v;
+  // per-wave results side by side, then one thread per statistic adds the block's four: one barrier for all of them
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  auto put = [&](int k, double v) {
+    if (lane == 0) sh[w][k] = v;
+  };
+  put(0, wave_all(rr));
+  put(1, wave_max(rmax));
+  put(2, wave_all(bad));
+  if (store)
+    for (int k = 0; k < p.m; ++k) put(3 + k, wave_all(dots[k]));
+  __syncthreads();
+  const int k = threadIdx.x;
+  if (k >= 3 + p.m) return;
+  double v = 0.0;
+  if (k < 3 || store) {
+    v = sh[0][k];
+    for (int x = 1; x < kThreads / 64; ++x) v = k == 1 ? fmax(v, sh[x][k]) : v + sh[x][k];
   }
+  p.partial[(long)blockIdx.x * p.nstat + k] = v;
 }
 
-// Bordered DIIS system over the valid slots, oldest first; returns false if a pivot is tiny.
-// A and xs: (kMaxDiis + 1) x (kMaxDiis + 2) and kMaxDiis + 1 doubles of the caller's LDS (one thread
-// eliminates; LDS rather than private arrays, which would live in scratch memory).
-__device__ bool diis_solve(DiisState* st, int m, double* A, double* xs) {
-  int order[kMaxDiis];
-  int nv = 0;
-  for (int k = 0; k < m; ++k)
-    if (st->slot_age[k] >= 0) order[nv++] = k;
-  for (int x = 1; x < nv; ++x)  // insertion sort by age (oldest first)
-    for (int y = x; y > 0 && st->slot_age[order[y - 1]] > st->slot_age[order[y]]; --y) {
-      const int t = order[y];
-      order[y] = order[y - 1];
-      order[y - 1] = t;
-    }
+// Orders this wave's LDS accesses as written (they execute in order; the compiler is kept from moving them).
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Bordered DIIS system over the valid slots (ages age[k] >= 0), oldest first, from the overlaps Bm; returns false if a
+// pivot is tiny, else leaves the coefficients in coef by slot.  One wave: rows and columns of an elimination
+// step over its lanes (as a chain of one thread the 9 x 9 system took 25 of the update's 45 us at o5 v20).
+__device__ bool diis_solve(const int* age, const double* Bm, int m, double* A, double* xs, int* order, double* coef) {
   constexpr int W = kMaxDiis + 2;
+  const int lane = threadIdx.x & 63;
+  int nv = 0, rank = 0;
+  for (int k = 0; k < m; ++k) {
+    if (age[k] < 0) continue;
+    ++nv;
+    if (lane < m && age[k] < age[lane]) ++rank;
+  }
+  if (lane < m && age[lane] >= 0) order[rank] = lane;
+  wave_fence();
   const int nn = nv + 1;
   double scale = 0.0;
-  for (int r = 0; r < nv; ++r)
-    for (int c = 0; c < nv; ++c) scale = fmax(scale, fabs(st->Bm[order[r] * kMaxDiis + order[c]]));
-  for (int r = 0; r < nn; ++r)
-    for (int c = 0; c <= nn; ++c) {
-      double x;
-      if (c == nn)
-        x = (r == nv) ? -1.0 : 0.0;
-      else if (r < nv && c < nv)
-        x = st->Bm[order[r] * kMaxDiis + order[c]];
-      else if (r == nv && c == nv)
-        x = 0.0;
-      else
-        x = -1.0;
-      A[r * W + c] = x;
-    }
+  for (int x = lane; x < nn * (nn + 1); x += 64) {
+    const int r = x / (nn + 1), c = x % (nn + 1);
+    double y = -1.0;
+    if (c == nn)
+      y = (r == nv) ? -1.0 : 0.0;
+    else if (r < nv && c < nv)
+      scale = fmax(scale, fabs(y = Bm[order[r] * kMaxDiis + order[c]]));
+    else if (r == nv && c == nv)
+      y = 0.0;
+    A[r * W + c] = y;
+  }
+  scale = wave_max(scale);
+  wave_fence();
   for (int c = 0; c < nn; ++c) {
-    int piv = c;
-    for (int r = c + 1; r < nn; ++r)
-      if (fabs(A[r * W + c]) > fabs(A[piv * W + c])) piv = r;
-    if (!(fabs(A[piv * W + c]) >= 1e-14 * scale)) return false;
-    if (piv != c)
-      for (int k = 0; k <= nn; ++k) {
-        const double t = A[c * W + k];
-        A[c * W + k] = A[piv * W + k];
-        A[piv * W + k] = t;
+    int piv = c + lane;  // the first of the largest entries at or below the diagonal
+    double best = piv < nn ? fabs(A[piv * W + c]) : -1.0;
+    if (lane > 0 && !(best >= 0.0)) best = -1.0;  // a NaN is not larger than the diagonal
+    for (int off = 16; off > 0; off >>= 1) {
+      const double y = __shfl_xor(best, off, 64);
+      const int q = __shfl_xor(piv, off, 64);
+      if (y > best || (y == best && q < piv)) {
+        best = y;
+        piv = q;
       }
-    for (int r = c + 1; r < nn; ++r) {
-      const double f = A[r * W + c] / A[c * W + c];
-      for (int k = c; k <= nn; ++k) A[r * W + k] -= f * A[c * W + k];
     }
+    piv = __shfl(piv, 0, 64);
+    const bool ok = fabs(A[piv * W + c]) >= 1e-14 * scale;
+    if (!ok) return false;
+    if (piv != c && lane <= nn) {
+      const double t = A[c * W + lane];
+      A[c * W + lane] = A[piv * W + lane];
+      A[piv * W + lane] = t;
+    }
+    wave_fence();
+    // columns past c only: the lower triangle is not read again
+    for (int x = lane; x < (nn - 1 - c) * (nn - c); x += 64) {
+      const int r = c + 1 + x / (nn - c), k = c + 1 + x % (nn - c);
+      A[r * W + k] -= A[r * W + c] / A[c * W + c] * A[c * W + k];
+    }
+    wave_fence();
   }
+  double acc = lane < nn ? A[lane * W + nn] : 0.0;
   for (int r = nn - 1; r >= 0; --r) {
-    double acc = A[r * W + nn];
-    for (int k = r + 1; k < nn; ++k) acc -= A[r * W + k] * xs[k];
-    xs[r] = acc / A[r * W + r];
+    if (lane == r) xs[r] = acc / A[r * W + r];
+    wave_fence();
+    if (lane < r) acc -= A[lane * W + r] * xs[r];
   }
-  for (int k = 0; k < kMaxDiis; ++k) st->coef[k] = 0.0;
-  for (int r = 0; r < nv; ++r) st->coef[order[r]] = xs[r];
+  if (lane < nv) coef[order[lane]] = xs[lane];
+  wave_fence();
   return true;
 }
 
@@ -670,69 +685,75 @@ __global__ __launch_bounds__(kThreads) void update_stage2(DiisState* st, const d
     e = in_slot(e, k, ss);
     stats += 8 * k;
   }
-  const bool store = st->calls >= start;
-  __shared__ double sh[kThreads / 64];
-  __shared__ double red[3 + kMaxDiis];
-  __shared__ double sysA[(kMaxDiis + 1) * (kMaxDiis + 2)], sysx[kMaxDiis + 1];
-  double a = 0.0;
-  for (int k = threadIdx.x; k < nblk; k += blockDim.x) a += partial[(long)k * nstat + 0];
-  double v = block_sum(a, sh);
-  if (threadIdx.x == 0) red[0] = v;
-  a = 0.0;
-  for (int k = threadIdx.x; k < nblk; k += blockDim.x) a = fmax(a, partial[(long)k * nstat + 1]);
-  v = block_max(a, sh);
-  if (threadIdx.x == 0) red[1] = v;
-  a = 0.0;
-  for (int k = threadIdx.x; k < nblk; k += blockDim.x) a += partial[(long)k * nstat + 2];
-  v = block_sum(a, sh);
-  if (threadIdx.x == 0) red[2] = v;
-  for (int q = 0; q < m; ++q) {
-    a = 0.0;
-    for (int k = threadIdx.x; k < nblk; k += blockDim.x) a += partial[(long)k * nstat + 3 + q];
-    v = block_sum(a, sh);
-    if (threadIdx.x == 0) red[3 + q] = v;
+  __shared__ double red[3 + kMaxDiis], Bm[kMaxDiis * kMaxDiis], coef[kMaxDiis];
+  __shared__ double A[(kMaxDiis + 1) * (kMaxDiis + 2)], xs[kMaxDiis + 1];
+  __shared__ int age[kMaxDiis], order[kMaxDiis];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  // one wave per statistic
+  for (int q = w; q < 3 + m; q += kThreads / 64) {
+    double a = 0.0;
+    for (int k = lane; k < nblk; k += 64) {
+      const double y = partial[(long)k * nstat + q];
+      a = q == 1 ? fmax(a, y) : a + y;
+    }
+    a = q == 1 ? wave_max(a) : wave_all(a);
+    if (lane == 0) red[q] = a;
   }
-  if (threadIdx.x != 0) return;
+  for (int x = threadIdx.x; x < kMaxDiis * kMaxDiis; x += kThreads) Bm[x] = st->Bm[x];
+  if (threadIdx.x < kMaxDiis) age[threadIdx.x] = st->slot_age[threadIdx.x];
+  __syncthreads();
+  if (w != 0) return;
 
   const double E = *e;
-  int flags = 0;
+  int flags = 0, nvec = st->nvec;
   if (red[2] > 0.0 || !isfinite(E) || !isfinite(red[0])) flags |= 1;
-  if (store) {
-    const int head = st->head;
-    for (int k = 0; k < m; ++k)
-      if (k == head || st->slot_age[k] >= 0) {
-        st->Bm[head * kMaxDiis + k] = red[3 + k];
-        st->Bm[k * kMaxDiis + head] = red[3 + k];
-      }
-    st->slot_age[head] = st->counter++;
-    st->head = (head + 1) % m;
-    int nvalid = 0;
-    for (int k = 0; k < m; ++k) nvalid += (st->slot_age[k] >= 0);
-    st->nvec = nvalid;
-    for (int k = 0; k < kMaxDiis; ++k) st->coef[k] = 0.0;
-    while (st->nvec >= 2 && !(flags & 1)) {
-      if (diis_solve(st, m, sysA, sysx)) break;
+  const int calls = st->calls;
+  if (calls >= start) {
+    const int head = st->head, counter = st->counter;
+    if (lane < m && (lane == head || age[lane] >= 0)) {
+      Bm[head * kMaxDiis + lane] = Bm[lane * kMaxDiis + head] = red[3 + lane];
+      st->Bm[head * kMaxDiis + lane] = st->Bm[lane * kMaxDiis + head] = red[3 + lane];
+    }
+    if (lane == 0) age[head] = counter;
+    wave_fence();
+    nvec = 0;
+    for (int k = 0; k < m; ++k) nvec += (age[k] >= 0);
+    for (;;) {
+      if (lane < kMaxDiis) coef[lane] = 0.0;
+      wave_fence();
+      if (nvec < 2 || (flags & 1) || diis_solve(age, Bm, m, A, xs, order, coef)) break;
       int oldest = -1;
       for (int k = 0; k < m; ++k)
-        if (st->slot_age[k] >= 0 && (oldest < 0 || st->slot_age[k] < st->slot_age[oldest])) oldest = k;
-      st->slot_age[oldest] = -1;
-      st->nvec -= 1;
+        if (age[k] >= 0 && (oldest < 0 || age[k] < age[oldest])) oldest = k;
+      wave_fence();
+      if (lane == 0) age[oldest] = -1;
+      wave_fence();
+      nvec -= 1;
       flags |= 2;
-      for (int k = 0; k < kMaxDiis; ++k) st->coef[k] = 0.0;
+    }
+    if (lane < kMaxDiis) {
+      st->coef[lane] = coef[lane];
+      st->slot_age[lane] = age[lane];
+    }
+    if (lane == 0) {
+      st->counter = counter + 1;
+      st->head = (head + 1) % m;
+      st->nvec = nvec;
     }
   }
+  if (lane != 0) return;
   stats[0] = E;
   stats[1] = st->has_prev ? E - st->e_prev : INFINITY;
   stats[2] = red[1];
   stats[3] = sqrt(red[0]);
-  stats[4] = st->nvec;
+  stats[4] = nvec;
   stats[5] = flags;
-  stats[6] = st->calls;
+  stats[6] = calls;
   stats[7] = shift;
   st->e_prev = E;
   st->has_prev = 1;
   st->flags = flags;
-  st->calls += 1;
+  st->calls = calls + 1;
 }
 
 // t <- sum_k coef[k] hist_t[k] once two or more pairs are stored (no-op otherwise).
@@ -1108,6 +1129,10 @@ __global__ __launch_bounds__(kThreads) void pack_full_kernel(double* __restrict_
     dst[pair_order(c, d, v)] = (c == d) ? 0.5 * w : w;
   }
 }
+
+// First-stage blocks of a reduction over total elements: two of a thread's each, as far as kRedBlocks go (the second stage
+// reads one row of partial sums per block).
+inline int red_blocks(long total) { return (int)std::clamp<long>((total + 2 * kThreads - 1) / (2 * kThreads), 1, kRedBlocks); }
 
 inline int grid_for(long total) {
   long g = (total + kThreads - 1) / kThreads;
@@ -1585,8 +1610,8 @@ hipError_t energy(double* e, double* partial, const double* t1, const double* t2
         range_ok(Lijab, 0, total - 1, 8, "energy L") && range_ok(fov, 0, (long)no * nv - 1, 8, "energy fov")))
     return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
-  hipLaunchKernelGGL(energy_stage1, dim3(kRedBlocks), dim3(kThreads), 0, s, partial, t1, t2, Lijab, no, nv, total);
-  hipLaunchKernelGGL(energy_stage2, dim3(1), dim3(kThreads), 0, s, e, partial, kRedBlocks, t1, fov, no * nv);
+  hipLaunchKernelGGL(energy_stage1, dim3(red_blocks(total)), dim3(kThreads), 0, s, partial, t1, t2, Lijab, no, nv, total);
+  hipLaunchKernelGGL(energy_stage2, dim3(1), dim3(kThreads), 0, s, e, partial, red_blocks(total), t1, fov, no * nv);
   return hipGetLastError();
 }
 
@@ -1703,6 +1728,8 @@ hipError_t diis_update(const UpdateArgs& u, hipStream_t s) {
   // Whether this call stores a pair is decided by the caller; the device state decides the
   // slot, which stored pairs are valid and the coefficients.
   UK p;
+  p.t1i = u.t1i ? u.t1i : u.t1;
+  p.t2i = u.t2i ? u.t2i : u.t2;
   p.t1 = u.t1;
   p.t2 = u.t2;
   p.r1 = u.r1;
@@ -1729,7 +1756,8 @@ hipError_t diis_update(const UpdateArgs& u, hipStream_t s) {
     for (long k = 0; k < (p.ss ? nk : 1); ++k) {
       const long o8 = k * p.ss / 8;  // slot offset in doubles
       auto at = [&](const void* q) { return reinterpret_cast<const char*>(q) + k * p.ss; };
-      if (!(range_ok(at(u.t1), 0, ov - 1, 8, "update t1") && range_ok(at(u.t2), 0, u.len - ov - 1, 8, "update t2") &&
+      if (!(range_ok(at(p.t1i), 0, ov - 1, 8, "update t1 in") && range_ok(at(p.t2i), 0, u.len - ov - 1, 8, "update t2 in") &&
+            range_ok(at(u.t1), 0, ov - 1, 8, "update t1") && range_ok(at(u.t2), 0, u.len - ov - 1, 8, "update t2") &&
             range_ok(at(u.r1), 0, ov - 1, 8, "update r1") && range_ok(at(u.r2), 0, u.len - ov - 1, 8, "update r2") &&
             range_ok(at(u.e), 0, 0, 8, "update e") && range_ok(at(u.eps), 0, u.no + u.nv - 1, 8, "update eps") &&
             range_ok(at(u.hist_t), 0, (long)u.m * u.len - 1, 8, "update hist_t") &&
@@ -1743,8 +1771,9 @@ hipError_t diis_update(const UpdateArgs& u, hipStream_t s) {
   }
   if (u.m < 1 || u.m > kMaxDiis) return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
-  hipLaunchKernelGGL(update_stage1, dim3(kRedBlocks, u.nslot), dim3(kThreads), 0, s, p);
-  hipLaunchKernelGGL(update_stage2, dim3(1, u.nslot), dim3(kThreads), 0, s, u.st, u.partial, kRedBlocks, 3 + kMaxDiis,
+  const int nblk = red_blocks(u.len);
+  hipLaunchKernelGGL(update_stage1, dim3(nblk, u.nslot), dim3(kThreads), 0, s, p);
+  hipLaunchKernelGGL(update_stage2, dim3(1, u.nslot), dim3(kThreads), 0, s, u.st, u.partial, nblk, 3 + kMaxDiis,
                      u.m, u.start, u.e, u.stats, u.shift, p.ss, u.tab);
   hipLaunchKernelGGL(update_stage3, dim3(grid_for(u.len), u.nslot), dim3(kThreads), 0, s, u.t1, u.t2, u.hist_t, u.st,
                      u.m, (long)u.no * u.nv, u.len, p.ss, u.tab);

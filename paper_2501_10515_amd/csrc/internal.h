@@ -323,8 +323,10 @@ struct DiisState {
 };
 
 struct UpdateArgs {
-  double* t1;
+  double* t1;  // written; read as the step's start too unless t1i, t2i are given
   double* t2;
+  const double* t1i = nullptr;
+  const double* t2i = nullptr;
   const double* r1;
   const double* r2;
   const double* e;
