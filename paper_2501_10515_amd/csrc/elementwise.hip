@@ -190,42 +190,79 @@ __global__ __launch_bounds__(kThreads) void assemble_r2_kernel(double* __restric
 // written in the layout that the contractions over Q read, in two passes over B (o20 v180 Q600, with the Fock
 // matrix: 0.53 ms as products, block copies and traces of [Q][p][q] arrays, 0.2 ms so).
 //
-// Right side: D[k][p] = B[p][k] + sum_c B[p][o + c] t1[k][c], all p, k < o.  One thread per Q column of one p
-// and KC values of k: B's virtual columns are read once per KC, coalesced.
-constexpr int kDressCols = 128, kDressC = 32;
-template <int KC>
-__global__ __launch_bounds__(kDressCols) void dress_right_kernel(double* __restrict__ D, const double* __restrict__ B,
-                                                                 const double* __restrict__ t1, int o, int v, long ldq) {
-  __shared__ double t[kDressC][KC];
-  const int n = o + v, p = blockIdx.y, k0 = blockIdx.z * KC;
-  const long q = blockIdx.x * (long)kDressCols + threadIdx.x;
-  const bool in = q < ldq;
-  const double* Bp = B + (long)p * n * ldq + q;
-  double acc[KC];
+// Both sides are products with the fitting index as their columns, on v_mfma_f64_16x16x4 (lane l supplies A(l%16, l/16) and
+// B(l/16, l%16) and holds rows l/16 + 4r of column l%16): fragments of B come straight from its rows (four pieces of
+// 128 bytes a load), and no value has to reach all lanes (with t1 broadcast from LDS the reads of it took four times as
+// long as the products).  Bound by the reads of B.
+//
+// Right side: D[k][p] = B[p][k] + sum_c B[p][o + c] t1[k][c], all p, k < o.  A workgroup holds 64 Q of one p and
+// 16 MT values of k; its four waves share the columns c and their sums are added through LDS.  One Q column a
+// thread and its chain over c took o8 v72 27, o13 v117 80, o20 v180 82 us, now 7, 17 and 69 (2.8 TB/s).
+typedef double dress_d4 __attribute__((ext_vector_type(4)));
+template <int MT>
+__global__ __launch_bounds__(kThreads) void dress_right_kernel(double* __restrict__ D, const double* __restrict__ B,
+                                                              const double* __restrict__ t1, int o, int v, long ldq) {
+  __shared__ dress_d4 sh[2][MT * 4][64];  // two waves' sums
+  const int n = o + v, p = blockIdx.y, k0 = blockIdx.z * 16 * MT, lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double* Bp = B + (long)p * n * ldq;
+  // this lane's columns j of the four tiles: q + j, four values side by side (rows are a multiple of 16 long; columns past the
+  // row's end repeat its first ones and are not stored)
+  const long q0 = blockIdx.x * 64L + 4 * l16, q = q0 < ldq ? q0 : 0;
+  dress_d4 acc[MT][4];
 #pragma unroll
-  for (int r = 0; r < KC; ++r) acc[r] = (in && k0 + r < o) ? Bp[(k0 + r) * ldq] : 0.0;
-  for (int c0 = 0; c0 < v; c0 += kDressC) {
-    const int nc = min(kDressC, v - c0);
-    __syncthreads();
-    for (int x = threadIdx.x; x < kDressC * KC; x += kDressCols) {
-      const int r = x / kDressC, c = x % kDressC;
-      t[c][r] = (c < nc && k0 + r < o) ? t1[(long)(k0 + r) * v + c0 + c] : 0.0;
-    }
-    __syncthreads();
-    if (in) {
-      const double* b = Bp + (long)(o + c0) * ldq;
-#pragma unroll 4
-      for (int c = 0; c < nc; ++c) {
-        const double x = b[c * ldq];
+  for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int r = 0; r < KC; ++r) acc[r] += t[c][r] * x;
+    for (int j = 0; j < 4; ++j) acc[m][j] = dress_d4{0.0, 0.0, 0.0, 0.0};
+  constexpr int UN = 2;  // groups of four c in flight
+  const int ng = (v + 3) / 4;
+  for (int g = wave; g < ng; g += 4 * UN) {
+    double a[UN][MT];
+    dress_d4 x[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int c = 4 * (g + 4 * u) + lq, cc = min(c, v - 1);
+      const dress_d4 y = *reinterpret_cast<const dress_d4*>(Bp + (o + cc) * ldq + q);
+      x[u] = c < v ? y : dress_d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        const int k = k0 + 16 * m + l16;
+        const double y = t1[(long)min(k, o - 1) * v + cc];
+        a[u][m] = c < v ? y : 0.0;
       }
     }
-  }
-  if (!in) return;
 #pragma unroll
-  for (int r = 0; r < KC; ++r)
-    if (k0 + r < o) D[((long)(k0 + r) * n + p) * ldq + q] = acc[r];
+    for (int u = 0; u < UN; ++u)
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[m][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][m], x[u][j], acc[m][j], 0, 0, 0);
+  }
+  // (wave 0 + wave 2) + (wave 1 + wave 3)
+#pragma unroll
+  for (int half = 2; half > 0; half >>= 1) {
+    if (half == 1) __syncthreads();
+    if (wave >= half && wave < 2 * half) {
+#pragma unroll
+      for (int y = 0; y < 4 * MT; ++y) sh[wave - half][y][lane] = acc[y / 4][y % 4];
+    }
+    __syncthreads();
+    if (wave < half) {
+#pragma unroll
+      for (int y = 0; y < 4 * MT; ++y) acc[y / 4][y % 4] += sh[wave][y][lane];
+    }
+  }
+  if (wave != 0 || q0 >= ldq) return;
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int k = k0 + 16 * m + lq + 4 * r;
+      if (k >= o) continue;
+      const dress_d4 y = *reinterpret_cast<const dress_d4*>(Bp + k * ldq + q);
+      *reinterpret_cast<dress_d4*>(D + ((long)k * n + p) * ldq + q) =
+          y + dress_d4{acc[m][0][r], acc[m][1][r], acc[m][2][r], acc[m][3][r]};
+    }
 }
 
 // Wave sum over the 64 lanes, every lane gets it (a fixed order).
@@ -245,9 +282,9 @@ __device__ __forceinline__ double wave_max(double x) {
 //   x = v + i:       bvo[i][a] = D[i][o+a]   - sum_k t1[k][a] D[i][k],  and boo[k][i] = D[i][k]
 // and the Coulomb part of the Fock matrix, f[p][q] = h[p][q] + 2 sum_Q J_Q B[p][q], J_Q = sum_k D[k][k]: its
 // virtual-virtual rows from the same reads, the others by the workgroups behind the columns.
-// A workgroup holds one column x and 32 values of a (eight per wave) and walks the Q in chunks of 64 with the
-// chunk's w rows in LDS.
-constexpr int kDressA = 32, kDressK = 128;
+// A workgroup holds one column x and 32 values of a; each wave takes every fourth chunk of 64 Q by itself (with a chunk
+// shared through LDS, each waited for its reads and three barriers: o8 v72 20, o13 v117 45, o20 v180 150 us, now 12, 37 and 112).
+constexpr int kDressA = 32;
 struct DressP {
   const double *B, *D, *t1, *h;
   double *bvv, *bvo, *boo, *f;
@@ -255,104 +292,105 @@ struct DressP {
   long ldq;
 };
 __global__ __launch_bounds__(kThreads) void dress_left_kernel(DressP p) {
-  extern __shared__ double sh[];  // of kDressK k at a time: w [.][64], t1 [.][kDressA]; J parts [4][64]
-  const int o = p.o, v = p.v, n = o + v, tid = threadIdx.x, lane = tid & 63, ok = min(o, kDressK);
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __shared__ double part[kDressA][4][17];  // sums of J B over a wave's chunks, by row and column of a tile
+  const int o = p.o, v = p.v, n = o + v, lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const long ldq = p.ldq;
-  double* w = sh;
-  double* t = sh + ok * 64;
-  double* jp = t + ok * kDressA;
-  // J of one chunk of 64 Q, for this lane
-  auto trace = [&](long q0) -> double {
-    double s = 0.0;
-    if (q0 + lane < ldq)
-      for (int k = wave; k < o; k += 4) s += p.D[((long)k * n + k) * ldq + q0 + lane];
-    __syncthreads();
-    jp[wave * 64 + lane] = s;
-    __syncthreads();
-    return ((jp[lane] + jp[64 + lane]) + jp[128 + lane]) + jp[192 + lane];
+  const int x = blockIdx.x, a0 = blockIdx.y * kDressA, i = x - v;
+  const bool vv = x < v, coul = x >= n, dots = vv || coul;
+  const int nrow = n * n - v * v, y0 = ((x - n) * (int)gridDim.y + (int)blockIdx.y) * 32;
+  if (coul && y0 >= nrow) return;
+  const int valid = coul ? min(32, nrow - y0) : min(32, v - a0);  // rows past it repeat the last one and are not stored
+  // row of the block: of the a of column x or, behind the columns, of the pairs (p, q) with p or q occupied (rows of
+  // the occupied p first, then (o + a, k))
+  auto row_of = [&](int z) -> int {
+    z = min(z, valid - 1);
+    if (!coul) return vv ? (o + a0 + z) * n + o + x : i * n + o + a0 + z;
+    const int y = y0 + z;
+    return y < o * n ? y : (o + (y - o * n) / o) * n + (y - o * n) % o;
   };
-  const int x = blockIdx.x, a0 = blockIdx.y * kDressA;
-  if (x >= n) {  // Coulomb rows (p, q) with p or q occupied: 32 per workgroup
-    const long nrow = (long)n * n - (long)v * v, r0 = ((long)(x - n) * gridDim.y + blockIdx.y) * 32;
-    if (r0 >= nrow) return;
-    double dot[8];
-    long row[8];
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const long y = r0 + wave * 8 + r;  // rows of the occupied p first, then (o + a, k)
-      row[r] = y >= nrow ? -1 : y < (long)o * n ? y : (o + (y - (long)o * n) / o) * n + (y - (long)o * n) % o;
-      dot[r] = 0.0;
-    }
-    for (long q0 = 0; q0 < ldq; q0 += 64) {
-      const double j = trace(q0);
-      if (q0 + lane < ldq) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-          if (row[r] >= 0) dot[r] += j * p.B[row[r] * ldq + q0 + lane];
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const double s = wave_all(dot[r]);
-      if (lane == 0 && row[r] >= 0) p.f[row[r]] = p.h[row[r]] + 2.0 * s;
-    }
-    return;
-  }
-  const bool vv = x < v;
-  const int i = x - v;
-  const double* in = vv ? p.B + ((long)o * n + o + x) * ldq : p.D + ((long)i * n + o) * ldq;  // of a = 0
-  const long sin = vv ? n * ldq : ldq;
-  const double* wsrc = vv ? p.B + (long)(o + x) * ldq : p.D + (long)i * n * ldq;  // of k = 0
+  const double* in = vv || coul ? p.B : p.D;
+  const double* w = vv ? p.B + (long)(o + x) * ldq : p.D + (long)i * n * ldq;  // of k = 0
   const long sw = vv ? n * ldq : ldq;
-  double* out = vv ? p.bvv + (long)x * ldq : p.bvo + (long)i * v * ldq;
+  double* out = vv ? p.bvv + ((long)a0 * v + x) * ldq : p.bvo + ((long)i * v + a0) * ldq;
   const long sout = vv ? v * ldq : ldq;
-  double dot[8];
+  long row[2][4];
 #pragma unroll
-  for (int r = 0; r < 8; ++r) dot[r] = 0.0;
-  const int ab = a0 + wave * 8;
-  for (long q0 = 0; q0 < ldq; q0 += 64) {
-    const double j = vv ? trace(q0) : 0.0;
-    const long q = q0 + lane;
-    double acc[8];
+  for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      acc[r] = (q < ldq && ab + r < v) ? in[(ab + r) * sin + q] : 0.0;
-      dot[r] += j * acc[r];
-    }
-    for (int k0 = 0; k0 < o; k0 += kDressK) {
-      const int nk = min(kDressK, o - k0);
-      __syncthreads();
-      if (q0 == 0 || o > kDressK)
-        for (int y = tid; y < nk * kDressA; y += kThreads) {
-          const int a = a0 + y % kDressA;
-          t[y] = a < v ? p.t1[(long)(k0 + y / kDressA) * v + a] : 0.0;
-        }
-      for (int y = tid; y < nk * 64; y += kThreads) {
-        const long k = k0 + (y >> 6), qy = q0 + (y & 63);
-        const double z = qy < ldq ? wsrc[k * sw + qy] : 0.0;
-        w[y] = z;
-        if (!vv && blockIdx.y == 0 && qy < ldq) p.boo[(k * o + i) * ldq + qy] = z;
+    for (int r = 0; r < 4; ++r) row[m][r] = row_of(16 * m + lq + 4 * r) * ldq;
+  double dot[2][4] = {};
+  for (long qc = 64 * wave; qc < ldq; qc += 256) {
+    const long q0 = qc + 4 * l16, q = q0 < ldq ? q0 : 0;
+    const bool inq = q0 < ldq;
+    auto load = [](const double* x) { return *reinterpret_cast<const dress_d4*>(x); };
+    dress_d4 acc[2][4];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const dress_d4 y = load(in + row[m][r] + q);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[m][j][r] = y[j];
       }
-      __syncthreads();
-      for (int k = 0; k < nk; ++k) {
-        const double z = w[k * 64 + lane];
+    if (dots) {  // J: every fourth k per lane group
+      dress_d4 J{0.0, 0.0, 0.0, 0.0};
+      for (int k = lq; k < o; k += 4) J += load(p.D + (long)k * (n + 1) * ldq + q);
 #pragma unroll
-        for (int r = 0; r < 8; ++r) acc[r] -= t[k * kDressA + wave * 8 + r] * z;
+      for (int j = 0; j < 4; ++j) {
+        double y = J[j];
+        y += __shfl_xor(y, 16, 64);
+        y += __shfl_xor(y, 32, 64);
+        if (inq)
+#pragma unroll
+          for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dot[m][r] += y * acc[m][j][r];
       }
     }
-    if (q < ldq) {
+    if (coul) continue;
+#pragma unroll 2
+    for (int kg = 0; kg < o; kg += 4) {
+      const int k = kg + lq, kk = min(k, o - 1);
+      double t[2];
 #pragma unroll
-      for (int r = 0; r < 8; ++r)
-        if (ab + r < v) out[(ab + r) * sout + q] = acc[r];
+      for (int m = 0; m < 2; ++m) {
+        const double y = p.t1[(long)kk * v + min(a0 + 16 * m + l16, v - 1)];
+        t[m] = k < o ? -y : 0.0;
+      }
+      dress_d4 z = load(w + kk * sw + q);
+      if (!vv && blockIdx.y == 0 && k < o && inq) *reinterpret_cast<dress_d4*>(p.boo + ((long)k * o + i) * ldq + q) = z;
+      z = k < o ? z : dress_d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[m][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[m], z[j], acc[m][j], 0, 0, 0);
     }
+    if (!inq) continue;
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (16 * m + lq + 4 * r < valid)
+          *reinterpret_cast<dress_d4*>(out + (16 * m + lq + 4 * r) * sout + q) =
+              dress_d4{acc[m][0][r], acc[m][1][r], acc[m][2][r], acc[m][3][r]};
   }
-  if (!vv) return;
+  if (!dots) return;
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const double s = wave_all(dot[r]);
-    const long row = (long)(o + ab + r) * n + o + x;
-    if (lane == 0 && ab + r < v) p.f[row] = p.h[row] + 2.0 * s;
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[16 * m + lq + 4 * r][wave][l16] = dot[m][r];
+  __syncthreads();
+  // eight lanes per row, eight of its 64 sums each
+  const int z = threadIdx.x >> 3, e = threadIdx.x & 7;
+  double s = 0.0;
+#pragma unroll
+  for (int y = 0; y < 8; ++y) s += part[z][e >> 1][8 * (e & 1) + y];
+#pragma unroll
+  for (int off = 4; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  if (e == 0 && z < valid) {
+    const int f = row_of(z);
+    p.f[f] = p.h[f] + 2.0 * s;
   }
 }
 
@@ -1279,38 +1317,29 @@ static bool chk(const void* p, long n, const char* what) { return range_ok(p, 0,
 
 hipError_t dress_right(double* D, const double* B, const double* t1, int o, int v, long ldq, hipStream_t s) {
   const long n = o + v;
-  if (o < 1 || v < 1 || ldq < 1 || n > 65535) return hipErrorInvalidValue;
+  if (o < 1 || v < 1 || ldq < 1 || ldq % 4 || n > 65535) return hipErrorInvalidValue;
   if (bounds_checking() && !(chk(D, o * n * ldq, "dress D") && chk(B, n * n * ldq, "dress B") && chk(t1, (long)o * v, "dress t1")))
     return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
-  // sums per thread: the multiple of 8 that holds o in the fewest passes over B (at most 40)
-  const int passes = (o + 39) / 40, kc = ((o + passes - 1) / passes + 7) / 8 * 8;
-  const dim3 grid((unsigned)((ldq + kDressCols - 1) / kDressCols), (unsigned)n, (unsigned)((o + kc - 1) / kc));
-  switch (kc) {
-    case 8: hipLaunchKernelGGL(dress_right_kernel<8>, grid, dim3(kDressCols), 0, s, D, B, t1, o, v, ldq); break;
-    case 16: hipLaunchKernelGGL(dress_right_kernel<16>, grid, dim3(kDressCols), 0, s, D, B, t1, o, v, ldq); break;
-    case 24: hipLaunchKernelGGL(dress_right_kernel<24>, grid, dim3(kDressCols), 0, s, D, B, t1, o, v, ldq); break;
-    case 32: hipLaunchKernelGGL(dress_right_kernel<32>, grid, dim3(kDressCols), 0, s, D, B, t1, o, v, ldq); break;
-    default: hipLaunchKernelGGL(dress_right_kernel<40>, grid, dim3(kDressCols), 0, s, D, B, t1, o, v, ldq);
-  }
+  // the fewest passes over B with at most 48 values of k each
+  const int passes = (o + 47) / 48, mt = ((o + passes - 1) / passes + 15) / 16;
+  const dim3 grid((unsigned)((ldq + 63) / 64), (unsigned)n, (unsigned)((o + 16 * mt - 1) / (16 * mt)));
+  hipLaunchKernelGGL(mt == 1 ? dress_right_kernel<1> : mt == 2 ? dress_right_kernel<2> : dress_right_kernel<3>, grid, dim3(kThreads), 0,
+                     s, D, B, t1, o, v, ldq);
   return hipGetLastError();
 }
 
 hipError_t dress_left(double* bvv, double* bvo, double* boo, double* f, const double* B, const double* D,
                       const double* t1, const double* h, int o, int v, long ldq, hipStream_t s) {
   const long n = o + v, oo = (long)o * o, ov = (long)o * v, vv = (long)v * v;
-  if (o < 1 || v < 1 || o > 256 || ldq < 1) return hipErrorInvalidValue;
+  if (o < 1 || v < 1 || o > 256 || ldq < 1 || ldq % 4) return hipErrorInvalidValue;
   if (bounds_checking() && !(chk(bvv, vv * ldq, "dress B^vv") && chk(bvo, ov * ldq, "dress B^vo") && chk(boo, oo * ldq, "dress B^oo") &&
                              chk(f, n * n, "dress f") && chk(B, n * n * ldq, "dress B") && chk(D, o * n * ldq, "dress D") &&
                              chk(t1, ov, "dress t1") && chk(h, n * n, "dress h")))
     return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
   const long ga = (v + kDressA - 1) / kDressA, rest = (n * n - vv + 31) / 32;  // a blocks; Coulomb workgroups
-  const size_t lds = ((size_t)std::min(o, kDressK) * (64 + kDressA) + 256) * sizeof(double);
-  if (lds > 64 * 1024 &&
-      hipFuncSetAttribute(reinterpret_cast<const void*>(dress_left_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-    return hipErrorInvalidValue;
-  hipLaunchKernelGGL(dress_left_kernel, dim3((unsigned)(n + (rest + ga - 1) / ga), (unsigned)ga), dim3(kThreads), lds, s,
+  hipLaunchKernelGGL(dress_left_kernel, dim3((unsigned)(n + (rest + ga - 1) / ga), (unsigned)ga), dim3(kThreads), 0, s,
                      DressP{B, D, t1, h, bvv, bvo, boo, f, o, v, ldq});
   return hipGetLastError();
 }
