@@ -907,8 +907,10 @@ hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
   const bool amf = (g.sam == 1 && g.sak != 1);
   const bool bnf = (g.sbn == 1) || (g.sbk != 1);
   const long tiles128 = (long)((g.M + 127) / 128) * ((g.N + 127) / 128) * nbatch;
-  if (g.M >= 96 && g.N >= 96 && tiles128 >= 256) {
-    // Large outputs: among 128x128 (4 waves), 256x128 and 192x192 (8 waves) take the least
+  if (g.M >= 96 && g.N >= 96 && tiles128 >= 256 && (long)g.K * g.nred > 512) {
+    // Large outputs over more than a few stages (a short K is bound by the output's traffic, which two 64 x 64 workgroups per
+    // CU keep in flight: -= t1^T W' over 400 outputs of 180 x 180 and K = 20 94 -> 62 us, hole-hole pairs o20 v180 111 -> 102):
+    // among 128x128 (4 waves), 256x128 and 192x192 (8 waves) take the least
     // estimated time = whole rounds of 256 tiles x tile area / sustained rate (measured on full
     // rounds: 59.5, 60, 61.5 TFLOP/s), which prices both the padding of M and N and the partly
     // filled last round.
