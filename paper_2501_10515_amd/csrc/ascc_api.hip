@@ -889,7 +889,9 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2;
   phase_begin(I, PH_DRESS, s);
   EACH_SLOT HIPCHK(dress_right(S(I->D), S(I->B), S(t1), o, v, lq, s));
-  EACH_SLOT HIPCHK(dress_left(S(I->Bvv), S(I->BvoTt), S(I->Boo), S(I->Fh), S(I->B), S(I->D), S(t1), S(I->h), o, v, lq, s));
+  EACH_SLOT HIPCHK(dress_left(S(I->Bvv), S(I->BvoTt), S(I->Boo), S(I->Fh), S(I->B), S(I->D), S(t1), S(I->h), o, v, lq,
+                              lowp_kind(I), lowp ? S(I->BvvTf) : nullptr, lowp ? S(I->BvoTtf) : nullptr,
+                              lowp ? S(I->BooTf) : nullptr, s));
   phase_end(I, s);
   // --- amplitude views: Tx[iajb] = t2[ijba], U[iajb] = 2 t2[ijab] - t2[ijba] and, where the ladder is computed
   // here, its pair rows t+-
@@ -944,9 +946,6 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   }
   HIPCHK(mm_group(I, first, s));
   if (lowp) {  // the same products on low-precision shadows (B^_kc ones are constant)
-    HIPCHK(shadow_q(I, I->BvoTtf, I->BvoTt, ov, s));
-    HIPCHK(shadow_q(I, I->BooTf, I->Boo, oo, s));
-    HIPCHK(shadow_q(I, I->BvvTf, I->Bvv, vv, s));
     HIPCHK(glp(lp_nt(I, oo, vv, Q, 1, I->BooTf, lQ, 0, I->BvvTf, lQ, 0, I->G2, vv, 0), s));    // g^_kiac
     HIPCHK(glp(lp_nt(I, ov, ov, Q, 1, I->BvoTtf, lQ, 0, I->BovTf, lQ, 0, I->G3, ov, 0), s));   // g^_aikc
     GemmLP g = lp_nt(I, Q, ov, ov, 1, I->Bovf, lov, 0, I->TUf + ov * lov, lov, 0, I->Nq, 1, 0);
@@ -972,7 +971,8 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   }
   phase_end(I, s);
   phase_begin(I, PH_RING_XZ, s);
-  EACH_SLOT HIPCHK(ring_xz(S(I->XZ), S(I->XZ) + ov * ldov, ldov, S(I->G2), S(I->G3), S(I->Y), S(I->Y) + ovov, o, v, s));
+  if (lowp) EACH_SLOT HIPCHK(ring_xz_lowp(lowp_kind(I), S(I->XZf), lov, S(I->G2), S(I->G3), S(I->Y), S(I->Y) + ovov, o, v, s));
+  else EACH_SLOT HIPCHK(ring_xz(S(I->XZ), S(I->XZ) + ov * ldov, ldov, S(I->G2), S(I->G3), S(I->Y), S(I->Y) + ovov, o, v, s));
   phase_end(I, s);
 
   // --- products of N_Q: F'_bc = F^_bc - sum_Qk N_Q[k,b] B_Q,kc, F''_kj = F^_kj + sum_Qd B_Q,kd N_Q[j,d] (E term) and
@@ -1054,7 +1054,6 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   // --- rings: P1 = Tx Xc^T, P2 = U Zd^T (batched pair)
   phase_begin(I, PH_RING_P, s);
   if (lowp) {
-    HIPCHK(shadow_ov(I, I->XZf, I->XZ, s));
     HIPCHK(glp(lp_nt(I, ov, ov, ov, 2, I->TUf, lov, ov * lov, I->XZf, lov, ov * lov, I->P, ov, ovov), s));
   } else if (!ring_p_done) {
     HIPCHK(mm(I, ring_p, s));

@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "lowp.h"
 
 namespace ascc {
 namespace {
@@ -290,8 +291,10 @@ struct DressP {
   double *bvv, *bvo, *boo, *f;
   int o, v;
   long ldq;
+  Shadow svv, svo, soo;  // of bvv, bvo and boo, or none
 };
-__global__ __launch_bounds__(kThreads) void dress_left_kernel(DressP p) {
+template <bool SHADOW>
+__global__ __launch_bounds__(kThreads, 2) void dress_left_kernel(DressP p) {
   __shared__ double part[kDressA][4][17];  // sums of J B over a wave's chunks, by row and column of a tile
   const int o = p.o, v = p.v, n = o + v, lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -324,6 +327,12 @@ __global__ __launch_bounds__(kThreads) void dress_left_kernel(DressP p) {
     const long q0 = qc + 4 * l16, q = q0 < ldq ? q0 : 0;
     const bool inq = q0 < ldq;
     auto load = [](const double* x) { return *reinterpret_cast<const dress_d4*>(x); };
+    // this lane's four columns of a shadow's row; past ldq (less than a chunk) zeros
+    auto shadow = [&](const Shadow& s, long srow, double y0, double y1, double y2, double y3) {
+      if (q0 >= s.ld) return;
+      const double d[4] = {inq ? y0 : 0.0, inq ? y1 : 0.0, inq ? y2 : 0.0, inq ? y3 : 0.0};
+      put_lowp4(s, srow, q0, d);
+    };
     dress_d4 acc[2][4];
 #pragma unroll
     for (int m = 0; m < 2; ++m)
@@ -359,21 +368,28 @@ __global__ __launch_bounds__(kThreads) void dress_left_kernel(DressP p) {
         t[m] = k < o ? -y : 0.0;
       }
       dress_d4 z = load(w + kk * sw + q);
-      if (!vv && blockIdx.y == 0 && k < o && inq) *reinterpret_cast<dress_d4*>(p.boo + ((long)k * o + i) * ldq + q) = z;
+      if (!vv && blockIdx.y == 0 && k < o) {
+        if (inq) *reinterpret_cast<dress_d4*>(p.boo + ((long)k * o + i) * ldq + q) = z;
+        if constexpr (SHADOW) shadow(p.soo, (long)k * o + i, z[0], z[1], z[2], z[3]);
+      }
       z = k < o ? z : dress_d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int m = 0; m < 2; ++m)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[m][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[m], z[j], acc[m][j], 0, 0, 0);
     }
-    if (!inq) continue;
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (16 * m + lq + 4 * r < valid)
-          *reinterpret_cast<dress_d4*>(out + (16 * m + lq + 4 * r) * sout + q) =
-              dress_d4{acc[m][0][r], acc[m][1][r], acc[m][2][r], acc[m][3][r]};
+      for (int r = 0; r < 4; ++r) {
+        const int z = 16 * m + lq + 4 * r;
+        if (z >= valid) continue;
+        if (inq)
+          *reinterpret_cast<dress_d4*>(out + z * sout + q) = dress_d4{acc[m][0][r], acc[m][1][r], acc[m][2][r], acc[m][3][r]};
+        if constexpr (SHADOW)
+          shadow(vv ? p.svv : p.svo, vv ? (long)(a0 + z) * v + x : (long)i * v + a0 + z, acc[m][0][r], acc[m][1][r], acc[m][2][r],
+                 acc[m][3][r]);
+      }
   }
   if (!dots) return;
 #pragma unroll
@@ -1004,6 +1020,34 @@ __global__ __launch_bounds__(kThreads) void ring_xz_kernel(double* __restrict__ 
   }
 }
 
+// The same, written as low-precision shadows alone (rows ia and, for Zd, o v + ia, zero past o v): four columns per thread, which
+// makes the stores 8 or 16 bytes (o20 v180: 132 + 53 us with FP64 rows and their conversion, 144 us as one pass).
+__global__ __launch_bounds__(kThreads) void ring_xz_lowp_kernel(Shadow s, const double* __restrict__ g2,
+                                                               const double* __restrict__ g3, const double* __restrict__ y1,
+                                                               const double* __restrict__ y2, int o, int v) {
+  const long ia = blockIdx.x, ov = (long)o * v, row = ia * ov;
+  const double* g = g2 + ia * v;
+  for (int x = 4 * threadIdx.x; x < s.ld; x += 4 * kThreads) {
+    double a[4], b[4];
+    int k = x / v, c = x - k * v;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      a[j] = b[j] = 0.0;
+      if (x + j < ov) {
+        const double q = g[(long)k * ov * v + c];
+        a[j] = q - 0.5 * y1[row + x + j];
+        b[j] = 2.0 * g3[row + x + j] - q + 0.5 * y2[row + x + j];
+      }
+      if (++c == v) {
+        c = 0;
+        ++k;
+      }
+    }
+    put_lowp4(s, ia, x, a);
+    put_lowp4(s, ov + ia, x, b);
+  }
+}
+
 // From the pair rows Rw+-[p(i,j)][m] of W/Z (m = k*v + b: W_ij[k,b] = sum_cd (kc|bd) t_ij^cd, m = ov + k*o + l:
 // Z_ij[k,l] = sum_cd (kc|ld) t_ij^cd; X_ij = X+ + X-, X_ji = X+ - X-), with rows at stride ldr:
 //   wp[ij][k][b] = W_ij[k,b] - 1/2 sum_l Z_ij[k,l] t1[l][b]   (rows at stride ldw)
@@ -1330,7 +1374,13 @@ hipError_t dress_right(double* D, const double* B, const double* t1, int o, int 
 }
 
 hipError_t dress_left(double* bvv, double* bvo, double* boo, double* f, const double* B, const double* D,
-                      const double* t1, const double* h, int o, int v, long ldq, hipStream_t s) {
+                      const double* t1, const double* h, int o, int v, long ldq, int prec, float* svv, float* svo, float* soo,
+                      hipStream_t s) {
+  const long ls = lowp_ld(ldq);  // naux <= ldq <= naux rounded up to 16
+  if (svv && bounds_checking() && !(range_ok(svv, 0, (long)v * v * ls - 1, 4, "B^vv shadow") &&
+                                    range_ok(svo, 0, (long)o * v * ls - 1, 4, "B^vo shadow") &&
+                                    range_ok(soo, 0, (long)o * o * ls - 1, 4, "B^oo shadow")))
+    return hipErrorInvalidValue;
   const long n = o + v, oo = (long)o * o, ov = (long)o * v, vv = (long)v * v;
   if (o < 1 || v < 1 || o > 256 || ldq < 1 || ldq % 4) return hipErrorInvalidValue;
   if (bounds_checking() && !(chk(bvv, vv * ldq, "dress B^vv") && chk(bvo, ov * ldq, "dress B^vo") && chk(boo, oo * ldq, "dress B^oo") &&
@@ -1339,8 +1389,8 @@ hipError_t dress_left(double* bvv, double* bvo, double* boo, double* f, const do
     return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
   const long ga = (v + kDressA - 1) / kDressA, rest = (n * n - vv + 31) / 32;  // a blocks; Coulomb workgroups
-  hipLaunchKernelGGL(dress_left_kernel, dim3((unsigned)(n + (rest + ga - 1) / ga), (unsigned)ga), dim3(kThreads), 0, s,
-                     DressP{B, D, t1, h, bvv, bvo, boo, f, o, v, ldq});
+  hipLaunchKernelGGL(svv ? dress_left_kernel<true> : dress_left_kernel<false>, dim3((unsigned)(n + (rest + ga - 1) / ga), (unsigned)ga), dim3(kThreads), 0, s,
+                     DressP{B, D, t1, h, bvv, bvo, boo, f, o, v, ldq, {svv, ls, prec}, {svo, ls, prec}, {soo, ls, prec}});
   return hipGetLastError();
 }
 
@@ -1688,6 +1738,18 @@ hipError_t amp_views(double* Tx, double* U, long ld, double* tplus, double* tmin
   if (dry_run()) return hipSuccess;
   hipLaunchKernelGGL(amp_views_kernel, dim3((unsigned)To, (unsigned)(nblk * (nblk + 1) / 2)), dim3(kThreads), 0, s, Tx, U,
                      ld, tplus, tminus, ldo, t2, o, v);
+  return hipGetLastError();
+}
+
+hipError_t ring_xz_lowp(int prec, float* xz, long ld, const double* g2, const double* g3, const double* y1, const double* y2,
+                        int o, int v, hipStream_t s) {
+  const long ov = (long)o * v;
+  if (ld < ov || ld % 32) return hipErrorInvalidValue;
+  if (bounds_checking() && !(range_ok(xz, 0, 2 * ov * ld - 1, 4, "ring Xc|Zd shadow") && chk(g2, ov * ov, "ring g_kiac") &&
+                             chk(g3, ov * ov, "ring g_aikc") && chk(y1, ov * ov, "ring Y1") && chk(y2, ov * ov, "ring Y2")))
+    return hipErrorInvalidValue;
+  if (dry_run()) return hipSuccess;
+  hipLaunchKernelGGL(ring_xz_lowp_kernel, dim3((unsigned)ov), dim3(kThreads), 0, s, Shadow{xz, ld, prec}, g2, g3, y1, y2, o, v);
   return hipGetLastError();
 }
 

@@ -25,6 +25,7 @@
 #include <utility>
 
 #include "internal.h"
+#include "lowp.h"
 
 namespace ascc {
 namespace {
@@ -39,15 +40,6 @@ typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 // element has one writer (the lane that owns it) and its chunks arrive in order, so the sums are
 // those of a load-add-store; the stores of a chunk are waited for before any add follows.
 __device__ __forceinline__ void add_to(double* p, double v) { unsafeAtomicAdd(p, v); }
-
-// Round-to-nearest-even FP32 -> bf16 bits (finite inputs; NaN stays NaN).
-__device__ __forceinline__ unsigned short bf16_rne(float f) {
-  const uint32_t u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u) return (unsigned short)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-  const uint32_t r = u + 0x7fffu + ((u >> 16) & 1u);
-  return (unsigned short)(r >> 16);
-}
-__device__ __forceinline__ float bf16_to_f(unsigned short h) { return __uint_as_float(((uint32_t)h) << 16); }
 
 // Workgroup to tile, walked in groups of 8 M-tiles (M fastest inside a group): the workgroups resident on one
 // XCD at a time cover a compact block of C and share A and B slices in its L2.

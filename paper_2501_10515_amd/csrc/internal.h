@@ -235,6 +235,8 @@ hipError_t pack_gwz(double* gplus, double* gminus, long ldo, const double* kcbd,
 // (formulas at the kernels)
 hipError_t amp_views(double* Tx, double* U, long ld, double* tplus, double* tminus, long ldo, const double* t2, int o,
                      int v, hipStream_t s);
+hipError_t ring_xz_lowp(int prec, float* xz, long ld, const double* g2, const double* g3, const double* y1, const double* y2,
+                        int o, int v, hipStream_t s);  // as the shadow [2][ov][ld] alone
 hipError_t ring_xz(double* xc, double* zd, long ld, const double* g2, const double* g3, const double* y1,
                    const double* y2, int o, int v, hipStream_t s);
 // W' and chi+- from the W/Z columns of the ladder's pair rows (formulas at the kernel)
@@ -250,8 +252,10 @@ hipError_t unpack_rpm(double* RL, const double* Rplus, const double* Rminus, lon
 //   coulomb      f = f0 + alpha sum_Q J_Q B, J_Q = sum_k B[k][k]
 //   fock_finish  F^ = X f Y^T: fvv [v][v], foo [o][o], r1 = F^_ai at [i][a], fov [o][v] (zero to ldf elements)
 hipError_t dress_right(double* D, const double* B, const double* t1, int o, int v, long ldq, hipStream_t s);
+// (with svv given also their low-precision shadows, rows at stride lowp_ld(ldq))
 hipError_t dress_left(double* bvv, double* bvo, double* boo, double* f, const double* B, const double* D,
-                      const double* t1, const double* h, int o, int v, long ldq, hipStream_t s);
+                      const double* t1, const double* h, int o, int v, long ldq, int prec, float* svv, float* svo, float* soo,
+                      hipStream_t s);
 hipError_t coulomb(double* f, const double* f0, const double* B, double alpha, int o, int n, long ldq, hipStream_t s);
 hipError_t fock_finish(double* fvv, double* foo, double* r1, double* fov, long ldf, const double* f, const double* t1,
                        int o, int v, hipStream_t s);
