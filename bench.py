@@ -698,7 +698,7 @@ def headline(args):
         },
         "roofline": {
             "bound": "mfma",
-            "kernel": "ring products: gemm_f64_dma_kernel 192x192, one launch per pair (Y1 = Tx K with Y2 = U L, "
+            "kernel": "ring products: gemm_f64_dma_kernel, one launch per pair (Y1 = Tx K with Y2 = U L, "
                       "then P1 with P2)",
             "achieved": fp64.get("ring_tflops"), "peak": PEAKS["fp64"], "unit": "TFLOP/s",
             "frac": fp64.get("ring_frac"), "traffic": None, "launch_ms": ring_ms,
@@ -975,34 +975,41 @@ def summarize_counters(passes, args):
     out["bf16x3_step"] = agg(list(range(ends[2] + 1, ends[3] + 1)))
     fp32_first = ends[4] + 1  # the FP32 step follows its warm-up
     out["fp32_step"] = agg(list(range(fp32_first, ends[5] + 1)))
-    # the pp-ladder launch of each step: its first contraction after the pair packing
+    # the pp-ladder launch of each step: the longest contraction between the ring operands and the kernel that reads the
+    # ladder's pair rows (in FP64 a packed ladder carries the W/Z rows as well)
     def ladder(rng, tag):
         ks = list(rng)
-        pk = [k for k in ks if "pack_tpm" in seq[k][0]["kernel"]]
-        if not pk:
+        first = [k for k in ks if "ring_xz" in seq[k][0]["kernel"]]
+        last = [k for k in ks if "wz_chi" in seq[k][0]["kernel"] or "unpack_rpm" in seq[k][0]["kernel"]]
+        if not first or not last:
             return None
-        gm = [k for k in ks if k > pk[0] and "gemm_" in seq[k][0]["kernel"]]
+        gm = [k for k in ks if first[0] < k < last[0] and "gemm_" in seq[k][0]["kernel"] and "group" not in seq[k][0]["kernel"]]
         if not gm:
             return None
-        # a ladder whose last row tile runs as tail tiles is two launches
-        parts = gm[:2] if len(gm) > 1 and "_tail_" in seq[gm[1]][0]["kernel"] else gm[:1]
-        a = agg(parts)
-        name = seq[gm[0]][0]["kernel"]
+        top = max(gm, key=lambda k: seq[k][0]["c"].get("GRBM_GUI_ACTIVE", 0.0))
+        a = agg([top])
+        name = seq[top][0]["kernel"]
         name = name[name.find("gemm_"):]
-        return {"kernel": name[:max(name.find("("), 0) or len(name)][:60] + (" + tail" if len(parts) > 1 else ""),
-                "traffic_bytes": a["hbm_bytes"],
-                "mfma_util": a["mfma_util"], "algorithmic_flops": ladder_flops(o, v),
+        flops = ladder_flops(o, v)
+        if tag == "fp64" and args.vvvv == "packed":
+            flops += 4.0 * (o * (o + 1) // 2) * (v * (v + 1) // 2) * (o * v + o * o)
+        return {"kernel": name[:max(name.find("("), 0) or len(name)][:60], "traffic_bytes": a["hbm_bytes"],
+                "mfma_util": a["mfma_util"], "algorithmic_flops": flops,
                 "mfma_flops_executed": a["mfma_flops_executed"], "step": tag}
     for tag, rng in (("fp64", fp64_step), ("bf16x3", range(ends[2] + 1, ends[3] + 1)),
                      ("fp32", range(fp32_first, ends[5] + 1))):
         lad = ladder(rng, tag)
         if lad:
             out[f"{tag}_ladder_launch"] = lad
-    # the ring launches of the FP64 step: its direct-to-LDS FP64 GEMM dispatches with the largest grid
+    # the ring launches of the FP64 step: its longest direct-to-LDS FP64 GEMM before the ring operands are formed and
+    # the longest after the ladder's pair rows are read
+    active = lambda k: seq[k][0]["c"].get("GRBM_GUI_ACTIVE", 0.0)
     dma = [k for k in fp64_step if "gemm_f64_dma_kernel" in seq[k][0]["kernel"]]
-    if dma:
-        gmax = max(seq[k][0]["grid"] for k in dma)
-        ring = [k for k in dma if seq[k][0]["grid"] == gmax]
+    xz = [k for k in fp64_step if "ring_xz" in seq[k][0]["kernel"]]
+    wz = [k for k in fp64_step if "wz_chi" in seq[k][0]["kernel"]]
+    early, late = [k for k in dma if xz and k < xz[0]], [k for k in dma if wz and k > wz[-1]]
+    ring = [max(ks, key=active) for ks in (early, late) if ks]
+    if ring:
         per = [agg([k]) for k in ring]
         name = seq[ring[0]][0]["kernel"]
         name = name[name.find("gemm_f64_dma_kernel"):]

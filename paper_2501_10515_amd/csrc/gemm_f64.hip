@@ -653,16 +653,18 @@ hipError_t launch_dma(GP p, int nb1, int split, double* ws, bool ordered, hipStr
 //   6 us + (stages of a slice + 2) x max(tiles per CU x t, t1) + 5 us and the partial tiles' traffic if split
 // with t the time of one stage of one tile on a busy CU and t1 its latency alone (us, measured: sweeps of tile
 // and split over 100..3600 squared outputs; the choice stays within 10 % of the best of them).  Where the
-// outputs are few, small tiles with K split keep every CU busy: 1521 x 1521 x 1522 twice 450 -> 254 us,
-// 576 x 576 x 240 75 -> 17 us, 390 x 1521 x 1522 70 -> 55 us against 192- to 256-row tiles.
+// outputs are few, small tiles with K split keep every CU busy: 576 x 576 x 240 75 -> 17 us, 390 x 1521 x 1522 70 -> 55 us
+// against 192- to 256-row tiles; in between, the height that fills a round: 1521 x 1521 x 1522 twice takes 254 us in 96 x 96
+// tiles (two rounds), 235 in 160 x 128 ones (240 workgroups).
 // nb1d: the outer batch count the choice is made for; where the partial tiles of all blocks do not fit the
 // scratch, the blocks run in several launches, so that a block's sums never depend on the batch.
 struct DmaCfg {
   int bm, bn;
   double t, t1;
 };
-constexpr DmaCfg kDmaCfg[] = {{192, 192, 4.19, 4.19}, {256, 128, 3.80, 3.80}, {224, 128, 3.45, 3.45}, {128, 128, 1.93, 1.93},
-                              {96, 96, 1.31, 1.45},   {64, 64, 0.58, 0.70},   {32, 32, 0.185, 0.50}};
+constexpr DmaCfg kDmaCfg[] = {{192, 192, 4.06, 4.06}, {256, 128, 3.68, 3.68}, {224, 128, 3.25, 3.25}, {128, 128, 1.88, 1.88},
+                              {96, 96, 1.27, 1.41},   {64, 64, 0.57, 0.69},   {32, 32, 0.185, 0.50},  {192, 128, 2.80, 2.80},
+                              {160, 128, 2.36, 2.36}};
 struct DmaPlan {
   int cfg, split;
   double us;
@@ -717,6 +719,8 @@ hipError_t launch_dma_auto(const GP& p0, int nb1, int nb1d, double* ws, long ws_
     switch (best) {
       case 0: e = launch_dma<192, 192, 2, 4, 3>(p, n, best_split, ws, false, s); break;
       case 1: e = launch_dma<256, 128, 4, 2, 3>(p, n, best_split, ws, false, s); break;
+      case 7: e = launch_dma<192, 128, 2, 4, 3>(p, n, best_split, ws, false, s); break;
+      case 8: e = launch_dma<160, 128, 2, 4, 3>(p, n, best_split, ws, false, s); break;
       case 2: e = launch_dma<224, 128, 2, 4, 3>(p, n, best_split, ws, false, s); break;
       case 3: e = launch_dma<128, 128, 2, 4, 3>(p, n, best_split, ws, false, s); break;
       case 4: e = launch_dma<96, 96, 2, 2, 3>(p, n, best_split, ws, false, s); break;
