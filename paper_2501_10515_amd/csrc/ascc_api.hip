@@ -637,7 +637,7 @@ LadderRows own_rows(const ascc_ints* I) {
 // G+- = (kc|bd) +- (kd|bc) | (kc|ld) +- (kd|lc) join them: W_ij[k,b] = sum_cd (kc|bd) t_ij^cd and
 // Z_ij[k,l] = sum_cd (kc|ld) t_ij^cd in the same halves, half the products of the full sum over c, d.  PACKED
 // stores V+- and G+- as one matrix, one launch for both (a fuller last round: o30 v270 53.5 + 19.8 ms as
-// two launches, 44 as one); FULL stores the (ac|bd) matrix in pair order, whose halves V[n][k] +- V[pm[n]][k]
+// two launches, 46.8 as one); FULL stores the (ac|bd) matrix in pair order, whose halves V[n][k] +- V[pm[n]][k]
 // are formed while they are staged, and G+- apart.  The S states' rows are stacked, so the vvvv operand
 // is streamed once for all of them; a state's sums are those it has alone.
 int ladder_launch(ascc_ints* I, long S, const double* Tp, double* Rp, const LadderBatch* lb, hipStream_t s) {
