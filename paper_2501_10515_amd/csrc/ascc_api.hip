@@ -639,8 +639,9 @@ LadderRows own_rows(const ascc_ints* I) {
 // stores V+- and G+- as one matrix, one launch for both (a fuller last round: o30 v270 53.5 + 19.8 ms as
 // two launches, 46.8 as one); FULL stores the (ac|bd) matrix in pair order, whose halves V[n][k] +- V[pm[n]][k]
 // are formed while they are staged, and G+- apart.  The S states' rows are stacked, so the vvvv operand
-// is streamed once for all of them; a state's sums are those it has alone.
-int ladder_launch(ascc_ints* I, long S, const double* Tp, double* Rp, const LadderBatch* lb, hipStream_t s) {
+// is streamed once for all of them; a state's sums are those it has alone.  wz_done: the G+- rows of a FULL set are.
+int ladder_launch(ascc_ints* I, long S, const double* Tp, double* Rp, const LadderBatch* lb, hipStream_t s,
+                  bool wz_done = false) {
   const int o = I->no, v = I->nv;
   const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2, wzl = I->ov + I->oo, M = S * To;
   const bool full = I->vvvv_mode == ASCC_VVVV_FULL;
@@ -664,6 +665,7 @@ int ladder_launch(ascc_ints* I, long S, const double* Tp, double* Rp, const Ladd
     L.vrows = I->vv;
     L.pm = pair_minus(I);
     HIPCHK(gemm_f64_ladder(L, s));
+    if (wz_done) return ASCC_OK;
     L.pm = nullptr;
     L.V = I->G;
     L.N = (int)wzl;
@@ -685,7 +687,7 @@ int ladder_launch(ascc_ints* I, long S, const double* Tp, double* Rp, const Ladd
 // Phases: pp_pack (pair packing and low-precision operands), pp_ladder (the contraction launch, nothing
 // else), pp_unpack (back to [i][j][a][b], where it is done).
 int pp_ladder_states(ascc_ints* I, int S, const double* const* t2s, double* Tp, double* Rp, float* Tpf,
-                     hipStream_t s) {
+                     hipStream_t s, bool wz_done = false) {
   const int o = I->no, v = I->nv;
   const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2;
   const long M = S * To, ldT = I->ldT;
@@ -703,7 +705,7 @@ int pp_ladder_states(ascc_ints* I, int S, const double* const* t2s, double* Tp, 
     g.m_dec = (int)To;  // the kernel choice of one state's rows
     HIPCHK(gemm_lowp(g, s));
   } else {
-    const int rc = ladder_launch(I, S, Tp, Rp, nullptr, s);
+    const int rc = ladder_launch(I, S, Tp, Rp, nullptr, s, wz_done);
     if (rc) return rc;
   }
   phase_end(I, s);
@@ -712,7 +714,7 @@ int pp_ladder_states(ascc_ints* I, int S, const double* const* t2s, double* Tp, 
 
 // The ladder of every slot of a batch, each against its own integral set, one contraction launch over
 // the slots.
-int pp_ladder_slots(ascc_ints* I, hipStream_t s) {
+int pp_ladder_slots(ascc_ints* I, hipStream_t s, bool wz_done) {
   const int o = I->no, v = I->nv;
   const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2, M = To;
   const bool lowp = I->cur_prec != ASCC_PREC_FP64;
@@ -734,7 +736,7 @@ int pp_ladder_slots(ascc_ints* I, hipStream_t s) {
     lb.sv = slot_stride(I->V) / 8;
     lb.sc = slot_stride(I->Rp) / 8;
     if (g_sb->bad) return fail(ASCC_E_STATE, "ladder operands outside the batch's slot ranges");
-    const int rc = ladder_launch(I, 1, I->Tp, I->Rp, &lb, s);
+    const int rc = ladder_launch(I, 1, I->Tp, I->Rp, &lb, s, wz_done);
     if (rc) return rc;
   }
   phase_end(I, s);
@@ -742,9 +744,9 @@ int pp_ladder_slots(ascc_ints* I, hipStream_t s) {
 }
 
 // The ladder of the amplitudes whose t+- rows amp_views has written.
-int pp_ladder(ascc_ints* I, hipStream_t s) {
-  if (nslots() > 1) return pp_ladder_slots(I, s);
-  return pp_ladder_states(I, 1, nullptr, I->Tp, I->Rp, I->Tpf, s);
+int pp_ladder(ascc_ints* I, hipStream_t s, bool wz_done) {
+  if (nslots() > 1) return pp_ladder_slots(I, s, wz_done);
+  return pp_ladder_states(I, 1, nullptr, I->Tp, I->Rp, I->Tpf, s, wz_done);
 }
 
 size_t ints_footprint(long o, long v, long Q, int precision, int mode) {
@@ -925,23 +927,28 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   ring_y.sb2 = ov * ldov;
   ring_y.sc2 = ovov;
   ring_y.nb2 = 2;
-  bool ring_y_done = false, ladder_done = lad != nullptr;
+  bool ring_y_done = false, ladder_done = lad != nullptr, wz_done = false;
   if (!lowp) {
     first.push_back(gemm_rm(oo, vv, kq, 1.0, I->Boo, lq, false, I->Bvv, lq, true, 0.0, I->G2, vv));    // g^_kiac
     first.push_back(gemm_rm(ov, ov, kq, 1.0, I->BvoTt, lq, false, I->BovT, lq, true, 0.0, I->G3, ov));  // g^_aikc
     first.push_back(gemm_rm(ov, lq, pad_even(ov), 1.0, U, ldov, false, I->Bov, ldov, true, 0.0, I->Nq, lq));
     ring_y_done = mm_small(I, ring_y);
     if (ring_y_done) first.push_back(ring_y);
-    // a ladder whose K is too short to be cut (ladder_plan) is summed whole by every kernel, stacked or not
-    if (!lad && I->vvvv_mode == ASCC_VVVV_PACKED && Tv <= kLadderWhole) {
-      Gemm g = gemm_rm(To, Tv + wzl, pad_even(Tv), 1.0, rows.Tp, I->ldT, false, I->V, I->ldT, true, 0.0, rows.Rp, I->ldR);
+    // a ladder whose K is too short to be cut (ladder_plan) is summed whole by every kernel, stacked or not; of a FULL
+    // set the W/Z rows join (o5 v20: 11 us as a launch of their own)
+    if (!lad && Tv <= kLadderWhole) {
+      const bool full = I->vvvv_mode == ASCC_VVVV_FULL;
+      const long n0 = full ? Tv : 0, rows_b = full ? wzl : Tv + wzl;
+      Gemm g = gemm_rm(To, rows_b, pad_even(Tv), 1.0, rows.Tp, I->ldT, false, full ? I->G : I->V, I->ldT, true, 0.0, rows.Rp + n0, I->ldR);
       g.sa2 = rows.st;
-      g.sb2 = (Tv + wzl) * I->ldT;
+      g.sb2 = rows_b * I->ldT;
       g.sc2 = rows.sr;
       g.nb2 = 2;
       g.fixed = true;
-      ladder_done = mm_small(I, g);
-      if (ladder_done) first.push_back(g);
+      if (mm_small(I, g)) {
+        (full ? wz_done : ladder_done) = true;
+        first.push_back(g);
+      }
     }
   }
   HIPCHK(mm_group(I, first, s));
@@ -1017,7 +1024,7 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     phase_end(I, s);
   }
   // --- particle-particle ladder over the undressed (ac|bd) (with W/Z in FP64), plus the hole-hole ladder
-  if (!ladder_done && (rc = pp_ladder(I, s))) return rc;
+  if (!ladder_done && (rc = pp_ladder(I, s, wz_done))) return rc;
   const bool pairs = !lowp && I->pl_hole < 0;  // the assembly reads the ladders as pair rows
   if (lowp) {
     phase_begin(I, PH_UNPACK, s);
