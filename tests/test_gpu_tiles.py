@@ -6,8 +6,8 @@ from gen.synth_df import make_system, random_amplitudes
 
 pytestmark = pytest.mark.gpu
 
-# FP64: a residual element is a sum of at most about 3000 products of the integrals and amplitudes, each product chain
-# rounded a few times: 3000 u = 3e-13 of the largest term, which is no larger than max|R| times ten here.
+# FP64: a residual element is a sum of at most about 5000 products of the integrals and amplitudes, each product chain
+# rounded a few times: 5000 u = 6e-13 of the largest term, which is no larger than max|R| times five here.
 # FP32 and split-BF16x3: as in test_gpu_lowp.py.
 REL = {"fp64": 3e-12, "fp32": 2e-6, "bf16x3": 4e-5}
 
@@ -23,6 +23,9 @@ REL = {"fp64": 3e-12, "fp32": 2e-6, "bf16x3": 4e-5}
     (9, 11, 40),   # ov = 99, T(v) = 66
     (13, 15, 48),  # ov = 195: one 192-row tile and three rows
     (16, 17, 64),  # o^2 = 256, T(o) = 136
+    (34, 6, 20),   # three tiles of occupied rows in the dressing
+    (52, 4, 24),   # two passes of them
+    (66, 3, 81),   # two chunks of fitting indices, the second almost empty
 ])
 def test_tile_edges(o, v, Q, mode, prec):
     import torch
