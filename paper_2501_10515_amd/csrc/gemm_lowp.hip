@@ -503,21 +503,13 @@ __global__ __launch_bounds__(256) void lowp_splitk_reduce(double* C, long scm, l
   }
 }
 
-// Split-K plan for a launch of `tiles` workgroups (one per CU) over nkt K-tiles of 32: slices of
-// at least 16 K-tiles, enough of them for one round of 256 workgroups, as the scratch allows.
-struct SplitPlan {
-  int split = 1, ktps = 0;
-};
-SplitPlan plan_split(const GemmLP& g, long tiles, int nkt) {
-  SplitPlan sp;
-  sp.ktps = nkt;
-  const long outs = (long)g.M * g.N * g.nb * g.nb1;
-  if (!g.ws || tiles >= 192 || nkt < 32) return sp;
-  long n = std::min<long>({(256 + tiles - 1) / tiles, (long)nkt / 16, g.ws_elems / std::max<long>(outs, 1)});
-  if (n < 2) return sp;
-  sp.ktps = (int)((nkt + n - 1) / n);
-  sp.split = (nkt + sp.ktps - 1) / sp.ktps;
-  return sp;
+// Stages of a split-K slice for a launch of `tiles` workgroups (one per CU) over nkt stages of 32: slices of at least
+// 16 stages (the last one of what is left), enough of them for one round of 256 workgroups, of which the scratch holds
+// fit sets of partial tiles.
+int stages_per_slice(long tiles, int nkt, long fit) {
+  if (tiles >= 192 || nkt < 32) return nkt;
+  const long n = std::min<long>({(256 + tiles - 1) / tiles, (long)nkt / 16, fit});
+  return n < 2 ? nkt : (int)((nkt + n - 1) / n);
 }
 
 // Tile shapes.  A launch of c = ceil(workgroups / 256) tiles per CU and k stages is taken as f + k max(t1, c ts) + c e:
@@ -607,28 +599,30 @@ hipError_t gemm_lowp(const GemmLP& g, hipStream_t s) {
       return hipErrorInvalidValue;
   }
   if (dry_run()) return hipSuccess;
-  const int nbz = g.nb * g.nb1;              // grid.y
-  const int nbd = g.per_block ? g.nb : nbz;  // the batch the order and the slices are chosen for
+  const int nbd = g.per_block ? g.nb : g.nb * g.nb1;  // the batch the order and the slices are chosen for
   const int mdec = g.m_dec > 0 ? g.m_dec : g.M;
   // The order and the slices, which the bits of a result depend on, follow from the shape of one state alone: the wide
   // orders (32 x 32 products, one read per FP32 fragment) from half a round of 256 x 256 tiles on, or a quarter with
-  // scratch, K cut so that all slices fill one round; the others in slices of at least 512.
+  // scratch, K cut so that all slices fill one round; the others in slices of at least 512.  The scratch counts with the
+  // partial tiles of one state too: blocks whose partial tiles it does not hold together run in several launches.
   const long t2 = (long)((mdec + 255) / 256) * ((g.N + 255) / 256) * nbd;
+  const long fit = g.ws ? g.ws_elems / ((long)g.M * g.N * nbd) : 0;  // slices of the deciding batch that the scratch holds
   int kind = bf ? kBf16 : kF32Seq, ktps = nkt;
   if (t2 >= 128) {
     kind = bf ? kBf32 : kF32Str;
   } else {
-    const long outs = (long)g.M * g.N * g.nb * g.nb1;
-    const long n = (g.ws && t2 >= 64) ? std::min<long>({256 / t2, (long)nkt / 16, g.ws_elems / std::max<long>(outs, 1)}) : 0;
+    const long n = t2 >= 64 ? std::min<long>({256 / t2, (long)nkt / 16, fit}) : 0;
     if (n >= 2) {
       kind = bf ? kBf32 : kF32Str;
       ktps = (int)((nkt + n - 1) / n);
     } else {
       const long bm = bf ? 256 : 128;
-      ktps = plan_split(g, ((g.M + bm - 1) / bm) * ((g.N + 127) / 128) * nbd, nkt).ktps;
+      ktps = stages_per_slice(((g.M + bm - 1) / bm) * ((g.N + 127) / 128) * nbd, nkt, fit);
     }
   }
   const int split = (nkt + ktps - 1) / ktps;
+  const int nz = split > 1 && g.per_block ? (int)std::min<long>(g.nb1, fit / split) : g.nb1;  // outer blocks of a launch
+  const int nbz = g.nb * nz;                                                                  // its grid.y
   const Shape* best = nullptr;
   double best_us = 0.0;
   for (const Shape& f : kShapes) {
@@ -647,13 +641,10 @@ hipError_t gemm_lowp(const GemmLP& g, hipStream_t s) {
   p.M = g.M;
   p.N = g.N;
   p.K = g.K;
-  p.A = reinterpret_cast<const char*>(g.A);
   p.lda = g.lda * el;
   p.sa2 = g.sa2 * el;
-  p.B = reinterpret_cast<const char*>(g.B);
   p.ldb = g.ldb * el;
   p.sb2 = g.sb2 * el;
-  p.C = g.C;
   p.scm = g.scm;
   p.scn = g.scn;
   p.sc2 = g.sc2;
@@ -665,27 +656,36 @@ hipError_t gemm_lowp(const GemmLP& g, hipStream_t s) {
   p.cslice = 0;
   p.nb = g.nb;
   p.part = 0;
-  p.tab1 = g.tab1;
   p.sa1 = g.sa1 * el;
   p.sb1 = g.sb1 * el;
   p.sc1 = g.sc1;
-  if (split > 1) {  // partial tiles [split][nb1][nb][M][N] in the scratch
-    p.C = g.ws;
+  if (split > 1) {  // partial tiles [split][nz][nb][M][N] in the scratch
     p.scm = g.N;
     p.scn = 1;
     p.sc2 = (long)g.M * g.N;
     p.sc1 = (long)g.M * g.N * g.nb;
-    p.cslice = (long)g.M * g.N * nbz;
     p.beta = 0.0;
     p.part = 1;
   }
-  hipLaunchKernelGGL(best->kernel, dim3(p.tiles_m * p.tiles_n, nbz, split), dim3(best->threads), 0, s, p);
-  if (split > 1) {
-    const long total = (long)g.M * g.N * nbz;
-    hipLaunchKernelGGL(lowp_splitk_reduce, dim3((unsigned)std::min<long>((total + 255) / 256, 4096)), dim3(256), 0, s,
-                       g.C, g.scm, g.scn, g.sc2, g.sc1, g.nb, g.tab1, g.beta, g.ws, g.M, g.N, total, split);
+  for (int z0 = 0; z0 < g.nb1; z0 += nz) {
+    const int n = std::min(nz, g.nb1 - z0);  // blocks z0 .. z0 + n - 1
+    const long zo = g.tab1 ? 0 : z0;
+    double* C = g.C + zo * g.sc1;
+    p.tab1 = g.tab1 ? g.tab1 + z0 : nullptr;
+    p.A = reinterpret_cast<const char*>(g.A) + zo * p.sa1;
+    p.B = reinterpret_cast<const char*>(g.B) + zo * p.sb1;
+    p.C = split > 1 ? g.ws : C;
+    if (split > 1) p.cslice = (long)g.M * g.N * g.nb * n;
+    hipLaunchKernelGGL(best->kernel, dim3(p.tiles_m * p.tiles_n, g.nb * n, split), dim3(best->threads), 0, s, p);
+    if (split > 1) {
+      const long total = (long)g.M * g.N * g.nb * n;
+      hipLaunchKernelGGL(lowp_splitk_reduce, dim3((unsigned)std::min<long>((total + 255) / 256, 4096)), dim3(256), 0, s, C,
+                         g.scm, g.scn, g.sc2, g.sc1, g.nb, p.tab1, g.beta, g.ws, g.M, g.N, total, split);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t to_lowp_gwz(int prec, float* out, long ldo, const double* kcbd, const double* kcld, int o, int v,

@@ -141,8 +141,8 @@ struct GemmLP {
   // rows zero-padded to whole K-blocks of 32; BF16X3: interleaved splits (see to_lowp_2d), lda, ldb,
   // sa2, sb2 count bf16 elements
   // Optional split-K scratch: an output with too few tiles to fill the chip has its K range cut
-  // into slices (each at least 512 of K, each FP32 chunk starting at its slice's start) whose
-  // FP64 partial tiles land here and are then summed in slice order (deterministic).
+  // into slices (all but the last at least 512 of K, each FP32 chunk starting at its slice's start)
+  // whose FP64 partial tiles land here and are then summed in slice order (deterministic).
   double* ws = nullptr;
   long ws_elems = 0;
   // Optional outer batch level over operand blocks: nb1 blocks at strides sa1, sb1 (in the units of
@@ -152,7 +152,9 @@ struct GemmLP {
   long sa1 = 0, sb1 = 0, sc1 = 0;
   const int* tab1 = nullptr;
   int tab1_max = 0;
-  bool per_block = false;  // kernel and split-K choices as for one outer block (see Gemm)
+  // kernel and split-K choices as for one outer block: the bits of each block do not depend on nb1 (blocks whose
+  // partial tiles the scratch does not hold together run in several launches)
+  bool per_block = false;
   // rows that decide the kernel (0: M): operands stacking the rows of several states pass one
   // state's rows, so that every state's rows are summed exactly as when it is alone
   int m_dec = 0;

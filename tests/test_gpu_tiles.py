@@ -61,3 +61,44 @@ def test_tile_edges(o, v, Q, mode, prec):
     for k in range(S):
         assert np.array_equal(host(b1[k]), alone[k][0]) and np.array_equal(host(b2[k]), alone[k][1])
         assert float(host(e)[k]) == alone[k][2]
+
+
+def _grouped_equals_alone(o, v, Q, S, G, prec, mode):
+    """Residuals of S states in passes of G, from a workspace of the reported size, against each state alone: the same
+    bits."""
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2501_10515_amd as P
+
+    from .gpu_util import dev, gpu_residual, host
+
+    print(f"case o={o} v={v} Q={Q} S={S} G={G} vvvv={mode} prec={prec}", flush=True)
+    B, eps = make_system(o, v, Q, 19, sigma=0.1)
+    amps = [random_amplitudes(o, v, 600 + k, 0.05, 0.05) for k in range(S)]
+    pc = {"fp64": P.ASCC_PREC_FP64, "fp32": P.ASCC_PREC_FP32, "bf16x3": P.ASCC_PREC_BF16X3}[prec]
+    vm = P.ASCC_VVVV_FULL if mode == "full" else P.ASCC_VVVV_PACKED
+    ints = P.ascc_build_ints(dev(B), dev(eps), o, precision=pc, vvvv_mode=vm)
+    nbytes = P.ascc_batch_workspace_bytes(o, v, Q, S, G, precision=pc, vvvv_mode=vm)
+    ws = torch.full((nbytes // 8,), float("nan"), dtype=torch.float64, device="cuda")
+    P.ascc_batch_reserve_ws(ints, S, G, ws)
+    T1, T2 = dev(np.stack([a[0] for a in amps])), dev(np.stack([a[1] for a in amps]))
+    R1, R2 = torch.empty_like(T1), torch.empty_like(T2)
+    e = torch.empty(S, dtype=torch.float64, device="cuda")
+    P.ascc_residual_batch(ints, list(T1), list(T2), list(R1), list(R2), e)
+    torch.cuda.synchronize()
+    R1, R2, e = host(R1), host(R2), host(e)
+    for k in range(S):
+        r1, r2, ek = gpu_residual(P, ints, *amps[k])
+        assert np.array_equal(R1[k], r1) and np.array_equal(R2[k], r2) and e[k] == ek, f"state {k}"
+    ints.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3"])
+@pytest.mark.parametrize("o,v,Q,S,G", [
+    (10, 90, 300, 8, 8),   # W/Z in 15 slices, whose partial tiles the scratch holds for 5 states
+    (12, 108, 360, 4, 4),  # rings in 2 slices, W/Z in 22: partial tiles of one state
+])
+def test_slices_do_not_depend_on_the_batch(o, v, Q, S, G, prec):
+    _grouped_equals_alone(o, v, Q, S, G, prec, "packed")
