@@ -238,41 +238,60 @@ __global__ __launch_bounds__(256) void splitk_reduce(GP p, int nb1, long total) 
 // grid of splitk_reduce for `outs` outputs
 inline unsigned splitk_blocks(long outs) { return (unsigned)((outs + 63) / 64); }
 
+// p advanced to operand block z0 of batch level 1
+GP at_block(GP p, long z0) {
+  if (p.tab1) {
+    p.tab1 += z0;
+  } else {
+    p.A += z0 * p.sa1;
+    p.B += z0 * p.sb1;
+    p.C += z0 * p.sc1;
+  }
+  return p;
+}
+
 // nb1d: the outer batch count the split-K decision is made for (1: as for one operand block, so a
-// block's sums take the same order whatever the batch; nb1 otherwise).
+// block's sums take the same order whatever the batch; nb1 otherwise).  Where the scratch does not hold the
+// partial tiles of all blocks, they run in several launches.
 template <int BM, int BN, int BK, int WM, int WN, int MINB>
 hipError_t launch_cfg(const GP& p0, bool amf, bool bnf, int nb1, int nb1d, double* ws, long ws_elems, hipStream_t s) {
   GP p = p0;
   p.tiles_m = (p.M + BM - 1) / BM;
   p.tiles_n = (p.N + BN - 1) / BN;
   const long tiles = (long)p.tiles_m * p.tiles_n * p.nb2 * nb1d;
+  const long outs = (long)p.M * p.N * p.nb2;  // of one operand block
   const int nit = ((p.K + BK - 1) / BK) * p.nred;
   p.split = 1;
   p.it_per_split = nit;
   p.part = nullptr;
-  const long outs = (long)p.M * p.N * p.nb2 * nb1;
   if (ws && tiles < 192 && nit >= 16) {
     // slices enough for one full round of resident workgroups (MINB per CU)
     int sp = (int)std::min<long>({(256L * MINB + tiles - 1) / tiles, (long)nit / 8, 256L});
-    if (ws_elems > 0) sp = (int)std::min<long>(sp, ws_elems / std::max<long>(outs, 1));
+    if (ws_elems > 0) sp = (int)std::min<long>(sp, ws_elems / (outs * nb1d));
     if (sp > 1) {
       p.it_per_split = (nit + sp - 1) / sp;
       p.split = (nit + p.it_per_split - 1) / p.it_per_split;
       p.part = ws;
     }
   }
-  dim3 grid(p.tiles_m * p.tiles_n * p.split, p.nb2, nb1);
-  dim3 block(WM * WN * 64);
-  if (amf && bnf)
-    hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, true, true>), grid, block, 0, s, p);
-  else if (amf)
-    hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, true, false>), grid, block, 0, s, p);
-  else if (bnf)
-    hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, false, true>), grid, block, 0, s, p);
-  else
-    hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, false, false>), grid, block, 0, s, p);
-  if (p.split > 1) hipLaunchKernelGGL(splitk_reduce, dim3(splitk_blocks(outs)), dim3(256), 0, s, p, nb1, outs);
-  return hipGetLastError();
+  const int fit = p.split > 1 && ws_elems > 0 ? (int)std::clamp<long>(ws_elems / (p.split * outs), 1, nb1) : nb1;
+  for (int z0 = 0; z0 < nb1; z0 += fit) {
+    const GP q = at_block(p, z0);
+    const int n = std::min(fit, nb1 - z0);
+    const dim3 grid(p.tiles_m * p.tiles_n * p.split, p.nb2, n), block(WM * WN * 64);
+    if (amf && bnf)
+      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, true, true>), grid, block, 0, s, q);
+    else if (amf)
+      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, true, false>), grid, block, 0, s, q);
+    else if (bnf)
+      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, false, true>), grid, block, 0, s, q);
+    else
+      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, false, false>), grid, block, 0, s, q);
+    if (p.split > 1) hipLaunchKernelGGL(splitk_reduce, dim3(splitk_blocks(outs * n)), dim3(256), 0, s, q, n, outs * n);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -692,18 +711,6 @@ DmaPlan plan_dma(const GP& p0, int nb1d, bool ws, long ws_elems) {
     }
   }
   return best;
-}
-
-// p advanced to operand block z0 of batch level 1
-GP at_block(GP p, long z0) {
-  if (p.tab1) {
-    p.tab1 += z0;
-  } else {
-    p.A += z0 * p.sa1;
-    p.B += z0 * p.sb1;
-    p.C += z0 * p.sc1;
-  }
-  return p;
 }
 
 hipError_t launch_dma_auto(const GP& p0, int nb1, int nb1d, double* ws, long ws_elems, hipStream_t s) {

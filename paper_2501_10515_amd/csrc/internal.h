@@ -64,7 +64,7 @@ struct Gemm {
   const int* tab1 = nullptr;
   int tab1_max = 0;
   // tile and split-K choices as for one block of batch level 1 (the same summation order for
-  // each block whatever nb1 is, as long as the split-K scratch holds the partials of every block)
+  // each block whatever nb1 is)
   bool per_block = false;
   // C = A B with B(k, n) = A(n, k) is symmetric: when M == N, beta == 0 and the rows qualify for
   // the direct-to-LDS kernel, only the tiles on and below the diagonal are computed, each stored

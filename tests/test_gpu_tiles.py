@@ -95,10 +95,13 @@ def _grouped_equals_alone(o, v, Q, S, G, prec, mode):
     ints.close()
 
 
-@pytest.mark.parametrize("prec", ["fp32", "bf16x3"])
-@pytest.mark.parametrize("o,v,Q,S,G", [
-    (10, 90, 300, 8, 8),   # W/Z in 15 slices, whose partial tiles the scratch holds for 5 states
-    (12, 108, 360, 4, 4),  # rings in 2 slices, W/Z in 22: partial tiles of one state
+@pytest.mark.parametrize("o,v,Q,S,G,prec", [
+    # low precision: W/Z in 15 slices, whose partial tiles the scratch holds for 5 states
+    (10, 90, 300, 8, 8, "fp32"), (10, 90, 300, 8, 8, "bf16x3"),
+    # ... rings in 2 slices, W/Z in 22: partial tiles of one state
+    (12, 108, 360, 4, 4, "fp32"), (12, 108, 360, 4, 4, "bf16x3"),
+    # hole-hole ladder (300 x 1176 x 300, the pairs as rows of t+-) in 2 slices: partial tiles of 5 states
+    (24, 48, 60, 7, 7, "fp64"),
 ])
 def test_slices_do_not_depend_on_the_batch(o, v, Q, S, G, prec):
     _grouped_equals_alone(o, v, Q, S, G, prec, "packed")
