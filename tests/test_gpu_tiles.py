@@ -105,3 +105,15 @@ def _grouped_equals_alone(o, v, Q, S, G, prec, mode):
 ])
 def test_slices_do_not_depend_on_the_batch(o, v, Q, S, G, prec):
     _grouped_equals_alone(o, v, Q, S, G, prec, "packed")
+
+
+EDGES = [(1, 2, 3), (2, 8, 16), (4, 16, 32), (5, 13, 17), (8, 12, 33), (9, 11, 40), (13, 15, 48), (16, 17, 64),
+         (34, 6, 20), (52, 4, 24), (66, 3, 81)]  # as in test_tile_edges
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
+@pytest.mark.parametrize("mode", ["full", "packed"])
+@pytest.mark.parametrize("o,v,Q", EDGES)
+def test_tile_edges_in_groups(o, v, Q, mode, prec):
+    """Every term in passes of three states, the last one of two: launches over operand blocks at these sizes."""
+    _grouped_equals_alone(o, v, Q, 5, 3, prec, mode)
