@@ -117,3 +117,46 @@ EDGES = [(1, 2, 3), (2, 8, 16), (4, 16, 32), (5, 13, 17), (8, 12, 33), (9, 11, 4
 def test_tile_edges_in_groups(o, v, Q, mode, prec):
     """Every term in passes of three states, the last one of two: launches over operand blocks at these sizes."""
     _grouped_equals_alone(o, v, Q, 5, 3, prec, mode)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3"])
+@pytest.mark.parametrize("o,v,stacks", [
+    # the narrow orders (fewer than 128 tiles of 256 x 256): 64 x 64 tiles alone, then 128 x 64, 128 x 128 and 256 x 128
+    # ones (split-BF16x3), 64 x 64 with three stages instead of four and 128 x 64 (FP32)
+    (12, 60, (4, 8, 12, 16)),
+    # the wide orders: 64 x 128, 192 x 256, 256 x 256 and 256 x 128; FP32 64 x 64, 224 x 192, 256 x 256 and 128 x 256
+    (24, 126, (2, 3, 4, 8)),
+])
+def test_every_tile_of_an_order_gives_the_same_bits(o, v, stacks, prec):
+    """The ladders of several stacked states take the tiles that fit all their rows, in the order of one state: residuals
+    of the first state at the front of growing stacks, and of the last one at their end, against those alone."""
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2501_10515_amd as P
+
+    from .gpu_util import dev
+
+    print(f"case o={o} v={v} states={stacks} prec={prec}", flush=True)
+    B, eps = make_system(o, v, 40, 23, sigma=0.1)
+    pc = {"fp32": P.ASCC_PREC_FP32, "bf16x3": P.ASCC_PREC_BF16X3}[prec]
+    ints = P.ascc_build_ints(dev(B), dev(eps), o, precision=pc, vvvv_mode=P.ASCC_VVVV_PACKED)
+    S = max(stacks)
+    P.ascc_batch_reserve(ints, S)
+    g = torch.Generator(device="cuda").manual_seed(29)
+    T1 = 0.05 * torch.randn((S, o, v), dtype=torch.float64, device="cuda", generator=g)
+    T2 = 0.05 * torch.randn((S, o, o, v, v), dtype=torch.float64, device="cuda", generator=g)
+    T2 = 0.5 * (T2 + T2.permute(0, 2, 1, 4, 3))
+    r1, r2 = torch.empty_like(T1), torch.empty_like(T2)
+    e = torch.empty(S, dtype=torch.float64, device="cuda")
+    for k in {0} | {n - 1 for n in stacks}:
+        P.ascc_residual(ints, T1[k], T2[k], r1[k], r2[k], e[k:k + 1])
+    R1, R2, E = torch.empty_like(T1), torch.empty_like(T2), torch.empty_like(e)
+    for n in stacks:
+        P.ascc_residual_batch(ints, list(T1[:n]), list(T2[:n]), list(R1[:n]), list(R2[:n]), E[:n])
+        torch.cuda.synchronize()
+        for k in (0, n - 1):
+            assert torch.equal(R1[k], r1[k]) and torch.equal(R2[k], r2[k]) and E[k] == e[k], (n, k)
+    assert float(r2[0].abs().max()) > 1e-2
+    ints.close()
