@@ -349,17 +349,19 @@ std::vector<std::pair<float* ascc_ints::*, long>> lowp_plan(long o, long v, long
 // packed set needs the slabs with b >= a and computes those with b >= the chunk's first a: n chunks cost (1 + 1/n)/2 of
 // all products (6 v^5 flops with naux = 3 v, at 70 TFLOP/s) and two launches each, least near n = sqrt(time / 20 us); more
 // than 16 gain nothing (chunks that fit the last-level cache pack 20 % faster, but their products run at 52 instead of
-// 62 TFLOP/s: o18 v162 15.6 instead of 14.7 ms).
+// 62 TFLOP/s: o18 v162 15.6 instead of 14.7 ms).  A small system's few chunks are the larger part of its memory
+// (o4 v36: 13 MB of 92): those longer than max(o, v / 16) values of a are kept to what the set's split-K scratch holds and
+// are formed there, so *chunk_a times v^3 can exceed the result, which is what has to be allocated.
 long build_temp_elems(long o, long v, int mode, long* chunk_a) {
   const long vvv = v * v * v;
-  long ac = std::max<long>(1, std::min<long>(v, (256L << 20) / std::max<long>(vvv, 1)));
+  long ac = std::max<long>(1, std::min<long>(v, (256L << 20) / std::max<long>(vvv, 1))), own = std::max(o, ac);
   if (mode == ASCC_VVVV_PACKED) {
     const long n = std::lround(std::sqrt(6.0 * (double)vvv * v * v / 70e12 / 20e-6));
-    ac = std::min<long>(ac, (v + std::clamp<long>(n, 1, 16) - 1) / std::clamp<long>(n, 1, 16));
+    own = std::max(o, (v + 15) / 16);
+    ac = std::min({ac, (v + std::clamp<long>(n, 1, 16) - 1) / std::clamp<long>(n, 1, 16), std::max(own, kSplitKElems / vvv)});
   }
   if (chunk_a) *chunk_a = ac;
-  const long wtmp = o * v * v * v;
-  return std::max(wtmp, ac * vvv);
+  return vvv * (ac > own ? o : std::max(o, ac));
 }
 
 
@@ -1296,29 +1298,34 @@ int build_constants(ascc_ints* I, const double* Bsrc, const double* fock, int fo
   // (batched over a and b in tiles of v x v, o18 v162 reached 40 TFLOP/s: 162 of 192 rows and columns).  The packed
   // halves read only the slabs with b >= a ((ad|bc) is in the same slab), so a packed build starts b at the chunk's first
   // a; the full matrix needs every b.
-  auto vslab = [&](int a0, int na, double* dst) -> hipError_t {
+  auto vslab = [&](int a0, int na, double* dst, double* ws, long ws_elems) -> hipError_t {
     const long b0 = full ? 0 : a0, nbd = (v - b0) * v;
-    return mm(I, gemm_rm(na * (long)v, nbd, pad_even(Q), 1.0, I->Bvv + a0 * v * lq, lq, false, I->Bvv + b0 * v * lq, lq, true, 0.0,
-                         dst, nbd), s);
+    Gemm g = gemm_rm(na * (long)v, nbd, pad_even(Q), 1.0, I->Bvv + a0 * v * lq, lq, false, I->Bvv + b0 * v * lq, lq, true, 0.0, dst, nbd);
+    g.ws = ws;
+    g.ws_elems = ws_elems;
+    return gemm_f64(g, s);
   };
   // in chunks of a through a temporary: scattered to the full matrix in pair order, or packed
   const bool lowp = I->precision != ASCC_PREC_FP64;
   if (full) HIPCHK(pair_minus_rows(pair_minus(I), v, s));
   long ac = 1;
-  const long elems = build_temp_elems(o, v, I->vvvv_mode, &ac);
-  double* tmp = nullptr;
+  const long elems = build_temp_elems(o, v, I->vvvv_mode, &ac), chunk = ac * vv * v;
+  const long used = chunk > elems ? chunk : 0;  // a chunk in the split-K scratch: the rest of it is scratch
+  double* tmp = I->splitk;
   Pool tmp_alloc = sub_pool(I->pool);
-  int rc3 = dalloc(tmp_alloc, &tmp, (size_t)elems);
-  if (rc3) return rc3;
+  if (!used) {
+    int rc3 = dalloc(tmp_alloc, &tmp, (size_t)chunk);
+    if (rc3) return rc3;
+  }
   hipError_t e = hipSuccess;
   for (int a0 = 0; a0 < v && e == hipSuccess; a0 += (int)ac) {
     const int na = (int)std::min<long>(ac, v - a0);
-    e = vslab(a0, na, tmp);
-    if (e == hipSuccess) 
+    e = vslab(a0, na, tmp, used < kSplitKElems ? I->splitk + used : nullptr, kSplitKElems - used);
+    if (e == hipSuccess)
       e = full ? pack_full(I->V, I->ldV, tmp, a0, a0 + na, v, s)
                : pack_vvvv(I->V, I->V + vhalf, I->ldT, tmp, a0, a0 + na, v, s);
   }
-  if (e == hipSuccess && !tmp_alloc.base) e = d_sync(s);  // carved temporaries need no wait
+  if (e == hipSuccess && !tmp_alloc.base && !used) e = d_sync(s);  // carved temporaries need no wait
   free_all(tmp_alloc);
   if (e != hipSuccess) {
     if (!(bounds_checking() && e == hipErrorInvalidValue)) set_error(std::string("building vvvv: ") + hipGetErrorString(e));

@@ -94,3 +94,31 @@ def test_every_launch_stays_in_bounds_dry_run(shapes):
                        text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
     assert r.stdout.count("OK ") == len(shapes)
+
+
+def _one_of_each(o, v, Q, prec, mode):
+    """Bytes of one array of each kind that an integral set works with, without padding."""
+    import paper_2501_10515_amd as P
+
+    n, ov, oo, vv = o + v, o * v, o * o, v * v
+    To, Tv, packed = o * (o + 1) // 2, v * (v + 1) // 2, mode == P.ASCC_VVVV_PACKED
+    factors = Q * (n * n + 4 * ov) + Q * (n * n + n * o + oo + vv)      # B, B_ov, N; what T1 dressing forms
+    blocks = (2 * Tv * Tv if packed else vv * vv) + vv * (ov + oo)      # (ac|bd); (kc|bd), (kc|ld)
+    ladder = 4 * To * Tv                                                # pair rows of the amplitudes and of the ladder
+    doubles = 16 * ov * ov + 2 * oo * oo + oo * (ov + oo)               # rings, assembly; hole-hole ladder; W, Z
+    chunk = -(-v // 16) if packed else min(v, max(1, 2**28 // v**3))
+    words = factors + blocks + ladder + doubles + 2**23 + max(o, chunk) * v**3
+    if prec != P.ASCC_PREC_FP64:  # shadows, four bytes a value
+        words += (2 * Tv * Tv + vv * (ov + oo) + 2 * To * Tv + 7 * ov * ov + Q * (3 * ov + oo + vv) + oo * vv + oo * oo) / 2
+    return 8 * words
+
+
+@pytest.mark.parametrize("prec", ["fp64", "bf16x3"])
+@pytest.mark.parametrize("o,v,Q", [(4, 36, 120), (5, 20, 60), (8, 72, 240), (12, 108, 360)])
+def test_small_packed_sets_take_no_more_than_their_arrays(o, v, Q, prec):
+    """A served request is admitted by this size; whole-line rows and alignment are within 1 %."""
+    import paper_2501_10515_amd as P
+
+    pc = {"fp64": P.ASCC_PREC_FP64, "bf16x3": P.ASCC_PREC_BF16X3}[prec]
+    got = P.ascc_workspace_bytes(o, v, Q, pc, P.ASCC_VVVV_PACKED)[0]
+    assert got <= 1.01 * _one_of_each(o, v, Q, pc, P.ASCC_VVVV_PACKED)
