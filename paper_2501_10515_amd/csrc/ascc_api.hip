@@ -194,9 +194,10 @@ struct ascc_ints {
   double *TU, *XZ;               // [2][ov] rows at stride ldov: Tx | U, Xc | Zd
   double *Y, *P;                 // [2][ov][ov]
   double *Nq;                    // [o][v] rows at stride ldQ: N_Q[k,a] at [k][a]
-  double *WZ;                    // [o^2][ov + o^2] (FP64: W' in the first ov columns)
-  double *chi;                   // [o^2][o^2] (FP64: chi+-, [2][T(o)][T(o)])
-  double *RL, *EM;               // [o^2][v^2]
+  double *WZ;                    // low precision: [o^2][ov + o^2], W | Z, then W' | chi.  FP64: W', [o^2][ov], and chi+-
+  // in arrays whose values are no longer needed by then (bind_views)
+  double *chi;                   // FP64: chi+-, [2][T(o)][T(o)], behind W'
+  double *RL, *EM;               // [o^2][v^2]: in G3, and in the second half of XZ
   double *Abc, *Bkj, *Fvvp, *Foop, *Fovh;  // small (Abc, Bkj: PLASCC)
   double *partial;               // reduction scratch
   double *splitk;                // split-K partial tiles of small-output contractions
@@ -301,10 +302,11 @@ inline long pad_line(long x) { return (x + 15) / 16 * 16; }  // rows of whole 12
 
 // Every device array of an integral set with its element count, in allocation order; the
 // same list gives ascc_workspace_bytes its exact answer.
-std::vector<std::pair<double* ascc_ints::*, long>> ints_plan(long o, long v, long Q, int mode) {
+std::vector<std::pair<double* ascc_ints::*, long>> ints_plan(long o, long v, long Q, int precision, int mode) {
   const long n = o + v, nn = n * n, ov = o * v, oo = o * o, vv = v * v, ovov = ov * ov;
   const long To = o * (o + 1) / 2, Tv = v * (v + 1) / 2;
-  const bool full = (mode == ASCC_VVVV_FULL);
+  const bool full = (mode == ASCC_VVVV_FULL), lowp = precision != ASCC_PREC_FP64;
+  const long chi = lowp ? oo * lowp_ld(oo) : 0;  // elements of chi's shadow
   const long wzl = ov + oo, ldT = pad_line(Tv), ldR = pad_line(Tv + wzl), ldov = pad_line(ov), ldQ = pad_line(Q);
   return {
       {&ascc_ints::B, nn * ldQ},      {&ascc_ints::h, nn},           {&ascc_ints::eps, n},
@@ -317,14 +319,26 @@ std::vector<std::pair<double* ascc_ints::*, long>> ints_plan(long o, long v, lon
       {&ascc_ints::Tp, 2 * To * ldT}, {&ascc_ints::Rp, 2 * To * ldR},
       {&ascc_ints::D, o * n * ldQ},   {&ascc_ints::Fh, nn},          {&ascc_ints::BvoTt, ov * ldQ},
       {&ascc_ints::Boo, oo * ldQ},    {&ascc_ints::Bvv, vv * ldQ},   {&ascc_ints::G1, ovov},
-      {&ascc_ints::G2, oo * vv},      {&ascc_ints::G3, ovov},        {&ascc_ints::G4, oo * oo},
+      {&ascc_ints::G2, oo * vv},      {&ascc_ints::G3, ovov},        {&ascc_ints::G4, std::max(oo * oo, (chi + 1) / 2)},
       {&ascc_ints::TU, 2 * ov * ldov}, {&ascc_ints::Y, 2 * ovov},    {&ascc_ints::XZ, 2 * ov * ldov},
-      {&ascc_ints::P, 2 * ovov},      {&ascc_ints::Nq, ov * ldQ},    {&ascc_ints::WZ, oo * (ov + oo)},
-      {&ascc_ints::chi, std::max(oo * oo, 2 * To * To)}, {&ascc_ints::RL, oo * vv},     {&ascc_ints::EM, oo * vv},
+      {&ascc_ints::P, 2 * ovov},      {&ascc_ints::Nq, ov * ldQ},
+      {&ascc_ints::WZ, std::max(pad_line(oo * ov) + 2 * To * To, lowp ? oo * wzl : oo * oo)},
       {&ascc_ints::Abc, vv},          {&ascc_ints::Bkj, oo},         {&ascc_ints::Fvvp, vv},
       {&ascc_ints::Foop, oo},         {&ascc_ints::Fovh, ldov},        {&ascc_ints::partial, 8192},
       {&ascc_ints::splitk, kSplitKElems},
   };
+}
+
+// The arrays that live inside others: RL is first written when ring_xz has read G3 for the last time, EM when the ring
+// products have read XZ (its first half is PLASCC's scratch then), chi's shadow when chi has taken up G4, and chi+-
+// follow W' where a low-precision residual has W | Z (nothing of this reaches into the next residual).  As arrays of
+// their own, beside the W/Z columns of Rp, they made sets with many occupied orbitals a fifth to a third larger (o100
+// v10 2.62 -> 3.42 GiB, o256 v100 205 -> 248 GiB; now 2.59 and 194).
+void bind_views(ascc_ints* I) {
+  I->RL = I->G3;
+  I->EM = I->XZ + I->ov * I->ldov;
+  I->chi = I->WZ + pad_line(I->oo * I->ov);
+  I->chif = reinterpret_cast<float*>(I->G4);
 }
 
 // FP32 shadows allocated for a low-precision integral set.
@@ -341,7 +355,7 @@ std::vector<std::pair<float* ascc_ints::*, long>> lowp_plan(long o, long v, long
       {&ascc_ints::XZf, 2 * ov * lov}, {&ascc_ints::BvoTtf, ov * lQ},
       {&ascc_ints::BooTf, oo * lQ},    {&ascc_ints::BvvTf, vv * lQ},
       {&ascc_ints::BovTf, ov * lQ},    {&ascc_ints::Bovf, Q * lov},
-      {&ascc_ints::t2Tf, vv * loo},    {&ascc_ints::chif, oo * loo},
+      {&ascc_ints::t2Tf, vv * loo},
   };
 }
 
@@ -753,7 +767,7 @@ int pp_ladder(ascc_ints* I, hipStream_t s, bool wz_done) {
 
 size_t ints_footprint(long o, long v, long Q, int precision, int mode) {
   size_t off = 0;
-  for (const auto& item : ints_plan(o, v, Q, mode))
+  for (const auto& item : ints_plan(o, v, Q, precision, mode))
     off = align_up(off) + std::max<size_t>((size_t)item.second, 1) * sizeof(double);
   if (precision != ASCC_PREC_FP64)
     for (const auto& item : lowp_plan(o, v, Q, mode))
@@ -777,7 +791,7 @@ size_t ints_footprint(long o, long v, long Q, int precision, int mode) {
 // cross ab.  Every product is split along those crosses into slabs: N^5 work.  The ring term is a
 // symmetric matrix; its (X, X) and (X, not X) blocks come from the X rows of Y = T K that the ring
 // stage has just formed, the (not X, not X) block is C_p K_pp C_p^T with C_p the X columns of the
-// rows outside X.  Runs after the rings and E terms, in G2, chi, Abc and Bkj, which those are
+// rows outside X.  Runs after the rings and E terms, in G2, WZ, the first half of XZ, Abc and Bkj, which those are
 // done with, and in the compact buffers of ascc_set_plascc.
 int plascc_remove(ascc_ints* I, const double* t2, double* RL, hipStream_t s) {
   const int o = I->no, v = I->nv, h = I->pl_hole, pa = I->pl_pa;
@@ -794,7 +808,7 @@ int plascc_remove(ascc_ints* I, const double* t2, double* RL, hipStream_t s) {
     Perm4In x = pin(I->KL, (long)v * I->ldov, v, 1, I->ldov, 1.0);
     HIPCHK(permute4(G, d, 0.0, &x, 1, s));
   }
-  double* ZM = I->chi;
+  double* ZM = I->WZ;  // (the E terms are done with W')
   HIPCHK(cross_gather_rows(I->plTa, vv, tM, vv, oo, vv, Xo, false, s));
   HIPCHK(cross_gather_cols(I->plTc, mvp, tM, vv, oo, Xv, &Xo, s));
   HIPCHK(cross_gather_cols(I->plGc, mvp, G, vv, oo, Xv, nullptr, s));
@@ -881,7 +895,7 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   const LadderRows rows = lad ? *lad : own_rows(I);
   const int o = I->no, v = I->nv, Q = I->naux;
   const long n = I->n, nn = n * n, ov = I->ov, oo = I->oo, vv = I->vv, ovov = I->ovov;
-  const long wzl = ov + oo;  // row length of WZ
+  const long wzl = ov + oo;  // row length of W | Z
   int rc;
 
   // --- T1 dressing: the dressed blocks of B, and the dressed Fock matrix: F^ = X (h + 2 sum_Q J_Q B - sum_kQ D B) Y^T
@@ -1014,14 +1028,35 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     const long ld = lowp_ld(vv);
     HIPCHK(shadow(I, I->t2f, t2, oo, vv, s));
     HIPCHK(glp(lp_nt(I, oo, wzl, vv, 1, I->t2f, ld, 0, I->GwzTf, ld, 0, I->WZ, wzl, 0), s));
+    {  // W'_ij[k,b] = W_ij[k,b] - 1/2 sum_l Z_ij[k,l] t_l^b   (batched over ij, in place)
+      Gemm g;
+      g.M = o;
+      g.N = v;
+      g.K = o;
+      g.A = I->WZ + ov;
+      g.sam = o;
+      g.sak = 1;
+      g.sa2 = wzl;
+      g.B = t1;
+      g.sbk = v;
+      g.sbn = 1;
+      g.C = I->WZ;
+      g.scm = v;
+      g.scn = 1;
+      g.sc2 = wzl;
+      g.alpha = -0.5;
+      g.beta = 1.0;
+      g.nb2 = oo;
+      HIPCHK(mm(I, g, s));
+    }
     phase_end(I, s);
-    // --- chi[ij][kl] = g^_kilj + Z_ij[k,l]
+    // --- chi[ij][kl] = g^_kilj + Z_ij[k,l], in place
     phase_begin(I, PH_HH, s);
     EACH_SLOT {
       int d[4] = {o, o, o, o};
-      const long o2 = oo, o3 = oo * o;
-      Perm4In x[2] = {pin(S(I->G4), o2, 1, o3, o, 1.0), pin(S(I->WZ) + ov, (long)o * wzl, wzl, o, 1, 1.0)};
-      HIPCHK(permute4(S(I->chi), d, 0.0, x, 2, s));
+      const long o2 = oo, o3 = oo * o, os[4] = {o * wzl, wzl, o, 1};
+      Perm4In x = pin(S(I->G4), o2, 1, o3, o, 1.0);
+      HIPCHK(permute4_strided(S(I->WZ) + ov, os, d, 1.0, &x, 1, s));
     }
     phase_end(I, s);
   }
@@ -1034,7 +1069,7 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     phase_end(I, s);
     phase_begin(I, PH_HH, s);
     // RL[ij][ab] += sum_kl chi[ij][kl] t2[kl][ab], with t2 transposed to K = kl contiguous
-    HIPCHK(shadow(I, I->chif, I->chi, oo, oo, s));
+    EACH_SLOT HIPCHK(to_lowp_2d(lowp_kind(I), S(I->chif), loo, S(I->WZ) + ov, wzl, oo, oo, s));
     HIPCHK(shadow_t(I, I->t2Tf, t2, vv, vv, oo, s));
     GemmLP g = lp_nt(I, oo, vv, oo, 1, I->chif, loo, 0, I->t2Tf, loo, 0, RL, vv, 0);
     g.beta = 1.0;
@@ -1044,7 +1079,7 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     // W', chi+- with F'' in it, and R+- += chi+- t+- over the pairs k <= l: a quarter of the products of
     // the full sum over k, l (and the F'' t2 product rides along)
     phase_begin(I, PH_HH, s);
-    EACH_SLOT HIPCHK(wz_chi(S(I->WZ), wzl, S(I->chi), S(I->chi) + To * To, S(rows.Rp) + Tv, S(rows.Rp) + rows.sr + Tv,
+    EACH_SLOT HIPCHK(wz_chi(S(I->WZ), ov, S(I->chi), S(I->chi) + To * To, S(rows.Rp) + Tv, S(rows.Rp) + rows.sr + Tv,
                             I->ldR, S(I->G4), S(I->Foop), S(t1), o, v, s));
     Gemm g = gemm_rm(To, Tv, To, 1.0, I->chi, To, false, rows.Tp, I->ldT, false, 1.0, rows.Rp, I->ldR);
     g.sa2 = To * To;
@@ -1092,27 +1127,6 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     g.nb2 = o;
     HIPCHK(mm(I, g, s));
   }
-  if (lowp) {  // W'_ij[k,b] = W_ij[k,b] - 1/2 sum_l Z_ij[k,l] t_l^b   (batched over ij, in place)
-    Gemm g;
-    g.M = o;
-    g.N = v;
-    g.K = o;
-    g.A = I->WZ + ov;
-    g.sam = o;
-    g.sak = 1;
-    g.sa2 = wzl;
-    g.B = t1;
-    g.sbk = v;
-    g.sbn = 1;
-    g.C = I->WZ;
-    g.scm = v;
-    g.scn = 1;
-    g.sc2 = wzl;
-    g.alpha = -0.5;
-    g.beta = 1.0;
-    g.nb2 = oo;
-    HIPCHK(mm(I, g, s));
-  }
   {  // EM[ij][a][b] -= sum_k t_k^a W'_ij[k,b]
     Gemm g;
     g.M = v;
@@ -1124,7 +1138,7 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     g.B = I->WZ;
     g.sbk = v;
     g.sbn = 1;
-    g.sb2 = wzl;
+    g.sb2 = lowp ? wzl : ov;
     g.C = I->EM;
     g.scm = v;
     g.scn = 1;
@@ -1376,7 +1390,7 @@ bool is_constant(float* ascc_ints::*m) {
 }
 size_t work_block_bytes(long o, long v, long Q, int precision, int mode) {
   size_t off = 0;
-  for (const auto& item : ints_plan(o, v, Q, mode))
+  for (const auto& item : ints_plan(o, v, Q, precision, mode))
     if (!is_constant(item.first)) off = align_up(off) + std::max<size_t>((size_t)item.second, 1) * sizeof(double);
   if (precision != ASCC_PREC_FP64)
     for (const auto& item : lowp_plan(o, v, Q, mode))
@@ -1443,7 +1457,7 @@ int residual_group(ascc_ints* I, int n, int nstates, const double* const* t1, co
   std::vector<std::pair<double* ascc_ints::*, double*>> saved;
   std::vector<std::pair<float* ascc_ints::*, float*>> savedf;
   size_t off = 0;
-  for (const auto& item : ints_plan(o, v, Q, I->vvvv_mode))
+  for (const auto& item : ints_plan(o, v, Q, I->precision, I->vvvv_mode))
     if (!is_constant(item.first)) {
       off = align_up(off);
       saved.push_back({item.first, I->*(item.first)});
@@ -1458,6 +1472,7 @@ int residual_group(ascc_ints* I, int n, int nstates, const double* const* t1, co
         I->*(item.first) = reinterpret_cast<float*>(I->group_base + off);
         off += std::max<size_t>((size_t)item.second, 1) * sizeof(float);
       }
+  bind_views(I);
   SlotBatch sb;
   sb.n = n;
   auto add = [&](const void* p, size_t bytes, long stride) {
@@ -1476,7 +1491,7 @@ int residual_group(ascc_ints* I, int n, int nstates, const double* const* t1, co
   const long trow = 8 * (o * (o + 1) / 2) * I->ldT, rrow = 8 * (o * (o + 1) / 2) * I->ldR;  // bytes of a state's rows
   add(lad.Tp, trow, trow);
   add(lad.Rp, rrow, rrow);
-  for (const auto& item : ints_plan(o, v, Q, I->vvvv_mode))  // shared integrals: stride 0
+  for (const auto& item : ints_plan(o, v, Q, I->precision, I->vvvv_mode))  // shared integrals: stride 0
     if (is_constant(item.first) && I->*(item.first))
       add(I->*(item.first), std::max<size_t>((size_t)item.second, 1) * sizeof(double), 0);
   if (I->precision != ASCC_PREC_FP64)
@@ -1490,6 +1505,7 @@ int residual_group(ascc_ints* I, int n, int nstates, const double* const* t1, co
   }
   for (auto& x : saved) I->*(x.first) = x.second;
   for (auto& x : savedf) I->*(x.first) = x.second;
+  bind_views(I);
   return rc;
 }
 
@@ -1784,7 +1800,7 @@ static int build_ints_impl(const double* d_B, const double* d_fock, int fock_is_
     register_buffer(ws, ws_bytes);
   }
   rc = ASCC_OK;
-  for (const auto& item : ints_plan(no, nv, naux, vvvv_mode)) {
+  for (const auto& item : ints_plan(no, nv, naux, precision, vvvv_mode)) {
     if (!rc) rc = dalloc(I->pool, &(I->*(item.first)), (size_t)item.second);
   }
   if (precision != ASCC_PREC_FP64) {
@@ -1792,6 +1808,7 @@ static int build_ints_impl(const double* d_B, const double* d_fock, int fock_is_
       if (!rc) rc = dalloc(I->pool, &(I->*(item.first)), (size_t)item.second);
     }
   }
+  if (!rc) bind_views(I);
   I->cur_prec = precision;
   ScopedBuffers user;
   user.add(d_B, sizeof(double) * Q * nn);

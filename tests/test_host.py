@@ -122,3 +122,17 @@ def test_small_packed_sets_take_no_more_than_their_arrays(o, v, Q, prec):
     pc = {"fp64": P.ASCC_PREC_FP64, "bf16x3": P.ASCC_PREC_BF16X3}[prec]
     got = P.ascc_workspace_bytes(o, v, Q, pc, P.ASCC_VVVV_PACKED)[0]
     assert got <= 1.01 * _one_of_each(o, v, Q, pc, P.ASCC_VVVV_PACKED)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("mode", ["full", "packed"])
+@pytest.mark.parametrize("o,v,Q", [(30, 15, 120), (60, 30, 270), (100, 10, 300), (256, 4, 700), (256, 100, 1000),
+                                   (20, 20, 120), (20, 180, 600)])
+def test_sets_with_many_occupied_orbitals_take_no_more_than_their_arrays(o, v, Q, mode, prec):
+    """The W/Z pair rows are the largest array of such a set besides the o^4 ones."""
+    import paper_2501_10515_amd as P
+
+    pc = {"fp64": P.ASCC_PREC_FP64, "fp32": P.ASCC_PREC_FP32}[prec]
+    vm = P.ASCC_VVVV_FULL if mode == "full" else P.ASCC_VVVV_PACKED
+    got = P.ascc_workspace_bytes(o, v, Q, pc, vm)[0]
+    assert got <= 1.001 * _one_of_each(o, v, Q, pc, vm)
