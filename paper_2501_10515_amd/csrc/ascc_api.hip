@@ -185,7 +185,9 @@ struct ascc_ints {
   double* pairtab;  // FULL: int32 [T(v)]: row R(b,a) of V for pair p(a,b), a <= b
   double *Tp, *Rp;  // ladder operands: t+- [2][T(o)] rows at stride ldT (pack_tpm), and R+- with the W/Z
                     // pair rows behind each (unpack_rpm, wz_chi), [2][T(o)] rows at stride ldR
-  long ldT, ldV, ldR, ldov, ldQ;  // row strides: whole 128-byte lines, zero past the row
+  double* Rw;       // W/Z pair rows of a stacked state where they are apart (wz_apart): the W/Z columns of Rp, or rows of a
+                    // group's work block; stride ldW, halves T(o) rows apart
+  long ldT, ldV, ldR, ldW, ldov, ldQ;  // row strides: whole 128-byte lines, zero past the row
   // residual work arrays
   double* D;                     // [o][n] rows at stride ldQ: (B Y^T)_pk at [k][p]
   double* Fh;                    // [n][n] X^-1 F^ Y^-T (build: scratch)
@@ -300,6 +302,17 @@ constexpr long kSplitKElems = 1L << 23;  // 64 MiB of split-K partials
 inline long pad_even(long x) { return x + (x & 1); }  // compact slab widths, even for the direct-to-LDS path
 inline long pad_line(long x) { return (x + 15) / 16 * 16; }  // rows of whole 128-byte lines
 
+// Whether the stacked ladder rows of a batch go without the W/Z columns, whose products then run with each state's other
+// terms, into one set of rows per state at work: where these columns are longer than the unpacked ladder of a state,
+// [o^2][v^2] (more occupied orbitals than about 0.6 of the virtuals), they would be most of a stacked state (o60 v30: 158 of
+// 186 MB; a batch of four takes 8.9 ms without them, 8.7 with them).  From 32 MB of them on: smaller states keep the one
+// launch (o30 v15, 10 MB: six states 1.18 ms, 1.23 apart).
+inline bool wz_apart(long o, long v) {
+  const long wz = o * (o + 1) * (o * v + o * o);
+  return wz > o * o * v * v && wz > (4L << 20);
+}
+inline long stacked_row(long o, long v) { return pad_line(v * (v + 1) / 2 + (wz_apart(o, v) ? 0 : o * v + o * o)); }
+
 // Every device array of an integral set with its element count, in allocation order; the
 // same list gives ascc_workspace_bytes its exact answer.
 std::vector<std::pair<double* ascc_ints::*, long>> ints_plan(long o, long v, long Q, int precision, int mode) {
@@ -335,6 +348,8 @@ std::vector<std::pair<double* ascc_ints::*, long>> ints_plan(long o, long v, lon
 // their own, beside the W/Z columns of Rp, they made sets with many occupied orbitals a fifth to a third larger (o100
 // v10 2.62 -> 3.42 GiB, o256 v100 205 -> 248 GiB; now 2.59 and 194).
 void bind_views(ascc_ints* I) {
+  I->Rw = I->Rp + (long)I->nv * (I->nv + 1) / 2;
+  I->ldW = I->ldR;
   I->RL = I->G3;
   I->EM = I->XZ + I->ov * I->ldov;
   I->chi = I->WZ + pad_line(I->oo * I->ov);
@@ -635,15 +650,22 @@ hipError_t shadow_pairs(const ascc_ints* I, float* out, const double* in, long r
   return to_lowp_2d(lowp_kind(I), out, lowp_ld(Tv), in, I->ldT, rows, Tv, s);
 }
 
-// The rows of one state among the stacked ladder operands: t+- at Tp and R+- (with the W/Z columns behind
-// them in FP64) at Rp, the - halves st and sr elements further on.
+// The rows of one state among the stacked ladder operands: t+- at Tp (stride ldT) and R+- at Rp (stride ldr; with the W/Z
+// columns behind them in FP64, unless they are apart), the - halves st and sr elements further on.
 struct LadderRows {
   double *Tp, *Rp;
-  long st, sr;
+  long st, sr, ldr;
 };
 LadderRows own_rows(const ascc_ints* I) {
   const long To = (long)I->no * (I->no + 1) / 2;
-  return {I->Tp, I->Rp, To * I->ldT, To * I->ldR};
+  return {I->Tp, I->Rp, To * I->ldT, To * I->ldR, I->ldR};
+}
+// G+- and the stride of its halves.
+const double* g_rows(const ascc_ints* I, long* half) {
+  const long Tv = (long)I->nv * (I->nv + 1) / 2, wzl = I->ov + I->oo;
+  const bool full = I->vvvv_mode == ASCC_VVVV_FULL;
+  *half = (full ? wzl : Tv + wzl) * I->ldT;
+  return full ? I->G : I->V + Tv * I->ldT;
 }
 
 // Particle-particle ladder R_s[p(i,j)] = sum_cd (t_s)_ij^cd (ac|bd) of S states in one launch, computed for
@@ -655,44 +677,75 @@ LadderRows own_rows(const ascc_ints* I) {
 // stores V+- and G+- as one matrix, one launch for both (a fuller last round: o30 v270 53.5 + 19.8 ms as
 // two launches, 46.8 as one); FULL stores the (ac|bd) matrix in pair order, whose halves V[n][k] +- V[pm[n]][k]
 // are formed while they are staged, and G+- apart.  The S states' rows are stacked, so the vvvv operand
-// is streamed once for all of them; a state's sums are those it has alone.  wz_done: the G+- rows of a FULL set are.
-int ladder_launch(ascc_ints* I, long S, const double* Tp, double* Rp, const LadderBatch* lb, hipStream_t s,
-                  bool wz_done = false) {
+// is streamed once for all of them; a state's sums are those it has alone.  apart: without the W/Z rows (wz_launch).
+// wz_done: the G+- rows of a FULL set are there already.
+int ladder_launch(ascc_ints* I, long S, const double* Tp, double* Rp, long ldr, bool apart, const LadderBatch* lb,
+                  hipStream_t s, bool wz_done = false) {
   const int o = I->no, v = I->nv;
   const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2, wzl = I->ov + I->oo, M = S * To;
   const bool full = I->vvvv_mode == ASCC_VVVV_FULL;
   Ladder L;
   L.M = (int)M;
   L.Mdec = (int)To;
+  L.Ndec = (int)(full ? Tv : Tv + wzl);
+  L.N = apart ? (int)Tv : L.Ndec;
   L.K = (int)pad_even(Tv);
   L.A = Tp;
   L.lda = I->ldT;
   L.sa2 = M * I->ldT;
   L.C = Rp;
-  L.ldc = I->ldR;
-  L.sc2 = M * I->ldR;
+  L.ldc = ldr;
+  L.sc2 = M * ldr;
   L.ws = I->splitk;
   L.ws_elems = kSplitKElems;
   if (lb) L.lb = *lb;
   L.V = I->V;
   if (full) {
-    L.N = (int)Tv;
     L.ldv = I->ldV;
     L.vrows = I->vv;
     L.pm = pair_minus(I);
-    HIPCHK(gemm_f64_ladder(L, s));
-    if (wz_done) return ASCC_OK;
-    L.pm = nullptr;
-    L.V = I->G;
-    L.N = (int)wzl;
-    L.ldv = I->ldT;
-    L.sv2 = wzl * I->ldT;
-    L.C = Rp + Tv;
-    if (lb) L.lb.sv = slot_stride(I->G) / 8;
   } else {
-    L.N = (int)(Tv + wzl);
     L.ldv = I->ldT;
     L.sv2 = (Tv + wzl) * I->ldT;
+  }
+  HIPCHK(gemm_f64_ladder(L, s));
+  if (!full || apart || wz_done) return ASCC_OK;
+  L.pm = nullptr;
+  L.V = g_rows(I, &L.sv2);
+  L.N = L.Ndec = (int)wzl;
+  L.ldv = I->ldT;
+  L.C = Rp + Tv;
+  if (lb) L.lb.sv = slot_stride(L.V) / 8;
+  HIPCHK(gemm_f64_ladder(L, s));
+  return ASCC_OK;
+}
+
+// The W/Z rows of a stacked state (or of every state of a group) into Rw, in the slices of the launch with the ladder.
+int wz_launch(ascc_ints* I, const LadderRows& rows, hipStream_t s) {
+  const long To = (long)I->no * (I->no + 1) / 2, Tv = (long)I->nv * (I->nv + 1) / 2, wzl = I->ov + I->oo;
+  Ladder L;
+  L.M = L.Mdec = (int)To;
+  L.N = (int)wzl;
+  L.Ndec = (int)(I->vvvv_mode == ASCC_VVVV_FULL ? wzl : Tv + wzl);
+  L.K = (int)pad_even(Tv);
+  L.A = rows.Tp;
+  L.lda = I->ldT;
+  L.sa2 = rows.st;
+  L.V = g_rows(I, &L.sv2);
+  L.ldv = I->ldT;
+  L.C = I->Rw;
+  L.ldc = I->ldW;
+  L.sc2 = To * I->ldW;
+  L.ws = I->splitk;
+  L.ws_elems = kSplitKElems;
+  if (nslots() > 1) {
+    L.lb.n = g_sb->n;
+    L.lb.tab = g_sb->dtab;
+    L.lb.tab_max = g_sb->tab_max;
+    L.lb.sa = slot_stride(L.A) / 8;
+    L.lb.sv = slot_stride(L.V) / 8;
+    L.lb.sc = slot_stride(L.C) / 8;
+    if (g_sb->bad) return fail(ASCC_E_STATE, "W/Z operands outside the batch's slot ranges");
   }
   HIPCHK(gemm_f64_ladder(L, s));
   return ASCC_OK;
@@ -702,8 +755,8 @@ int ladder_launch(ascc_ints* I, long S, const double* Tp, double* Rp, const Ladd
 // nullptr: the t+- rows are there already.
 // Phases: pp_pack (pair packing and low-precision operands), pp_ladder (the contraction launch, nothing
 // else), pp_unpack (back to [i][j][a][b], where it is done).
-int pp_ladder_states(ascc_ints* I, int S, const double* const* t2s, double* Tp, double* Rp, float* Tpf,
-                     hipStream_t s, bool wz_done = false) {
+int pp_ladder_states(ascc_ints* I, int S, const double* const* t2s, double* Tp, double* Rp, long ldr, bool apart,
+                     float* Tpf, hipStream_t s, bool wz_done = false) {
   const int o = I->no, v = I->nv;
   const long To = (long)o * (o + 1) / 2, Tv = (long)v * (v + 1) / 2;
   const long M = S * To, ldT = I->ldT;
@@ -716,12 +769,12 @@ int pp_ladder_states(ascc_ints* I, int S, const double* const* t2s, double* Tp, 
   phase_end(I, s);
   phase_begin(I, PH_LADDER, s);
   if (lowp) {  // no split-K: a state's rows are summed in the same order whatever S is
-    GemmLP g = lp_nt(I, M, Tv, Tv, 2, Tpf, ld, M * ld, I->Vf, ld, Tv * ld, Rp, I->ldR, M * I->ldR);
+    GemmLP g = lp_nt(I, M, Tv, Tv, 2, Tpf, ld, M * ld, I->Vf, ld, Tv * ld, Rp, ldr, M * ldr);
     g.ws = nullptr;
     g.m_dec = (int)To;  // the kernel choice of one state's rows
     HIPCHK(gemm_lowp(g, s));
   } else {
-    const int rc = ladder_launch(I, S, Tp, Rp, nullptr, s, wz_done);
+    const int rc = ladder_launch(I, S, Tp, Rp, ldr, apart, nullptr, s, wz_done);
     if (rc) return rc;
   }
   phase_end(I, s);
@@ -752,7 +805,7 @@ int pp_ladder_slots(ascc_ints* I, hipStream_t s, bool wz_done) {
     lb.sv = slot_stride(I->V) / 8;
     lb.sc = slot_stride(I->Rp) / 8;
     if (g_sb->bad) return fail(ASCC_E_STATE, "ladder operands outside the batch's slot ranges");
-    const int rc = ladder_launch(I, 1, I->Tp, I->Rp, &lb, s, wz_done);
+    const int rc = ladder_launch(I, 1, I->Tp, I->Rp, I->ldR, false, &lb, s, wz_done);
     if (rc) return rc;
   }
   phase_end(I, s);
@@ -762,7 +815,7 @@ int pp_ladder_slots(ascc_ints* I, hipStream_t s, bool wz_done) {
 // The ladder of the amplitudes whose t+- rows amp_views has written.
 int pp_ladder(ascc_ints* I, hipStream_t s, bool wz_done) {
   if (nslots() > 1) return pp_ladder_slots(I, s, wz_done);
-  return pp_ladder_states(I, 1, nullptr, I->Tp, I->Rp, I->Tpf, s, wz_done);
+  return pp_ladder_states(I, 1, nullptr, I->Tp, I->Rp, I->ldR, false, I->Tpf, s, wz_done);
 }
 
 size_t ints_footprint(long o, long v, long Q, int precision, int mode) {
@@ -893,6 +946,7 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
                   const LadderRows* lad, hipStream_t s) {
   double* RL = I->RL;
   const LadderRows rows = lad ? *lad : own_rows(I);
+  const bool apart = lad && wz_apart(I->no, I->nv);
   const int o = I->no, v = I->nv, Q = I->naux;
   const long n = I->n, nn = n * n, ov = I->ov, oo = I->oo, vv = I->vv, ovov = I->ovov;
   const long wzl = ov + oo;  // row length of W | Z
@@ -1062,10 +1116,15 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   }
   // --- particle-particle ladder over the undressed (ac|bd) (with W/Z in FP64), plus the hole-hole ladder
   if (!ladder_done && (rc = pp_ladder(I, s, wz_done))) return rc;
+  if (apart && !lowp) {
+    phase_begin(I, PH_WZ, s);
+    if ((rc = wz_launch(I, rows, s))) return rc;
+    phase_end(I, s);
+  }
   const bool pairs = !lowp && I->pl_hole < 0;  // the assembly reads the ladders as pair rows
   if (lowp) {
     phase_begin(I, PH_UNPACK, s);
-    EACH_SLOT HIPCHK(unpack_rpm(S(RL), S(rows.Rp), S(rows.Rp) + rows.sr, I->ldR, o, v, s));
+    EACH_SLOT HIPCHK(unpack_rpm(S(RL), S(rows.Rp), S(rows.Rp) + rows.sr, rows.ldr, o, v, s));
     phase_end(I, s);
     phase_begin(I, PH_HH, s);
     // RL[ij][ab] += sum_kl chi[ij][kl] t2[kl][ab], with t2 transposed to K = kl contiguous
@@ -1079,9 +1138,10 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     // W', chi+- with F'' in it, and R+- += chi+- t+- over the pairs k <= l: a quarter of the products of
     // the full sum over k, l (and the F'' t2 product rides along)
     phase_begin(I, PH_HH, s);
-    EACH_SLOT HIPCHK(wz_chi(S(I->WZ), ov, S(I->chi), S(I->chi) + To * To, S(rows.Rp) + Tv, S(rows.Rp) + rows.sr + Tv,
-                            I->ldR, S(I->G4), S(I->Foop), S(t1), o, v, s));
-    Gemm g = gemm_rm(To, Tv, To, 1.0, I->chi, To, false, rows.Tp, I->ldT, false, 1.0, rows.Rp, I->ldR);
+    double* wz = apart ? I->Rw : rows.Rp + Tv;
+    const long sw = apart ? To * I->ldW : rows.sr;
+    EACH_SLOT HIPCHK(wz_chi(S(I->WZ), ov, S(I->chi), S(I->chi) + To * To, S(wz), S(wz) + sw, apart ? I->ldW : rows.ldr, S(I->G4), S(I->Foop), S(t1), o, v, s));
+    Gemm g = gemm_rm(To, Tv, To, 1.0, I->chi, To, false, rows.Tp, I->ldT, false, 1.0, rows.Rp, rows.ldr);
     g.sa2 = To * To;
     g.sb2 = rows.st;
     g.sc2 = rows.sr;
@@ -1090,7 +1150,7 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
     phase_end(I, s);
     if (!pairs) {
       phase_begin(I, PH_UNPACK, s);
-      EACH_SLOT HIPCHK(unpack_rpm(S(RL), S(rows.Rp), S(rows.Rp) + rows.sr, I->ldR, o, v, s));
+      EACH_SLOT HIPCHK(unpack_rpm(S(RL), S(rows.Rp), S(rows.Rp) + rows.sr, rows.ldr, o, v, s));
       phase_end(I, s);
     }
   }
@@ -1159,7 +1219,7 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   // --- doubles assembly and energy
   phase_begin(I, PH_ASSEMBLE, s);
   EACH_SLOT HIPCHK(assemble_r2(S(r2), S(I->G1), pairs ? S(rows.Rp) : S(RL), S(I->EM), S(I->P), S(I->P) + ovov, o, v, s,
-                               pairs ? S(rows.Rp) + rows.sr : nullptr, I->ldR));
+                               pairs ? S(rows.Rp) + rows.sr : nullptr, rows.ldr));
   phase_end(I, s);
   phase_begin(I, PH_ENERGY, s);
   EACH_SLOT HIPCHK(energy(S(e), S(I->partial), S(t1), S(t2), S(I->Lijab), S(I->fov), o, v, s));
@@ -1395,12 +1455,13 @@ size_t work_block_bytes(long o, long v, long Q, int precision, int mode) {
   if (precision != ASCC_PREC_FP64)
     for (const auto& item : lowp_plan(o, v, Q, mode))
       if (!is_constant(item.first)) off = align_up(off) + std::max<size_t>((size_t)item.second, 1) * sizeof(float);
+  if (wz_apart(o, v)) off = align_up(off) + sizeof(double) * (size_t)(o * (o + 1) * pad_line(o * v + o * o));
   return align_up(off);
 }
 // Stacked ladder operands and results for max_states states, then `group` work blocks (group > 1).
 size_t batch_footprint(long o, long v, long Q, int precision, int mode, long max_states, int group) {
   const long To = o * (o + 1) / 2, Tv = v * (v + 1) / 2;
-  const long trows = 2 * To * pad_line(Tv), rrows = 2 * To * pad_line(Tv + o * v + o * o), lrows = 2 * To * lowp_ld(Tv);
+  const long trows = 2 * To * pad_line(Tv), rrows = 2 * To * stacked_row(o, v), lrows = 2 * To * lowp_ld(Tv);
   size_t off = align_up(sizeof(double) * (size_t)(max_states * trows));
   off += align_up(sizeof(double) * (size_t)(max_states * rrows));
   if (precision != ASCC_PREC_FP64) off += align_up(sizeof(float) * (size_t)(max_states * lrows));
@@ -1428,7 +1489,7 @@ int batch_reserve_impl(ascc_ints* I, int max_states, int group, void* ws, size_t
   }
   const long o = I->no, v = I->nv, To = o * (o + 1) / 2, Tv = v * (v + 1) / 2, lrows = 2 * To * lowp_ld(Tv);
   int rc = dalloc(I->batch, &I->Tp_all, (size_t)(max_states * 2 * To * I->ldT));
-  if (!rc) rc = dalloc(I->batch, &I->Rp_all, (size_t)(max_states * 2 * To * I->ldR));
+  if (!rc) rc = dalloc(I->batch, &I->Rp_all, (size_t)(max_states * 2 * To * stacked_row(o, v)));
   if (!rc && I->precision != ASCC_PREC_FP64) rc = dalloc(I->batch, &I->Tpf_all, (size_t)(max_states * lrows));
   if (!rc && group > 1) {
     I->group_block = work_block_bytes(o, v, I->naux, I->precision, I->vvvv_mode);
@@ -1473,6 +1534,10 @@ int residual_group(ascc_ints* I, int n, int nstates, const double* const* t1, co
         off += std::max<size_t>((size_t)item.second, 1) * sizeof(float);
       }
   bind_views(I);
+  if (wz_apart(o, v)) {
+    I->Rw = reinterpret_cast<double*>(I->group_base + align_up(off));
+    I->ldW = pad_line(I->ov + I->oo);
+  }
   SlotBatch sb;
   sb.n = n;
   auto add = [&](const void* p, size_t bytes, long stride) {
@@ -1488,7 +1553,7 @@ int residual_group(ascc_ints* I, int n, int nstates, const double* const* t1, co
   add(r1[0], sizeof(double) * I->ov, step((const void* const*)r1));
   add(r2[0], sizeof(double) * I->oovv, step((const void* const*)r2));
   add(e, sizeof(double), (long)sizeof(double));
-  const long trow = 8 * (o * (o + 1) / 2) * I->ldT, rrow = 8 * (o * (o + 1) / 2) * I->ldR;  // bytes of a state's rows
+  const long trow = 8 * (o * (o + 1) / 2) * I->ldT, rrow = 8 * (o * (o + 1) / 2) * lad.ldr;  // bytes of a state's rows
   add(lad.Tp, trow, trow);
   add(lad.Rp, rrow, rrow);
   for (const auto& item : ints_plan(o, v, Q, I->precision, I->vvvv_mode))  // shared integrals: stride 0
@@ -1914,11 +1979,12 @@ int ascc_residual_batch(ascc_ints* I, int nstates, const double* const* t1, cons
     user.add(r2[k], sizeof(double) * I->oovv);
   }
   user.add(e, sizeof(double) * nstates);
-  int rc = pp_ladder_states(I, nstates, t2, I->Tp_all, I->Rp_all, I->Tpf_all, s);
+  const long ldr = stacked_row(I->no, I->nv);
+  int rc = pp_ladder_states(I, nstates, t2, I->Tp_all, I->Rp_all, ldr, wz_apart(I->no, I->nv), I->Tpf_all, s);
   if (rc) return rc;
-  const long To = (long)I->no * (I->no + 1) / 2, tstate = To * I->ldT, rstate = To * I->ldR;
+  const long To = (long)I->no * (I->no + 1) / 2, tstate = To * I->ldT, rstate = To * ldr;
   auto rows = [&](int k) {
-    return LadderRows{I->Tp_all + k * tstate, I->Rp_all + k * rstate, nstates * tstate, nstates * rstate};
+    return LadderRows{I->Tp_all + k * tstate, I->Rp_all + k * rstate, nstates * tstate, nstates * rstate, ldr};
   };
   if (!grouped) {
     for (int k = 0; k < nstates && !rc; ++k) {

@@ -754,35 +754,35 @@ hipError_t launch_ladder(const GP& p, int nb1, int split, double* ws, hipStream_
 
 // Tile height and split-K count of a ladder of M rows (N columns, both halves).  Time of a launch: whole
 // rounds of 256 workgroups x stages of a slice (and about 6 to fill and drain) x (rows + 24 of B staging).
-// The split is that of one state's rows Mdec alone, so a state's sums do not depend on how many states
-// are stacked, and takes only counts whose partial tiles fit the scratch; it pays where one state leaves CUs
+// The split is that of one state's rows Mdec and Ndec columns, so a state's sums do not depend on how many states
+// are stacked or which columns are computed together, and takes only counts whose partial tiles fit the scratch; it pays where one state leaves CUs
 // idle: its partial tiles cost a pass over the outputs.  Against the best of all heights and splits, us:
 // o8 v72 48 / 45, o10 v90 108 / 104, o12 v108 252 / 243, o15 v135 881 / 853, o20 v180 4266 / 4259.
 struct LadderPlan {
   int bm, split;
 };
-LadderPlan ladder_plan(long M, long Mdec, long N, long K, long ws_elems) {
+LadderPlan ladder_plan(long M, long Mdec, long N, long Ndec, long K, long ws_elems) {
   constexpr int kBM[] = {32, 48, 64, 80, 96, 112, 128, 144, 160, 176, 192, 208, 224, 240, 256};
-  const long nkt = (K + kStageK - 1) / kStageK, tn = (N + 127) / 128;
-  auto cost = [&](long m, int bm, int sp) {
-    const double wg = (double)((m + bm - 1) / bm * tn * 2 * sp);
+  const long nkt = (K + kStageK - 1) / kStageK;
+  auto cost = [&](int bm, int sp) {
+    const double wg = (double)((Mdec + bm - 1) / bm * ((Ndec + 127) / 128) * 2 * sp);
     const double stages = (double)((nkt + sp - 1) / sp + 6) * (bm + 24) * std::ceil(wg / 256);
-    return stages + (sp > 1 ? 400.0 + 2.0e-5 * (double)(sp + 1) * (double)m * (double)N * 2 : 0.0);
+    return stages + (sp > 1 ? 400.0 + 2.0e-5 * (double)(sp + 1) * (double)Mdec * (double)Ndec * 2 : 0.0);
   };
   LadderPlan best{256, 1};
   double least = -1;
   for (int bm : kBM)
-    for (int sp = 1; sp <= 8 && (sp == 1 || (K > kLadderWhole && nkt >= 16 * sp && 2 * sp * Mdec * N <= ws_elems)); ++sp) {
-      const double c = cost(Mdec, bm, sp);
+    for (int sp = 1; sp <= 8 && (sp == 1 || (K > kLadderWhole && nkt >= 16 * sp && 2 * sp * Mdec * Ndec <= ws_elems)); ++sp) {
+      const double c = cost(bm, sp);
       if (least < 0 || c < least) {
         least = c;
         best = {bm, sp};
       }
     }
-  if (M != Mdec) {
+  if (M != Mdec || N != Ndec) {
     least = -1;
     for (int bm : kBM) {
-      const double c = std::ceil((double)((M + bm - 1) / bm * tn * 2) / 256) * (bm + 24);
+      const double c = std::ceil((double)((M + bm - 1) / bm * ((N + 127) / 128) * 2) / 256) * (bm + 24);
       if (least < 0 || c < least) {
         least = c;
         best.bm = bm;
@@ -1077,7 +1077,7 @@ hipError_t gemm_f64_ladder(const Ladder& L, hipStream_t s) {
   if (L.M <= 0 || L.N <= 0) return hipSuccess;
   const bool pmode = L.pm != nullptr;
   const LadderBatch& lb = L.lb;
-  if (L.K <= 0 || lb.n > 65535 || L.Mdec <= 0 || L.M % L.Mdec) return hipErrorInvalidValue;
+  if (L.K <= 0 || lb.n > 65535 || L.Mdec <= 0 || L.M % L.Mdec || L.Ndec < L.N) return hipErrorInvalidValue;
   if (bounds_checking()) {
     const long e1 = lb.tab ? lb.tab_max : lb.n - 1;  // last operand block of batch level 1
     const long vlast = pmode ? (L.vrows - 1) * L.ldv + L.K - 1 : L.sv2 + (L.N - 1L) * L.ldv + L.K - 1;
@@ -1115,7 +1115,7 @@ hipError_t gemm_f64_ladder(const Ladder& L, hipStream_t s) {
   p.sc1 = lb.sc;
   p.tab1 = lb.tab;
   if (!dma_eligible(p) || std::max(p.sam, p.sbn) >= 1L << 20) return hipErrorInvalidValue;  // rows laid out for this kernel
-  const LadderPlan pl = ladder_plan(L.M, L.Mdec, L.N, L.K, L.ws ? L.ws_elems : 0);
+  const LadderPlan pl = ladder_plan(L.M, L.Mdec, L.N, L.Ndec, L.K, L.ws ? L.ws_elems : 0);
   // one slice after another where the partial tiles do not fit the scratch: the same sums
   double* ws = (long)pl.split * L.M * L.N * 2 * lb.n <= L.ws_elems ? L.ws : nullptr;
   return pmode ? launch_ladder_plan<true>(p, lb.n, pl, ws, s) : launch_ladder_plan<false>(p, lb.n, pl, ws, s);

@@ -105,10 +105,10 @@ bool gemm_f64_small(const Gemm& g);
 // N rows at stride ldv, the halves sv2 apart.  Otherwise V is the full (ac|bd) matrix in pair order
 // (see pack_full), vrows rows at stride ldv, and V_h(n, k) = V[n][k] +- V[pm[n]][k] = (ac|bd) +- (ad|bc)
 // for n = (a <= b), k = (c <= d) (its diagonal columns hold (ac|bc) / 2, so V_+ is (ac|bc) there).
-// Rows are 16-byte aligned, K even (zero past T(v)).  A row's sums do not depend on M: K is cut into
-// slices as for Mdec rows (those of one state; M a multiple of it), summed in slice order.
+// Rows are 16-byte aligned, K even (zero past T(v)).  A row's sums do not depend on M or N: K is cut into
+// slices as for Mdec rows (those of one state; M a multiple of it) and Ndec columns, summed in slice order.
 struct Ladder {
-  int M = 0, Mdec = 0, N = 0, K = 0;
+  int M = 0, Mdec = 0, N = 0, Ndec = 0, K = 0;
   const double* A = nullptr;
   long lda = 0, sa2 = 0;
   const double* V = nullptr;

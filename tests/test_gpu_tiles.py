@@ -160,3 +160,11 @@ def test_every_tile_of_an_order_gives_the_same_bits(o, v, stacks, prec):
             assert torch.equal(R1[k], r1[k]) and torch.equal(R2[k], r2[k]) and E[k] == e[k], (n, k)
     assert float(r2[0].abs().max()) > 1e-2
     ints.close()
+
+
+@pytest.mark.parametrize("mode", ["full", "packed"])
+@pytest.mark.parametrize("o,v,Q", [(40, 39, 60), (64, 9, 30)])  # T(v) = 780: K in slices; T(v) = 45, odd
+def test_stacked_states_without_their_wz_columns(o, v, Q, mode):
+    """W/Z columns of more than 32 MB: products of their own, with each state and in groups (the last one of one state)."""
+    _grouped_equals_alone(o, v, Q, 3, 2, "fp64", mode)
+    _grouped_equals_alone(o, v, Q, 2, 1, "fp64", mode)

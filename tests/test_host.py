@@ -136,3 +136,16 @@ def test_sets_with_many_occupied_orbitals_take_no_more_than_their_arrays(o, v, Q
     vm = P.ASCC_VVVV_FULL if mode == "full" else P.ASCC_VVVV_PACKED
     got = P.ascc_workspace_bytes(o, v, Q, pc, vm)[0]
     assert got <= 1.001 * _one_of_each(o, v, Q, pc, vm)
+
+
+@pytest.mark.parametrize("mode", ["full", "packed"])
+@pytest.mark.parametrize("o,v,Q", [(40, 40, 240), (60, 30, 270), (100, 10, 300), (256, 100, 1000), (13, 117, 390), (20, 180, 600)])
+def test_a_stacked_state_takes_no_more_than_its_pair_rows_and_ladder(o, v, Q, mode):
+    """A batch holds for every state the pair rows of its amplitudes and of its ladder (whole lines of 16 values) and no
+    more than another [o][o][v][v]: not the W/Z columns of states with many occupied orbitals, of more than 32 MB."""
+    import paper_2501_10515_amd as P
+
+    vm = P.ASCC_VVVV_FULL if mode == "full" else P.ASCC_VVVV_PACKED
+    To, ldT, S = o * (o + 1) // 2, -(-v * (v + 1) // 32) * 16, 8
+    got = P.ascc_batch_workspace_bytes(o, v, Q, S, 1, vvvv_mode=vm)
+    assert got <= S * 8 * (4 * To * ldT + (o * v) ** 2) + 1024
