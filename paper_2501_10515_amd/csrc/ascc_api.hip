@@ -503,7 +503,7 @@ T* S(T* p) {
 }
 #define EACH_SLOT for (g_slot = 0; g_slot < nslots(); ++g_slot)
 
-// A contraction with the integral set's split-K scratch (shared by the slots of a batch), over the slots.
+// A contraction over the slots, with the split-K scratch that each of them has.
 inline hipError_t over_slots(const ascc_ints* I, Gemm& g) {
   g.ws = I->splitk;
   g.ws_elems = kSplitKElems;
@@ -517,7 +517,8 @@ inline hipError_t over_slots(const ascc_ints* I, Gemm& g) {
     g.sc1 = c / 8;
     g.tab1 = g_sb->dtab;
     g.tab1_max = g_sb->tab_max;
-    g.per_block = true;  // each slot sums in the order it would alone
+    g.ws1 = slot_stride(g.ws) / 8;
+    if (g_sb->bad) return hipErrorInvalidValue;
   }
   return hipSuccess;
 }
@@ -552,7 +553,8 @@ inline hipError_t glp(GemmLP g, hipStream_t s) {
     g.sc1 = c / 8;
     g.tab1 = g_sb->dtab;
     g.tab1_max = g_sb->tab_max;
-    g.per_block = true;
+    g.ws1 = g.ws ? slot_stride(g.ws) / 8 : 0;
+    if (g_sb->bad) return hipErrorInvalidValue;
   }
   return gemm_lowp(g, s);
 }
@@ -745,6 +747,7 @@ int wz_launch(ascc_ints* I, const LadderRows& rows, hipStream_t s) {
     L.lb.sa = slot_stride(L.A) / 8;
     L.lb.sv = slot_stride(L.V) / 8;
     L.lb.sc = slot_stride(L.C) / 8;
+    L.lb.sw = slot_stride(L.ws) / 8;
     if (g_sb->bad) return fail(ASCC_E_STATE, "W/Z operands outside the batch's slot ranges");
   }
   HIPCHK(gemm_f64_ladder(L, s));
@@ -804,6 +807,7 @@ int pp_ladder_slots(ascc_ints* I, hipStream_t s, bool wz_done) {
     lb.sa = slot_stride(I->Tp) / 8;
     lb.sv = slot_stride(I->V) / 8;
     lb.sc = slot_stride(I->Rp) / 8;
+    lb.sw = slot_stride(I->splitk) / 8;
     if (g_sb->bad) return fail(ASCC_E_STATE, "ladder operands outside the batch's slot ranges");
     const int rc = ladder_launch(I, 1, I->Tp, I->Rp, I->ldR, false, &lb, s, wz_done);
     if (rc) return rc;

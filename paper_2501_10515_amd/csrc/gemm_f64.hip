@@ -42,7 +42,8 @@ struct GP {
   int tiles_m, tiles_n;
   int split, it_per_split;  // split-K: slices of the (nred x K-tile) iteration space
   int per;                  // direct-to-LDS: workgroups of one slice
-  double* part;             // partial tiles [split][nb1*nb2][M][N] when split > 1
+  double* part;             // partial tiles [split][nb2][M][N] when split > 1, of block z1 at stride sp1
+  long sp1;
   int seq;                  // split > 1 without partial tiles: a workgroup runs all slices of its tile,
                             // each added to C in turn (the sums of the partial tiles, in slice order)
   const int* pm;            // pair-combined B (ladder): second row of pair n
@@ -201,8 +202,7 @@ __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_f64_kernel(GP p) {
         if (gm < p.M && gn < p.N) {
           const double v = p.alpha * acc[i][j][r];
           if (p.split > 1) {
-            const long zl = (long)z1 * gridDim.y + z2;
-            p.part[(((long)slice * gridDim.z * gridDim.y + zl) * p.M + gm) * p.N + gn] = v;
+            p.part[zs * p.sp1 + (((long)slice * gridDim.y + z2) * p.M + gm) * p.N + gn] = v;
           } else {
             double* c = Cb + gm * p.scm + gn * p.scn;
             *c = (p.beta == 0.0) ? v : v + p.beta * *c;
@@ -211,55 +211,38 @@ __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_f64_kernel(GP p) {
       }
 }
 
-// C_z(m,n) = beta * C_z(m,n) + sum_s part[s][z][m][n].  Each block takes 64 consecutive outputs; its
+// C_z(m,n) = beta * C_z(m,n) + sum_s part[s][z2][m][n] for block z1 = blockIdx.z.  Each workgroup takes 64 consecutive outputs; its
 // four waves sum four contiguous slice ranges in slice order, and the four partial sums are added
 // in wave order (a fixed order, so the result is deterministic).
-__global__ __launch_bounds__(256) void splitk_reduce(GP p, int nb1, long total) {
+__global__ __launch_bounds__(256) void splitk_reduce(GP p, long outs) {
   __shared__ double red[4][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const long x = blockIdx.x * 64L + lane;
   const int s0 = (int)((long)p.split * w / 4), s1 = (int)((long)p.split * (w + 1) / 4);
+  const int zs = p.tab1 ? p.tab1[blockIdx.z] : blockIdx.z;
   double acc = 0.0;
-  if (x < total)
-    for (int sl = s0; sl < s1; ++sl) acc += p.part[(long)sl * total + x];
+  if (x < outs)
+    for (int sl = s0; sl < s1; ++sl) acc += p.part[zs * p.sp1 + sl * outs + x];
   red[w][lane] = acc;
   __syncthreads();
-  if (w != 0 || x >= total) return;
+  if (w != 0 || x >= outs) return;
   const double sum = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
-  const long mn = (long)p.M * p.N;
-  const long zl = x / mn, r = x % mn;
-  const int gm = r / p.N, gn = r % p.N;
-  const int z1 = zl / p.nb2, z2 = zl % p.nb2;
-  const int zs = p.tab1 ? p.tab1[z1] : z1;
+  const long mn = (long)p.M * p.N, r = x % mn;
+  const int z2 = (int)(x / mn), gm = r / p.N, gn = r % p.N;
   double* c = p.C + zs * p.sc1 + z2 * p.sc2 + gm * p.scm + gn * p.scn;
   *c = (p.beta == 0.0) ? sum : sum + p.beta * *c;
 }
 
-// grid of splitk_reduce for `outs` outputs
-inline unsigned splitk_blocks(long outs) { return (unsigned)((outs + 63) / 64); }
+// grid of splitk_reduce for `outs` outputs of each of nb1 blocks
+inline dim3 splitk_grid(long outs, int nb1) { return dim3((unsigned)((outs + 63) / 64), 1, (unsigned)nb1); }
 
-// p advanced to operand block z0 of batch level 1
-GP at_block(GP p, long z0) {
-  if (p.tab1) {
-    p.tab1 += z0;
-  } else {
-    p.A += z0 * p.sa1;
-    p.B += z0 * p.sb1;
-    p.C += z0 * p.sc1;
-  }
-  return p;
-}
-
-// nb1d: the outer batch count the split-K decision is made for (1: as for one operand block, so a
-// block's sums take the same order whatever the batch; nb1 otherwise).  Where the scratch does not hold the
-// partial tiles of all blocks, they run in several launches.
+// The split-K decision is made for one operand block, so that a block's sums take the same order whatever the batch.
 template <int BM, int BN, int BK, int WM, int WN, int MINB>
-hipError_t launch_cfg(const GP& p0, bool amf, bool bnf, int nb1, int nb1d, double* ws, long ws_elems, hipStream_t s) {
+hipError_t launch_cfg(const GP& p0, bool amf, bool bnf, int nb1, double* ws, long ws_elems, hipStream_t s) {
   GP p = p0;
   p.tiles_m = (p.M + BM - 1) / BM;
   p.tiles_n = (p.N + BN - 1) / BN;
-  const long tiles = (long)p.tiles_m * p.tiles_n * p.nb2 * nb1d;
-  const long outs = (long)p.M * p.N * p.nb2;  // of one operand block
+  const long tiles = (long)p.tiles_m * p.tiles_n * p.nb2, outs = (long)p.M * p.N * p.nb2;
   const int nit = ((p.K + BK - 1) / BK) * p.nred;
   p.split = 1;
   p.it_per_split = nit;
@@ -267,31 +250,24 @@ hipError_t launch_cfg(const GP& p0, bool amf, bool bnf, int nb1, int nb1d, doubl
   if (ws && tiles < 192 && nit >= 16) {
     // slices enough for one full round of resident workgroups (MINB per CU)
     int sp = (int)std::min<long>({(256L * MINB + tiles - 1) / tiles, (long)nit / 8, 256L});
-    if (ws_elems > 0) sp = (int)std::min<long>(sp, ws_elems / (outs * nb1d));
+    if (ws_elems > 0) sp = (int)std::min<long>(sp, ws_elems / outs);
     if (sp > 1) {
       p.it_per_split = (nit + sp - 1) / sp;
       p.split = (nit + p.it_per_split - 1) / p.it_per_split;
       p.part = ws;
     }
   }
-  const int fit = p.split > 1 && ws_elems > 0 ? (int)std::clamp<long>(ws_elems / (p.split * outs), 1, nb1) : nb1;
-  for (int z0 = 0; z0 < nb1; z0 += fit) {
-    const GP q = at_block(p, z0);
-    const int n = std::min(fit, nb1 - z0);
-    const dim3 grid(p.tiles_m * p.tiles_n * p.split, p.nb2, n), block(WM * WN * 64);
-    if (amf && bnf)
-      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, true, true>), grid, block, 0, s, q);
-    else if (amf)
-      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, true, false>), grid, block, 0, s, q);
-    else if (bnf)
-      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, false, true>), grid, block, 0, s, q);
-    else
-      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, false, false>), grid, block, 0, s, q);
-    if (p.split > 1) hipLaunchKernelGGL(splitk_reduce, dim3(splitk_blocks(outs * n)), dim3(256), 0, s, q, n, outs * n);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  const dim3 grid(p.tiles_m * p.tiles_n * p.split, p.nb2, nb1), block(WM * WN * 64);
+  if (amf && bnf)
+    hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, true, true>), grid, block, 0, s, p);
+  else if (amf)
+    hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, true, false>), grid, block, 0, s, p);
+  else if (bnf)
+    hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, false, true>), grid, block, 0, s, p);
+  else
+    hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, WM, WN, MINB, false, false>), grid, block, 0, s, p);
+  if (p.split > 1) hipLaunchKernelGGL(splitk_reduce, splitk_grid(outs, nb1), dim3(256), 0, s, p, outs);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------
@@ -344,10 +320,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const double* base, 
 }
 
 // One workgroup's tile (and slices): bid numbers the workgroups of p (tiles x slices), z2 and z1 are its batch
-// levels (nz1 operand blocks).  RED: nred products of K-values each (K a multiple of 16 if there are several)
+// levels.  RED: nred products of K-values each (K a multiple of 16 if there are several)
 // run through one K loop, product r at strides sar, sbr.
 template <int BM, int BN, int WM, int WN, int S, bool PM, bool RED>
-__device__ __forceinline__ void dma_tile(const GP& p, int bid, int z2, const int z1, const int nz1) {
+__device__ __forceinline__ void dma_tile(const GP& p, int bid, int z2, const int z1) {
   typedef double dd2 __attribute__((ext_vector_type(2)));
   typedef double d4 __attribute__((ext_vector_type(4)));
   constexpr int NW = WM * WN;
@@ -550,8 +526,7 @@ __device__ __forceinline__ void dma_tile(const GP& p, int bid, int z2, const int
           if (gm < p.M && gn < p.N) {
             const double v = p.alpha * acc[i][j][r];
             if (p.part) {
-              const long zl = (long)z1 * p.nb2 + z2;
-              p.part[(((long)slice * nz1 * p.nb2 + zl) * p.M + gm) * p.N + gn] = v;
+              p.part[zs * p.sp1 + (((long)slice * p.nb2 + z2) * p.M + gm) * p.N + gn] = v;
             } else {
               double* c = Cb + (long)gm * p.scm + (long)gn * p.scn;
               *c = (slice != slice0) ? *c + v : (p.beta == 0.0) ? v : v + p.beta * *c;
@@ -564,7 +539,7 @@ __device__ __forceinline__ void dma_tile(const GP& p, int bid, int z2, const int
 
 template <int BM, int BN, int WM, int WN, int S, bool PM, bool RED>
 __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_f64_dma_kernel(GP p) {
-  dma_tile<BM, BN, WM, WN, S, PM, RED>(p, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z);
+  dma_tile<BM, BN, WM, WN, S, PM, RED>(p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // Several independent contractions as one launch: problem i takes the workgroups start[i] .. start[i + 1] - 1
@@ -580,7 +555,7 @@ __global__ __launch_bounds__(W* W * 64, 1) void gemm_f64_group_kernel(GroupP g) 
   while (i + 1 < g.n && (int)blockIdx.x >= g.start[i + 1]) ++i;
   const GP& p = g.p[i];
   const int local = (int)blockIdx.x - g.start[i], per2 = p.per * p.split, z2 = local / per2;
-  dma_tile<BT, BT, W, W, 3, false, true>(p, local - z2 * per2, z2, blockIdx.z, gridDim.z);
+  dma_tile<BT, BT, W, W, 3, false, true>(p, local - z2 * per2, z2, blockIdx.z);
 }
 
 // The partial tiles of a group: job i sums slices of outs values per operand block (as splitk_reduce) and takes
@@ -596,17 +571,17 @@ __global__ __launch_bounds__(256) void group_reduce_kernel(GroupR g) {
   while (i + 1 < g.n && (int)blockIdx.x >= g.start[i + 1]) ++i;
   const GP& p = g.p[i];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, z1 = blockIdx.z, ns = g.slices[i];
+  const int zs = p.tab1 ? p.tab1[z1] : z1;
   const long mn = (long)p.M * p.N, outs = mn * p.nb2, x = ((int)blockIdx.x - g.start[i]) * 64L + lane;
   const int s0 = (int)((long)ns * w / 4), s1 = (int)((long)ns * (w + 1) / 4);
   double acc = 0.0;
   if (x < outs)
-    for (int sl = s0; sl < s1; ++sl) acc += p.part[((long)sl * gridDim.z + z1) * outs + x];
+    for (int sl = s0; sl < s1; ++sl) acc += p.part[zs * p.sp1 + sl * outs + x];
   red[w][lane] = acc;
   __syncthreads();
   if (w != 0 || x >= outs) return;
   const double sum = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
   const int z2 = (int)(x / mn), gm = (int)(x % mn / p.N), gn = (int)(x % p.N);
-  const int zs = p.tab1 ? p.tab1[z1] : z1;
   double* c = p.C + zs * p.sc1 + z2 * p.sc2 + gm * p.scm + gn * p.scn;
   *c = (p.beta == 0.0) ? sum : sum + p.beta * *c;
 }
@@ -622,18 +597,18 @@ bool dma_eligible(const GP& p) {
          p.sa1 % 2 == 0 && p.sa2 % 2 == 0 && p.sb1 % 2 == 0 && p.sb2 % 2 == 0 && al(p.A) && al(p.B);
 }
 
-// C_z(m, n) = sum_s part[s][z][m][n], in slice order (the order of a workgroup that runs all slices).
-__global__ __launch_bounds__(256) void ordered_reduce(GP p, int nb1) {
+// C_z(m, n) = sum_s part[s][z2][m][n], in slice order (the order of a workgroup that runs all slices).
+__global__ __launch_bounds__(256) void ordered_reduce(GP p) {
   const int n = blockIdx.x * 256 + threadIdx.x, zl = blockIdx.z;
   if (n >= p.N) return;
-  const long nz = (long)nb1 * p.nb2, mn = (long)p.M * p.N;
+  const long mn = (long)p.M * p.N;
   const int z1 = zl / p.nb2, z2 = zl % p.nb2;
   const int zs = p.tab1 ? p.tab1[z1] : z1;
   double* C = p.C + zs * p.sc1 + z2 * p.sc2;
   for (int m = blockIdx.y; m < p.M; m += gridDim.y) {
-    const double* x = p.part + zl * mn + (long)m * p.N + n;
+    const double* x = p.part + zs * p.sp1 + z2 * mn + (long)m * p.N + n;
     double sum = *x;
-    for (int sl = 1; sl < p.split; ++sl) sum += x[sl * nz * mn];
+    for (int sl = 1; sl < p.split; ++sl) sum += x[sl * p.nb2 * mn];
     C[m * p.scm + n * p.scn] = sum;
   }
 }
@@ -657,14 +632,11 @@ hipError_t launch_dma(GP p, int nb1, int split, double* ws, bool ordered, hipStr
   p.per = PM ? 2 * ((tiles + 7) / 8 * 8) : tiles;  // PM: both halves in grid.x, padded to groups of 8
   dim3 grid(p.per * (p.seq ? 1 : p.split), PM ? 1 : p.nb2, nb1);
   hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, S, PM, RED>), grid, dim3(WM * WN * 64), 0, s, p);
-  if (p.part) {
-    const long outs = (long)p.M * p.N * p.nb2 * nb1;
-    if (ordered)
-      hipLaunchKernelGGL(ordered_reduce, dim3((p.N + 255) / 256, std::min(p.M, 65535), p.nb2 * nb1), dim3(256),
-                         0, s, p, nb1);
-    else
-      hipLaunchKernelGGL(splitk_reduce, dim3(splitk_blocks(outs)), dim3(256), 0, s, p, nb1, outs);
-  }
+  const long outs = (long)p.M * p.N * p.nb2;
+  if (p.part && ordered)
+    hipLaunchKernelGGL(ordered_reduce, dim3((p.N + 255) / 256, std::min(p.M, 65535), p.nb2 * nb1), dim3(256), 0, s, p);
+  else if (p.part)
+    hipLaunchKernelGGL(splitk_reduce, splitk_grid(outs, nb1), dim3(256), 0, s, p, outs);
   return hipGetLastError();
 }
 
@@ -675,8 +647,7 @@ hipError_t launch_dma(GP p, int nb1, int split, double* ws, bool ordered, hipStr
 // outputs are few, small tiles with K split keep every CU busy: 576 x 576 x 240 75 -> 17 us, 390 x 1521 x 1522 70 -> 55 us
 // against 192- to 256-row tiles; in between, the height that fills a round: 1521 x 1521 x 1522 twice takes 254 us in 96 x 96
 // tiles (two rounds), 235 in 160 x 128 ones (240 workgroups).
-// nb1d: the outer batch count the choice is made for; where the partial tiles of all blocks do not fit the
-// scratch, the blocks run in several launches, so that a block's sums never depend on the batch.
+// The choice is made for one operand block, so that a block's sums never depend on the batch.
 struct DmaCfg {
   int bm, bn;
   double t, t1;
@@ -693,16 +664,16 @@ long dma_tiles(const GP& p, int bm, int bn) {  // of one operand block
   return p.lower ? tm * (tm + 1) / 2 : tm * tn;
 }
 inline long dma_stages(const GP& p) { return (long)((p.K + kStageK - 1) / kStageK) * p.nred; }
-DmaPlan plan_dma(const GP& p0, int nb1d, bool ws, long ws_elems) {
+DmaPlan plan_dma(const GP& p0, bool ws, long ws_elems) {
   const bool red = p0.nred > 1;
-  const long nbatch = (long)p0.nb2 * nb1d, outs = (long)p0.M * p0.N * nbatch;  // of the deciding batch
+  const long outs = (long)p0.M * p0.N * p0.nb2;
   const long nkt = dma_stages(p0);
   DmaPlan best{-1, 1, 0.0};
   for (int c = 0; c < (int)(sizeof kDmaCfg / sizeof kDmaCfg[0]); ++c) {
     const DmaCfg& f = kDmaCfg[c];
     if ((red && f.bm > 64) || (p0.lower && f.bm != f.bn)) continue;
     if (std::max(p0.sam, p0.sbn) * f.bm >= 1L << 28) continue;  // rows past a descriptor's 2 GiB
-    const long tiles = dma_tiles(p0, f.bm, f.bn) * nbatch;
+    const long tiles = dma_tiles(p0, f.bm, f.bn) * p0.nb2;
     for (long sp = 1; sp <= 256; sp += sp < 4 ? 1 : sp / 2) {
       if (sp > 1 && (p0.lower || !ws || tiles * sp > 1536 || nkt < 4 * sp || sp * outs > ws_elems)) break;
       const double per = std::max((double)((tiles * sp + 255) / 256) * f.t, f.t1);
@@ -713,35 +684,24 @@ DmaPlan plan_dma(const GP& p0, int nb1d, bool ws, long ws_elems) {
   return best;
 }
 
-hipError_t launch_dma_auto(const GP& p0, int nb1, int nb1d, double* ws, long ws_elems, hipStream_t s) {
-  const bool red = p0.nred > 1;
-  const long outs = (long)p0.M * p0.N * p0.nb2 * nb1d;
-  const DmaPlan pl = plan_dma(p0, nb1d, ws != nullptr, ws_elems);
-  const int best = pl.cfg, best_split = pl.split;
-  const long fit = best_split > 1 ? std::max<long>(1, ws_elems / (best_split * (outs / nb1d))) : nb1;
-  for (long z0 = 0; z0 < nb1; z0 += fit) {
-    const GP p = at_block(p0, z0);
-    const int n = (int)std::min<long>(fit, nb1 - z0);
-    hipError_t e;
-    switch (best) {
-      case 0: e = launch_dma<192, 192, 2, 4, 3>(p, n, best_split, ws, false, s); break;
-      case 1: e = launch_dma<256, 128, 4, 2, 3>(p, n, best_split, ws, false, s); break;
-      case 7: e = launch_dma<192, 128, 2, 4, 3>(p, n, best_split, ws, false, s); break;
-      case 8: e = launch_dma<160, 128, 2, 4, 3>(p, n, best_split, ws, false, s); break;
-      case 2: e = launch_dma<224, 128, 2, 4, 3>(p, n, best_split, ws, false, s); break;
-      case 3: e = launch_dma<128, 128, 2, 4, 3>(p, n, best_split, ws, false, s); break;
-      case 4: e = launch_dma<96, 96, 2, 2, 3>(p, n, best_split, ws, false, s); break;
-      case 5:
-        e = red ? launch_dma<64, 64, 2, 2, 3, false, true>(p, n, best_split, ws, false, s)
-                : launch_dma<64, 64, 2, 2, 3>(p, n, best_split, ws, false, s);
-        break;
-      default:
-        e = red ? launch_dma<32, 32, 1, 1, 3, false, true>(p, n, best_split, ws, false, s)
-                : launch_dma<32, 32, 1, 1, 3>(p, n, best_split, ws, false, s);
-    }
-    if (e != hipSuccess) return e;
+hipError_t launch_dma_auto(const GP& p, int nb1, double* ws, long ws_elems, hipStream_t s) {
+  const bool red = p.nred > 1;
+  const DmaPlan pl = plan_dma(p, ws != nullptr, ws_elems);
+  switch (pl.cfg) {
+    case 0: return launch_dma<192, 192, 2, 4, 3>(p, nb1, pl.split, ws, false, s);
+    case 1: return launch_dma<256, 128, 4, 2, 3>(p, nb1, pl.split, ws, false, s);
+    case 7: return launch_dma<192, 128, 2, 4, 3>(p, nb1, pl.split, ws, false, s);
+    case 8: return launch_dma<160, 128, 2, 4, 3>(p, nb1, pl.split, ws, false, s);
+    case 2: return launch_dma<224, 128, 2, 4, 3>(p, nb1, pl.split, ws, false, s);
+    case 3: return launch_dma<128, 128, 2, 4, 3>(p, nb1, pl.split, ws, false, s);
+    case 4: return launch_dma<96, 96, 2, 2, 3>(p, nb1, pl.split, ws, false, s);
+    case 5:
+      return red ? launch_dma<64, 64, 2, 2, 3, false, true>(p, nb1, pl.split, ws, false, s)
+                 : launch_dma<64, 64, 2, 2, 3>(p, nb1, pl.split, ws, false, s);
+    default:
+      return red ? launch_dma<32, 32, 1, 1, 3, false, true>(p, nb1, pl.split, ws, false, s)
+                 : launch_dma<32, 32, 1, 1, 3>(p, nb1, pl.split, ws, false, s);
   }
-  return hipSuccess;
 }
 
 // Ladder tiles: BM x 128, the eight waves side by side (BM / 16 fragment rows each).  Three stages, or
@@ -857,7 +817,7 @@ static void affine_range(const long* ext, const long* str, int n, long& lo, long
 
 static bool gemm_in_bounds(const Gemm& g) {
   long lo, hi;
-  const long e1 = g.tab1 ? g.tab1_max + 1 : g.nb1;  // batch level 1 spans the table's entries
+  const long e1 = g.tab1 ? g.tab1_max + 1L : g.nb1;  // batch level 1 spans the table's entries
   const long ea[5] = {g.M, g.K, e1, g.nb2, g.nred}, sa[5] = {g.sam, g.sak, g.sa1, g.sa2, g.sar};
   affine_range(ea, sa, 5, lo, hi);
   if (!range_ok(g.A, lo, hi, sizeof(double), "gemm A")) return false;
@@ -867,7 +827,7 @@ static bool gemm_in_bounds(const Gemm& g) {
   const long ec[4] = {g.M, g.N, e1, g.nb2}, sc[4] = {g.scm, g.scn, g.sc1, g.sc2};
   affine_range(ec, sc, 4, lo, hi);
   if (!range_ok(g.C, lo, hi, sizeof(double), "gemm C")) return false;
-  return !g.ws || range_ok(g.ws, 0, g.ws_elems - 1, sizeof(double), "gemm split-K scratch");
+  return !g.ws || range_ok(g.ws, 0, (e1 - 1) * g.ws1 + g.ws_elems - 1, sizeof(double), "gemm split-K scratch");
 }
 
 static GP to_gp(const Gemm& g) {
@@ -896,6 +856,7 @@ static GP to_gp(const Gemm& g) {
   p.beta = g.beta;
   p.nb2 = g.nb2;
   p.nred = g.nred;
+  p.sp1 = g.ws1;
   p.seq = 0;
   p.pm = nullptr;
   p.tab1 = g.tab1;
@@ -909,15 +870,14 @@ hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
   if (bounds_checking() && !gemm_in_bounds(g)) return hipErrorInvalidValue;
   if (dry_run()) return hipSuccess;
   if (g.nb1 > 65535 || g.nb2 > 65535) return hipErrorInvalidValue;
-  // tile and split-K choices: for the whole batch, or as for one block of the outer level
-  const int nb1d = g.per_block ? 1 : g.nb1, nbatch = nb1d * g.nb2;
   if (g.K <= 0 || g.nred <= 0) return hipErrorInvalidValue;  // callers never pass an empty contraction
+  if (g.ws && g.nb1 > 1 && g.ws1 < g.ws_elems) return hipErrorInvalidValue;  // the blocks' scratches overlap
   GP p = to_gp(g);
-  if (dma_eligible(p)) return launch_dma_auto(p, g.nb1, nb1d, g.fixed ? nullptr : g.ws, g.ws_elems, s);
+  if (dma_eligible(p)) return launch_dma_auto(p, g.nb1, g.fixed ? nullptr : g.ws, g.ws_elems, s);
   // Global-load order: an operand whose m (n) stride is 1 is read m-fast (n-fast).
   const bool amf = (g.sam == 1 && g.sak != 1);
   const bool bnf = (g.sbn == 1) || (g.sbk != 1);
-  const long tiles128 = (long)((g.M + 127) / 128) * ((g.N + 127) / 128) * nbatch;
+  const long tiles128 = (long)((g.M + 127) / 128) * ((g.N + 127) / 128) * g.nb2;
   if (g.M >= 96 && g.N >= 96 && tiles128 >= 256 && (long)g.K * g.nred > 512) {
     // Large outputs over more than a few stages (a short K is bound by the output's traffic, which two 64 x 64 workgroups per
     // CU keep in flight: -= t1^T W' over 400 outputs of 180 x 180 and K = 20 94 -> 62 us, hole-hole pairs o20 v180 111 -> 102):
@@ -926,34 +886,34 @@ hipError_t gemm_f64(const Gemm& g, hipStream_t s) {
     // rounds: 59.5, 60, 61.5 TFLOP/s), which prices both the padding of M and N and the partly
     // filled last round.
     auto est = [&](int bm, int bn, double rate) {
-      const long t = (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * nbatch;
+      const long t = (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.nb2;
       return (double)((t + 255) / 256) * bm * bn / rate;
     };
     const double e128 = est(128, 128, 59.5), e256 = est(256, 128, 60.0), e192 = est(192, 192, 61.5);
-    if (e192 < e128 && e192 <= e256) return launch_cfg<192, 192, 16, 2, 4, 1>(p, amf, bnf, g.nb1, nb1d, nullptr, 0, s);
-    if (e256 < e128) return launch_cfg<256, 128, 16, 4, 2, 1>(p, amf, bnf, g.nb1, nb1d, nullptr, 0, s);
-    return launch_cfg<128, 128, 16, 2, 2, 2>(p, amf, bnf, g.nb1, nb1d, g.ws, g.ws_elems, s);
+    if (e192 < e128 && e192 <= e256) return launch_cfg<192, 192, 16, 2, 4, 1>(p, amf, bnf, g.nb1, nullptr, 0, s);
+    if (e256 < e128) return launch_cfg<256, 128, 16, 4, 2, 1>(p, amf, bnf, g.nb1, nullptr, 0, s);
+    return launch_cfg<128, 128, 16, 2, 2, 2>(p, amf, bnf, g.nb1, g.ws, g.ws_elems, s);
   }
   // a long K lets split-K make up for too few 128 x 128 tiles (down to 16 of them: split into up
   // to 32 slices, a long K still leaves each slice enough iterations to hide its reduction)
   const bool long_k = g.ws && (long)g.K * g.nred >= 2048 && tiles128 >= 16;
   if (g.M >= 96 && g.N >= 96 && long_k) {
-    return launch_cfg<128, 128, 16, 2, 2, 2>(p, amf, bnf, g.nb1, nb1d, g.ws, g.ws_elems, s);
+    return launch_cfg<128, 128, 16, 2, 2, 2>(p, amf, bnf, g.nb1, g.ws, g.ws_elems, s);
   }
-  const long tiles64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * nbatch;
+  const long tiles64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.nb2;
   if (g.M >= 48 && g.N >= 48 && tiles64 >= 128)
-    return launch_cfg<64, 64, 16, 2, 2, 2>(p, amf, bnf, g.nb1, nb1d, g.ws, g.ws_elems, s);
+    return launch_cfg<64, 64, 16, 2, 2, 2>(p, amf, bnf, g.nb1, g.ws, g.ws_elems, s);
   // a narrow output over a long K: 64 x 64 tiles of four waves, split along K, keep more of each
   // CU busy (and more loads in flight) than single-wave 32 x 32 tiles
   if (g.ws && g.M >= 16 && g.N >= 16 && (long)g.K * g.nred >= 2048 && tiles64 < 192)
-    return launch_cfg<64, 64, 16, 2, 2, 2>(p, amf, bnf, g.nb1, nb1d, g.ws, g.ws_elems, s);
-  return launch_cfg<32, 32, 16, 1, 1, 3>(p, amf, bnf, g.nb1, nb1d, g.ws, g.ws_elems, s);
+    return launch_cfg<64, 64, 16, 2, 2, 2>(p, amf, bnf, g.nb1, g.ws, g.ws_elems, s);
+  return launch_cfg<32, 32, 16, 1, 1, 3>(p, amf, bnf, g.nb1, g.ws, g.ws_elems, s);
 }
 
 bool gemm_f64_small(const Gemm& g) {
   const GP p = to_gp(g);
   if (g.M <= 0 || g.N <= 0 || g.K <= 0 || !dma_eligible(p)) return false;
-  const DmaPlan pl = plan_dma(p, g.per_block ? 1 : g.nb1, g.ws && !g.fixed, g.ws_elems);
+  const DmaPlan pl = plan_dma(p, g.ws && !g.fixed, g.ws_elems);
   return pl.cfg >= 0 && kDmaCfg[pl.cfg].bm <= 64;
 }
 
@@ -966,7 +926,7 @@ hipError_t gemm_f64_group(const Gemm* all, int count, hipStream_t s) {
   GP p[kMaxGroup];
   int n = 0;
   auto joins_group = [&](const Gemm& g) {
-    return !dry_run() && g.nb1 == nb1 && nb1 <= 65535 && g.ws && g.ws == all[0].ws && gemm_f64_small(g);
+    return !dry_run() && g.nb1 == nb1 && nb1 <= 65535 && g.ws && g.ws == all[0].ws && g.ws1 == all[0].ws1 && gemm_f64_small(g);
   };
   bool together = true;
   for (int i = 0; i < count; ++i)
@@ -982,7 +942,7 @@ hipError_t gemm_f64_group(const Gemm* all, int count, hipStream_t s) {
     if (bounds_checking() && !gemm_in_bounds(g)) return hipErrorInvalidValue;
     gs[n] = g;
     p[n++] = to_gp(g);
-    if (!g.fixed) solo += plan_dma(p[n - 1], g.per_block ? 1 : g.nb1, true, g.ws_elems).us;
+    if (!g.fixed) solo += plan_dma(p[n - 1], true, g.ws_elems).us;
   }
   const bool group = n > 1;
   struct Choice {
@@ -1024,53 +984,43 @@ hipError_t gemm_f64_group(const Gemm* all, int count, hipStream_t s) {
     return hipSuccess;
   }
   // slices, scratch and launch order (problems that share an output: their slices follow one another)
-  long parts = 0;
+  if (nb1 > 1 && gs[0].ws1 < gs[0].ws_elems) return hipErrorInvalidValue;  // the blocks' scratches overlap
+  GroupP gp{};
+  GroupR gr{};
+  double* ws = gs[0].ws;
+  gp.n = n;
   for (int i = 0; i < n; ++i) {
-    const long sp = split_of(i, best.unit);
-    p[i].tiles_m = (p[i].M + best.bt - 1) / best.bt;
-    p[i].tiles_n = (p[i].N + best.bt - 1) / best.bt;
-    p[i].per = (int)dma_tiles(p[i], best.bt, best.bt);
-    const long nkt = dma_stages(p[i]);
-    p[i].it_per_split = (int)((nkt + sp - 1) / sp);
-    p[i].split = (int)((nkt + p[i].it_per_split - 1) / p[i].it_per_split);
-    if (p[i].split > 1 || gs[i].acc >= 0) parts += (long)p[i].split * p[i].M * p[i].N * p[i].nb2;
-  }
-  const long fit = parts ? std::max(1L, std::min<long>(nb1, gs[0].ws_elems / parts)) : nb1;
-  for (long z0 = 0; z0 < nb1; z0 += fit) {
-    const int nz = (int)std::min<long>(fit, nb1 - z0);
-    GroupP gp{};
-    GroupR gr{};
-    double* ws = gs[0].ws;
-    gp.n = n;
-    for (int i = 0; i < n; ++i) {
-      GP q = at_block(p[i], z0);
-      const bool joins = gs[i].acc >= 0 && i > 0 && gs[i - 1].acc == gs[i].acc;  // adds to the job before it
-      if (q.split > 1 || gs[i].acc >= 0) {
-        q.part = ws;
-        ws += (long)q.split * q.M * q.N * q.nb2 * nz;
-        if (joins) {
-          gr.slices[gr.n - 1] += q.split;
-        } else {
-          gr.p[gr.n] = q;
-          gr.slices[gr.n] = q.split;
-          gr.start[gr.n + 1] = gr.start[gr.n] + (int)(((long)q.M * q.N * q.nb2 + 63) / 64);
-          ++gr.n;
-        }
+    GP& q = p[i];
+    const long sp = split_of(i, best.unit), nkt = dma_stages(q);
+    q.tiles_m = (q.M + best.bt - 1) / best.bt;
+    q.tiles_n = (q.N + best.bt - 1) / best.bt;
+    q.per = (int)dma_tiles(q, best.bt, best.bt);
+    q.it_per_split = (int)((nkt + sp - 1) / sp);
+    q.split = (int)((nkt + q.it_per_split - 1) / q.it_per_split);
+    const bool joins = gs[i].acc >= 0 && i > 0 && gs[i - 1].acc == gs[i].acc;  // adds to the job before it
+    if (q.split > 1 || gs[i].acc >= 0) {
+      q.part = ws;
+      ws += (long)q.split * q.M * q.N * q.nb2;
+      if (joins) {
+        gr.slices[gr.n - 1] += q.split;
+      } else {
+        gr.p[gr.n] = q;
+        gr.slices[gr.n] = q.split;
+        gr.start[gr.n + 1] = gr.start[gr.n] + (int)(((long)q.M * q.N * q.nb2 + 63) / 64);
+        ++gr.n;
       }
-      gp.p[i] = q;
-      gp.start[i + 1] = gp.start[i] + q.per * q.split * q.nb2;
     }
-    const dim3 grid((unsigned)gp.start[n], 1, (unsigned)nz);
-    if (best.bt == 64)
-      hipLaunchKernelGGL((gemm_f64_group_kernel<64, 2>), grid, dim3(256), 0, s, gp);
-    else
-      hipLaunchKernelGGL((gemm_f64_group_kernel<32, 1>), grid, dim3(64), 0, s, gp);
-    if (gr.n)
-      hipLaunchKernelGGL(group_reduce_kernel, dim3((unsigned)gr.start[gr.n], 1, (unsigned)nz), dim3(256), 0, s, gr);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    gp.p[i] = q;
+    gp.start[i + 1] = gp.start[i] + q.per * q.split * q.nb2;
   }
-  return hipSuccess;
+  const dim3 grid((unsigned)gp.start[n], 1, (unsigned)nb1);
+  if (best.bt == 64)
+    hipLaunchKernelGGL((gemm_f64_group_kernel<64, 2>), grid, dim3(256), 0, s, gp);
+  else
+    hipLaunchKernelGGL((gemm_f64_group_kernel<32, 1>), grid, dim3(64), 0, s, gp);
+  if (gr.n)
+    hipLaunchKernelGGL(group_reduce_kernel, dim3((unsigned)gr.start[gr.n], 1, (unsigned)nb1), dim3(256), 0, s, gr);
+  return hipGetLastError();
 }
 
 hipError_t gemm_f64_ladder(const Ladder& L, hipStream_t s) {
@@ -1085,7 +1035,7 @@ hipError_t gemm_f64_ladder(const Ladder& L, hipStream_t s) {
           range_ok(L.C, 0, e1 * lb.sc + L.sc2 + (L.M - 1L) * L.ldc + L.N - 1, sizeof(double), "ladder C") &&
           range_ok(L.V, 0, e1 * lb.sv + vlast, sizeof(double), "ladder V") &&
           (!pmode || range_ok(L.pm, 0, L.N - 1, sizeof(int), "ladder pair rows")) &&
-          (!L.ws || range_ok(L.ws, 0, L.ws_elems - 1, sizeof(double), "ladder split-K scratch"))))
+          (!L.ws || range_ok(L.ws, 0, e1 * lb.sw + L.ws_elems - 1, sizeof(double), "ladder split-K scratch"))))
       return hipErrorInvalidValue;
   }
   if (dry_run()) return hipSuccess;
@@ -1113,10 +1063,12 @@ hipError_t gemm_f64_ladder(const Ladder& L, hipStream_t s) {
   p.sa1 = lb.sa;
   p.sb1 = lb.sv;
   p.sc1 = lb.sc;
+  p.sp1 = lb.sw;
   p.tab1 = lb.tab;
+  if (L.ws && lb.n > 1 && lb.sw < L.ws_elems) return hipErrorInvalidValue;  // the blocks' scratches overlap
   if (!dma_eligible(p) || std::max(p.sam, p.sbn) >= 1L << 20) return hipErrorInvalidValue;  // rows laid out for this kernel
   const LadderPlan pl = ladder_plan(L.M, L.Mdec, L.N, L.Ndec, L.K, L.ws ? L.ws_elems : 0);
-  // one slice after another where the partial tiles do not fit the scratch: the same sums
+  // one slice after another where the partial tiles do not fit the scratch or the blocks fill the chip: the same sums
   double* ws = (long)pl.split * L.M * L.N * 2 * lb.n <= L.ws_elems ? L.ws : nullptr;
   return pmode ? launch_ladder_plan<true>(p, lb.n, pl, ws, s) : launch_ladder_plan<false>(p, lb.n, pl, ws, s);
 }

@@ -268,8 +268,8 @@ struct LP {
   int ktps;     // stages per split-K slice (blockIdx.z); the whole K when not split
   long cslice;  // C offset between slices (partial tiles of a split launch), 0 otherwise
   // batch: blockIdx.y = z1 * nb + z; z1 selects operand block tab1[z1] (or z1) at strides
-  // sa1, sb1, sc1 (partial tiles of a split launch: block z1 itself)
-  int nb, part;
+  // sa1, sb1, sc1
+  int nb;
   const int* tab1;
   long sa1, sb1, sc1;
 };
@@ -337,7 +337,7 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_lowp_kernel(LP p) {
   const int zs = __builtin_amdgcn_readfirstlane(p.tab1 ? p.tab1[z1] : z1);  // uniform: scalar buffer descriptors
   const char* At = p.A + z * p.sa2 + zs * p.sa1 + (long)m0 * p.lda;
   const char* Bt = p.B + z * p.sb2 + zs * p.sb1 + (long)n0 * p.ldb;
-  double* Cb = p.C + z * p.sc2 + (p.part ? z1 : zs) * p.sc1 + blockIdx.z * p.cslice;
+  double* Cb = p.C + z * p.sc2 + zs * p.sc1 + blockIdx.z * p.cslice;
   const uint32_t bytes_a = (uint32_t)(min(BM, p.M - m0) * p.lda), bytes_b = (uint32_t)(min(BN, p.N - n0) * p.ldb);
   uint32_t off[NPW];  // this lane's source in each load its wave issues: byte offset in the tile's rows
 #pragma unroll
@@ -486,18 +486,17 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_lowp_kernel(LP p) {
   __builtin_amdgcn_s_waitcnt(0xF70);  // no load may reach LDS after the workgroup has left
 }
 
-// C_z(m,n) = beta * C_z(m,n) + sum_s part[s][z][m][n], summed in slice order.
+// C_z(m,n) = beta * C_z(m,n) + sum_s part[s][z][m][n] for outer block blockIdx.y (partial tiles ws1 apart), summed in slice order.
 __global__ __launch_bounds__(256) void lowp_splitk_reduce(double* C, long scm, long scn, long sc2, long sc1, int nb,
-                                                          const int* tab1, double beta, const double* part, int M,
-                                                          int N, long total, int split) {
-  for (long x = blockIdx.x * 256L + threadIdx.x; x < total; x += (long)gridDim.x * 256) {
-    const long mn = (long)M * N;
-    const long za = x / mn, r = x % mn;
-    const int z = (int)(za % nb), z1 = (int)(za / nb);
-    const int zs = tab1 ? tab1[z1] : z1;
-    const int m = (int)(r / N), n = (int)(r % N);
+                                                          const int* tab1, double beta, const double* part, long ws1,
+                                                          int M, int N, int split) {
+  const long mn = (long)M * N, outs = mn * nb;
+  const int zs = tab1 ? tab1[blockIdx.y] : blockIdx.y;
+  for (long x = blockIdx.x * 256L + threadIdx.x; x < outs; x += (long)gridDim.x * 256) {
     double acc = 0.0;
-    for (int sl = 0; sl < split; ++sl) acc += part[(long)sl * total + x];
+    for (int sl = 0; sl < split; ++sl) acc += part[zs * ws1 + sl * outs + x];
+    const long r = x % mn;
+    const int z = (int)(x / mn), m = (int)(r / N), n = (int)(r % N);
     double* c = C + z * sc2 + zs * sc1 + m * scm + n * scn;
     *c = (beta == 0.0) ? acc : acc + beta * *c;
   }
@@ -595,18 +594,18 @@ hipError_t gemm_lowp(const GemmLP& g, hipStream_t s) {
       if (d < 0) lo += d; else hi += d;
     }
     if (!(range_ok(g.A, 0, la, el, "lowp A") && range_ok(g.B, 0, lb, el, "lowp B") && range_ok(g.C, lo, hi, 8, "lowp C") &&
-          (!g.ws || range_ok(g.ws, 0, g.ws_elems - 1, 8, "lowp split-K scratch"))))
+          (!g.ws || range_ok(g.ws, 0, (nz1 - 1) * g.ws1 + g.ws_elems - 1, 8, "lowp split-K scratch"))))
       return hipErrorInvalidValue;
   }
   if (dry_run()) return hipSuccess;
-  const int nbd = g.per_block ? g.nb : g.nb * g.nb1;  // the batch the order and the slices are chosen for
+  if (g.ws && g.nb1 > 1 && g.ws1 < g.ws_elems) return hipErrorInvalidValue;  // the blocks' scratches overlap
+  const int nbz = g.nb * g.nb1;  // grid.y
   const int mdec = g.m_dec > 0 ? g.m_dec : g.M;
   // The order and the slices, which the bits of a result depend on, follow from the shape of one state alone: the wide
   // orders (32 x 32 products, one read per FP32 fragment) from half a round of 256 x 256 tiles on, or a quarter with
-  // scratch, K cut so that all slices fill one round; the others in slices of at least 512.  The scratch counts with the
-  // partial tiles of one state too: blocks whose partial tiles it does not hold together run in several launches.
-  const long t2 = (long)((mdec + 255) / 256) * ((g.N + 255) / 256) * nbd;
-  const long fit = g.ws ? g.ws_elems / ((long)g.M * g.N * nbd) : 0;  // slices of the deciding batch that the scratch holds
+  // scratch, K cut so that all slices fill one round; the others in slices of at least 512.
+  const long t2 = (long)((mdec + 255) / 256) * ((g.N + 255) / 256) * g.nb;
+  const long fit = g.ws ? g.ws_elems / ((long)g.M * g.N * g.nb) : 0;  // slices that the scratch of a block holds
   int kind = bf ? kBf16 : kF32Seq, ktps = nkt;
   if (t2 >= 128) {
     kind = bf ? kBf32 : kF32Str;
@@ -617,12 +616,10 @@ hipError_t gemm_lowp(const GemmLP& g, hipStream_t s) {
       ktps = (int)((nkt + n - 1) / n);
     } else {
       const long bm = bf ? 256 : 128;
-      ktps = stages_per_slice(((g.M + bm - 1) / bm) * ((g.N + 127) / 128) * nbd, nkt, fit);
+      ktps = stages_per_slice(((g.M + bm - 1) / bm) * ((g.N + 127) / 128) * g.nb, nkt, fit);
     }
   }
   const int split = (nkt + ktps - 1) / ktps;
-  const int nz = split > 1 && g.per_block ? (int)std::min<long>(g.nb1, fit / split) : g.nb1;  // outer blocks of a launch
-  const int nbz = g.nb * nz;                                                                  // its grid.y
   const Shape* best = nullptr;
   double best_us = 0.0;
   for (const Shape& f : kShapes) {
@@ -641,10 +638,13 @@ hipError_t gemm_lowp(const GemmLP& g, hipStream_t s) {
   p.M = g.M;
   p.N = g.N;
   p.K = g.K;
+  p.A = reinterpret_cast<const char*>(g.A);
   p.lda = g.lda * el;
   p.sa2 = g.sa2 * el;
+  p.B = reinterpret_cast<const char*>(g.B);
   p.ldb = g.ldb * el;
   p.sb2 = g.sb2 * el;
+  p.C = g.C;
   p.scm = g.scm;
   p.scn = g.scn;
   p.sc2 = g.sc2;
@@ -655,37 +655,26 @@ hipError_t gemm_lowp(const GemmLP& g, hipStream_t s) {
   p.ktps = ktps;
   p.cslice = 0;
   p.nb = g.nb;
-  p.part = 0;
+  p.tab1 = g.tab1;
   p.sa1 = g.sa1 * el;
   p.sb1 = g.sb1 * el;
   p.sc1 = g.sc1;
-  if (split > 1) {  // partial tiles [split][nz][nb][M][N] in the scratch
+  if (split > 1) {  // partial tiles [split][nb][M][N] in the scratch of each block
+    p.C = g.ws;
     p.scm = g.N;
     p.scn = 1;
     p.sc2 = (long)g.M * g.N;
-    p.sc1 = (long)g.M * g.N * g.nb;
+    p.sc1 = g.ws1;
+    p.cslice = (long)g.M * g.N * g.nb;
     p.beta = 0.0;
-    p.part = 1;
   }
-  for (int z0 = 0; z0 < g.nb1; z0 += nz) {
-    const int n = std::min(nz, g.nb1 - z0);  // blocks z0 .. z0 + n - 1
-    const long zo = g.tab1 ? 0 : z0;
-    double* C = g.C + zo * g.sc1;
-    p.tab1 = g.tab1 ? g.tab1 + z0 : nullptr;
-    p.A = reinterpret_cast<const char*>(g.A) + zo * p.sa1;
-    p.B = reinterpret_cast<const char*>(g.B) + zo * p.sb1;
-    p.C = split > 1 ? g.ws : C;
-    if (split > 1) p.cslice = (long)g.M * g.N * g.nb * n;
-    hipLaunchKernelGGL(best->kernel, dim3(p.tiles_m * p.tiles_n, g.nb * n, split), dim3(best->threads), 0, s, p);
-    if (split > 1) {
-      const long total = (long)g.M * g.N * g.nb * n;
-      hipLaunchKernelGGL(lowp_splitk_reduce, dim3((unsigned)std::min<long>((total + 255) / 256, 4096)), dim3(256), 0, s, C,
-                         g.scm, g.scn, g.sc2, g.sc1, g.nb, p.tab1, g.beta, g.ws, g.M, g.N, total, split);
-    }
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(best->kernel, dim3(p.tiles_m * p.tiles_n, nbz, split), dim3(best->threads), 0, s, p);
+  if (split > 1) {
+    const dim3 grid((unsigned)std::min<long>((p.cslice + 255) / 256, 4096), (unsigned)g.nb1);
+    hipLaunchKernelGGL(lowp_splitk_reduce, grid, dim3(256), 0, s, g.C, g.scm, g.scn, g.sc2, g.sc1, g.nb, g.tab1, g.beta, g.ws,
+                       g.ws1, g.M, g.N, split);
   }
-  return hipSuccess;
+  return hipGetLastError();
 }
 
 hipError_t to_lowp_gwz(int prec, float* out, long ldo, const double* kcbd, const double* kcld, int o, int v,

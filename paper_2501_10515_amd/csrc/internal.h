@@ -56,16 +56,15 @@ struct Gemm {
   int nb1 = 1, nb2 = 1, nred = 1;
   // Optional scratch for split-K: when the output has too few tiles to fill the chip, the
   // (reduction x K) iteration space is cut into slices whose partial tiles land here and
-  // are then summed in a fixed order (deterministic).  nullptr disables splitting.
+  // are then summed in a fixed order (deterministic).  nullptr disables splitting.  Every block of batch level 1
+  // has ws_elems of its own, ws1 apart, and takes the tiles and slices that it takes alone, so that its
+  // sums do not depend on nb1.
   double* ws = nullptr;
-  long ws_elems = 0;
+  long ws_elems = 0, ws1 = 0;
   // Optional table of batch level 1: grid index z1 takes operand block tab1[z1] (device array of
   // nb1 entries, each at most tab1_max); nullptr: block z1.
   const int* tab1 = nullptr;
   int tab1_max = 0;
-  // tile and split-K choices as for one block of batch level 1 (the same summation order for
-  // each block whatever nb1 is)
-  bool per_block = false;
   // C = A B with B(k, n) = A(n, k) is symmetric: when M == N, beta == 0 and the rows qualify for
   // the direct-to-LDS kernel, only the tiles on and below the diagonal are computed, each stored
   // at its transposed place too (otherwise the full product)
@@ -76,14 +75,14 @@ struct Gemm {
   bool fixed = false;
 };
 
-// Batch level of the particle-particle ladder: n operand blocks (A, V and C offset by sa, sv, sc
+// Batch level of the particle-particle ladder: n operand blocks (A, V, C and the scratch offset by sa, sv, sc, sw
 // elements per block; the pair-row table, which depends on v only, is shared), block z taken from
 // tab[z] when tab is given (entries at most tab_max).
 struct LadderBatch {
   int n = 1;
   const int* tab = nullptr;
   int tab_max = 0;
-  long sa = 0, sv = 0, sc = 0;
+  long sa = 0, sv = 0, sc = 0, sw = 0;
 };
 
 // Convenience constructors for row-major matrices:
@@ -142,9 +141,10 @@ struct GemmLP {
   // sa2, sb2 count bf16 elements
   // Optional split-K scratch: an output with too few tiles to fill the chip has its K range cut
   // into slices (all but the last at least 512 of K, each FP32 chunk starting at its slice's start)
-  // whose FP64 partial tiles land here and are then summed in slice order (deterministic).
+  // whose FP64 partial tiles land here and are then summed in slice order (deterministic).  Every outer block has
+  // ws_elems of its own, ws1 apart, and takes the order and the slices that it takes alone (see Gemm).
   double* ws = nullptr;
-  long ws_elems = 0;
+  long ws_elems = 0, ws1 = 0;
   // Optional outer batch level over operand blocks: nb1 blocks at strides sa1, sb1 (in the units of
   // lda) and sc1 (FP64 elements); block z1 taken from tab1[z1] when tab1 is given (entries at most
   // tab1_max).
@@ -152,9 +152,6 @@ struct GemmLP {
   long sa1 = 0, sb1 = 0, sc1 = 0;
   const int* tab1 = nullptr;
   int tab1_max = 0;
-  // kernel and split-K choices as for one outer block: the bits of each block do not depend on nb1 (blocks whose
-  // partial tiles the scratch does not hold together run in several launches)
-  bool per_block = false;
   // rows that decide the kernel (0: M): operands stacking the rows of several states pass one
   // state's rows, so that every state's rows are summed exactly as when it is alone
   int m_dec = 0;
