@@ -629,13 +629,14 @@ def phase_avg(phases, name):
 def step_summary(run, flops, o, v, prec, nstates=1):
     ph = run["phases"]
     lad = phase_avg(ph, "pp_ladder")
-    out = {"tflops": round(flops / (run["ms_step"] * 1e-3) / 1e12, 3), "ms_per_step": round(run["ms_step"], 4),
-           "pp_ladder_ms": round(lad, 4)}
-    lach = nstates * ladder_flops(o, v) / (lad * 1e-3) / 1e12
-    out["pp_ladder_tflops"] = round(lach, 3)
-    out["pp_ladder_frac"] = round(lach / PEAKS[prec], 4)
+    out = {"tflops": round(flops / (run["ms_step"] * 1e-3) / 1e12, 3), "ms_per_step": round(run["ms_step"], 4)}
+    if lad:  # (the ladder and the rings of a small set join other products in one launch)
+        lach = nstates * ladder_flops(o, v) / (lad * 1e-3) / 1e12
+        out["pp_ladder_ms"] = round(lad, 4)
+        out["pp_ladder_tflops"] = round(lach, 3)
+        out["pp_ladder_frac"] = round(lach / PEAKS[prec], 4)
     ry, rp = ph.get("ring_y", (0.0, 0)), ph.get("ring_p", (0.0, 0))
-    if ry[1] and rp[1]:
+    if ry[0] and rp[0]:
         # per step, each state's two ring launches (several states share a launch in a grouped
         # pass); in the low modes ring_p also holds the shadow of its operand
         ms_step_rings = (ry[0] + rp[0]) / run["steps"]

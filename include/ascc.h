@@ -353,8 +353,10 @@ void ascc_ints_free(ascc_ints* ints); /* NULL is a no-op; waits for the device f
 void ascc_diis_free(ascc_diis* diis); /* NULL is a no-op; synchronises the device first */
 
 /* Per-phase timing of ascc_residual / ascc_update on a handle, with HIP events recorded on the
- * caller's stream around each phase (pp_ladder is the particle-particle ladder contraction,
- * etc.; names from ascc_phase_name).  ascc_timing_enable(ints, 1) starts recording;
+ * caller's stream around each phase (names from ascc_phase_name).  pp_ladder is the
+ * particle-particle ladder contraction, in FP64 with the W/Z rows in the same launch or the next
+ * one; a phase whose products join another one's launch (the ladder and the rings of small sets)
+ * has no interval.  ascc_timing_enable(ints, 1) starts recording;
  * ascc_timing_read waits for the recorded events, returns per phase the summed milliseconds
  * and the number of recorded intervals (arrays of at least ascc_phase_count() entries), and
  * clears the record.  Timing adds two event records per phase and no synchronisation.

@@ -1044,13 +1044,13 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   phase_end(I, s);
 
   // --- rings: Y1, Y2 (batched pair), then Xc and Zd
-  phase_begin(I, PH_RING_Y, s);
+  if (!ring_y_done) phase_begin(I, PH_RING_Y, s);
   if (lowp) {  // K and L are symmetric matrices, so B[n][k] = B[k][n]
     HIPCHK(glp(lp_nt(I, ov, ov, ov, 2, I->TUf, lov, ov * lov, I->KLf, lov, ov * lov, I->Y, ov, ovov), s));
   } else if (!ring_y_done) {
     HIPCHK(mm(I, ring_y, s));
   }
-  phase_end(I, s);
+  if (!ring_y_done) phase_end(I, s);
   phase_begin(I, PH_RING_XZ, s);
   if (lowp) EACH_SLOT HIPCHK(ring_xz_lowp(lowp_kind(I), S(I->XZf), lov, S(I->G2), S(I->G3), S(I->Y), S(I->Y) + ovov, o, v, s));
   else EACH_SLOT HIPCHK(ring_xz(S(I->XZ), S(I->XZ) + ov * ldov, ldov, S(I->G2), S(I->G3), S(I->Y), S(I->Y) + ovov, o, v, s));
@@ -1160,13 +1160,13 @@ int residual_core(ascc_ints* I, const double* t1, const double* t2, double* r1, 
   }
 
   // --- rings: P1 = Tx Xc^T, P2 = U Zd^T (batched pair)
-  phase_begin(I, PH_RING_P, s);
+  if (!ring_p_done) phase_begin(I, PH_RING_P, s);
   if (lowp) {
     HIPCHK(glp(lp_nt(I, ov, ov, ov, 2, I->TUf, lov, ov * lov, I->XZf, lov, ov * lov, I->P, ov, ovov), s));
   } else if (!ring_p_done) {
     HIPCHK(mm(I, ring_p, s));
   }
-  phase_end(I, s);
+  if (!ring_p_done) phase_end(I, s);
   phase_begin(I, PH_N5, s);
   // EM = sum_c t_ij^ac F'_bc
   HIPCHK(mm(I, gemm_rm(oo * v, v, v, 1.0, t2, v, false, I->Fvvp, v, true, 0.0, I->EM, v), s));

@@ -149,3 +149,12 @@ def test_a_stacked_state_takes_no_more_than_its_pair_rows_and_ladder(o, v, Q, mo
     To, ldT, S = o * (o + 1) // 2, -(-v * (v + 1) // 32) * 16, 8
     got = P.ascc_batch_workspace_bytes(o, v, Q, S, 1, vvvv_mode=vm)
     assert got <= S * 8 * (4 * To * ldT + (o * v) ** 2) + 1024
+
+
+def test_step_summary_of_a_small_set():
+    """The ladder and the rings of a small set share a launch with other products: their phases have no intervals."""
+    import bench
+
+    run = {"ms_step": 0.2, "steps": 10, "phases": {"dress": (0.3, 10), "df_ints": (0.5, 10), "ring_xz": (0.1, 10)}}
+    out = bench.step_summary(run, 1.3e7, 5, 20, "fp64")
+    assert out["ms_per_step"] == 0.2 and not [k for k in out if k.startswith(("pp_ladder", "ring_"))]
