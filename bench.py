@@ -73,6 +73,11 @@ def ladder_flops(o, v):
     return 2 * (tri(o) * tri(v) ** 2 + stri(o) * stri(v) ** 2)
 
 
+def ladder_phase_flops(o, v, prec):
+    """The pp_ladder phase: the ladder, in FP64 with the W/Z rows, sum_cd over the pair halves of (kc|bd) and (kc|ld)."""
+    return ladder_flops(o, v) + (4 * tri(o) * tri(v) * (o * v + o * o) if prec == "fp64" else 0)
+
+
 def _host_info():
     info = {"affinity_cores": len(os.sched_getaffinity(0))}
     try:
@@ -631,7 +636,7 @@ def step_summary(run, flops, o, v, prec, nstates=1):
     lad = phase_avg(ph, "pp_ladder")
     out = {"tflops": round(flops / (run["ms_step"] * 1e-3) / 1e12, 3), "ms_per_step": round(run["ms_step"], 4)}
     if lad:  # (the ladder and the rings of a small set join other products in one launch)
-        lach = nstates * ladder_flops(o, v) / (lad * 1e-3) / 1e12
+        lach = nstates * ladder_phase_flops(o, v, prec) / (lad * 1e-3) / 1e12
         out["pp_ladder_ms"] = round(lad, 4)
         out["pp_ladder_tflops"] = round(lach, 3)
         out["pp_ladder_frac"] = round(lach / PEAKS[prec], 4)
@@ -991,9 +996,7 @@ def summarize_counters(passes, args):
         a = agg([top])
         name = seq[top][0]["kernel"]
         name = name[name.find("gemm_"):]
-        flops = ladder_flops(o, v)
-        if tag == "fp64" and args.vvvv == "packed":
-            flops += 4.0 * (o * (o + 1) // 2) * (v * (v + 1) // 2) * (o * v + o * o)
+        flops = ladder_phase_flops(o, v, tag) if args.vvvv == "packed" else ladder_flops(o, v)
         return {"kernel": name[:max(name.find("("), 0) or len(name)][:60], "traffic_bytes": a["hbm_bytes"],
                 "mfma_util": a["mfma_util"], "algorithmic_flops": flops,
                 "mfma_flops_executed": a["mfma_flops_executed"], "step": tag}

@@ -158,3 +158,18 @@ def test_step_summary_of_a_small_set():
     run = {"ms_step": 0.2, "steps": 10, "phases": {"dress": (0.3, 10), "df_ints": (0.5, 10), "ring_xz": (0.1, 10)}}
     out = bench.step_summary(run, 1.3e7, 5, 20, "fp64")
     assert out["ms_per_step"] == 0.2 and not [k for k in out if k.startswith(("pp_ladder", "ring_"))]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "bf16x3"])
+def test_ladder_rate_counts_what_its_phase_holds(prec):
+    """In FP64 the W/Z rows, [T(o)] x [ov + o^2] sums over T(v) pairs in two halves, are products of the ladder's phase."""
+    import bench
+
+    o, v, ms = 20, 180, 4.0
+    run = {"ms_step": 12.0, "steps": 1, "phases": {"pp_ladder": (ms, 1)}}
+    out = bench.step_summary(run, 1e12, o, v, prec)
+    To, Tv = o * (o + 1) // 2, v * (v + 1) // 2
+    flops = 2 * (To * Tv**2 + (To - o) * (Tv - v) ** 2)
+    if prec == "fp64":
+        flops += 2 * 2 * To * Tv * (o * v + o * o)
+    assert out["pp_ladder_tflops"] == pytest.approx(flops / (ms * 1e-3) / 1e12, abs=1e-3)
