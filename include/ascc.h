@@ -376,8 +376,8 @@ int ascc_timing_read(ascc_ints* ints, double* ms, int* counts, int n);
  *   hole      occupied orbital index in [0, no), or < 0 to return to the full equations.
  *   particle  virtual orbital index in [no, no + nv) (full orbital numbering).
  * The first call with hole >= 0 allocates the removal's device work buffers (compact slabs along
- * the primary crosses; their exact size is what ascc_plascc_workspace_bytes reports, up to
- * even padding 8 m no nv + 3 m^2 + naux (no nv + 2 m) + 2 (2 no - 1) nv^2 + 3 no^2 (2 nv - 1) +
+ * the primary crosses; their exact size is what ascc_plascc_workspace_bytes reports: up to
+ * even widths and naux rounded up to 16, 8 m no nv + 3 m^2 + naux (no nv + 2 m) + 2 (2 no - 1) nv^2 + 3 no^2 (2 nv - 1) +
  * 2 no^2 (2 no - 1) doubles, m = no + nv - 1), clears
  * them and waits for the clears (released by ascc_ints_free).  The removal costs N^5 work per
  * residual.  Synchronous.  Errors: ASCC_E_ARG (NULL handle, indices out of range), ASCC_E_NOMEM,

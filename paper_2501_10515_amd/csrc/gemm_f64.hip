@@ -13,12 +13,14 @@
 // K-step of 4 instead of 64 and 20.  Lane layout (measured): lane l supplies A(l%16, l/16) and
 // B(l/16, l%16); register r of the result holds D(l/16 + 4r, l%16).
 //
-// Tile configurations: 128 x 128 (4 waves, two workgroups per CU), 256 x 128 and 192 x 192
-// (8 waves, one per CU), all with K staged 16 deep, chosen per call by how well whole rounds of 256 workgroups cover
-// the output; 64 x 64 and 32 x 32 for small outputs; 128 x 128 with split-K when a long K meets
-// too few tiles.  The particle-particle ladder has its own entry point (gemm_f64_ladder): tiles of a
-// height that fits the pair dimension, K split where one state leaves CUs idle, and optionally the
-// symmetric/antisymmetric vvvv combinations formed while staging from the stored full (ac|bd).
+// K-contiguous operands run on a direct-to-LDS kernel in tiles of 32 x 32 to 192 x 192 and 160 x 128 to 256 x 128 (kDmaCfg),
+// tile and K slices from a measured cost; small ones of one stage share a launch (gemm_f64_group).  Strided operands
+// run on a register-staged kernel: 128 x 128 (4 waves, two workgroups per CU), 256 x 128 and 192 x 192 (8 waves, one
+// per CU) by how well whole rounds of 256 workgroups cover the output, 64 x 64 and 32 x 32 for small outputs or a short
+// K, 128 x 128 with split-K when a long K meets too few tiles; all with K staged 16 deep.  The particle-particle ladder has
+// its own entry point (gemm_f64_ladder) on the direct-to-LDS kernel: tiles of a height that fits the pair dimension, K
+// split where one state leaves CUs idle, and optionally the symmetric/antisymmetric vvvv combinations
+// formed at the fragment reads from the stored full (ac|bd).
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
@@ -290,7 +292,7 @@ hipError_t launch_cfg(const GP& p0, bool amf, bool bnf, int nb1, double* ws, lon
 // 256x128 69.0 -> 71.0, 224x128 66.3 -> 71, 240x128 64.0 -> 72.6, 208x128 63.2 -> 71.6, 128x128
 // 65.4 -> 68.8.  Spreading the loads over the whole stage was slower (66-68).
 //
-// PM: B is pair-combined as in gemm_f64_kernel, both rows of each pair staged and combined once
+// PM: B is pair-combined, V+- = V[n] +- V[pm[n]], both rows of each pair staged and combined once
 // read (two B rows per pair leave room for two stages only).  The second rows of a tile's pairs lie
 // anywhere in the stored matrix, past a descriptor's range, and are loaded by address.
 typedef __attribute__((address_space(3))) void lds_void_t;

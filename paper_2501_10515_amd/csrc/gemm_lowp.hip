@@ -513,8 +513,9 @@ int stages_per_slice(long tiles, int nkt, long fit) {
 
 // Tile shapes.  A launch of c = ceil(workgroups / 256) tiles per CU and k stages is taken as f + k max(t1, c ts) + c e:
 // t1 is the stage of a workgroup with a CU to itself (load and LDS latency), ts that of one among many
-// (MFMA and load rate), e the store of a tile; us, fitted (6 % rms) to 50 contractions of o4 v36 to o40 v130 systems, over
-// which the choice comes within 1 % of the best shape in the mean.  All shapes of an order give the same bits.
+// (MFMA and load rate), e the store of a tile; us, fitted (1 to 13 % rms by shape) to 194 contractions of o4 v36 to o40 v130
+// and o36 v260 systems, over which the choice comes within 0.5 to 1.3 % of the best shape in the mean (14 % at most).  Where
+// the fit put t1 below ts it has no effect, and ts stands for it.  All shapes of an order give the same bits.
 // Measured there against register-staged 256 x 128 / 128 x 128 tiles (kBf16, kF32Seq) and 256 x 256 direct-to-LDS
 // ones: 2.2 and 2.05 times as fast, 1.2 (kBf32) and 1.4 (kF32Str).  Split-BF16x3, o8 v72: ladder 36 x 2628 x 2628 108 -> 22 us,
 // rings 576^3 30 -> 8.8 us; o20 v180: ladder 210 x 16290 x 16290 910 -> 643 us, rings 3600^3 460 -> 423 us.  FP32,
@@ -527,16 +528,16 @@ struct Shape {
 #define SHAPE(KIND, BM, BN, WM, WN, S, T1, TS, F, E) \
   { KIND, BM, BN, WM * WN * 64, T1, TS, F, E, gemm_lowp_kernel<KIND, BM, BN, WM, WN, S> }
 const Shape kShapes[] = {
-    SHAPE(kBf16, 64, 64, 2, 2, 3, 0.219, 0.238, 4.0, 0.0),    SHAPE(kBf16, 64, 64, 2, 2, 4, 0.169, 0.236, 3.6, 0.54),
+    SHAPE(kBf16, 64, 64, 2, 2, 3, 0.238, 0.238, 4.0, 0.0),    SHAPE(kBf16, 64, 64, 2, 2, 4, 0.236, 0.236, 3.6, 0.54),
     SHAPE(kBf16, 96, 96, 2, 2, 3, 0.415, 0.374, 3.9, 1.28),   SHAPE(kBf16, 128, 64, 2, 2, 3, 0.373, 0.365, 4.4, 0.63),
-    SHAPE(kBf16, 128, 128, 2, 2, 4, 0.043, 0.565, 1.6, 5.44), SHAPE(kBf16, 256, 128, 4, 2, 3, 0.910, 0.867, 6.9, 0.0),
+    SHAPE(kBf16, 128, 128, 2, 2, 4, 0.565, 0.565, 1.6, 5.44), SHAPE(kBf16, 256, 128, 4, 2, 3, 0.910, 0.867, 6.9, 0.0),
     SHAPE(kBf32, 64, 128, 2, 2, 3, 1.0, 0.386, 0.0, 1.57),    SHAPE(kBf32, 128, 256, 2, 4, 3, 1.240, 1.042, 0.0, 8.87),
     SHAPE(kBf32, 192, 192, 2, 2, 3, 1.239, 1.156, 0.0, 11.8), SHAPE(kBf32, 256, 128, 4, 2, 3, 1.231, 1.025, 0.0, 8.55),
-    SHAPE(kBf32, 192, 256, 2, 4, 2, 0.339, 1.563, 0.0, 9.75), SHAPE(kBf32, 256, 256, 2, 4, 2, 0.798, 1.849, 0.0, 15.0),
+    SHAPE(kBf32, 192, 256, 2, 4, 2, 1.563, 1.563, 0.0, 9.75), SHAPE(kBf32, 256, 256, 2, 4, 2, 1.849, 1.849, 0.0, 15.0),
     SHAPE(kF32Seq, 64, 64, 2, 2, 3, 0.706, 0.561, 3.1, 1.17), SHAPE(kF32Seq, 64, 64, 2, 2, 4, 0.691, 0.583, 2.7, 1.72),
     SHAPE(kF32Seq, 96, 96, 2, 2, 3, 1.526, 1.243, 1.1, 4.38), SHAPE(kF32Seq, 128, 64, 2, 2, 3, 1.204, 1.031, 2.3, 2.89),
     SHAPE(kF32Str, 64, 64, 2, 2, 3, 0.706, 0.499, 6.3, 0.78), SHAPE(kF32Str, 128, 256, 2, 4, 3, 3.731, 3.665, 1.0, 8.94),
-    SHAPE(kF32Str, 224, 192, 2, 4, 3, 4.9, 4.938, 1.0, 10.2), SHAPE(kF32Str, 256, 256, 2, 4, 2, 7.1, 7.135, 5.9, 10.4),
+    SHAPE(kF32Str, 224, 192, 2, 4, 3, 4.938, 4.938, 1.0, 10.2), SHAPE(kF32Str, 256, 256, 2, 4, 2, 7.135, 7.135, 5.9, 10.4),
 };
 #undef SHAPE
 
